@@ -254,15 +254,17 @@ int coarse_apply_internal(ddamg_ctx* ctx, void* out, const void* in, int nrhs);
  * For callers that cannot allocate device memory during a call: code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.
  * dirac_apply_noalloc computes what dirac_apply computes, with the same
- * kernels and the same result, but stages the internal-layout copies of in
- * and out in a fixed device array of DDAMG_NOALLOC_SCRATCH_BYTES that the
- * library holds on every GPU it runs on until the process ends (its address
- * is looked up once per device, at ddamg_create), instead of workspace that
- * dirac_apply allocates on first use and whenever nrhs grows.  It calls no
- * hipMalloc, hipFree or allocating library routine.
+ * kernels and the same result.  Fields in and out that share no memory are
+ * read and written in place by both; for fields that overlap it stages the
+ * internal-layout copies of in and out in a fixed device array of
+ * DDAMG_NOALLOC_SCRATCH_BYTES that the library holds on every GPU it runs on
+ * until the process ends (its address is looked up once per device, at
+ * ddamg_create), instead of workspace that dirac_apply allocates on first
+ * such call and whenever nrhs grows.  It calls no hipMalloc, hipFree or
+ * allocating library routine.
  * Limit: 2 * nrhs * 12 * V * e bytes (each half rounded up to 256) must fit,
- * e = 16 for DDAMG_FP64 and 8 otherwise; larger calls return DDAMG_EARG
- * before any work.  Every call on one GPU, from any context or stream, uses
+ * e = 16 for DDAMG_FP64 and 8 otherwise, whether or not the fields overlap;
+ * larger calls return DDAMG_EARG before any work.  Every call on one GPU, from any context or stream, uses
  * that GPU's one array: calls that overlap in time on one GPU race, so
  * serialise them (e.g. one stream).  Nothing in the array is read before
  * this call writes it.  Asynchronous; out != in; 1 <= nrhs <= max_rhs. */

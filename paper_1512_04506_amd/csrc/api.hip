@@ -1725,7 +1725,9 @@ int dirac_apply_internal(ddamg_ctx* c, void* out, const void* in, int nrhs, int 
 }
 
 // out = D in on canonical fields through internal-layout copies a (of in)
-// and b (of out), each nrhs * 12 * V elements of the precision's type
+// and b (of out), each nrhs * 12 * V elements of the precision's type: for
+// fields that overlap in memory, where out may be written only once in has
+// been read
 static int dirac_apply_staged(ddamg_ctx* c, double* out, const double* in, int nrhs, int prec, void* a, void* b) {
   const Geom& g = c->g;
   const cx<double>* cin = reinterpret_cast<const cx<double>*>(in);
@@ -1741,6 +1743,27 @@ static int dirac_apply_staged(ddamg_ctx* c, double* out, const double* in, int n
     if (rc) return rc;
     launch_spinor_to_canonical<float>(cout, static_cast<cx<float>*>(b), g, nrhs, c->st);
   }
+  check_launch("dirac_apply");
+  return DDAMG_OK;
+}
+
+// whether the fields in and out of nrhs canonical spinors share memory
+static bool fields_overlap(const ddamg_ctx* c, const double* out, const double* in, int nrhs) {
+  const uintptr_t n = (uintptr_t)nrhs * 12 * c->g.V * sizeof(cx<double>);
+  const uintptr_t o = reinterpret_cast<uintptr_t>(out), i = reinterpret_cast<uintptr_t>(in);
+  return o < i + n && i < o + n;
+}
+
+// out = D in on canonical fields that share no memory
+static int dirac_apply_canon(ddamg_ctx* c, double* out, const double* in, int nrhs, int prec) {
+  const cx<double>* ci = reinterpret_cast<const cx<double>*>(in);
+  cx<double>* co = reinterpret_cast<cx<double>*>(out);
+  if (prec == DDAMG_FP64)
+    launch_dslash_canon<double, double>(co, ci, c->gv64(), c->g, nrhs, c->st);
+  else if (prec == DDAMG_FP32)
+    launch_dslash_canon<float, float>(co, ci, c->gv32(), c->g, nrhs, c->st);
+  else
+    launch_dslash_canon<__half, float>(co, ci, c->gvh(), c->g, nrhs, c->st);
   check_launch("dirac_apply");
   return DDAMG_OK;
 }
@@ -1762,6 +1785,7 @@ int dirac_apply(ddamg_ctx* c, double* out, const double* in, int nrhs, int prec)
   if (!c) return DDAMG_EARG;
   if (int e = dirac_apply_args(c, out, in, nrhs, prec)) return e;
   GUARD_BEGIN
+  if (!fields_overlap(c, out, in, nrhs)) return dirac_apply_canon(c, out, in, nrhs, prec);
   c->ensure_stage(nrhs);
   return dirac_apply_staged(c, out, in, nrhs, prec, c->stage_in.p, c->stage_out.p);
   GUARD_END
@@ -1782,6 +1806,7 @@ int dirac_apply_noalloc(ddamg_ctx* c, double* out, const double* in, int nrhs, i
     return DDAMG_ESTATE;
   }
   GUARD_BEGIN
+  if (!fields_overlap(c, out, in, nrhs)) return dirac_apply_canon(c, out, in, nrhs, prec);
   unsigned char* base = static_cast<unsigned char*>(c->scratch);
   return dirac_apply_staged(c, out, in, nrhs, prec, base, base + half);
   GUARD_END

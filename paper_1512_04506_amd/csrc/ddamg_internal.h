@@ -269,6 +269,12 @@ template <typename Tin, typename Tout, typename S, typename Tc>
 void launch_dslash(cx<Tout>* out, const cx<Tin>* in, const GaugeView<S>& gv, const Geom& g, int nrhs, int mode,
                    int mu, int chi_in, size_t in_rstride, size_t out_rstride, hipStream_t st);
 
+// out = D in on canonical fields (complex128 [rhs][site][4][3], not
+// overlapping), links and clover in storage S, arithmetic in Tc
+template <typename S, typename Tc>
+void launch_dslash_canon(cx<double>* out, const cx<double>* in, const GaugeView<S>& gv, const Geom& g, int nrhs,
+                         hipStream_t st);
+
 // loads the code object of the dslash kernels (see k_dslash.hip)
 void preload_dslash_code();
 

@@ -21,6 +21,8 @@
 // Workgroups walk the blocks in lexicographic order (through the XCD
 // swizzle), so face neighbours are processed at the same time on the same
 // XCD although blocks of opposite parity are far apart in memory.
+#include <algorithm>
+
 #include "dirac_device.h"
 
 namespace ddamg {
@@ -523,6 +525,241 @@ __global__ __launch_bounds__(HVB) void dslash_halo_kernel(cx<Tout>* __restrict__
     for (int k = 0; k < 3; ++k) out[(size_t)(3 * sp + k) * V + s] = cvt<Tout>(acc[0][sp][k]);
 }
 
+// ------------------------------------------------ canonical fields in place
+// D on canonical fields [rhs][site][12] complex128, read and written as they
+// are.  Going through internal copies costs four more field passes and two
+// more launches: 194 -> 120 us for 3 rhs on 24x20x16x18 in FP64 (2.7 TB/s of
+// algorithmic bytes; links and clover come from L2 once per rhs), 21.3 ->
+// 6.2 us for one on 8^4.  A canonical site is one 192-byte record, so a halo
+// site costs one and a half lines whatever face it lies on.
+
+// coordinates of site l of lexicographic block bl, its canonical index and
+// internal index
+struct CanonPos {
+  SitePos p;
+  int c[4];  // global coordinates
+  int lex;   // canonical site
+};
+__device__ inline CanonPos canon_pos(const Geom& g, int bl, int l) {
+  CanonPos q;
+  q.p.bc[0] = bl % g.NB[0];
+  q.p.bc[1] = (bl / g.NB[0]) % g.NB[1];
+  q.p.bc[2] = (bl / (g.NB[0] * g.NB[1])) % g.NB[2];
+  q.p.bc[3] = bl / (g.NB[0] * g.NB[1] * g.NB[2]);
+  q.p.ci = block_to_int(g, q.p.bc);
+  q.p.l = l;
+  q.p.S = q.p.ci * g.vblock + l;
+  local_coords(g, l, q.p.lc);
+#pragma unroll
+  for (int m = 0; m < 4; ++m) q.c[m] = q.p.bc[m] * g.bs[m] + q.p.lc[m];
+  q.lex = lex_site(g, q.c);
+  return q;
+}
+// canonical index of the neighbour in direction MU
+template <int MU, bool FWD>
+__device__ inline int canon_nbr(const Geom& g, const CanonPos& q) {
+  const int str = MU == 0 ? 1 : MU == 1 ? g.L[0] : MU == 2 ? g.L[0] * g.L[1] : g.L[0] * g.L[1] * g.L[2];
+  if (FWD) return q.c[MU] + 1 == g.L[MU] ? q.lex - (g.L[MU] - 1) * str : q.lex + str;
+  return q.c[MU] == 0 ? q.lex + (g.L[MU] - 1) * str : q.lex - str;
+}
+
+template <typename Tc>
+__device__ inline void load_canon(cx<Tc> p[4][3], const cx<double>* rec, Tc sign) {
+#pragma unroll
+  for (int k = 0; k < 12; ++k) p[k / 3][k % 3] = sign * cvt<Tc>(rec[k]);
+}
+
+// both hops of direction MU: in-block neighbours from the staged records,
+// the others straight from the canonical field
+template <int MU, typename S, typename Tc>
+__device__ inline void hops_canon_mu(cx<Tc> acc[1][4][3], const cx<Tc>* lds, int pl, int i, const cx<double>* in,
+                                     const GaugeView<S>& gv, const Geom& g, const CanonPos& q) {
+  const size_t V = g.V;
+  const int l = q.p.lc[MU];
+  const bool live = g.V > 0;  // opaque: each hop stays in its own region
+  if (live) {
+    cx<Tc> p[1][4][3];
+    if (l < g.bs[MU] - 1) {
+#pragma unroll
+      for (int k = 0; k < 12; ++k) p[0][k / 3][k % 3] = lds[k * pl + i + g.lstr[MU]];
+    } else {
+      const Tc sign = MU == 3 && q.c[3] + 1 == g.L[3] ? (Tc)-1 : (Tc)1;
+      load_canon<Tc>(p[0], in + (size_t)canon_nbr<MU, true>(g, q) * 12, sign);
+    }
+    hop_spinor_multi<MU, true, 1, Tc, S>(acc, p, gv, q.p.S, V);
+  }
+  asm volatile("" ::: "memory");
+  if (live) {
+    cx<Tc> p[1][4][3];
+    if (l > 0) {
+#pragma unroll
+      for (int k = 0; k < 12; ++k) p[0][k / 3][k % 3] = lds[k * pl + i - g.lstr[MU]];
+    } else {
+      const Tc sign = MU == 3 && q.c[3] == 0 ? (Tc)-1 : (Tc)1;
+      load_canon<Tc>(p[0], in + (size_t)canon_nbr<MU, false>(g, q) * 12, sign);
+    }
+    hop_spinor_multi<MU, false, 1, Tc, S>(acc, p, gv, nbr_bwd(g, q.p, MU), V);
+  }
+}
+
+constexpr int CT = 256;  // lanes of a workgroup
+
+// Workgroup = nu units of vblock lanes, a unit being one (block, rhs) with
+// the rhs fastest (the rhs of a block read its links side by side): blocks of
+// 90 sites fill 180 of 192 lanes in pairs instead of 90 of 128 alone.  The
+// unit's records are staged in LDS as 12 planes (read as whole records, one
+// 16-byte entry per lane, consecutive lanes consecutive entries; the planes
+// are padded by one entry so that the 12 entries of a record fall on
+// different banks), the result leaves through the same planes.
+template <typename S, typename Tc>
+__global__ __launch_bounds__(CT) void dslash_canon_kernel(cx<double>* __restrict__ out,
+                                                          const cx<double>* __restrict__ in, GaugeView<S> gv, Geom g,
+                                                          int nrhs, int nu, int nunits) {
+  extern __shared__ __attribute__((aligned(16))) char smem_raw[];
+  const int vb = g.vblock;
+  const int n = nu * vb;   // lanes with a site, n <= CT
+  const int pl = n + 1;
+  cx<Tc>* lds = reinterpret_cast<cx<Tc>*>(smem_raw);  // [12][pl]
+  __shared__ size_t rec[CT];                          // first entry of every lane's record
+  const int wl = xcd_swizzle(blockIdx.x, gridDim.x);
+  const int i = threadIdx.x;
+  const int ul = i / vb;
+  const int unit = wl * nu + ul;
+  const bool act = i < n && unit < nunits;
+  const int nvalid = min(nu, nunits - wl * nu) * vb;
+  CanonPos q = canon_pos(g, act ? unit / nrhs : 0, act ? i - ul * vb : 0);
+  const size_t rbase = act ? (size_t)(unit % nrhs) * g.V : 0;
+  if (act) rec[i] = (rbase + q.lex) * 12;
+  __syncthreads();
+  for (int e = i; e < 12 * nvalid; e += blockDim.x) {
+    const int site = e / 12, k = e - 12 * site;
+    lds[k * pl + site] = cvt<Tc>(in[rec[site] + k]);
+  }
+  __syncthreads();
+  cx<Tc> acc[1][4][3];
+#pragma unroll
+  for (int k = 0; k < 12; ++k) acc[0][k / 3][k % 3] = mk((Tc)0, (Tc)0);
+  if (act) {
+    const cx<double>* ir = in + rbase * 12;
+    {
+      cx<Tc> p[1][4][3];
+#pragma unroll
+      for (int k = 0; k < 12; ++k) p[0][k / 3][k % 3] = lds[k * pl + i];
+      clover_apply_multi<1, Tc, S>(acc, p, gv, q.p.S, g.V);
+    }
+    hops_canon_mu<0, S, Tc>(acc, lds, pl, i, ir, gv, g, q);
+    asm volatile("" ::: "memory");
+    hops_canon_mu<1, S, Tc>(acc, lds, pl, i, ir, gv, g, q);
+    asm volatile("" ::: "memory");
+    hops_canon_mu<2, S, Tc>(acc, lds, pl, i, ir, gv, g, q);
+    asm volatile("" ::: "memory");
+    hops_canon_mu<3, S, Tc>(acc, lds, pl, i, ir, gv, g, q);
+  }
+  __syncthreads();
+  if (act) {
+#pragma unroll
+    for (int k = 0; k < 12; ++k) lds[k * pl + i] = acc[0][k / 3][k % 3];
+  }
+  __syncthreads();
+  for (int e = i; e < 12 * nvalid; e += blockDim.x) {
+    const int site = e / 12, k = e - 12 * site;
+    out[rec[site] + k] = cvt<double>(lds[k * pl + site]);
+  }
+}
+
+// Small lattices: four waves per 64 sites, wave MU doing the two hops of
+// direction MU and three rows of the clover term (chirality MU & 1, rows
+// 3 (MU >> 1) ..), all loads issued before the arithmetic, the four partial
+// results added through LDS.  With a few dozen blocks the staged kernel is
+// one chain of ten dependent round trips on a few compute units; here it is
+// three, on four times as many waves.
+template <int MU, typename S, typename Tc>
+__device__ inline void canon_split_mu(cx<Tc> acc[4][3], const cx<double>* in, const GaugeView<S>& gv, const Geom& g,
+                                      const CanonPos& q) {
+  const size_t V = g.V;
+  const int sb = nbr_bwd(g, q.p, MU);
+  cx<Tc> pf[1][4][3], pb[1][4][3], Uf[3][3], Ub[3][3], own[6], a[15], d[3];
+  constexpr int h = MU & 1, row0 = 3 * (MU >> 1);
+  load_link<Tc, S>(Uf, gv, MU, q.p.S, V);
+  load_link<Tc, S>(Ub, gv, MU, sb, V);
+  load_canon<Tc>(pf[0], in + (size_t)canon_nbr<MU, true>(g, q) * 12,
+                 MU == 3 && q.c[3] + 1 == g.L[3] ? (Tc)-1 : (Tc)1);
+  load_canon<Tc>(pb[0], in + (size_t)canon_nbr<MU, false>(g, q) * 12, MU == 3 && q.c[3] == 0 ? (Tc)-1 : (Tc)1);
+  const stc_t<S>* Ah = gv.A + (size_t)h * CLOVER_PAIRS * V;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) d[k] = ldc<Tc>(Ah + (size_t)k * V, (unsigned)q.p.S);
+#pragma unroll
+  for (int k = 0; k < 15; ++k) a[k] = ldc<Tc>(Ah + (size_t)(3 + k) * V, (unsigned)q.p.S);
+#pragma unroll
+  for (int k = 0; k < 6; ++k) own[k] = cvt<Tc>(in[(size_t)q.lex * 12 + 6 * h + k]);
+  Tc sc = (Tc)1, cf = (Tc)-0.5, cb = (Tc)-0.5;
+  if constexpr (is_half<S>()) {
+    sc = (Tc)gv.Asc[q.p.S];
+    cf *= (Tc)gv.Usc[q.p.S];
+    cb *= (Tc)gv.Usc[sb];
+  }
+  // rows row0 .. row0 + 2 of A_h own; a holds the entries (i, j), i < j, row by row
+#pragma unroll
+  for (int rr = 0; rr < 3; ++rr) {
+    const int i = row0 + rr;
+    cx<Tc> o = ((i & 1) ? d[i / 2].i : d[i / 2].r) * own[i];
+#pragma unroll
+    for (int j = 0; j < 6; ++j) {
+      if (j == i) continue;
+      const int lo = i < j ? i : j, hi = i < j ? j : i;
+      const cx<Tc> e = a[5 * lo - lo * (lo - 1) / 2 + hi - lo - 1];
+      o = i < j ? cfma(e, own[j], o) : cfmac(e, own[j], o);
+    }
+    acc[2 * h + i / 3][i % 3] = acc[2 * h + i / 3][i % 3] + sc * o;
+  }
+  cx<Tc> t[1][4][3];
+#pragma unroll
+  for (int k = 0; k < 12; ++k) t[0][k / 3][k % 3] = acc[k / 3][k % 3];
+  hop_spinor_multi_u<MU, true, 1, Tc>(t, pf, Uf, cf);
+  hop_spinor_multi_u<MU, false, 1, Tc>(t, pb, Ub, cb);
+#pragma unroll
+  for (int k = 0; k < 12; ++k) acc[k / 3][k % 3] = t[0][k / 3][k % 3];
+}
+
+template <typename S, typename Tc>
+__global__ __launch_bounds__(256) void dslash_canon_split_kernel(cx<double>* __restrict__ out,
+                                                                 const cx<double>* __restrict__ in, GaugeView<S> gv,
+                                                                 Geom g, int nrhs) {
+  __shared__ cx<Tc> part[4][12][65];
+  __shared__ size_t rec[64];
+  const int lane = threadIdx.x & 63, mu = threadIdx.x >> 6;
+  // sites in lexicographic-block order, the rhs of a site run 64 apart
+  const int total = nrhs * g.V;
+  const int u0 = blockIdx.x * 64;
+  const bool act = u0 + lane < total;
+  const int u = act ? u0 + lane : total - 1;
+  const int r = u / g.V, ls = u - r * g.V;
+  const int bl = ls / g.vblock;
+  const CanonPos q = canon_pos(g, bl, ls - bl * g.vblock);
+  const cx<double>* ir = in + (size_t)r * g.V * 12;
+  cx<Tc> acc[4][3];
+#pragma unroll
+  for (int k = 0; k < 12; ++k) acc[k / 3][k % 3] = mk((Tc)0, (Tc)0);
+  if (mu == 0)
+    canon_split_mu<0, S, Tc>(acc, ir, gv, g, q);
+  else if (mu == 1)
+    canon_split_mu<1, S, Tc>(acc, ir, gv, g, q);
+  else if (mu == 2)
+    canon_split_mu<2, S, Tc>(acc, ir, gv, g, q);
+  else
+    canon_split_mu<3, S, Tc>(acc, ir, gv, g, q);
+#pragma unroll
+  for (int k = 0; k < 12; ++k) part[mu][k][lane] = acc[k / 3][k % 3];
+  if (mu == 0) rec[lane] = ((size_t)r * g.V + q.lex) * 12;
+  __syncthreads();
+  const int nvalid = min(64, total - u0);
+  for (int e = threadIdx.x; e < 12 * nvalid; e += 256) {
+    const int site = e / 12, k = e - 12 * site;
+    const cx<Tc> v = (part[0][k][site] + part[1][k][site]) + (part[2][k][site] + part[3][k][site]);
+    out[rec[site] + k] = cvt<double>(v);
+  }
+}
+
 template <typename Tin, typename Tout, typename S, typename Tc, int NR>
 void launch_staged(cx<Tout>* out, const cx<Tin>* in, const GaugeView<S>& gv, const Geom& g, int nrhs, size_t in_rs,
                    size_t out_rs, hipStream_t st) {
@@ -595,6 +832,35 @@ void launch_dslash(cx<Tout>* out, const cx<Tin>* in, const GaugeView<S>& gv, con
       break;
   }
 }
+
+// The split kernel runs while its grid is one wave per SIMD or so: up to
+// 24576 sites times rhs in FP64 (one 1 us round trip after another bounds
+// the staged kernel there: 8^4, 1 rhs, 5.8 us split against 13.0 us; 24576
+// sites 12.3 against 13.7, 34560 sites 26.0 against 18.9 us), twice that in
+// FP32 (49152 sites 12.7 against 16.0, 65536 sites 19.1 against 17.8 us).
+constexpr size_t CANON_SPLIT_BYTES = 24576 * sizeof(double);
+
+template <typename S, typename Tc>
+void launch_dslash_canon(cx<double>* out, const cx<double>* in, const GaugeView<S>& gv, const Geom& g, int nrhs,
+                         hipStream_t st) {
+  if (nrhs <= 0) return;
+  const size_t total = (size_t)nrhs * g.V;
+  if (total * sizeof(Tc) <= CANON_SPLIT_BYTES) {
+    dslash_canon_split_kernel<S, Tc><<<(unsigned)((total + 63) / 64), 256, 0, st>>>(out, in, gv, g, nrhs);
+    return;
+  }
+  const int nu = std::max(1, CT / g.vblock);  // vblock <= 256
+  const int nunits = g.nblocks * nrhs;
+  const int threads = (nu * g.vblock + 63) / 64 * 64;
+  const size_t lds = (size_t)12 * (nu * g.vblock + 1) * sizeof(cx<Tc>);
+  dslash_canon_kernel<S, Tc><<<(unsigned)((nunits + nu - 1) / nu), threads, lds, st>>>(out, in, gv, g, nrhs, nu, nunits);
+}
+template void launch_dslash_canon<double, double>(cx<double>*, const cx<double>*, const GaugeView<double>&,
+                                                  const Geom&, int, hipStream_t);
+template void launch_dslash_canon<float, float>(cx<double>*, const cx<double>*, const GaugeView<float>&, const Geom&,
+                                                int, hipStream_t);
+template void launch_dslash_canon<__half, float>(cx<double>*, const cx<double>*, const GaugeView<__half>&,
+                                                 const Geom&, int, hipStream_t);
 
 // The runtime loads a file's code object (device memory for its kernels)
 // when one of them is first used; asking for a kernel's attributes does it
