@@ -560,12 +560,8 @@ struct Solver final : SolverBase {
   void schur(cx<T>* w, size_t wstr, const cx<T>* v, size_t vstr, int nrhs, const int* gate = nullptr) {
     const CoarseView<S> C = cv();
     c->timed(DDAMG_KERNEL_COARSE, nrhs, [&] {
-      launch_coarse_stencil<T, S>(te.get<cx<T>>(), esz(), 0, g.neven, nullptr, 0, nullptr, 0, 0, (T)0, v, vstr,
-                                  g.neven, (T)1, C, g, nrhs, st, gate);
-    });
-    c->timed(DDAMG_KERNEL_COARSE, nrhs, [&] {
-      launch_block_matvec<T>(ue.get<cx<T>>(), esz(), Dinv.get<cx<T>>(), te.get<cx<T>>(), esz(), g.neven, g.nc, nrhs,
-                             st, gate);
+      launch_coarse_stencil<T, S>(ue.get<cx<T>>(), esz(), 0, g.neven, nullptr, 0, nullptr, 0, 0, (T)0, v, vstr,
+                                  g.neven, (T)1, C, g, nrhs, st, gate, Dinv.get<cx<T>>());
     });
     c->timed(DDAMG_KERNEL_COARSE, nrhs, [&] {
       launch_coarse_stencil<T, S>(w, wstr, g.neven, nodd(), nullptr, 0, v, vstr, g.neven, (T)1, ue.get<cx<T>>(),
@@ -696,9 +692,8 @@ struct Solver final : SolverBase {
       launch_maxpy<T, T>(xo, cs_, Vb, vsj, vsr, k, ck.y.get<cx<double>>(), m, 1.0, osz(), nrhs, nullptr, st);
     }
     // x_e = D_ee^{-1} (y_e - D_eo x_o)
-    launch_coarse_stencil<T, S>(te.get<cx<T>>(), esz(), 0, g.neven, ycv, cs_, nullptr, 0, 0, (T)0, xo, cs_, g.neven,
-                                (T)-1, C, g, nrhs, st);
-    launch_block_matvec<T>(xcv, cs_, Dinv.get<cx<T>>(), te.get<cx<T>>(), esz(), g.neven, g.nc, nrhs, st);
+    launch_coarse_stencil<T, S>(xcv, cs_, 0, g.neven, ycv, cs_, nullptr, 0, 0, (T)0, xo, cs_, g.neven, (T)-1, C, g,
+                                nrhs, st, nullptr, Dinv.get<cx<T>>());
     check_launch("coarse solve");
     ++coarse_calls;
     coarse_its_total += its;

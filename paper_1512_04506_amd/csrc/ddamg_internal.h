@@ -298,16 +298,18 @@ void launch_prolong(cx<T>* x, size_t xstr, const cx<T>* xc, size_t cstr, const B
 // coarse stencil: for internal output sites [out_first, out_first + nout):
 // out = add + cs * D_self xs + cn * sum_{slot>0} D_slot xn(nbr)
 // vectors are addressed as ptr[r * str + (ci - first) * nc + k].
-// gate (device int, optional): the kernel does nothing when *gate == 0
+// gate (device int, optional): the kernel does nothing when *gate == 0;
+// M (optional): out = M[ci - out_first] times that, for dense nc x nc
+// column-major blocks M (the even-site inverses)
 template <typename T, typename S>
 void launch_coarse_stencil(cx<T>* out, size_t ostr, int out_first, int nout, const cx<T>* add, size_t astr,
                            const cx<T>* xs, size_t xsstr, int xs_first, T cs, const cx<T>* xn, size_t xnstr,
                            int xn_first, T cn, const CoarseView<S>& cv, const Geom& g, int nrhs, hipStream_t st,
-                           const int* gate = nullptr);
+                           const int* gate = nullptr, const cx<T>* M = nullptr);
 // out[k] = M[k] x[k] for dense nc x nc column-major blocks M (k < nsites)
 template <typename T>
 void launch_block_matvec(cx<T>* out, size_t ostr, const cx<T>* M, const cx<T>* x, size_t xstr, int nsites, int nc,
-                         int nrhs, hipStream_t st, const int* gate = nullptr);
+                         int nrhs, hipStream_t st);
 
 // setup kernels
 // tws: workspace of 2 nblocks * QR_TWS_PER_AGG complex doubles (per aggregate the

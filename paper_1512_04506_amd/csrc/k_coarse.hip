@@ -1,9 +1,7 @@
 // Coarse-grid kernels: restriction y_c = R y (Eq. R), prolongation
-// x = P x_c with P = R^dag (Alg. 2), the 9-slot coarse stencil D_c
-// (Eq. cgo), dense per-site block products (D_ee^{-1}), the backward
-// couplings from the forward ones (Eq. dagger), FP16 quantisation of D_c
-// and the inversion of the even self-coupling blocks for the even/odd coarse
-// solve.
+// x = P x_c with P = R^dag (Alg. 2), the backward couplings from the forward
+// ones (Eq. dagger), FP16 quantisation of D_c and the inversion of the even
+// self-coupling blocks for the even/odd coarse solve.
 //
 // Coarse vectors are [rhs][coarse site][2 ntv] complex with coarse sites in
 // the internal order (even parity first).  D_c is [site][slot][col][row]
@@ -411,274 +409,6 @@ __global__ __launch_bounds__(256) void prolong_kernel(cx<T>* __restrict__ x, siz
   }
 }
 
-// ------------------------------------------------------------ D_c stencil
-// One workgroup per (output coarse site, group of RB right-hand sides).
-// Thread (row group, cg) accumulates RP consecutive rows over the columns
-// col = cg (mod CG) of every slot, so each input value read from LDS (a
-// broadcast) feeds RP rows; each slot's input vectors are staged in LDS,
-// and the CG partial sums of a row are combined through LDS at the end.
-// RP = 2 for few rhs (the D_c stream), 1 for 12 rhs (the partial sums of
-// two rows would cost occupancy).
-//   out = add + cs D_self xs + cn sum_{slot>0} D_slot xn(nbr)
-// With Dmat != nullptr the kernel instead computes out = Dmat[k] x[k] for
-// dense column-major per-site matrices (the even-site D_ee^{-1}).
-template <typename T, typename S, int RB, int RP>
-__global__ __launch_bounds__(256) void coarse_stencil_kernel(cx<T>* __restrict__ out, size_t ostr, int out_first,
-                                                             const cx<T>* __restrict__ add, size_t astr,
-                                                             const cx<T>* __restrict__ xs, size_t xsstr, int xs_first,
-                                                             T cs, const cx<T>* __restrict__ xn, size_t xnstr,
-                                                             int xn_first, T cn, CoarseView<S> cv,
-                                                             const cx<T>* __restrict__ Dmat, int nc, int CG,
-                                                             int nrhs, const int* gate) {
-  if (gate && *gate == 0) return;
-  extern __shared__ __attribute__((aligned(16))) char smem_raw[];
-  cx<T>* xl = reinterpret_cast<cx<T>*>(smem_raw);  // [nc][RB], later [CG][nc][RB]
-  const int ci = out_first + blockIdx.x;
-  const int r0 = blockIdx.y * RB;
-  const int nr = min(RB, nrhs - r0);
-  const int t = threadIdx.x;
-  const int ngr = nc / RP;  // nc = 2 ntv is even
-  const int rg = t % ngr, cg = t / ngr;
-  const bool act = cg < CG;
-  const int row = RP * rg;
-  const size_t nn = (size_t)nc * nc;
-  cx<T> acc[RP][RB];
-#pragma unroll
-  for (int q = 0; q < RP; ++q)
-#pragma unroll
-    for (int j = 0; j < RB; ++j) acc[q][j] = mk((T)0, (T)0);
-  const int s_beg = Dmat ? 0 : (cs != (T)0 ? 0 : 1);
-  const int s_end = Dmat ? 1 : (cn != (T)0 ? 9 : 1);
-  for (int slot = s_beg; slot < s_end; ++slot) {
-    const int nb = slot == 0 ? ci : cv.nbr[ci * 9 + slot];
-    const cx<T>* xv = slot == 0 ? xs + (size_t)(nb - xs_first) * nc : xn + (size_t)(nb - xn_first) * nc;
-    const size_t xstr = slot == 0 ? xsstr : xnstr;
-    T coef = slot == 0 ? cs : cn;
-    if (Dmat) coef = (T)1;
-    if constexpr (is_half<S>()) {
-      if (!Dmat) coef *= (T)cv.Dsc[ci * 9 + slot];
-    }
-    __syncthreads();
-    for (int e = t; e < nc * nr; e += blockDim.x) {
-      const int col = e / nr, j = e % nr;
-      xl[col * RB + j] = xv[(size_t)(r0 + j) * xstr + col];
-    }
-    __syncthreads();
-    if (act) {
-      for (int col = cg; col < nc; col += CG) {
-        cx<T> d[RP];
-        if (Dmat) {
-          const cx<T>* Mk = Dmat + (size_t)(ci - out_first) * nn + (size_t)col * nc + row;
-#pragma unroll
-          for (int q = 0; q < RP; ++q) d[q] = Mk[q];
-        } else {
-          const size_t base = ((size_t)ci * 9 + slot) * nn + (size_t)col * nc + row;
-#pragma unroll
-          for (int q = 0; q < RP; ++q) d[q] = coef * ldc<T>(cv.D, base + q);
-        }
-#pragma unroll
-        for (int j = 0; j < RB; ++j) {
-          if (j < nr) {
-            const cx<T> xj = xl[col * RB + j];
-#pragma unroll
-            for (int q = 0; q < RP; ++q) acc[q][j] = acc[q][j] + d[q] * xj;
-          }
-        }
-      }
-    }
-  }
-  __syncthreads();
-  if (act)
-#pragma unroll
-    for (int q = 0; q < RP; ++q)
-#pragma unroll
-      for (int j = 0; j < RB; ++j) xl[((size_t)cg * nc + row + q) * RB + j] = acc[q][j];
-  __syncthreads();
-  for (int e = t; e < nc * nr; e += blockDim.x) {
-    const int rw = e / nr, j = e % nr;
-    cx<T> sum = add ? add[(size_t)(r0 + j) * astr + (size_t)(ci - out_first) * nc + rw] : mk((T)0, (T)0);
-    for (int k = 0; k < CG; ++k) sum = sum + xl[((size_t)k * nc + rw) * RB + j];
-    out[(size_t)(r0 + j) * ostr + (size_t)(ci - out_first) * nc + rw] = sum;
-  }
-}
-
-// The same stencil (without Dmat) for many rhs in FP32 on the matrix cores:
-// 16x16x4 MFMA with a tile of 16 rows of D_c per wave, up to 16 rhs as the
-// columns and the components of the neighbour as K.  The A operand (16
-// consecutive rows of one column of a column-major slot block) and the B
-// operand (4 components of 16 rhs of the neighbour vector, an L2-resident
-// read) come straight from memory; the slot's factor (and FP16 scale) is
-// applied to B.  At 12 rhs the FP32 multiply-adds per byte of D_c are above
-// what the vector ALUs sustain at HBM rate; on the matrix cores the stencil
-// streams D_c.  The workgroup is one coarse site and 16 rhs, one wave per
-// row tile.
-typedef float cm_v4 __attribute__((ext_vector_type(4)));
-constexpr int CM_RHS = 16;
-
-template <typename S>
-__global__ __launch_bounds__(256) void coarse_mfma_kernel(cx<float>* __restrict__ out, size_t ostr, int out_first,
-                                                          const cx<float>* __restrict__ add, size_t astr,
-                                                          const cx<float>* __restrict__ xs, size_t xsstr,
-                                                          int xs_first, float cs, const cx<float>* __restrict__ xn,
-                                                          size_t xnstr, int xn_first, float cn, CoarseView<S> cv,
-                                                          int nc, int nrhs, const int* gate) {
-  if (gate && *gate == 0) return;
-  const int ci = out_first + blockIdx.x;
-  const int r0 = blockIdx.y * CM_RHS;
-  const int nr = min(CM_RHS, nrhs - r0);
-  const int lane = threadIdx.x & 63, rt = threadIdx.x >> 6;
-  const int li = lane & 15, lk = lane >> 4;
-  const int arow = min(rt * 16 + li, nc - 1);  // A: row li of the tile (clamped)
-  const int bj = min(li, nr - 1);               // B: rhs li (clamped)
-  const size_t nn = (size_t)nc * nc;
-  cm_v4 accr = {0.f, 0.f, 0.f, 0.f}, acci = {0.f, 0.f, 0.f, 0.f};
-  const int s_beg = cs != 0.f ? 0 : 1;
-  const int s_end = cn != 0.f ? 9 : 1;
-  for (int slot = s_beg; slot < s_end; ++slot) {
-    const int nb = slot == 0 ? ci : cv.nbr[ci * 9 + slot];
-    const cx<float>* xv = slot == 0 ? xs + (size_t)(nb - xs_first) * nc + (size_t)(r0 + bj) * xsstr
-                                    : xn + (size_t)(nb - xn_first) * nc + (size_t)(r0 + bj) * xnstr;
-    float coef = slot == 0 ? cs : cn;
-    if constexpr (is_half<S>()) coef *= cv.Dsc[ci * 9 + slot];
-    const stc_t<S>* Dp = cv.D + ((size_t)ci * 9 + slot) * nn + arow;
-#pragma unroll 4
-    for (int k0 = 0; k0 < nc; k0 += 4) {
-      const int k = k0 + lk;
-      const bool kin = k < nc;
-      const int kc = kin ? k : nc - 1;
-      const cx<float> a = ldc<float>(Dp, (size_t)kc * nc);
-      const cx<float> xb = xv[kc];
-      const float br = kin ? coef * xb.r : 0.f, bi = kin ? coef * xb.i : 0.f;
-      accr = __builtin_amdgcn_mfma_f32_16x16x4f32(a.r, br, accr, 0, 0, 0);
-      accr = __builtin_amdgcn_mfma_f32_16x16x4f32(-a.i, bi, accr, 0, 0, 0);
-      acci = __builtin_amdgcn_mfma_f32_16x16x4f32(a.r, bi, acci, 0, 0, 0);
-      acci = __builtin_amdgcn_mfma_f32_16x16x4f32(a.i, br, acci, 0, 0, 0);
-    }
-  }
-  // lane: rows 4 lk + v of the tile, rhs li
-  if (li < nr) {
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int row = rt * 16 + 4 * lk + v;
-      if (row < nc) {
-        cx<float> o = mk(accr[v], acci[v]);
-        if (add) o = o + add[(size_t)(r0 + li) * astr + (size_t)(ci - out_first) * nc + row];
-        out[(size_t)(r0 + li) * ostr + (size_t)(ci - out_first) * nc + row] = o;
-      }
-    }
-  }
-}
-
-// The same stencil for many rhs when D_c is stored in FP16: on the f16
-// matrix cores (v_mfma_f32_16x16x16_f16), which take D_c as it is stored.
-// The FP32 input vectors are split into two FP16 parts per element, x s =
-// hi + lo 2^-11 with hi = f16(x s) and lo = f16((x s - hi) 2^11), where s
-// is a power of two per rhs that brings the largest |coef D_scale x| over
-// the nine neighbour vectors of the workgroup into [1/2, 1): the two
-// products then carry the input to within 2^-22 of its largest element,
-// the FP32 accumulation is exact to FP32 rounding, and the matrix cores
-// are no longer the bound (16 K per instruction instead of 4).  Complex
-// arithmetic in real form: Yr = Ar Xr - Ai Xi, Yi = Ai Xr + Ar Xi, every
-// loaded D_c element feeding eight MFMAs (two parts, four real products).
-// Workgroup = one coarse site and 16 rhs, one wave per 16-row tile; lane
-// layout of the instruction: A[l % 16][4 (l / 16) + i], B[4 (l / 16) + i]
-// [l % 16], D[4 (l / 16) + v][l % 16].
-typedef _Float16 cm_h4 __attribute__((ext_vector_type(4)));
-
-__global__ __launch_bounds__(256) void coarse_mfma16_kernel(cx<float>* __restrict__ out, size_t ostr, int out_first,
-                                                            const cx<float>* __restrict__ add, size_t astr,
-                                                            const cx<float>* __restrict__ xs, size_t xsstr,
-                                                            int xs_first, float cs, const cx<float>* __restrict__ xn,
-                                                            size_t xnstr, int xn_first, float cn,
-                                                            CoarseView<__half> cv, int nc, int nrhs,
-                                                            const int* gate) {
-  if (gate && *gate == 0) return;
-  __shared__ int smax[CM_RHS];
-  const int ci = out_first + blockIdx.x;
-  const int r0 = blockIdx.y * CM_RHS;
-  const int nr = min(CM_RHS, nrhs - r0);
-  const int t = threadIdx.x;
-  const int lane = t & 63, rt = t >> 6;
-  const int li = lane & 15, lg = lane >> 4;
-  const size_t nn = (size_t)nc * nc;
-  const int s_beg = cs != 0.f ? 0 : 1;
-  const int s_end = cn != 0.f ? 9 : 1;
-  auto slot_vec = [&](int slot) -> const cx<float>* {
-    const int nb = slot == 0 ? ci : cv.nbr[ci * 9 + slot];
-    return slot == 0 ? xs + (size_t)(nb - xs_first) * nc : xn + (size_t)(nb - xn_first) * nc;
-  };
-  auto slot_str = [&](int slot) -> size_t { return slot == 0 ? xsstr : xnstr; };
-  auto slot_coef = [&](int slot) -> float { return (slot == 0 ? cs : cn) * cv.Dsc[ci * 9 + slot]; };
-  // per-rhs largest |coef D_scale x| over the inputs of this workgroup
-  if (t < CM_RHS) smax[t] = 0;
-  __syncthreads();
-  for (int slot = s_beg; slot < s_end; ++slot) {
-    const cx<float>* xv = slot_vec(slot);
-    const size_t xstr = slot_str(slot);
-    const float ca = fabsf(slot_coef(slot));
-    for (int e = t; e < nc * nr; e += blockDim.x) {
-      const int j = e / nc, k = e - j * nc;
-      const cx<float> v = xv[(size_t)(r0 + j) * xstr + k];
-      const float m = ca * fmaxf(fabsf(v.r), fabsf(v.i));
-      atomicMax(&smax[j], __float_as_int(m));  // non-negative floats order as their bit patterns
-    }
-  }
-  __syncthreads();
-  // this lane's rhs (B column li) and its scale
-  const int bj = min(li, nr - 1);
-  int ex = 0;
-  const float mx = __int_as_float(smax[bj]);
-  if (mx > 0.f) (void)frexpf(mx, &ex);
-  const float sc = ldexpf(1.f, -ex);
-  const int arow = min(rt * 16 + li, nc - 1);
-  cm_v4 ar_h = {0.f, 0.f, 0.f, 0.f}, ai_h = ar_h, ar_l = ar_h, ai_l = ar_h;
-  for (int slot = s_beg; slot < s_end; ++slot) {
-    const cx<float>* xv = slot_vec(slot) + (size_t)(r0 + bj) * slot_str(slot);
-    const float coef = slot_coef(slot) * sc;
-    const __half2* Dp = cv.D + ((size_t)ci * 9 + slot) * nn + arow;
-    for (int k0 = 0; k0 < nc; k0 += 16) {
-      cm_h4 a_r, a_i, a_mi, xr_h, xi_h, xr_l, xi_l;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int k = k0 + 4 * lg + i;
-        const bool kin = k < nc;
-        const int kc = kin ? k : nc - 1;
-        const __half2 a = Dp[(size_t)kc * nc];
-        a_r[i] = (_Float16)__low2half(a);
-        a_i[i] = (_Float16)__high2half(a);
-        a_mi[i] = -a_i[i];
-        const cx<float> x = xv[kc];
-        const float br = kin ? coef * x.r : 0.f, bi = kin ? coef * x.i : 0.f;
-        xr_h[i] = (_Float16)br;
-        xi_h[i] = (_Float16)bi;
-        xr_l[i] = (_Float16)((br - (float)xr_h[i]) * 2048.f);
-        xi_l[i] = (_Float16)((bi - (float)xi_h[i]) * 2048.f);
-      }
-      ar_h = __builtin_amdgcn_mfma_f32_16x16x16f16(a_r, xr_h, ar_h, 0, 0, 0);
-      ar_h = __builtin_amdgcn_mfma_f32_16x16x16f16(a_mi, xi_h, ar_h, 0, 0, 0);
-      ai_h = __builtin_amdgcn_mfma_f32_16x16x16f16(a_i, xr_h, ai_h, 0, 0, 0);
-      ai_h = __builtin_amdgcn_mfma_f32_16x16x16f16(a_r, xi_h, ai_h, 0, 0, 0);
-      ar_l = __builtin_amdgcn_mfma_f32_16x16x16f16(a_r, xr_l, ar_l, 0, 0, 0);
-      ar_l = __builtin_amdgcn_mfma_f32_16x16x16f16(a_mi, xi_l, ar_l, 0, 0, 0);
-      ai_l = __builtin_amdgcn_mfma_f32_16x16x16f16(a_i, xr_l, ai_l, 0, 0, 0);
-      ai_l = __builtin_amdgcn_mfma_f32_16x16x16f16(a_r, xi_l, ai_l, 0, 0, 0);
-    }
-  }
-  // lane: rows 4 lg + v of the tile, rhs li
-  const float inv = 1.f / sc;
-  if (li < nr) {
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int row = rt * 16 + 4 * lg + v;
-      if (row < nc) {
-        cx<float> o = mk((ar_h[v] + ar_l[v] * (1.f / 2048.f)) * inv, (ai_h[v] + ai_l[v] * (1.f / 2048.f)) * inv);
-        if (add) o = o + add[(size_t)(r0 + li) * astr + (size_t)(ci - out_first) * nc + row];
-        out[(size_t)(r0 + li) * ostr + (size_t)(ci - out_first) * nc + row] = o;
-      }
-    }
-  }
-}
-
 // ------------------------------------------------------ Eq. (dagger) fill
 // backward block of the neighbour j = i + mu:
 //   D[j][2+2mu](row, col) = s_row s_col conj(D[i][1+2mu](col, row)),
@@ -916,67 +646,6 @@ void launch_prolong(cx<T>* x, size_t xstr, const cx<T>* xc, size_t cstr, const B
   prolong_kernel<T, S><<<g.nblocks * (12 / prolong_kp<T>()), threads, lds, st>>>(x, xstr, xc, cstr, bv, g, nrhs);
 }
 
-namespace {
-template <typename T, typename S>
-void stencil_launch(cx<T>* out, size_t ostr, int out_first, int nout, const cx<T>* add, size_t astr,
-                    const cx<T>* xs, size_t xsstr, int xs_first, T cs, const cx<T>* xn, size_t xnstr, int xn_first,
-                    T cn, const CoarseView<S>& cv, const cx<T>* Dmat, int nc, int nrhs, hipStream_t st,
-                    const int* gate) {
-  if (nrhs <= 0 || nout <= 0) return;
-  // CG column groups of nc / RP row groups (at most 256 threads), fewer if
-  // the CG partial sums of RB rhs would not fit 64 KB of LDS
-  auto cg_for = [&](int rb, int rp) {
-    const int cg = std::max(1, 256 * rp / nc);
-    const int cap = (int)(65536 / ((size_t)nc * rb * sizeof(cx<T>)));
-    return std::max(1, std::min(cg, cap));
-  };
-  if (nrhs == 1) {
-    const int CG = cg_for(1, 2);
-    coarse_stencil_kernel<T, S, 1, 2><<<dim3(nout, 1), CG * (nc / 2), (size_t)CG * nc * sizeof(cx<T>), st>>>(
-        out, ostr, out_first, add, astr, xs, xsstr, xs_first, cs, xn, xnstr, xn_first, cn, cv, Dmat, nc, CG, nrhs, gate);
-  } else if (nrhs <= 4) {
-    const int CG = cg_for(4, 2);
-    coarse_stencil_kernel<T, S, 4, 2><<<dim3(nout, 1), CG * (nc / 2), (size_t)CG * nc * 4 * sizeof(cx<T>), st>>>(
-        out, ostr, out_first, add, astr, xs, xsstr, xs_first, cs, xn, xnstr, xn_first, cn, cv, Dmat, nc, CG, nrhs, gate);
-  } else {
-    if constexpr (std::is_same<T, float>::value) {
-      // many rhs in FP32: matrix cores (a wave per 16-row tile, at most 4)
-      if (!Dmat && nc <= 64) {
-        const int tiles = (nc + 15) / 16;
-        const dim3 grid(nout, (nrhs + CM_RHS - 1) / CM_RHS);
-        if constexpr (is_half<S>())
-          coarse_mfma16_kernel<<<grid, 64 * tiles, 0, st>>>(out, ostr, out_first, add, astr, xs, xsstr, xs_first,
-                                                            cs, xn, xnstr, xn_first, cn, cv, nc, nrhs, gate);
-        else
-          coarse_mfma_kernel<S><<<grid, 64 * tiles, 0, st>>>(out, ostr, out_first, add, astr, xs, xsstr, xs_first,
-                                                             cs, xn, xnstr, xn_first, cn, cv, nc, nrhs, gate);
-        return;
-      }
-    }
-    const int CG = cg_for(12, 1);
-    coarse_stencil_kernel<T, S, 12, 1><<<dim3(nout, (nrhs + 11) / 12), CG * nc, (size_t)CG * nc * 12 * sizeof(cx<T>), st>>>(
-        out, ostr, out_first, add, astr, xs, xsstr, xs_first, cs, xn, xnstr, xn_first, cn, cv, Dmat, nc, CG, nrhs, gate);
-  }
-}
-}  // namespace
-
-template <typename T, typename S>
-void launch_coarse_stencil(cx<T>* out, size_t ostr, int out_first, int nout, const cx<T>* add, size_t astr,
-                           const cx<T>* xs, size_t xsstr, int xs_first, T cs, const cx<T>* xn, size_t xnstr,
-                           int xn_first, T cn, const CoarseView<S>& cv, const Geom& g, int nrhs, hipStream_t st,
-                           const int* gate) {
-  stencil_launch<T, S>(out, ostr, out_first, nout, add, astr, xs, xsstr, xs_first, cs, xn, xnstr, xn_first, cn, cv,
-                       nullptr, g.nc, nrhs, st, gate);
-}
-
-template <typename T>
-void launch_block_matvec(cx<T>* out, size_t ostr, const cx<T>* M, const cx<T>* x, size_t xstr, int nsites, int nc,
-                         int nrhs, hipStream_t st, const int* gate) {
-  CoarseView<T> none{nullptr, nullptr, nullptr};
-  stencil_launch<T, T>(out, ostr, 0, nsites, nullptr, 0, x, xstr, 0, (T)1, nullptr, 0, 0, (T)0, none, M, nc, nrhs, st,
-                       gate);
-}
-
 template <typename T>
 void launch_dagger_fill(cx<T>* Dc, const int* nbr, const Geom& g, hipStream_t st) {
   dagger_fill_kernel<T><<<dim3(g.nblocks, 4), 256, 0, st>>>(Dc, nbr, g.nc, g.ntv);
@@ -1019,9 +688,6 @@ void launch_coarse_to_canonical(cx<double>* canon, const cx<T>* in, const Geom& 
                                       const Geom&, int, hipStream_t, int);                                           \
   template void launch_prolong<T, S>(cx<T>*, size_t, const cx<T>*, size_t, const BasisView<S>&, const Geom&, int,    \
                                      hipStream_t);                                                                   \
-  template void launch_coarse_stencil<T, S>(cx<T>*, size_t, int, int, const cx<T>*, size_t, const cx<T>*, size_t,    \
-                                            int, T, const cx<T>*, size_t, int, T, const CoarseView<S>&, const Geom&, \
-                                            int, hipStream_t, const int*);                                           \
   template void launch_quantize_coarse<T, S>(stc_t<S>*, float*, const cx<T>*, const Geom&, hipStream_t);             \
   template void launch_invert_even_blocks<T, S>(cx<T>*, const CoarseView<S>&, const Geom&, int*, hipStream_t);       \
   template void launch_export_coarse<T, S>(cx<double>*, const CoarseView<S>&, const Geom&, hipStream_t);
@@ -1031,8 +697,6 @@ INST_TS(float, __half)
 #undef INST_TS
 
 #define INST_T(T)                                                                                                   \
-  template void launch_block_matvec<T>(cx<T>*, size_t, const cx<T>*, const cx<T>*, size_t, int, int, int,            \
-                                       hipStream_t, const int*);                                                     \
   template void launch_dagger_fill<T>(cx<T>*, const int*, const Geom&, hipStream_t);                                 \
   template void launch_coarse_import<T>(cx<T>*, const cx<double>*, const Geom&, hipStream_t);                        \
   template void launch_coarse_to_internal<T>(cx<T>*, const cx<double>*, const Geom&, int, hipStream_t);              \
