@@ -346,7 +346,7 @@ struct Krylov {
   int m = 0, maxr = 0, ldh = 0;
   size_t part_cap = 0;  // entries of part
   ArnoldiState st{};
-  void alloc(int m_, int maxr_, size_t n_per_rhs) {
+  void alloc(int m_, int maxr_, size_t n_per_rhs, hipStream_t stream) {
     m = m_;
     maxr = maxr_;
     ldh = m + 1;
@@ -360,6 +360,9 @@ struct Krylov {
     abstol.alloc<double>(maxr);
     active.alloc<int>(maxr);
     any.alloc<int>(1);
+    // no rhs is active yet (the fused coarse steps count the changes)
+    HIPCK(hipMemsetAsync(active.get<int>(), 0, sizeof(int) * maxr, stream));
+    HIPCK(hipMemsetAsync(any.get<int>(), 0, sizeof(int), stream));
     kdone.alloc<int>(maxr);
     h1.alloc<cx<double>>((size_t)maxr * ldh);
     h2.alloc<cx<double>>((size_t)maxr * ldh);
@@ -537,7 +540,7 @@ struct Solver final : SolverBase {
     cw.alloc<cx<T>>((size_t)maxr * osz());
     const int mc = c->p.coarse_restart;
     cV.alloc<cx<T>>((size_t)(mc + 1) * maxr * osz());
-    ck.alloc(mc, maxr, std::max(osz(), csz()));
+    ck.alloc(mc, maxr, std::max(osz(), csz()), st);
     npart_cap = setup_norm_part_entries(g.ntv, fsz());
     npart.alloc<cx<double>>(npart_cap);
     small_its.alloc<int>(2);
@@ -629,35 +632,44 @@ struct Solver final : SolverBase {
       ++coarse_calls;
       return 0;  // the iterations are counted on the device
     }
-    // ||y_c|| per rhs -> absolute tolerance (computed on the device)
-    need_part(launch_mdot<T>(ck.n2.get<cx<double>>(), 1, ck.part.get<cx<double>>(), ck.part_cap, ycv, 0, cs_, 1, ycv,
-                             cs_, cs_, nrhs, nullptr, st),
-              "coarse right-hand side norm");
-    launch_set_abstol(ck.abstol.get<double>(), ck.n2.get<cx<double>>(), fixed > 0 ? -1.0 : c->p.coarse_tol, nrhs, st);
+    // vectors that one workgroup per rhs holds: the fused steps
+    const bool fused = arnoldi_fits<T>(osz());
+    const double tol = fixed > 0 ? -1.0 : c->p.coarse_tol;
     // b_o = y_o - D_oe D_ee^{-1} y_e
     launch_block_matvec<T>(te.get<cx<T>>(), esz(), Dinv.get<cx<T>>(), ycv, cs_, g.neven, g.nc, nrhs, st);
     launch_coarse_stencil<T, S>(bo.get<cx<T>>(), osz(), g.neven, nodd(), ycv + esz(), cs_, nullptr, 0, 0, (T)0,
                                 te.get<cx<T>>(), esz(), 0, (T)-1, C, g, nrhs, st);
     cx<T>* xo = xcv + esz();
-    HIPCK(hipMemsetAsync(xcv, 0, sizeof(cx<T>) * cs_ * nrhs, st));
+    if (!fused) {
+      // ||y_c|| per rhs -> absolute tolerance (computed on the device)
+      need_part(launch_mdot<T>(ck.n2.get<cx<double>>(), 1, ck.part.get<cx<double>>(), ck.part_cap, ycv, 0, cs_, 1, ycv,
+                               cs_, cs_, nrhs, nullptr, st),
+                "coarse right-hand side norm");
+      launch_set_abstol(ck.abstol.get<double>(), ck.n2.get<cx<double>>(), tol, nrhs, st);
+      HIPCK(hipMemsetAsync(xcv, 0, sizeof(cx<T>) * cs_ * nrhs, st));
+    }
     cx<T>* Vb = cV.get<cx<T>>();
     const size_t vsr = osz(), vsj = (size_t)maxr * osz();
     int its = 0;
     bool first = true;
     while (its < maxit) {
       // r = b_o - S x_o into V_0
-      if (first) {
-        launch_copy<T, T>(Vb, vsr, bo.get<cx<T>>(), osz(), osz(), nrhs, st);
+      if (!first) schur(cw.get<cx<T>>(), osz(), xo, cs_, nrhs);
+      if (fused) {
+        launch_coarse_start<T>(ck.st, Vb, vsr, bo.get<cx<T>>(), first ? nullptr : cw.get<cx<T>>(), osz(), osz(), xo,
+                               cs_, ycv, cs_, cs_, tol, nrhs, st);
       } else {
-        schur(cw.get<cx<T>>(), osz(), xo, cs_, nrhs);
-        launch_sub<T>(Vb, vsr, bo.get<cx<T>>(), osz(), cw.get<cx<T>>(), osz(), osz(), nrhs, st);
+        if (first)
+          launch_copy<T, T>(Vb, vsr, bo.get<cx<T>>(), osz(), osz(), nrhs, st);
+        else
+          launch_sub<T>(Vb, vsr, bo.get<cx<T>>(), osz(), cw.get<cx<T>>(), osz(), osz(), nrhs, st);
+        need_part(launch_mdot<T>(ck.n2.get<cx<double>>(), 1, ck.part.get<cx<double>>(), ck.part_cap, Vb, 0, vsr, 1, Vb,
+                                 vsr, osz(), nrhs, nullptr, st),
+                  "coarse residual norm");
+        launch_arnoldi_start(ck.st, ck.n2.get<cx<double>>(), 1, nrhs, st);
+        launch_scale<T, T>(Vb, vsr, Vb, vsr, ck.inv_h.get<double>(), osz(), nrhs, nullptr, st);
       }
       first = false;
-      need_part(launch_mdot<T>(ck.n2.get<cx<double>>(), 1, ck.part.get<cx<double>>(), ck.part_cap, Vb, 0, vsr, 1, Vb,
-                               vsr, osz(), nrhs, nullptr, st),
-                "coarse residual norm");
-      launch_arnoldi_start(ck.st, ck.n2.get<cx<double>>(), 1, nrhs, st);
-      launch_scale<T, T>(Vb, vsr, Vb, vsr, ck.inv_h.get<double>(), osz(), nrhs, nullptr, st);
       // with a fixed iteration count the schedule is known: no host reads
       if ((fixed <= 0 || sync_each_coarse_it) && !read_any_active(ck, nrhs)) break;
       int k = 0;
@@ -667,6 +679,11 @@ struct Solver final : SolverBase {
         // active flags, and the operator on "some rhs active"
         replay_step(k, nrhs, [&] {
           schur(w, vsr, Vb + (size_t)k * vsj, vsr, nrhs, ck.any.get<int>());
+          if (fused) {
+            c->timed(DDAMG_KERNEL_COARSE_GS, nrhs,
+                     [&] { launch_coarse_arnoldi<T>(ck.st, k, Vb, vsj, vsr, osz(), nrhs, st); });
+            return;
+          }
           c->timed(DDAMG_KERNEL_COARSE_GS, nrhs, [&] { cgs2(ck, Vb, vsj, vsr, k, w, vsr, osz(), nrhs); });
           launch_arnoldi_column(ck.st, k, ck.h1.get<cx<double>>(), ck.h2.get<cx<double>>(), ck.ldh,
                                 ck.n2.get<cx<double>>(), 1, nrhs, st);
@@ -688,8 +705,7 @@ struct Solver final : SolverBase {
           break;
         }
       }
-      launch_arnoldi_solve(ck.st, nrhs, st);
-      launch_maxpy<T, T>(xo, cs_, Vb, vsj, vsr, k, ck.y.get<cx<double>>(), m, 1.0, osz(), nrhs, nullptr, st);
+      launch_coarse_finish<T>(ck.st, Vb, vsj, vsr, xo, cs_, osz(), nrhs, st);
     }
     // x_e = D_ee^{-1} (y_e - D_eo x_o)
     launch_coarse_stencil<T, S>(xcv, cs_, 0, g.neven, ycv, cs_, nullptr, 0, 0, (T)0, xo, cs_, g.neven, (T)-1, C, g,
@@ -956,7 +972,7 @@ struct Solver final : SolverBase {
     ow.alloc<cx<double>>((size_t)nrhs * n);
     of.alloc<cx<double>>((size_t)nrhs * n);
     ou.alloc<cx<double>>((size_t)nrhs * n);
-    ok.alloc(m, nrhs, n);
+    ok.alloc(m, nrhs, n, st);
   }
 
   // room for basis vectors 0..kv-1 (and Z vectors 0..kv-2), contents kept

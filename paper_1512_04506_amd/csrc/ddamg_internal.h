@@ -431,7 +431,7 @@ struct ArnoldiState {
   double* inv_h;       // [r] 1 / h_{k+1,k} (0 if breakdown or inactive)
   double* abstol;      // [r] stop threshold (< 0: never)
   int* active;         // [r]
-  int* any;            // [1] 1 if some rhs is active (written with active)
+  int* any;            // [1] nonzero if some rhs is active: 1, or their number (k_arnoldi.hip)
   int* kdone;          // [r] iterations done in this cycle
   int m;
 };
@@ -444,6 +444,22 @@ void launch_arnoldi_column(ArnoldiState s, int k, const cx<double>* h1, const cx
                            const cx<double>* norm2, int ldn, int nrhs, hipStream_t st);
 // y = H(1:kd, 1:kd)^{-1} g(1:kd) per rhs (upper triangular)
 void launch_arnoldi_solve(ArnoldiState s, int nrhs, hipStream_t st);
+// The coarse GMRES on vectors of n elements per rhs, one workgroup per rhs
+// (arnoldi_fits): the start of a cycle (r = bo - cw, or bo with xo zeroed and
+// the stop threshold tol |yc| set if cw is null), Arnoldi step k on V_{k+1},
+// and the end of a cycle (xo += V y; any n)
+template <typename T>
+bool arnoldi_fits(size_t n);
+template <typename T>
+void launch_coarse_start(ArnoldiState s, cx<T>* V0, size_t vsr, const cx<T>* bo, const cx<T>* cw, size_t bstr, size_t n,
+                         cx<T>* xo, size_t xstr, const cx<T>* yc, size_t ystr, size_t n_all, double tol, int nrhs,
+                         hipStream_t st);
+template <typename T>
+void launch_coarse_arnoldi(ArnoldiState s, int k, cx<T>* Vb, size_t vsj, size_t vsr, size_t n, int nrhs,
+                           hipStream_t st);
+template <typename T>
+void launch_coarse_finish(ArnoldiState s, const cx<T>* Vb, size_t vsj, size_t vsr, cx<T>* xo, size_t xstr, size_t n,
+                          int nrhs, hipStream_t st);
 // the whole coarse solve (Alg. 2) of each rhs in one workgroup, for coarse
 // lattices small enough that launch latency bounds the multi-kernel solve
 // (restart m <= COARSE_SMALL_MAX_RESTART; its_stat[0] += iterations,

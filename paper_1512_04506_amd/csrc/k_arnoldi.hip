@@ -1,0 +1,357 @@
+// The coarse GMRES around its operator (Alg. 2), one workgroup per rhs: the
+// start of a cycle, an Arnoldi step (classical Gram-Schmidt twice, the norm,
+// the Givens rotations and the convergence test) and the end of a cycle.
+//
+// A coarse vector of a lattice up to 16^3x32 is some 10^4 elements, 100 KB
+// that lie in L2: what bounds a step is the number of dependent launches and
+// of reductions over workgroups, not the data.  One workgroup holds the new
+// vector in registers through the whole step and reduces within itself, so a
+// step is one launch instead of ten (mdot and its final sum, maxpy, twice,
+// the norm, the column, the scaling: 9 + 3 + 3, 9 + 3 + 3, 9 + 3, 4, 2 us on
+// 16^3x32, 1 rhs, N_tv 24; now 15 us there, 9.8 us for 8 rhs on 16^4 at N_tv
+// 20) and a start one instead of five.  The solves: 16^3x32 5.15 -> 4.47 ms,
+// 16^4 with 8 rhs 8.57 -> 7.94 ms.  A thread holds at most 24 elements in
+// FP32, 16 in FP64 (the registers of a 1024-lane workgroup); longer vectors
+// keep the many-workgroup kernels of k_blas.hip.
+#include "krylov_device.h"
+
+namespace ddamg {
+
+namespace {
+
+using namespace dev;
+
+constexpr int AT = 1024;
+constexpr int AW = AT / 64;
+constexpr int AJ = 4;  // inner products per reduction (8 real sums)
+
+// v[0..7] summed over the 64 lanes: three halving steps leave one value per
+// lane (value 4 (lane / 32) + 2 (lane / 16 % 2) + lane / 8 % 2), three more
+// sum it over its eight lanes: 10 exchanges instead of 48
+__device__ inline double sum8(double v[8], int lane) {
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const bool up = (lane & 32) != 0;
+    const double send = up ? v[j] : v[j + 4], keep = up ? v[j + 4] : v[j];
+    v[j] = keep + __shfl_xor(send, 32, 64);
+  }
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const bool up = (lane & 16) != 0;
+    const double send = up ? v[j] : v[j + 2], keep = up ? v[j + 2] : v[j];
+    v[j] = keep + __shfl_xor(send, 16, 64);
+  }
+  {
+    const bool up = (lane & 8) != 0;
+    const double send = up ? v[0] : v[1], keep = up ? v[1] : v[0];
+    v[0] = keep + __shfl_xor(send, 8, 64);
+  }
+  v[0] += __shfl_xor(v[0], 4, 64);
+  v[0] += __shfl_xor(v[0], 2, 64);
+  v[0] += __shfl_xor(v[0], 1, 64);
+  return v[0];
+}
+
+// out[0 .. cnt) (LDS) = the workgroup's sums of acc[0 .. AJ), cnt <= AJ; red [8][AW]
+__device__ inline void block_sum(cx<double>* out, const cx<double> acc[AJ], int cnt, double (*red)[AW]) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  double v[8];
+#pragma unroll
+  for (int q = 0; q < AJ; ++q) {
+    v[2 * q] = acc[q].r;
+    v[2 * q + 1] = acc[q].i;
+  }
+  const double s = sum8(v, lane);
+  if ((lane & 7) == 0) red[lane >> 3][w] = s;
+  __syncthreads();
+  if (threadIdx.x < 2 * cnt) {
+    double t = 0.0;
+#pragma unroll
+    for (int k = 0; k < AW; ++k) t += red[threadIdx.x][k];
+    reinterpret_cast<double*>(out)[threadIdx.x] = t;
+  }
+  __syncthreads();
+}
+
+// elements whose loads may be in flight together: the registers of a
+// 1024-lane workgroup (128) hold no more beside the vector
+template <int EPT>
+constexpr int hold() { return EPT > 16 ? 4 : 8; }
+
+// h[j] = V_j^H w, j < nv (element e = t + AT i of the workgroup's vector in w[i])
+template <typename T, int EPT>
+__device__ inline void sw_dots(cx<double>* h, const cx<T>* V, size_t vsj, int nv, const cx<T> w[EPT], int n,
+                               double (*red)[AW]) {
+  constexpr int HOLD = hold<EPT>();
+  for (int j0 = 0; j0 < nv; j0 += AJ) {
+    cx<T> acc[AJ];
+#pragma unroll
+    for (int q = 0; q < AJ; ++q) acc[q] = mk((T)0, (T)0);
+#pragma unroll
+    for (int i = 0; i < EPT; ++i) {
+      if ((int)threadIdx.x < n - AT * i) {
+#pragma unroll
+        for (int q = 0; q < AJ; ++q)
+          if (j0 + q < nv) acc[q] = cfmac(elem(V + (size_t)(j0 + q) * vsj + AT * i, threadIdx.x), w[i], acc[q]);
+      }
+      if (i % HOLD == HOLD - 1) asm volatile("" ::: "memory");
+    }
+    cx<double> d[AJ];
+#pragma unroll
+    for (int q = 0; q < AJ; ++q) d[q] = cvt<double>(acc[q]);
+    block_sum(h + j0, d, min(AJ, nv - j0), red);
+  }
+}
+// |w|^2 into h[0].r
+template <typename T, int EPT>
+__device__ inline void sw_norm2(cx<double>* h, const cx<T> w[EPT], double (*red)[AW]) {
+  cx<double> d[AJ];
+#pragma unroll
+  for (int q = 0; q < AJ; ++q) d[q] = mk(0.0, 0.0);
+  T s = (T)0;
+#pragma unroll
+  for (int i = 0; i < EPT; ++i) s += w[i].r * w[i].r + w[i].i * w[i].i;  // elements beyond n are zero
+  d[0].r = (double)s;
+  block_sum(h, d, 1, red);
+}
+// w -= sum_j h_j V_j
+template <typename T, int EPT>
+__device__ inline void sw_update(cx<T> w[EPT], const cx<double>* h, const cx<T>* V, size_t vsj, int nv, int n) {
+  constexpr int HOLD = hold<EPT>();
+  for (int j = 0; j < nv; ++j) {
+    const cx<T> c = cvt<T>(-1.0 * h[j]);
+#pragma unroll
+    for (int i = 0; i < EPT; ++i) {
+      if ((int)threadIdx.x < n - AT * i) w[i] = cfma(c, elem(V + (size_t)j * vsj + AT * i, threadIdx.x), w[i]);
+      if (i % HOLD == HOLD - 1) asm volatile("" ::: "memory");
+    }
+  }
+}
+
+// Start of a cycle: V_0 = r / |r| with r = b_o - c_w (c_w null: b_o, the
+// first cycle, whose x_o is set to zero and whose stop threshold tol |y_c|
+// is computed, tol < 0: never test), the state of arnoldi_start_kernel.
+// s.any counts the active rhs: every rhs adds the change of its own flag.
+template <typename T, int EPT>
+__global__ __launch_bounds__(AT) void coarse_start_kernel(ArnoldiState s, cx<T>* V0, size_t vsr, const cx<T>* bo,
+                                                          const cx<T>* cw, size_t bstr, int n, cx<T>* xo, size_t xstr,
+                                                          const cx<T>* yc, size_t ystr, int nc_all, double tol) {
+  __shared__ double red[8][AW];
+  __shared__ cx<double> h[AJ];
+  const int r = blockIdx.x, t = threadIdx.x, m = s.m;
+  bo += (size_t)r * bstr;
+  V0 += (size_t)r * vsr;
+  cx<T> w[EPT];
+#pragma unroll
+  for (int i = 0; i < EPT; ++i) {
+    const int e = t + AT * i;
+    w[i] = e < n ? bo[e] : mk((T)0, (T)0);
+    if (cw && e < n) w[i] = w[i] - cw[(size_t)r * bstr + e];
+  }
+  double abstol;
+  if (!cw) {
+    const cx<T>* y = yc + (size_t)r * ystr;
+    cx<double> d[AJ];
+#pragma unroll
+    for (int q = 0; q < AJ; ++q) d[q] = mk(0.0, 0.0);
+    T a = (T)0;
+    for (int e = t; e < nc_all; e += AT) a += y[e].r * y[e].r + y[e].i * y[e].i;
+    d[0].r = (double)a;
+    block_sum(h, d, 1, red);
+    abstol = tol < 0.0 ? -1.0 : tol * sqrt(fmax(h[0].r, 0.0));
+    for (int e = t; e < n; e += AT) xo[(size_t)r * xstr + e] = mk((T)0, (T)0);
+    __syncthreads();  // h is written again
+  } else {
+    abstol = s.abstol[r];
+  }
+  sw_norm2<T, EPT>(h, w, red);
+  const double beta = sqrt(fmax(h[0].r, 0.0));
+  const bool act = abstol < 0.0 ? beta > 0.0 : beta > abstol;
+  const double inv = act ? 1.0 / beta : 0.0;
+#pragma unroll
+  for (int i = 0; i < EPT; ++i) {
+    const int e = t + AT * i;
+    if (e < n) V0[e] = cvt<T>(inv * cvt<double>(w[i]));
+  }
+  if (t <= m) s.g[(size_t)r * (m + 1) + t] = mk(t == 0 ? beta : 0.0, 0.0);
+  if (t == 0) {
+    const int was = s.active[r], now = act ? 1 : 0;
+    s.abstol[r] = abstol;
+    s.active[r] = now;
+    s.inv_h[r] = inv;
+    s.kdone[r] = 0;
+    s.est[r] = beta;
+    if (now != was) atomicAdd(s.any, now - was);
+  }
+}
+
+// Arnoldi step k: w = V_{k+1} (the operator applied to V_k) orthogonalised
+// against V_0 .. V_k by classical Gram-Schmidt twice and normalised in
+// place; the column of H, the rotations and the stop test of
+// arnoldi_column_kernel, whose state of the earlier columns is read into LDS
+// beside the vector (read one after the other by one lane it took as long as
+// the inner products).  An rhs that stops keeps its vector unscaled.
+template <typename T, int EPT>
+__global__ __launch_bounds__(AT) void coarse_arnoldi_kernel(ArnoldiState s, int k, cx<T>* Vb, size_t vsj, size_t vsr,
+                                                            int n) {
+  __shared__ double red[8][AW];
+  __shared__ cx<double> h1[64 + AJ], h2[64 + AJ], hn2[AJ], sn[64], H[66], gk;
+  __shared__ double cs[64], tol, inv;
+  const int r = blockIdx.x, t = threadIdx.x, m = s.m;
+  if (!s.active[r]) {
+    if (t == 0) s.inv_h[r] = 0.0;
+    return;
+  }
+  const cx<T>* V = Vb + (size_t)r * vsr;
+  cx<T>* wg = Vb + (size_t)(k + 1) * vsj + (size_t)r * vsr;
+  cx<T> w[EPT];
+#pragma unroll
+  for (int i = 0; i < EPT; ++i) {
+    w[i] = t < n - AT * i ? elem(wg + AT * i, (unsigned)t) : mk((T)0, (T)0);
+  }
+  if (t < k) {  // k < 64
+    cs[t] = s.cs[(size_t)r * m + t].r;
+    sn[t] = s.sn[(size_t)r * m + t];
+  }
+  if (t == 64) gk = s.g[(size_t)r * (m + 1) + k];
+  if (t == 128) tol = s.abstol[r];
+  sw_dots<T, EPT>(h1, V, vsj, k + 1, w, n, red);
+  sw_update<T, EPT>(w, h1, V, vsj, k + 1, n);
+  sw_dots<T, EPT>(h2, V, vsj, k + 1, w, n, red);
+  sw_update<T, EPT>(w, h2, V, vsj, k + 1, n);
+  sw_norm2<T, EPT>(hn2, w, red);
+  if (t == 0) {
+    for (int j = 0; j <= k; ++j) H[j] = h1[j] + h2[j];
+    const double hn = sqrt(fmax(hn2[0].r, 0.0));
+    H[k + 1] = mk(hn, 0.0);
+    for (int j = 0; j < k; ++j) {
+      const cx<double> u = cs[j] * H[j] + sn[j] * H[j + 1];
+      H[j + 1] = cs[j] * H[j + 1] - conj(sn[j]) * H[j];
+      H[j] = u;
+    }
+    double c;
+    cx<double> sv, rr;
+    givens(H[k], H[k + 1], c, sv, rr);
+    H[k] = rr;
+    H[k + 1] = mk(0.0, 0.0);
+    const cx<double> gn = neg(conj(sv) * gk);
+    const double est = sqrt(cabs2(gn));
+    const bool stop = !(hn > 0.0) || (tol >= 0.0 && est <= tol) || k + 1 >= m;
+    inv = stop ? 1.0 : 1.0 / hn;
+    s.cs[(size_t)r * m + k] = mk(c, 0.0);
+    s.sn[(size_t)r * m + k] = sv;
+    s.g[(size_t)r * (m + 1) + k] = c * gk;
+    s.g[(size_t)r * (m + 1) + k + 1] = gn;
+    s.est[r] = est;
+    s.kdone[r] = k + 1;
+    s.inv_h[r] = stop ? 0.0 : 1.0 / hn;
+    if (stop) {
+      s.active[r] = 0;
+      atomicAdd(s.any, -1);
+    }
+  }
+  __syncthreads();
+  if (t <= k + 1) s.H[(size_t)r * (m + 1) * m + (size_t)k * (m + 1) + t] = H[t];
+#pragma unroll
+  for (int i = 0; i < EPT; ++i) {
+    if (t < n - AT * i) wg[AT * i + t] = cvt<T>(inv * cvt<double>(w[i]));
+  }
+}
+
+// End of a cycle: y = H^{-1} g over the kdone columns of the rhs (back
+// substitution by columns, lane j of every wave holding g_j), x_o += V y for
+// the workgroup's elements
+constexpr int FT = 256;
+constexpr int F_ELEMS = 2048;
+template <typename T>
+__global__ __launch_bounds__(FT) void coarse_finish_kernel(ArnoldiState s, const cx<T>* Vb, size_t vsj, size_t vsr,
+                                                           cx<T>* xo, size_t xstr, size_t n) {
+  __shared__ cx<T> y[64];
+  const int r = blockIdx.y, lane = threadIdx.x & 63, m = s.m;
+  const int kd = s.kdone[r];  // <= m <= 64
+  if (kd == 0) return;
+  if (threadIdx.x < 64) {
+    const cx<double>* H = s.H + (size_t)r * (m + 1) * m;
+    cx<double> g = lane < kd ? s.g[(size_t)r * (m + 1) + lane] : mk(0.0, 0.0);
+    for (int i = kd - 1; i >= 0; --i) {
+      const cx<double> hc = lane <= i ? H[(size_t)i * (m + 1) + lane] : mk(0.0, 0.0);
+      const cx<double> d = mk(__shfl(hc.r, i, 64), __shfl(hc.i, i, 64));
+      const cx<double> gi = mk(__shfl(g.r, i, 64), __shfl(g.i, i, 64));
+      const double dn = cabs2(d);
+      const cx<double> yi = dn > 0.0 ? (1.0 / dn) * (conj(d) * gi) : mk(0.0, 0.0);
+      if (lane == i) g = yi;
+      if (lane < i) g = g - hc * yi;
+    }
+    if (lane < kd) y[lane] = cvt<T>(g);
+  }
+  __syncthreads();
+  const cx<T>* V = Vb + (size_t)r * vsr;
+  cx<T>* x = xo + (size_t)r * xstr;
+  const size_t e0 = (size_t)blockIdx.x * F_ELEMS;
+  for (size_t e = e0 + threadIdx.x; e < min(n, e0 + F_ELEMS); e += FT) {
+    cx<T> acc = x[e];
+    for (int j = 0; j < kd; ++j) acc = acc + y[j] * V[(size_t)j * vsj + e];
+    x[e] = acc;
+  }
+}
+
+// elements per thread: the narrowest of 4, 8, 16, 24 (FP64 to 16: registers)
+template <typename T, typename F>
+void with_ept(size_t n, F&& f) {
+  if (n <= (size_t)AT * 4)
+    f(std::integral_constant<int, 4>());
+  else if (n <= (size_t)AT * 8)
+    f(std::integral_constant<int, 8>());
+  else if (n <= (size_t)AT * 16)
+    f(std::integral_constant<int, 16>());
+  else if constexpr (sizeof(T) == 4)
+    f(std::integral_constant<int, 24>());
+}
+
+}  // namespace
+
+template <typename T>
+bool arnoldi_fits(size_t n) {
+  return n <= (size_t)AT * (sizeof(T) == 4 ? 24 : 16);
+}
+
+template <typename T>
+void launch_coarse_start(ArnoldiState s, cx<T>* V0, size_t vsr, const cx<T>* bo, const cx<T>* cw, size_t bstr, size_t n,
+                         cx<T>* xo, size_t xstr, const cx<T>* yc, size_t ystr, size_t n_all, double tol, int nrhs,
+                         hipStream_t st) {
+  if (nrhs <= 0) return;
+  with_ept<T>(n, [&](auto e) {
+    coarse_start_kernel<T, decltype(e)::value>
+        <<<nrhs, AT, 0, st>>>(s, V0, vsr, bo, cw, bstr, (int)n, xo, xstr, yc, ystr, (int)n_all, tol);
+  });
+}
+
+template <typename T>
+void launch_coarse_arnoldi(ArnoldiState s, int k, cx<T>* Vb, size_t vsj, size_t vsr, size_t n, int nrhs,
+                           hipStream_t st) {
+  if (nrhs <= 0) return;
+  with_ept<T>(n, [&](auto e) {
+    coarse_arnoldi_kernel<T, decltype(e)::value><<<nrhs, AT, 0, st>>>(s, k, Vb, vsj, vsr, (int)n);
+  });
+}
+
+template <typename T>
+void launch_coarse_finish(ArnoldiState s, const cx<T>* Vb, size_t vsj, size_t vsr, cx<T>* xo, size_t xstr, size_t n,
+                          int nrhs, hipStream_t st) {
+  if (nrhs <= 0 || n == 0) return;
+  coarse_finish_kernel<T>
+      <<<dim3((unsigned)((n + F_ELEMS - 1) / F_ELEMS), nrhs), FT, 0, st>>>(s, Vb, vsj, vsr, xo, xstr, n);
+}
+
+#define INST(T)                                                                                                        \
+  template bool arnoldi_fits<T>(size_t);                                                                               \
+  template void launch_coarse_start<T>(ArnoldiState, cx<T>*, size_t, const cx<T>*, const cx<T>*, size_t, size_t,       \
+                                       cx<T>*, size_t, const cx<T>*, size_t, size_t, double, int, hipStream_t);        \
+  template void launch_coarse_arnoldi<T>(ArnoldiState, int, cx<T>*, size_t, size_t, size_t, int, hipStream_t);         \
+  template void launch_coarse_finish<T>(ArnoldiState, const cx<T>*, size_t, size_t, cx<T>*, size_t, size_t, int,       \
+                                        hipStream_t);
+INST(double)
+INST(float)
+#undef INST
+
+}  // namespace ddamg

@@ -6,21 +6,17 @@
 // Reductions are deterministic: each workgroup writes one partial per
 // (rhs, vector, chunk) and a second kernel sums the chunks in a fixed
 // order, so repeated runs give bitwise identical results.
-#include "ddamg_internal.h"
+#include "krylov_device.h"
 
 namespace ddamg {
 
 namespace {
 
+using namespace dev;
+
 constexpr int BT = 256;
 constexpr int JG = 8;  // basis vectors per pass over the chunk
 constexpr int MAX_MDOT_VECS = 66;  // restart length 64 plus w itself
-
-__device__ inline double wave_sum_d(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
 
 // With a single chunk the workgroup's sums are the inner products: they go
 // straight to h (row stride ldh) and no final kernel runs.
@@ -330,30 +326,6 @@ inline unsigned grid_for(size_t n) {
 }
 
 // ----------------------------------------------------- Arnoldi / Givens
-__device__ inline double cabs2(cx<double> a) { return a.r * a.r + a.i * a.i; }
-
-// rotation [c s; -conj(s) c] (c real) with c a + s b = r, -conj(s) a + c b = 0
-__device__ inline void givens(cx<double> a, cx<double> b, double& c, cx<double>& s, cx<double>& r) {
-  const double na = sqrt(cabs2(a)), nb = sqrt(cabs2(b));
-  if (nb == 0.0) {
-    c = 1.0;
-    s = mk(0.0, 0.0);
-    r = a;
-    return;
-  }
-  if (na == 0.0) {
-    c = 0.0;
-    s = (1.0 / nb) * conj(b);
-    r = mk(nb, 0.0);
-    return;
-  }
-  const double nrm = sqrt(na * na + nb * nb);
-  const cx<double> ph = (1.0 / na) * a;
-  c = na / nrm;
-  s = (1.0 / nrm) * (ph * conj(b));
-  r = nrm * ph;
-}
-
 // active flags of all rhs into *any (one 64-lane wave, nrhs <= 64)
 __device__ inline void publish_any(const ArnoldiState& s, bool act) {
   const unsigned long long b = __ballot(act);
