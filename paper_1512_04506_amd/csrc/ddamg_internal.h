@@ -285,12 +285,10 @@ void launch_sap_phase(cx<T>* x, const cx<T>* y, const GaugeView<S>& gv, const Ge
                       hipStream_t st);
 
 // restriction / prolongation; coarse output addressed as
-// out[r * ostr_r + cint(b) * ostr_b + h * ntv + a].  face_mu >= 0: only the
-// last layer of every block in direction face_mu (lc[face_mu] =
-// bs[face_mu] - 1) is summed, whatever y holds elsewhere.
+// out[r * ostr_r + cint(b) * ostr_b + h * ntv + a].
 template <typename T, typename S>
 void launch_restrict(cx<T>* out, size_t ostr_r, size_t ostr_b, const cx<T>* y, size_t ystr, const BasisView<S>& bv,
-                     const Geom& g, int nrhs, hipStream_t st, int face_mu = -1);
+                     const Geom& g, int nrhs, hipStream_t st);
 template <typename T, typename S>
 void launch_prolong(cx<T>* x, size_t xstr, const cx<T>* xc, size_t cstr, const BasisView<S>& bv, const Geom& g,
                     int nrhs, hipStream_t st);

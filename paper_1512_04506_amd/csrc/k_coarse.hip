@@ -7,34 +7,29 @@
 // the internal order (even parity first).  D_c is [site][slot][col][row]
 // (column-major 2ntv x 2ntv blocks) so that the lanes of a wave, one per row,
 // read consecutive addresses for every column.
-#include "ddamg_internal.h"
+#include <algorithm>
+
+#include "mfma_device.h"
 
 namespace ddamg {
 
 namespace {
 
-template <typename T>
-__device__ inline T wave_sum(T v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
+using namespace dev;
 
 // ----------------------------------------------------------- restriction
-// One workgroup per block, one lane per site of the block (its sites are
-// contiguous in the block-major layout, so every load is coalesced).  For a
-// tile of RT right-hand sides (kept in registers) and AT test vectors at a
-// time each lane forms the 6-component partial products of its site for
-// both chiralities; the 64 lanes of a wave are then summed by a butterfly
-// reduce-scatter (63 shuffle-adds for 32 values) and the waves through LDS.
-// Register tiles: RT right-hand sides x AT test vectors per pass, NV real
-// partial sums per lane (smaller in FP64 to stay within the register file).
-template <typename T>
-struct RTile {
-  static constexpr int RT = sizeof(T) == 8 ? 2 : 4;
-  static constexpr int AT = sizeof(T) == 8 ? 1 : 2;
-  static constexpr int NV = AT * 2 * RT * 2;
-};
+// y_c[r](block, h, a) = sum over the block's sites and the six components of
+// chirality h of conj(W_a) y_r.  It is bound by reading the basis and the
+// fields once; on lattices of a few dozen blocks by too few waves in flight,
+// so the work of a block is cut over test vectors or sites as well.
+//
+// Few rhs, on the vector units: workgroup = (block, share of the test-vector
+// tiles), one lane per site of the block (its sites are contiguous in the
+// block-major layout, so every load is coalesced), RT right-hand sides kept
+// in registers and AT test vectors at a time; the 64 lanes of a wave are
+// summed by a butterfly reduce-scatter (63 shuffle-adds for 32 values) and
+// the waves through LDS.  One rhs: 8^4 (N_tv 16, FP32) 22.3 -> 5.1 us, 16^3x32
+// (N_tv 24, FP16) 49 -> 34.6 us = 5.0 TB/s; a lone rhs used to run as four.
 
 // One halving step of the butterfly, unrolled at compile time so that every
 // register index is static: lanes with bit HALF set keep the upper half of
@@ -64,288 +59,234 @@ __device__ inline T reduce_scatter(T v[NV], int lane) {
   return v[0];
 }
 
-template <typename T, typename S>
+template <typename T, typename S, int RT, int AT>
 __global__ __launch_bounds__(256) void restrict_kernel(cx<T>* __restrict__ out, size_t ostr_r, size_t ostr_b,
                                                        const cx<T>* __restrict__ y, size_t ystr, BasisView<S> bv,
-                                                       Geom g, int nrhs, int face_mu) {
-  constexpr int RT = RTile<T>::RT, AT = RTile<T>::AT, NV = RTile<T>::NV;
-  constexpr int MAXAT = 32 / AT;  // ntv <= 32
+                                                       Geom g, int nrhs, int na) {
+  constexpr int NV = AT * 2 * RT * 2;  // real partial sums per lane
+  constexpr int MAXAT = 32 / AT;       // ntv <= 32
   __shared__ T red[4][MAXAT][NV];
-  const int ci = blockIdx.x;
+  const int wl = xcd_swizzle(blockIdx.x, gridDim.x);
+  const int ci = wl / na, share = wl - ci * na;  // the shares of a block read the same y side by side
   const int l = threadIdx.x;
   const int lane = l & 63, w = l >> 6;
   const int nw = blockDim.x >> 6;
   const bool act = l < g.vblock;
   const size_t V = g.V;
-  const size_t site = (size_t)ci * g.vblock + (act ? l : 0);
+  const unsigned site = (unsigned)(ci * g.vblock + (act ? l : 0));
   const int nat = (g.ntv + AT - 1) / AT;
-  bool onface = true;  // face_mu >= 0: only the last layer in direction face_mu holds data
-  if (face_mu >= 0) {
-    int lc[4];
-    local_coords(g, act ? l : 0, lc);
-    onface = lc[face_mu] == g.bs[face_mu] - 1;
-  }
-  for (int r0 = 0; r0 < nrhs; r0 += RT) {
-    const int nr = min(RT, nrhs - r0);
-    // Every load below is unconditional (clamped to valid addresses and
-    // masked by a factor instead): a load guarded by a value that is itself
-    // loaded would serialise the memory accesses of the whole loop.
-    cx<T> yv[RT][12];
+  const int at0 = share * nat / na, at1 = (share + 1) * nat / na;
+  // Every load below is unconditional (clamped to valid addresses and
+  // masked by a factor instead): a load guarded by a value that is itself
+  // loaded would serialise the memory accesses of the whole loop.
+  cx<T> yv[RT][12];
 #pragma unroll
-    for (int j = 0; j < RT; ++j) {
-      const bool m = act && j < nr && onface;
-      const size_t r = (size_t)min(r0 + j, nrhs - 1);
+  for (int j = 0; j < RT; ++j) {
+    const bool m = act && j < nrhs;
+    const cx<T>* yr = y + (size_t)min(j, nrhs - 1) * ystr;
 #pragma unroll
-      for (int k = 0; k < 12; ++k) {
-        const cx<T> v = y[r * ystr + (size_t)k * V + site];
-        yv[j][k] = m ? v : mk((T)0, (T)0);  // a select: the other layers may hold stale values
-      }
-    }
-    // no barrier inside this loop: each wave parks its reduced values per
-    // test-vector tile and runs ahead
-    for (int at = 0; at < nat; ++at) {
-      const int a0 = at * AT;
-      T v[NV];
-#pragma unroll
-      for (int q = 0; q < AT; ++q) {
-        const int a = min(a0 + q, g.ntv - 1);
-        T sc = (act && a0 + q < g.ntv) ? (T)1 : (T)0;
-        if constexpr (is_half<S>()) sc *= (T)bv.Wsc[(size_t)a * V + site];
-        cx<T> wv[12];
-#pragma unroll
-        for (int k = 0; k < 12; ++k) wv[k] = sc * ldc<T>(bv.W, ((size_t)a * 12 + k) * V + site);
-#pragma unroll
-        for (int h = 0; h < 2; ++h)
-#pragma unroll
-          for (int j = 0; j < RT; ++j) {
-            cx<T> acc = mk((T)0, (T)0);
-#pragma unroll
-            for (int k = 0; k < 6; ++k) acc = acc + cmulc(wv[6 * h + k], yv[j][6 * h + k]);
-            const int idx = ((q * 2 + h) * RT + j) * 2;
-            v[idx] = acc.r;
-            v[idx + 1] = acc.i;
-          }
-      }
-      const T mine = reduce_scatter<NV, T>(v, lane);
-      if (lane < NV) red[w][at][lane] = mine;
-    }
-    __syncthreads();
-    for (int e = l; e < nat * NV; e += blockDim.x) {
-      const int at = e / NV, idx = e % NV;
-      T t = (T)0;
-      for (int k = 0; k < nw; ++k) t += red[k][at][idx];
-      // idx = ((q * 2 + h) * RT + j) * 2 + part
-      const int part = idx & 1, j = (idx >> 1) % RT, h = (idx / (2 * RT)) & 1, q = idx / (4 * RT);
-      const int a = at * AT + q;
-      if (a < g.ntv && j < nr) {
-        T* o = reinterpret_cast<T*>(out + (size_t)(r0 + j) * ostr_r + (size_t)ci * ostr_b + h * g.ntv + a);
-        o[part] = t;
-      }
-    }
-    __syncthreads();
-  }
-}
-
-// Restriction on the FP32 matrix cores, for many right-hand sides: per
-// block and chirality h, C (ntv x 32 rhs) = W_h^H Y_h is a GEMM over the rows
-// (site, spin-colour of chirality h).  v_mfma_f32_32x32x2f32 takes A[i][k]
-// in lane i + 32 k and B[k][j] in lane j + 32 k and leaves C[i][j] in lane
-// j + 32 ((i / 4) % 2), register 4 (i / 8) + i % 4.  The sites along k
-// cannot be spread over the lanes, so chunks of RM_CS sites are first read
-// with coalesced site-contiguous loads into LDS (basis scaled to FP32, rows
-// (site, component)), then fed to the MFMAs from there.  The complex
-// product takes four real GEMMs: conj(W) Y = (Wr Yr + Wi Yi) + i (Wr Yi -
-// Wi Yr).  Waves 2h and 2h+1 take the two halves of each chunk's rows of
-// chirality h and are summed through LDS at the end.
-typedef float mf_v16 __attribute__((ext_vector_type(16)));
-constexpr int RM_CS = 8;                  // sites per chunk
-constexpr int RM_ROWS = RM_CS * 6;        // rows per chirality and chunk
-constexpr int RM_LD = 33;                 // padded row length (float2) in LDS
-constexpr int RESTRICT_MFMA_MIN_RHS = 16;  // fewer rhs: the VALU kernel (an MFMA tile holds 32)
-
-template <typename S>
-__global__ __launch_bounds__(256) void restrict_mfma_kernel(cx<float>* __restrict__ out, size_t ostr_r, size_t ostr_b,
-                                                            const cx<float>* __restrict__ y, size_t ystr,
-                                                            BasisView<S> bv, Geom g, int nrhs, int face_mu) {
-  __shared__ float2 Ws[2][RM_ROWS][RM_LD];  // [h][row][a]
-  __shared__ float2 Ys[2][RM_ROWS][RM_LD];  // [h][row][rhs]
-  // [h][re, im][register][lane] of the upper-half waves, in the basis
-  // staging area once the chunks are done (three workgroups fit a CU)
-  static_assert(sizeof(float) * 2 * 2 * 16 * 64 <= sizeof(float2) * 2 * RM_ROWS * RM_LD, "reduction area");
-  auto red = reinterpret_cast<float(*)[2][16][64]>(&Ws[0][0][0]);
-  const int ci = blockIdx.x;
-  const int col0 = blockIdx.y * 32;
-  const int l = threadIdx.x, lane = l & 63, w = l >> 6;
-  const int h = w >> 1, kh = w & 1;
-  const int ntv = g.ntv;
-  const int ncol = min(32, nrhs - col0);
-  const size_t V = g.V;
-  const size_t base = (size_t)ci * g.vblock;
-  const int nsites = face_mu < 0 ? g.vblock : g.vblock / g.bs[face_mu];
-  // padding columns stay zero
-  for (int e = l; e < 2 * RM_ROWS * RM_LD; e += 256) {
-    (&Ws[0][0][0])[e] = make_float2(0.f, 0.f);
-    (&Ys[0][0][0])[e] = make_float2(0.f, 0.f);
-  }
-  mf_v16 RR, II, RI, IR;
-#pragma unroll
-  for (int v = 0; v < 16; ++v) RR[v] = II[v] = RI[v] = IR[v] = 0.f;
-  const int a = lane & 31, kk = lane >> 5;
-  // staging: lane (site xl of the chunk, test vector / rhs index idx) loads
-  // all 12 components of its basis vector and of its rhs at that site (the
-  // scale once); lanes 8 apart in idx, consecutive in xl, so each load is
-  // 8-site runs
-  static_assert(RM_CS * 32 == 256, "one (site, index) pair per lane");
-  const int xl = l % RM_CS, idx = l / RM_CS;
-  const bool wok = idx < ntv, yok = idx < ncol;
-  const int ia = min(idx, ntv - 1), ir = min(idx, ncol - 1);
-  stc_t<S> wraw[12];
-  cx<float> yraw[12];
-  float sraw = 1.f;
-  auto fetch = [&](int f0) {
-    const int f = min(f0 + xl, nsites - 1);
-    const unsigned x = (unsigned)(base + (face_mu < 0 ? f : face_site(g, face_mu, g.bs[face_mu] - 1, f)));
-    const stc_t<S>* wb = bv.W + (size_t)ia * 12 * V;
-    const cx<float>* yb = y + (size_t)(col0 + ir) * ystr;
-#pragma unroll
-    for (int comp = 0; comp < 12; ++comp) {
-      wraw[comp] = elem(wb + (size_t)comp * V, x);
-      yraw[comp] = elem(yb + (size_t)comp * V, x);
-    }
-    if constexpr (is_half<S>()) sraw = elem(bv.Wsc + (size_t)ia * V, x);
-  };
-  fetch(0);
-  for (int f0 = 0; f0 < nsites; f0 += RM_CS) {
-    __syncthreads();  // previous chunk consumed (and the zero fill done)
-    {
-      const bool fin = f0 + xl < nsites;
-#pragma unroll
-      for (int comp = 0; comp < 12; ++comp) {
-        const cx<float> wv = ldc<float>(&wraw[comp], (size_t)0);
-        Ws[comp / 6][xl * 6 + comp % 6][idx] =
-            (fin && wok) ? make_float2(sraw * wv.r, sraw * wv.i) : make_float2(0.f, 0.f);
-        Ys[comp / 6][xl * 6 + comp % 6][idx] = (fin && yok) ? make_float2(yraw[comp].r, yraw[comp].i) : make_float2(0.f, 0.f);
-      }
-    }
-    if (f0 + RM_CS < nsites) fetch(f0 + RM_CS);
-    __syncthreads();
-    // rows 2t, 2t+1 of chirality h; this wave takes half of the chunk
-#pragma unroll
-    for (int t = kh * (RM_ROWS / 4); t < (kh + 1) * (RM_ROWS / 4); ++t) {
-      const float2 wv = Ws[h][2 * t + kk][a];
-      const float2 yv = Ys[h][2 * t + kk][a];
-      RR = __builtin_amdgcn_mfma_f32_32x32x2f32(wv.x, yv.x, RR, 0, 0, 0);
-      II = __builtin_amdgcn_mfma_f32_32x32x2f32(wv.y, yv.y, II, 0, 0, 0);
-      RI = __builtin_amdgcn_mfma_f32_32x32x2f32(wv.x, yv.y, RI, 0, 0, 0);
-      IR = __builtin_amdgcn_mfma_f32_32x32x2f32(wv.y, yv.x, IR, 0, 0, 0);
+    for (int k = 0; k < 12; ++k) {
+      const cx<T> v = elem(yr + (size_t)k * V, site);
+      yv[j][k] = m ? v : mk((T)0, (T)0);
     }
   }
-  __syncthreads();  // every wave is done with the staging area
-  if (kh == 1) {
+  // no barrier inside this loop: each wave parks its reduced values per
+  // test-vector tile and runs ahead
+  for (int at = at0; at < at1; ++at) {
+    const int a0 = at * AT;
+    T v[NV];
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      red[h][0][v][lane] = RR[v] + II[v];
-      red[h][1][v][lane] = RI[v] - IR[v];
+    for (int q = 0; q < AT; ++q) {
+      const int a = min(a0 + q, g.ntv - 1);
+      T sc = (act && a0 + q < g.ntv) ? (T)1 : (T)0;
+      if constexpr (is_half<S>()) sc *= (T)elem(bv.Wsc + (size_t)a * V, site);
+      cx<T> wv[12];
+#pragma unroll
+      for (int k = 0; k < 12; ++k) wv[k] = sc * ldc<T>(bv.W + ((size_t)a * 12 + k) * V, site);
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int j = 0; j < RT; ++j) {
+          cx<T> acc = mk((T)0, (T)0);
+#pragma unroll
+          for (int k = 0; k < 6; ++k) acc = acc + cmulc(wv[6 * h + k], yv[j][6 * h + k]);
+          const int idx = ((q * 2 + h) * RT + j) * 2;
+          v[idx] = acc.r;
+          v[idx + 1] = acc.i;
+        }
     }
+    const T mine = reduce_scatter<NV, T>(v, lane);
+    if (lane < NV) red[w][at - at0][lane] = mine;
   }
   __syncthreads();
-  if (kh == 0) {
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int ai = 8 * (v / 4) + 4 * kk + (v % 4);
-      const int r = lane & 31;
-      if (ai < ntv && r < ncol)
-        out[(size_t)(col0 + r) * ostr_r + (size_t)ci * ostr_b + h * ntv + ai] =
-            mk(RR[v] + II[v] + red[h][0][v][lane], RI[v] - IR[v] + red[h][1][v][lane]);
+  for (int e = l; e < (at1 - at0) * NV; e += blockDim.x) {
+    const int at = e / NV, idx = e % NV;
+    T t = (T)0;
+    for (int k = 0; k < nw; ++k) t += red[k][at][idx];
+    // idx = ((q * 2 + h) * RT + j) * 2 + part
+    const int part = idx & 1, j = (idx >> 1) % RT, h = (idx / (2 * RT)) & 1, q = idx / (4 * RT);
+    const int a = (at0 + at) * AT + q;
+    if (a < g.ntv && j < nrhs) {
+      T* o = reinterpret_cast<T*>(out + (size_t)j * ostr_r + (size_t)ci * ostr_b + h * g.ntv + a);
+      o[part] = t;
     }
   }
 }
 
-// The FP64 restriction of many rhs on the FP64 matrix cores (16x16x4
-// MFMA).  Workgroup = (block, 32 rhs); wave = (chirality h, tile of 16 test
-// vectors), each over both 16-rhs tiles and every staged chunk, so no
-// partial sums cross waves.  Chunks of RD_CS sites (rows: site x component
-// of chirality h) are staged in LDS as in the FP32 kernel, the next chunk's
-// loads in flight during the products.
-typedef double rd_v4 __attribute__((ext_vector_type(4)));
-constexpr int RD_CS = 4;
-constexpr int RD_ROWS = RD_CS * 6;
-constexpr int RESTRICT_MFMA64_MIN_RHS = 4;
-
-__global__ __launch_bounds__(256) void restrict_mfma64_kernel(cx<double>* __restrict__ out, size_t ostr_r,
-                                                              size_t ostr_b, const cx<double>* __restrict__ y,
-                                                              size_t ystr, BasisView<double> bv, Geom g, int nrhs,
-                                                              int face_mu) {
-  __shared__ cx<double> Ws[2][RD_ROWS][RM_LD];  // [h][row][a]
-  __shared__ cx<double> Ys[2][RD_ROWS][RM_LD];  // [h][row][rhs]
-  const int ci = blockIdx.x;
-  const int col0 = blockIdx.y * 32;
-  const int l = threadIdx.x, lane = l & 63, w = l >> 6;
-  const int h = w >> 1, ti = w & 1;
-  const int ntv = g.ntv;
-  const int ncol = min(32, nrhs - col0);
+// Many rhs, on the matrix cores: per block and chirality a GEMM of ntv x nrhs
+// over the rows (site, component), 16x16x4 instructions, four real products
+// per complex one.  Lane (li, lg) holds test vector (and rhs) li of a 16-wide
+// tile and, of 16 consecutive sites, the sites 4 lg .. 4 lg + 3: one 16-byte
+// load of an FP16 basis plane (32 in FP32), the four lanes of a test vector
+// side by side, and the K order (site 4 lg + i in step i) is the same for
+// both operands, so they go from memory to the matrix cores with no LDS and
+// no barrier.  The waves of a workgroup take the 16-site runs of the block in
+// turn and are added through LDS at the end.  Test vectors and rhs beyond the
+// last are read as the last and their results dropped.  Against the basis
+// staged through LDS in chunks of 8 (FP64: 4) sites behind two barriers each,
+// and the vector units below 16 rhs, which read the basis once per four:
+// 24^3x48, FP16, N_tv 24: 24 rhs 917 -> 687 us (3.5 TB/s), 12 rhs 663 -> 414
+// us (3.9 TB/s); FP64: 16^4, N_tv 20, 4 rhs 194 -> 93 us, 8^3x16, N_tv 16,
+// 16 rhs 150 -> 25 us (32 blocks: 64 workgroups of eight waves instead of 32
+// of four).
+template <typename T, typename S, int MT, int NT>
+__global__ __launch_bounds__(512) void restrict_mm_kernel(cx<T>* __restrict__ out, size_t ostr_r, size_t ostr_b,
+                                                          const cx<T>* __restrict__ y, size_t ystr, BasisView<S> bv,
+                                                          Geom g, int nrhs) {
+  using Acc = typename MmAcc<T>::type;
+  using X = stc_t<S>;
+  extern __shared__ __attribute__((aligned(16))) char smem_raw[];
+  T* red = reinterpret_cast<T*>(smem_raw);  // [nw / 2][MT NT 8][64]
+  const int wl = xcd_swizzle(blockIdx.x, gridDim.x);
+  const int ci = wl >> 1, h = wl & 1;
+  const int r0 = blockIdx.y * (16 * NT);
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6, nw = blockDim.x >> 6;
+  const int li = lane & 15, lg = lane >> 4;
+  const int ntv = g.ntv, vb = g.vblock;
   const size_t V = g.V;
-  const size_t base = (size_t)ci * g.vblock;
-  const int nsites = face_mu < 0 ? g.vblock : g.vblock / g.bs[face_mu];
-  rd_v4 RR[2], II[2], RI[2], IR[2];
+  const X* Wp[MT];
+  const float* Sp[MT];
+  const cx<T>* Yp[NT];
 #pragma unroll
-  for (int tj = 0; tj < 2; ++tj)
+  for (int m = 0; m < MT; ++m) {
+    const int a = min(li + 16 * m, ntv - 1);
+    Wp[m] = bv.W + ((size_t)a * 12 + 6 * h) * V + (size_t)ci * vb;
+    Sp[m] = is_half<S>() ? bv.Wsc + (size_t)a * V + (size_t)ci * vb : nullptr;
+  }
 #pragma unroll
-    for (int v = 0; v < 4; ++v) RR[tj][v] = II[tj][v] = RI[tj][v] = IR[tj][v] = 0.0;
-  const int i16 = lane & 15, k4 = lane >> 4;
-  const int nW = 12 * ntv * RD_CS, nY = 12 * ncol * RD_CS;
-  constexpr int NQ = (12 * 32 * RD_CS + 255) / 256;
-  cx<double> wraw[NQ], yraw[NQ];
-  auto fetch = [&](int f0) {
+  for (int n = 0; n < NT; ++n)
+    Yp[n] = y + (size_t)min(r0 + li + 16 * n, nrhs - 1) * ystr + (size_t)(6 * h) * V + (size_t)ci * vb;
+  Acc re[MT][NT], im[MT][NT];
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      const int e = l + 256 * q;
-      const int xl = e % RD_CS, rest = e / RD_CS, comp = rest % 12, idx = rest / 12;
-      const int f = min(f0 + xl, nsites - 1);
-      const size_t x = base + (face_mu < 0 ? f : face_site(g, face_mu, g.bs[face_mu] - 1, f));
-      const int ia = min(idx, ntv - 1), ir = min(idx, ncol - 1);
-      wraw[q] = bv.W[((size_t)ia * 12 + comp) * V + x];
-      yraw[q] = y[(size_t)(col0 + ir) * ystr + (size_t)comp * V + x];
-    }
-  };
-  fetch(0);
-  for (int f0 = 0; f0 < nsites; f0 += RD_CS) {
-    __syncthreads();  // previous chunk consumed
+  for (int m = 0; m < MT; ++m)
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      const int e = l + 256 * q;
-      const int xl = e % RD_CS, rest = e / RD_CS, comp = rest % 12, idx = rest / 12;
-      const bool fin = f0 + xl < nsites;
-      if (idx < 32) {
-        Ws[comp / 6][xl * 6 + comp % 6][idx] = (fin && e < nW) ? wraw[q] : mk(0.0, 0.0);
-        Ys[comp / 6][xl * 6 + comp % 6][idx] = (fin && e < nY) ? yraw[q] : mk(0.0, 0.0);
+    for (int n = 0; n < NT; ++n)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) re[m][n][v] = im[m][n][v] = (T)0;
+  for (int s0 = 16 * w; s0 < vb; s0 += 16 * nw) {
+    const int s = s0 + 4 * lg;
+    const bool full = s0 + 16 <= vb;
+    float sc[MT][4];
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) sc[m][i] = 1.f;
+    if constexpr (is_half<S>()) {
+#pragma unroll
+      for (int m = 0; m < MT; ++m) {
+        if (full) {
+          const Run<float, 4> q = load_run<float, 4>(Sp[m] + s);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) sc[m][i] = q.v[i];
+        } else {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) sc[m][i] = Sp[m][min(s + i, vb - 1)];
+        }
       }
     }
-    if (f0 + RD_CS < nsites) fetch(f0 + RD_CS);
-    __syncthreads();
+#pragma unroll 2
+    for (int k = 0; k < 6; ++k) {
+      Run<X, 4> wv[MT];
+      Run<cx<T>, 4> yv[NT];
+      if (full) {
 #pragma unroll
-    for (int k0 = 0; k0 < RD_ROWS; k0 += 4) {
-      const cx<double> wv = Ws[h][k0 + k4][16 * ti + i16];
+        for (int m = 0; m < MT; ++m) wv[m] = load_run<X, 4>(Wp[m] + (size_t)k * V + s);
 #pragma unroll
-      for (int tj = 0; tj < 2; ++tj) {
-        const cx<double> yv = Ys[h][k0 + k4][16 * tj + i16];
-        RR[tj] = __builtin_amdgcn_mfma_f64_16x16x4f64(wv.r, yv.r, RR[tj], 0, 0, 0);
-        II[tj] = __builtin_amdgcn_mfma_f64_16x16x4f64(wv.i, yv.i, II[tj], 0, 0, 0);
-        RI[tj] = __builtin_amdgcn_mfma_f64_16x16x4f64(wv.r, yv.i, RI[tj], 0, 0, 0);
-        IR[tj] = __builtin_amdgcn_mfma_f64_16x16x4f64(wv.i, yv.r, IR[tj], 0, 0, 0);
+        for (int n = 0; n < NT; ++n) yv[n] = load_run<cx<T>, 4>(Yp[n] + (size_t)k * V + s);
+      } else {  // the sites beyond the block contribute zero
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int si = min(s + i, vb - 1);
+          const bool in = s + i < vb;
+#pragma unroll
+          for (int m = 0; m < MT; ++m) {
+            wv[m].v[i] = Wp[m][(size_t)k * V + si];
+            if (!in) sc[m][i] = 0.f;
+          }
+#pragma unroll
+          for (int n = 0; n < NT; ++n) {
+            const cx<T> v = Yp[n][(size_t)k * V + si];
+            yv[n].v[i] = in ? v : mk((T)0, (T)0);
+          }
+        }
       }
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int m = 0; m < MT; ++m) {
+          cx<T> a = ldc<T>(wv[m].v, (size_t)i);
+          if (is_half<S>() || !full) a = (T)sc[m][i] * a;
+#pragma unroll
+          for (int n = 0; n < NT; ++n) {
+            const cx<T> b = yv[n].v[i];
+            re[m][n] = mm_mfma(a.r, b.r, re[m][n]);
+            im[m][n] = mm_mfma(a.r, b.i, im[m][n]);
+            re[m][n] = mm_mfma(a.i, b.i, re[m][n]);
+            im[m][n] = mm_mfma(-a.i, b.r, im[m][n]);
+          }
+        }
     }
   }
-  // conj(w) y = (RR + II, RI - IR); result row lane / 16 + 4 v, column lane % 16
+  constexpr int NP = MT * NT * 8;
+  for (int half = nw >> 1; half >= 1; half >>= 1) {
+    if (w >= half && w < 2 * half) {
+      T* p = red + (size_t)(w - half) * NP * 64 + lane;
 #pragma unroll
-  for (int tj = 0; tj < 2; ++tj)
+      for (int m = 0; m < MT; ++m)
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int a = 16 * ti + k4 + 4 * v, r = 16 * tj + i16;
-      if (a < ntv && r < ncol)
-        out[(size_t)(col0 + r) * ostr_r + (size_t)ci * ostr_b + h * ntv + a] =
-            mk(RR[tj][v] + II[tj][v], RI[tj][v] - IR[tj][v]);
+        for (int n = 0; n < NT; ++n)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            p[((m * NT + n) * 8 + v) * 64] = re[m][n][v];
+            p[((m * NT + n) * 8 + 4 + v) * 64] = im[m][n][v];
+          }
     }
+    __syncthreads();
+    if (w < half) {
+      const T* p = red + (size_t)w * NP * 64 + lane;
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int n = 0; n < NT; ++n)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            re[m][n][v] += p[((m * NT + n) * 8 + v) * 64];
+            im[m][n][v] += p[((m * NT + n) * 8 + 4 + v) * 64];
+          }
+    }
+    __syncthreads();
+  }
+  if (w != 0) return;
+#pragma unroll
+  for (int m = 0; m < MT; ++m)
+#pragma unroll
+    for (int n = 0; n < NT; ++n)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int a = 16 * m + mm_row<T>(lg, v), r = r0 + 16 * n + li;
+        if (a < ntv && r < nrhs)
+          out[(size_t)r * ostr_r + (size_t)ci * ostr_b + h * ntv + a] = mk(re[m][n][v], im[m][n][v]);
+      }
 }
 
 // ---------------------------------------------------------- prolongation
@@ -616,25 +557,50 @@ __global__ void coarse_to_canonical_kernel(cx<double>* canon, const cx<T>* in, G
 
 }  // namespace
 
+namespace {
+template <typename T, typename S, int RT, int AT>
+void restrict_few(cx<T>* out, size_t ostr_r, size_t ostr_b, const cx<T>* y, size_t ystr, const BasisView<S>& bv,
+                  const Geom& g, int nrhs, hipStream_t st) {
+  // shares of the test vectors until there are about four workgroups per CU
+  const int nat = (g.ntv + AT - 1) / AT;
+  const int na = std::max(1, std::min(nat, 1024 / g.nblocks));
+  const int threads = ((g.vblock + 63) / 64) * 64;
+  restrict_kernel<T, S, RT, AT><<<g.nblocks * na, threads, 0, st>>>(out, ostr_r, ostr_b, y, ystr, bv, g, nrhs, na);
+}
+template <typename T, typename S, int MT, int NT>
+void restrict_many(cx<T>* out, size_t ostr_r, size_t ostr_b, const cx<T>* y, size_t ystr, const BasisView<S>& bv,
+                   const Geom& g, int nrhs, hipStream_t st) {
+  const int ngr = (nrhs + 16 * NT - 1) / (16 * NT);
+  // four waves, eight while the grid is under four workgroups per CU; no more than 16-site runs
+  int nw = 2 * g.nblocks * ngr < 1024 ? 8 : 4;
+  while (nw > 1 && 8 * nw >= g.vblock) nw /= 2;
+  const size_t lds = (size_t)(nw / 2) * MT * NT * 8 * 64 * sizeof(T);
+  restrict_mm_kernel<T, S, MT, NT><<<dim3(2 * g.nblocks, ngr), 64 * nw, lds, st>>>(out, ostr_r, ostr_b, y, ystr, bv,
+                                                                                     g, nrhs);
+}
+}  // namespace
+
 template <typename T, typename S>
 void launch_restrict(cx<T>* out, size_t ostr_r, size_t ostr_b, const cx<T>* y, size_t ystr, const BasisView<S>& bv,
-                     const Geom& g, int nrhs, hipStream_t st, int face_mu) {
+                     const Geom& g, int nrhs, hipStream_t st) {
   if (nrhs <= 0) return;
-  if constexpr (std::is_same<T, float>::value) {
-    if (nrhs >= RESTRICT_MFMA_MIN_RHS) {
-      dim3 grid(g.nblocks, (nrhs + 31) / 32);
-      restrict_mfma_kernel<S><<<grid, 256, 0, st>>>(out, ostr_r, ostr_b, y, ystr, bv, g, nrhs, face_mu);
-      return;
-    }
-  } else if constexpr (std::is_same<S, double>::value) {
-    if (nrhs >= RESTRICT_MFMA64_MIN_RHS && g.ntv <= 32) {
-      dim3 grid(g.nblocks, (nrhs + 31) / 32);
-      restrict_mfma64_kernel<<<grid, 256, 0, st>>>(out, ostr_r, ostr_b, y, ystr, bv, g, nrhs, face_mu);
-      return;
-    }
-  }
-  const int threads = ((g.vblock + 63) / 64) * 64;
-  restrict_kernel<T, S><<<g.nblocks, threads, 0, st>>>(out, ostr_r, ostr_b, y, ystr, bv, g, nrhs, face_mu);
+  // up to 4 rhs in FP32 and 2 in FP64 fit the registers of the vector kernel,
+  // which then reads the basis once; the matrix cores do 16 at one price
+  constexpr bool f32 = sizeof(T) == 4;
+  if (nrhs == 1)
+    restrict_few<T, S, 1, f32 ? 4 : 2>(out, ostr_r, ostr_b, y, ystr, bv, g, nrhs, st);
+  else if (nrhs == 2)
+    restrict_few<T, S, 2, f32 ? 2 : 1>(out, ostr_r, ostr_b, y, ystr, bv, g, nrhs, st);
+  else if (f32 && nrhs <= 4)
+    restrict_few<T, S, f32 ? 4 : 2, f32 ? 2 : 1>(out, ostr_r, ostr_b, y, ystr, bv, g, nrhs, st);
+  else if (g.ntv <= 16 && nrhs <= 16)
+    restrict_many<T, S, 1, 1>(out, ostr_r, ostr_b, y, ystr, bv, g, nrhs, st);
+  else if (g.ntv <= 16)
+    restrict_many<T, S, 1, 2>(out, ostr_r, ostr_b, y, ystr, bv, g, nrhs, st);
+  else if (nrhs <= 16)
+    restrict_many<T, S, 2, 1>(out, ostr_r, ostr_b, y, ystr, bv, g, nrhs, st);
+  else
+    restrict_many<T, S, 2, 2>(out, ostr_r, ostr_b, y, ystr, bv, g, nrhs, st);
 }
 
 template <typename T, typename S>
@@ -685,7 +651,7 @@ void launch_coarse_to_canonical(cx<double>* canon, const cx<T>* in, const Geom& 
 
 #define INST_TS(T, S)                                                                                               \
   template void launch_restrict<T, S>(cx<T>*, size_t, size_t, const cx<T>*, size_t, const BasisView<S>&,            \
-                                      const Geom&, int, hipStream_t, int);                                           \
+                                      const Geom&, int, hipStream_t);                                                \
   template void launch_prolong<T, S>(cx<T>*, size_t, const cx<T>*, size_t, const BasisView<S>&, const Geom&, int,    \
                                      hipStream_t);                                                                   \
   template void launch_quantize_coarse<T, S>(stc_t<S>*, float*, const cx<T>*, const Geom&, hipStream_t);             \

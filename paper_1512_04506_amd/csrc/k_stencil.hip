@@ -13,11 +13,13 @@
 // add the waves' partial results through LDS once at the end.
 #include <algorithm>
 
-#include "ddamg_internal.h"
+#include "mfma_device.h"
 
 namespace ddamg {
 
 namespace {
+
+using namespace dev;
 
 // the operands of one call; D: the first column used at site 0 (slot s_beg),
 // dsite entries from one site to the next; ncol = nslot nc columns
@@ -190,34 +192,13 @@ __global__ __launch_bounds__(ST_T) void stencil_gemv_kernel(StArgs<T, S> a, int 
 // of them for its own 16 rows: 314 -> 193 us for 12 rhs on 8192 sites
 // at N_tv 24 (D_c 679 MB: 3.9 TB/s), 28.6 -> 11.5 us for 8 rhs on 128 sites at
 // N_tv 20 in FP32 (the eight-wave workgroups of a small grid).
-typedef float st_f4 __attribute__((ext_vector_type(4)));
-typedef double st_d4 __attribute__((ext_vector_type(4)));
 typedef _Float16 st_h4 __attribute__((ext_vector_type(4)));
 constexpr int MM_RHS = 16;
-
-template <typename T> struct StAcc;
-template <> struct StAcc<float> { using type = st_f4; };
-template <> struct StAcc<double> { using type = st_d4; };
-__device__ inline st_f4 st_mfma(float a, float b, st_f4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
-__device__ inline st_d4 st_mfma(double a, double b, st_d4 c) {
-  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-}
-// row of the 16x16 result in register v of lane group lg
-template <typename T>
-__device__ inline int st_mrow(int lg, int v) {
-  return sizeof(T) == 8 ? lg + 4 * v : 4 * lg + v;
-}
-
-// RPL consecutive entries with the alignment of one
-template <typename X, int RPL>
-struct __attribute__((packed, aligned(sizeof(X) < 8 ? sizeof(X) : 8))) MmRows {
-  X v[RPL];
-};
 
 // one chunk as loaded: entries of D_c and of the input vector of this lane's rhs
 template <typename T, typename X, int RPL>
 struct MmChunk {
-  MmRows<X, RPL> d[4];
+  Run<X, RPL> d[4];
   cx<T> x[4];
   T coef;
 };
@@ -230,7 +211,7 @@ __device__ inline void mm_load(MmChunk<T, X, RPL>& c, const X* D, const cx<T>* x
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int kc = min(k + i, nc - 1);
-    c.d[i] = *reinterpret_cast<const MmRows<X, RPL>*>(D + (size_t)kc * nc);
+    c.d[i] = load_run<X, RPL>(D + (size_t)kc * nc);
     c.x[i] = x[kc];
   }
 #pragma unroll
@@ -239,23 +220,23 @@ __device__ inline void mm_load(MmChunk<T, X, RPL>& c, const X* D, const cx<T>* x
 }
 
 template <typename T, int RPL>
-__device__ inline void mm_chunk(typename StAcc<T>::type re[RPL], typename StAcc<T>::type im[RPL],
+__device__ inline void mm_chunk(typename MmAcc<T>::type re[RPL], typename MmAcc<T>::type im[RPL],
                                 const MmChunk<T, cx<T>, RPL>& c) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const T xr = c.coef * c.x[i].r, xi = c.coef * c.x[i].i;
 #pragma unroll
     for (int t = 0; t < RPL; ++t) {
-      re[t] = st_mfma(c.d[i].v[t].r, xr, re[t]);
-      im[t] = st_mfma(c.d[i].v[t].r, xi, im[t]);
-      re[t] = st_mfma(c.d[i].v[t].i, -xi, re[t]);
-      im[t] = st_mfma(c.d[i].v[t].i, xr, im[t]);
+      re[t] = mm_mfma(c.d[i].v[t].r, xr, re[t]);
+      im[t] = mm_mfma(c.d[i].v[t].r, xi, im[t]);
+      re[t] = mm_mfma(c.d[i].v[t].i, -xi, re[t]);
+      im[t] = mm_mfma(c.d[i].v[t].i, xr, im[t]);
     }
   }
 }
 
 template <typename T, int RPL>
-__device__ inline void mm_chunk(st_f4 re[RPL], st_f4 im[RPL], const MmChunk<float, __half2, RPL>& c) {
+__device__ inline void mm_chunk(mm_f4 re[RPL], mm_f4 im[RPL], const MmChunk<float, __half2, RPL>& c) {
   float m = 0.f;
 #pragma unroll
   for (int i = 0; i < 4; ++i) m = fmaxf(m, fmaxf(fabsf(c.x[i].r), fabsf(c.x[i].i)));
@@ -276,7 +257,7 @@ __device__ inline void mm_chunk(st_f4 re[RPL], st_f4 im[RPL], const MmChunk<floa
   }
   xm_h = -xi_h;
   xm_l = -xi_l;
-  const st_f4 zero = {0.f, 0.f, 0.f, 0.f};
+  const mm_f4 zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int t = 0; t < RPL; ++t) {
     st_h4 ar, ai;
@@ -285,10 +266,10 @@ __device__ inline void mm_chunk(st_f4 re[RPL], st_f4 im[RPL], const MmChunk<floa
       ar[i] = (_Float16)__low2half(c.d[i].v[t]);
       ai[i] = (_Float16)__high2half(c.d[i].v[t]);
     }
-    st_f4 hr = __builtin_amdgcn_mfma_f32_16x16x16f16(ar, xr_h, zero, 0, 0, 0);
-    st_f4 hi = __builtin_amdgcn_mfma_f32_16x16x16f16(ar, xi_h, zero, 0, 0, 0);
-    st_f4 lr = __builtin_amdgcn_mfma_f32_16x16x16f16(ar, xr_l, zero, 0, 0, 0);
-    st_f4 li = __builtin_amdgcn_mfma_f32_16x16x16f16(ar, xi_l, zero, 0, 0, 0);
+    mm_f4 hr = __builtin_amdgcn_mfma_f32_16x16x16f16(ar, xr_h, zero, 0, 0, 0);
+    mm_f4 hi = __builtin_amdgcn_mfma_f32_16x16x16f16(ar, xi_h, zero, 0, 0, 0);
+    mm_f4 lr = __builtin_amdgcn_mfma_f32_16x16x16f16(ar, xr_l, zero, 0, 0, 0);
+    mm_f4 li = __builtin_amdgcn_mfma_f32_16x16x16f16(ar, xi_l, zero, 0, 0, 0);
     hr = __builtin_amdgcn_mfma_f32_16x16x16f16(ai, xm_h, hr, 0, 0, 0);
     hi = __builtin_amdgcn_mfma_f32_16x16x16f16(ai, xr_h, hi, 0, 0, 0);
     lr = __builtin_amdgcn_mfma_f32_16x16x16f16(ai, xm_l, lr, 0, 0, 0);
@@ -304,16 +285,16 @@ __device__ inline void mm_chunk(st_f4 re[RPL], st_f4 im[RPL], const MmChunk<floa
 // adds the waves' tiles through red ([slots][16 rhs][nc + 1]): halves of the
 // waves fold until two are left, whose tiles stay in slots 0 and 1
 template <typename T, int RPL>
-__device__ inline void mm_store(cx<T>* slot, const typename StAcc<T>::type re[RPL],
-                                const typename StAcc<T>::type im[RPL], int nc, int li, int lg) {
+__device__ inline void mm_store(cx<T>* slot, const typename MmAcc<T>::type re[RPL],
+                                const typename MmAcc<T>::type im[RPL], int nc, int li, int lg) {
 #pragma unroll
   for (int t = 0; t < RPL; ++t)
 #pragma unroll
     for (int v = 0; v < 4; ++v)
-      slot[li * (nc + 1) + min(RPL * st_mrow<T>(lg, v), nc - RPL) + t] = mk(re[t][v], im[t][v]);
+      slot[li * (nc + 1) + min(RPL * mm_row<T>(lg, v), nc - RPL) + t] = mk(re[t][v], im[t][v]);
 }
 template <typename T, int RPL>
-__device__ inline void mm_fold(cx<T>* red, typename StAcc<T>::type re[RPL], typename StAcc<T>::type im[RPL], int nc,
+__device__ inline void mm_fold(cx<T>* red, typename MmAcc<T>::type re[RPL], typename MmAcc<T>::type im[RPL], int nc,
                                int li, int lg, int w, int nw) {
   const size_t ss = (size_t)MM_RHS * (nc + 1);
   for (int half = nw / 2; half >= 2; half >>= 1) {
@@ -325,7 +306,7 @@ __device__ inline void mm_fold(cx<T>* red, typename StAcc<T>::type re[RPL], type
       for (int t = 0; t < RPL; ++t)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-          const cx<T> o = slot[li * (nc + 1) + min(RPL * st_mrow<T>(lg, v), nc - RPL) + t];
+          const cx<T> o = slot[li * (nc + 1) + min(RPL * mm_row<T>(lg, v), nc - RPL) + t];
           re[t][v] += o.r;
           im[t][v] += o.i;
         }
@@ -339,7 +320,7 @@ __device__ inline void mm_fold(cx<T>* red, typename StAcc<T>::type re[RPL], type
 template <typename T, typename S, int RPL>
 __global__ __launch_bounds__(512) void stencil_mm_kernel(StArgs<T, S> a) {
   if (a.gate && *a.gate == 0) return;
-  using Acc = typename StAcc<T>::type;
+  using Acc = typename MmAcc<T>::type;
   using X = stc_t<S>;
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
   cx<T>* red = reinterpret_cast<cx<T>*>(smem_raw);
