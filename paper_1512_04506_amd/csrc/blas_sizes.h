@@ -8,11 +8,18 @@
 
 namespace ddamg {
 
-// workgroups per rhs (chunks) of a multi-dot over n elements per rhs
-inline int blas_nchunks(size_t n) {
+// workgroups per rhs (chunks) of a multi-dot over n elements per rhs: one per
+// 8192 elements (more of them cost long vectors of many rhs their overhead:
+// 16^4, 8 rhs, 79 us against 87 at 1024 elements each), at most 512, but
+// about 1024 over all rhs while each keeps 1024 elements (8^4, one rhs: six
+// workgroups took 27 us, 48 take 7.6 us; 16^3x32: 192, 41 us, 1024, 25 us).
+inline int blas_nchunks(size_t n, int nrhs) {
   size_t c = (n + 8191) / 8192;
-  if (c < 1) c = 1;
   if (c > 512) c = 512;
+  size_t fill = nrhs > 0 ? 1024 / (size_t)nrhs : 1;
+  if (fill > (n + 1023) / 1024) fill = (n + 1023) / 1024;
+  if (c < fill) c = fill;
+  if (c < 1) c = 1;
   return (int)c;
 }
 
@@ -20,16 +27,27 @@ inline int blas_nchunks(size_t n) {
 // rhs for nrhs rhs (the fused second Gram-Schmidt pass over nvec vectors
 // writes nvec + 1 of them per rhs and chunk: the extra one is |w|^2)
 inline size_t mdot_part_entries(size_t n, int nvec, int nrhs) {
-  return (size_t)(nrhs > 0 ? nrhs : 0) * (size_t)(nvec > 0 ? nvec : 0) * (size_t)blas_nchunks(n);
+  return (size_t)(nrhs > 0 ? nrhs : 0) * (size_t)(nvec > 0 ? nvec : 0) * (size_t)blas_nchunks(n, nrhs);
+}
+
+// the largest of them over calls of up to nrhs rhs (fewer rhs take more chunks each)
+inline size_t mdot_part_capacity(size_t n, int nvec, int nrhs) {
+  size_t c = 0;
+  for (int r = 1; r <= nrhs; ++r) {
+    const size_t e = mdot_part_entries(n, nvec, r);
+    if (e > c) c = e;
+  }
+  return c;
 }
 
 // Krylov workspace of GMRES(m) on vectors of n elements per rhs: the
 // widest multi-dot is the Gram-Schmidt of a new vector against all m + 1
-// basis vectors of a cycle
-inline size_t krylov_part_entries(int m, int nrhs, size_t n) { return mdot_part_entries(n, m + 1, nrhs); }
+// basis vectors of a cycle; the norm of a coarse right-hand side runs over
+// more elements than the basis vectors, so n is the longest of a call
+inline size_t krylov_part_entries(int m, int nrhs, size_t n) { return mdot_part_capacity(n, m + 1, nrhs); }
 
 // normalisation of the ntv fine test vectors of the setup (one norm per
 // vector over 12 V elements)
-inline size_t setup_norm_part_entries(int ntv, size_t fine_elems) { return mdot_part_entries(fine_elems, 1, ntv); }
+inline size_t setup_norm_part_entries(int ntv, size_t fine_elems) { return mdot_part_capacity(fine_elems, 1, ntv); }
 
 }  // namespace ddamg

@@ -785,7 +785,7 @@ bool launch_mdot(cx<double>* h, int ldh, cx<double>* part, size_t part_cap, cons
                  int nvec, const cx<T>* w, size_t wsr, size_t n, int nrhs, const int* active, hipStream_t st) {
   if (nrhs <= 0 || nvec <= 0) return true;
   if (nvec > MAX_MDOT_VECS || mdot_part_entries(n, nvec, nrhs) > part_cap) return false;
-  const int nchunk = blas_nchunks(n);
+  const int nchunk = blas_nchunks(n, nrhs);
   const size_t chunk = (n + nchunk - 1) / nchunk;
   mdot_partial_kernel<T><<<dim3(nchunk, nrhs), BT, 0, st>>>(part, Vb, vsj, vsr, nvec, w, wsr, n, chunk, nchunk,
                                                             active, h, ldh);
@@ -807,7 +807,7 @@ bool launch_gs_fused(cx<double>* h2, int ldh, cx<double>* part, size_t part_cap,
                      const int* active, hipStream_t st) {
   if (nrhs <= 0 || nvec <= 0) return true;
   if (nvec > GS_FUSED_MAXV || mdot_part_entries(n, nvec + 1, nrhs) > part_cap) return false;
-  const int nchunk = blas_nchunks(n);
+  const int nchunk = blas_nchunks(n, nrhs);
   const size_t chunk = (n + nchunk - 1) / nchunk;
   // the narrowest instance that holds nvec basis entries per element (fewer
   // registers, more waves in flight for this streaming kernel)
@@ -832,7 +832,7 @@ bool launch_gs_defer(cx<double>* h2, int ldh, cx<double>* part, size_t part_cap,
   if (nrhs <= 0) return true;
   const int nvec = k + 1;
   if (nvec > GS_FUSED_MAXV || mdot_part_entries(n, nvec + 1, nrhs) > part_cap) return false;
-  const int nchunk = blas_nchunks(n);
+  const int nchunk = blas_nchunks(n, nrhs);
   const size_t chunk = (n + nchunk - 1) / nchunk;
   dim3 grid(nchunk, nrhs);
   const int cr = correct ? 1 : 0;
