@@ -546,15 +546,43 @@ struct Solver final : SolverBase {
     small_its.alloc<int>(2);
     HIPCK(hipMemsetAsync(small_its.get<int>(), 0, 2 * sizeof(int), st));
     u_nonzero.alloc<int>(maxr);
+    if (sap4_applies<S>(g) && c->p.max_rhs > g.ntv) {
+      sap_r.alloc<cx<T>>((size_t)c->p.max_rhs * fsz());
+      sap_f.alloc<cx<T>>((size_t)c->p.max_rhs * fsz());
+    }
   }
 
   // ------------------------------------------------------------ smoother
-  // nu cycles of red/black SAP on (x, y), Alg. 3
-  void sap(cx<T>* x, const cx<T>* y, int nrhs, int nu) {
+  // nu cycles of red/black SAP on (x, y), Alg. 3; x_zero: x is taken as zero
+  // whatever it holds
+  void sap(cx<T>* x, const cx<T>* y, int nrhs, int nu, bool x_zero = false) {
+    if (sap4_applies<S>(g) && nu > 0) {
+      // the residual of every field and the faces of the last corrections: in
+      // setup workspace that is idle whenever the smoother runs and holds
+      // N_tv fields, or in buffers of their own for more rhs
+      const bool own = nrhs > g.ntv;
+      cx<T>* r = own ? sap_r.get<cx<T>>() : ws_Z.get<cx<T>>();
+      cx<T>* faces = own ? sap_f.get<cx<T>>() : ws_Wd.get<cx<T>>();
+      Sap4Args<T, S> a{x, nullptr, r, faces, gv, g, 0, 0, c->p.n_mr, nrhs, false, false, false};
+      const int phases = 2 * nu;
+      for (int ph = 0; ph < phases; ++ph) {
+        const bool first = ph < 2;  // of its colour
+        a.colour = ph & 1;
+        a.src = first ? y : r;
+        a.mode = first && !x_zero ? SAP4_FULL : (ph == 0 ? SAP4_SRC : SAP4_FACES);
+        a.x_zero = first && x_zero;
+        a.store_r = ph + 2 < phases;
+        a.store_faces = ph + 1 < phases && (x_zero || ph >= 1);
+        c->timed(DDAMG_KERNEL_SAP, nrhs, [&] { launch_sap4<T, S>(a, st); });
+      }
+      return;
+    }
+    if (x_zero) HIPCK(hipMemsetAsync(x, 0, sizeof(cx<T>) * fsz() * nrhs, st));
     for (int n = 0; n < nu; ++n)
       for (int col = 0; col < 2; ++col)
         c->timed(DDAMG_KERNEL_SAP, nrhs, [&] { launch_sap_phase<T, S>(x, y, gv, g, col, c->p.n_mr, nrhs, st); });
   }
+  DevBuf sap_r, sap_f;
 
   // -------------------------------------------------------- coarse solve
   // S v = D_oo v - D_oe D_ee^{-1} D_eo v on odd compact vectors
@@ -805,6 +833,7 @@ struct Solver final : SolverBase {
   }
 
   void setup(const double* tv_canon) override {
+    ensure_setup_ws();  // the smoother works in it
     const int n = g.ntv;
     cx<T>* V = tv.get<cx<T>>();
     if (tv_canon)
@@ -818,8 +847,7 @@ struct Solver final : SolverBase {
     for (int k = 1; k <= c->p.init_passes; ++k) {
       tv.swap(fy);
       V = tv.get<cx<T>>();
-      HIPCK(hipMemsetAsync(V, 0, sizeof(cx<T>) * fsz() * n, st));
-      sap(V, fy.get<cx<T>>(), n, k);
+      sap(V, fy.get<cx<T>>(), n, k, true);
     }
     build_coarse();
     normalise(V, n);

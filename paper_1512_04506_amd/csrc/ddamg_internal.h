@@ -284,6 +284,33 @@ template <typename T, typename S>
 void launch_sap_phase(cx<T>* x, const cx<T>* y, const GaugeView<S>& gv, const Geom& g, int colour, int n_mr, int nrhs,
                       hipStream_t st);
 
+// The same on 4^4 blocks with the residual carried from phase to phase
+// (k_sap4.hip): src is y or the stored residual, in the mode
+//   SAP4_SRC    the residual is src
+//   SAP4_FACES  src minus the hops of the other colour's last correction,
+//               whose projections on its block faces are in faces
+//   SAP4_FULL   src - D x (src = y)
+// then the MR steps; x += e (x = e if x_zero), r = the residual after them if
+// store_r, faces = the projections of e on its own blocks' faces if
+// store_faces.  x, src, r: [nrhs][12][V]; faces: [nrhs][block][SAP4_FACE_ENTRIES].
+constexpr int SAP4_FACE_ENTRIES = 3072;  // 8 faces x 6 components x 64 sites = 12 x 256: a field's size
+enum { SAP4_SRC = 0, SAP4_FACES = 1, SAP4_FULL = 2 };
+template <typename T, typename S>
+struct Sap4Args {
+  cx<T>* x;
+  const cx<T>* src;
+  cx<T>* r;
+  cx<T>* faces;
+  GaugeView<S> gv;
+  Geom g;
+  int colour, mode, n_mr, nrhs;
+  bool x_zero, store_r, store_faces;
+};
+template <typename S>
+bool sap4_applies(const Geom& g);
+template <typename T, typename S>
+void launch_sap4(const Sap4Args<T, S>& a, hipStream_t st);
+
 // restriction / prolongation; coarse output addressed as
 // out[r * ostr_r + cint(b) * ostr_b + h * ntv + a].
 template <typename T, typename S>
