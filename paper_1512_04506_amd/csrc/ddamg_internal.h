@@ -373,7 +373,6 @@ void launch_coarse_to_canonical(cx<double>* canon, const cx<T>* in, const Geom& 
 // (k_learn.hip) fields FP32 internal [channel][12][V]; layer weights
 // [C_out][C_in][NET_NFEAT] complex
 constexpr int NET_NFEAT = 18;
-constexpr int NET_WGRAD_SPT = 16;  // sites per thread of the weight-gradient kernel
 // out = layer(in); gate_in: in holds pre-gate activations; gate_bwd_pre != NULL:
 // the transposed layer's result passed back through the gate of the
 // channels whose pre-gate activations are gate_bwd_pre

@@ -12,9 +12,11 @@
 // U_mu(x - mu)^dag phi(x - mu) under the boundary conditions of D.  Between
 // layers every channel passes the gate phi / sqrt(1 + |phi(x)|^2 / 12); the
 // kernels apply it when they load a hidden layer's stored pre-gate output.
+#include <algorithm>
 #include <cmath>
 
 #include "dirac_device.h"
+#include "mfma_device.h"
 
 namespace ddamg {
 
@@ -23,35 +25,6 @@ namespace {
 using namespace dev;
 constexpr int NTPB = 256;
 constexpr int NFEAT = 18;
-
-// g_mu p in the chiral basis: a signed / phased permutation of the spins
-template <int MU>
-__device__ inline void gamma_mul(cx<float> o[4][3], const cx<float> p[4][3]) {
-#pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    if (MU == 0) {
-      o[0][c] = times_mi(p[3][c]);
-      o[1][c] = times_mi(p[2][c]);
-      o[2][c] = times_i(p[1][c]);
-      o[3][c] = times_i(p[0][c]);
-    } else if (MU == 1) {
-      o[0][c] = neg(p[3][c]);
-      o[1][c] = p[2][c];
-      o[2][c] = p[1][c];
-      o[3][c] = neg(p[0][c]);
-    } else if (MU == 2) {
-      o[0][c] = times_mi(p[2][c]);
-      o[1][c] = times_i(p[3][c]);
-      o[2][c] = times_i(p[0][c]);
-      o[3][c] = times_mi(p[1][c]);
-    } else {
-      o[0][c] = neg(p[2][c]);
-      o[1][c] = neg(p[3][c]);
-      o[2][c] = neg(p[0][c]);
-      o[3][c] = neg(p[1][c]);
-    }
-  }
-}
 
 // spinor of one channel (plane base f = channel * 12 V) at internal site s,
 // times sign; GATE: the stored value is a pre-gate activation, apply the gate
@@ -87,46 +60,47 @@ __device__ inline void transport(cx<float> t[4][3], const cx<float> p[4][3], con
     }
 }
 
-// the transported neighbour of hop (MU, FWD) of channel plane f at site p
+// The layers and their weight gradients run on the FP32 matrix cores
+// (16x16x4): both are products over channels of spinor fields that a lane
+// transports itself.  g_mu is a phase times a permutation of the spins, so
+// g_mu T_h phi is the same operand at another spin with the phase on the
+// other side.
+struct SpinMap {
+  int src[4];    // (g_mu p)[s] = i^phase[s] p[src[s]]
+  int phase[4];
+};
+template <int MU>
+__device__ constexpr SpinMap gamma_map() {
+  if constexpr (MU == 0) return {{3, 2, 1, 0}, {3, 3, 1, 1}};
+  if constexpr (MU == 1) return {{3, 2, 1, 0}, {2, 0, 0, 2}};
+  if constexpr (MU == 2) return {{2, 3, 0, 1}, {3, 1, 1, 3}};
+  return {{2, 3, 0, 1}, {2, 2, 2, 2}};
+}
+
+// re + i im += (wr + i wi) x, with n... the negatives (the instructions negate nothing)
+__device__ inline void mm_c(mm_f4& re, mm_f4& im, float wr, float wi, float nwi, cx<float> x) {
+  re = mm_mfma(wr, x.r, re);
+  im = mm_mfma(wr, x.i, im);
+  re = mm_mfma(nwi, x.i, re);
+  im = mm_mfma(wi, x.r, im);
+}
+// the same with the weight times i^ph
+__device__ inline void mm_cp(mm_f4& re, mm_f4& im, int ph, cx<float> w, cx<float> nw, cx<float> x) {
+  if (ph == 0)
+    mm_c(re, im, w.r, w.i, nw.i, x);
+  else if (ph == 1)
+    mm_c(re, im, nw.i, w.r, nw.r, x);
+  else if (ph == 2)
+    mm_c(re, im, nw.r, nw.i, w.i, x);
+  else
+    mm_c(re, im, w.i, nw.r, w.r, x);
+}
+
+// hop (MU, FWD) of every input channel for 16 sites and 16 output channels
 template <int MU, bool FWD, bool GATE>
-__device__ inline void hop_feature(cx<float> t[4][3], const cx<float>* f, const SitePos& p, const Geom& g,
-                                   const GaugeView<float>& gv, size_t V) {
-  cx<float> ph[4][3], U[3][3];
-  if (FWD) {
-    const int sn = nbr_fwd(g, p, MU);
-    const bool wrap = MU == 3 && p.lc[3] == g.bs[3] - 1 && p.bc[3] == g.NB[3] - 1;
-    load_in<GATE>(ph, f, sn, V, wrap ? -1.f : 1.f);
-    load_link<float, float>(U, gv, MU, p.S, V);
-  } else {
-    const int sb = nbr_bwd(g, p, MU);
-    const bool wrap = MU == 3 && p.lc[3] == 0 && p.bc[3] == 0;
-    load_in<GATE>(ph, f, sb, V, wrap ? -1.f : 1.f);
-    load_link<float, float>(U, gv, MU, sb, V);
-  }
-  transport<FWD>(t, ph, U);
-}
-
-template <int OG>
-__device__ inline void mix_hop(cx<float> acc[OG][4][3], const cx<float> t[4][3], const cx<float> gt[4][3],
-                               const cx<float>* const w[OG], int k) {
-#pragma unroll
-  for (int q = 0; q < OG; ++q) {
-    const cx<float> cw = w[q][k], dw = w[q][k + 1];
-#pragma unroll
-    for (int sp = 0; sp < 4; ++sp)
-#pragma unroll
-      for (int c = 0; c < 3; ++c) acc[q][sp][c] = cfma(dw, gt[sp][c], cfma(cw, t[sp][c], acc[q][sp][c]));
-  }
-}
-
-// hop (MU, FWD) of every input channel for the OG outputs: the link, the
-// neighbour index and its boundary sign are loaded once, then each channel's
-// neighbour spinor is transported and mixed in (the link loads dominated the
-// traffic when they were repeated for every input channel)
-template <int MU, bool FWD, int OG, bool GATE>
-__device__ inline void layer_hop_all(cx<float> acc[OG][4][3], const cx<float>* in, int cin,
-                                     const cx<float>* const w0[OG], const SitePos& p, const Geom& g,
-                                     const GaugeView<float>& gv, size_t V) {
+__device__ inline void layer_hop(mm_f4 re[12], mm_f4 im[12], const cx<float>* in, int cin, const cx<float>* Wi,
+                                 const SitePos& p, const Geom& g, const GaugeView<float>& gv, size_t V, int lg) {
+  constexpr SpinMap G = gamma_map<MU>();
   cx<float> U[3][3];
   int sn;
   float sign;
@@ -139,97 +113,132 @@ __device__ inline void layer_hop_all(cx<float> acc[OG][4][3], const cx<float>* i
     sign = MU == 3 && p.lc[3] == 0 && p.bc[3] == 0 ? -1.f : 1.f;
     load_link<float, float>(U, gv, MU, sn, V);
   }
-  const int k = 2 + 2 * (2 * MU + (FWD ? 0 : 1));
-  for (int j = 0; j < cin; ++j) {
-    cx<float> ph[4][3], t[4][3], gt[4][3];
+  constexpr int k = 2 + 2 * (2 * MU + (FWD ? 0 : 1));
+  for (int j0 = 0; j0 < cin; j0 += 4) {
+    const int j = min(j0 + lg, cin - 1);
+    const float on = j0 + lg < cin ? 1.f : 0.f;  // channels beyond the last weigh nothing
+    const Run<cx<float>, 2> w = load_run<cx<float>, 2>(Wi + (size_t)j * NFEAT + k);
+    cx<float> ph[4][3], t[4][3];
     load_in<GATE>(ph, in + (size_t)j * 12 * V, sn, V, sign);
     transport<FWD>(t, ph, U);
-    gamma_mul<MU>(gt, t);
-    const cx<float>* w[OG];
+    const cx<float> c = on * w.v[0], d = on * w.v[1], nc = neg(c), nd = neg(d);
 #pragma unroll
-    for (int q = 0; q < OG; ++q) w[q] = w0[q] + (size_t)j * NFEAT;
-    mix_hop<OG>(acc, t, gt, w, k);
+    for (int sp = 0; sp < 4; ++sp)
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        mm_c(re[3 * sp + q], im[3 * sp + q], c.r, c.i, nc.i, t[sp][q]);
+        mm_cp(re[3 * sp + q], im[3 * sp + q], G.phase[sp], d, nd, t[G.src[sp]][q]);
+      }
   }
   asm volatile("" ::: "memory");
 }
 
-// out[i] = sum_jk W[i][j][k] F_k(in_j) for the OG output channels
-// i0 .. i0 + OG - 1 of this workgroup (blockIdx.y); one thread per site.
+// out[i] = sum_jk W[i][j][k] F_k(in_j) for 16 output channels (blockIdx.y).
+// A wave takes 16 sites: lane (li, lg) transports channel 4 jj + lg at site
+// li, which makes it the B operand (K = 4 channels, N = 16 sites) of the
+// products with the weights of 16 outputs, one tile per spin and colour; the
+// result holds four output channels of a site with all twelve components, as
+// the gate's backward wants them.  Bound: the FP32 matrix cores (816 products
+// of 32 cycles per 16 sites and 4 channels beside some 1200 cycles of
+// vector work).  16 -> 16 channels on 16^4: 420 us (first layer without gate
+// 270), from 850 (500) with a lane per site and four output channels that
+// repeated loads, gate and transport for each group of four.  The sum runs in
+// two chains of half the length: one chain of this order was up to 1.24e-6
+// off in the gradients where the vector units were 1.19e-6, two are 0.88e-6.
 // GATE_IN: the input planes hold pre-gate activations (gate applied on load).
 // GATE_BWD: the result is the gradient with respect to the gate's output of
 // the channels whose pre-gate values are in pre; store instead the gradient
 // with respect to those pre-gate values (the gate's backward).
-template <int OG, bool GATE_IN, bool GATE_BWD>
-__global__ __launch_bounds__(NTPB) __attribute__((amdgpu_waves_per_eu(3))) void net_layer_kernel(cx<float>* __restrict__ out, const cx<float>* __restrict__ in,
-                                                         const cx<float>* __restrict__ W, int cin, int cout,
-                                                         GaugeView<float> gv, Geom g,
-                                                         const cx<float>* __restrict__ pre) {
-  const int s = blockIdx.x * NTPB + threadIdx.x;
-  if (s >= g.V) return;
-  const int i0 = blockIdx.y * OG;
+template <bool GATE_IN, bool GATE_BWD>
+__global__ __launch_bounds__(NTPB, 2) void net_layer_kernel(cx<float>* __restrict__ out,
+                                                            const cx<float>* __restrict__ in,
+                                                            const cx<float>* __restrict__ W, int cin, int cout,
+                                                            GaugeView<float> gv, Geom g,
+                                                            const cx<float>* __restrict__ pre) {
+  const int lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
+  const int unit = blockIdx.x * (NTPB / 64) + (threadIdx.x >> 6);
+  if (unit * 16 >= g.V) return;  // V is a multiple of 16: two or more blocks in each direction
+  const int s = unit * 16 + li;
+  const int i0 = blockIdx.y * 16;
   const size_t V = g.V;
   const SitePos p = site_pos(g, s);
-  cx<float> acc[OG][4][3];
+  const cx<float>* Wi = W + (size_t)min(i0 + li, cout - 1) * cin * NFEAT;  // rows beyond the last are dropped
+  mm_f4 re[12], im[12];
 #pragma unroll
-  for (int q = 0; q < OG; ++q)
+  for (int c = 0; c < 12; ++c)
 #pragma unroll
-    for (int sp = 0; sp < 4; ++sp)
-#pragma unroll
-      for (int c = 0; c < 3; ++c) acc[q][sp][c] = mk(0.f, 0.f);
-  // weights of the OG outputs for input channel 0; channel j is j * NFEAT on
-  const cx<float>* w0[OG];
-#pragma unroll
-  for (int q = 0; q < OG; ++q) w0[q] = W + (size_t)min(i0 + q, cout - 1) * cin * NFEAT;
-  for (int j = 0; j < cin; ++j) {
+    for (int v = 0; v < 4; ++v) re[c][v] = im[c][v] = 0.f;
+  for (int j0 = 0; j0 < cin; j0 += 4) {
+    const int j = min(j0 + lg, cin - 1);
+    const float on = j0 + lg < cin ? 1.f : 0.f;
+    const Run<cx<float>, 2> w = load_run<cx<float>, 2>(Wi + (size_t)j * NFEAT);
     cx<float> ph[4][3];
     load_in<GATE_IN>(ph, in + (size_t)j * 12 * V, s, V, 1.f);
     // a phi + b g5 phi, g5 = diag(-1, -1, +1, +1)
+    const cx<float> lo = on * (w.v[0] - w.v[1]), hi = on * (w.v[0] + w.v[1]);
 #pragma unroll
-    for (int q = 0; q < OG; ++q) {
-      const cx<float> a = w0[q][(size_t)j * NFEAT], b = w0[q][(size_t)j * NFEAT + 1];
-      const cx<float> lo = a - b, hi = a + b;
-#pragma unroll
-      for (int sp = 0; sp < 4; ++sp)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) acc[q][sp][c] = cfma(sp < 2 ? lo : hi, ph[sp][c], acc[q][sp][c]);
+    for (int c = 0; c < 12; ++c) {
+      const cx<float> ww = c < 6 ? lo : hi;
+      mm_c(re[c], im[c], ww.r, ww.i, -ww.i, ph[c / 3][c % 3]);
     }
   }
-  layer_hop_all<0, true, OG, GATE_IN>(acc, in, cin, w0, p, g, gv, V);
-  layer_hop_all<0, false, OG, GATE_IN>(acc, in, cin, w0, p, g, gv, V);
-  layer_hop_all<1, true, OG, GATE_IN>(acc, in, cin, w0, p, g, gv, V);
-  layer_hop_all<1, false, OG, GATE_IN>(acc, in, cin, w0, p, g, gv, V);
-  layer_hop_all<2, true, OG, GATE_IN>(acc, in, cin, w0, p, g, gv, V);
-  layer_hop_all<2, false, OG, GATE_IN>(acc, in, cin, w0, p, g, gv, V);
-  layer_hop_all<3, true, OG, GATE_IN>(acc, in, cin, w0, p, g, gv, V);
-  layer_hop_all<3, false, OG, GATE_IN>(acc, in, cin, w0, p, g, gv, V);
+  layer_hop<0, true, GATE_IN>(re, im, in, cin, Wi, p, g, gv, V, lg);
+  layer_hop<0, false, GATE_IN>(re, im, in, cin, Wi, p, g, gv, V, lg);
+  layer_hop<1, true, GATE_IN>(re, im, in, cin, Wi, p, g, gv, V, lg);
+  layer_hop<1, false, GATE_IN>(re, im, in, cin, Wi, p, g, gv, V, lg);
+  // two chains of half the length: the first half of the sum waits, as far as
+  // they go in registers, the other components in the output planes
+  constexpr int HOLD = 8;
+  mm_f4 hr[HOLD], hi[HOLD];
 #pragma unroll
-  for (int q = 0; q < OG; ++q) {
-    const int i = i0 + q;
-    if (i >= cout) break;
+  for (int c = 0; c < 12; ++c)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int i = i0 + 4 * lg + v;
+      if (c < HOLD) {
+        hr[c][v] = re[c][v];
+        hi[c][v] = im[c][v];
+      } else if (i < cout) {
+        out[((size_t)i * 12 + c) * V + s] = mk(re[c][v], im[c][v]);
+      }
+      re[c][v] = im[c][v] = 0.f;
+    }
+  layer_hop<2, true, GATE_IN>(re, im, in, cin, Wi, p, g, gv, V, lg);
+  layer_hop<2, false, GATE_IN>(re, im, in, cin, Wi, p, g, gv, V, lg);
+  layer_hop<3, true, GATE_IN>(re, im, in, cin, Wi, p, g, gv, V, lg);
+  layer_hop<3, false, GATE_IN>(re, im, in, cin, Wi, p, g, gv, V, lg);
+  // lane: site li, output channels i0 + 4 lg + v
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int i = i0 + 4 * lg + v;
+    if (i >= cout) continue;
+#pragma unroll
+    for (int c = 0; c < 12; ++c) {
+      const cx<float> o = c < HOLD ? mk(hr[c][v], hi[c][v]) : out[((size_t)i * 12 + c) * V + s];
+      re[c][v] += o.r;
+      im[c][v] += o.i;
+    }
+    float gg = 1.f, cr = 0.f;
+    cx<float> ps[12];
     if (GATE_BWD) {
       // gradient through psi -> psi g(n), n = |psi|^2 / 12, g = (1 + n)^(-1/2):
       // g gam + (rho g'(n) / 6) psi with rho = Re <psi, gam>, g' = -g^3 / 2
-      cx<float> ps[4][3];
       float n = 0.f, rho = 0.f;
 #pragma unroll
-      for (int sp = 0; sp < 4; ++sp)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-          ps[sp][c] = elem(pre + ((size_t)i * 12 + 3 * sp + c) * V, (unsigned)s);
-          n += ps[sp][c].r * ps[sp][c].r + ps[sp][c].i * ps[sp][c].i;
-          rho += ps[sp][c].r * acc[q][sp][c].r + ps[sp][c].i * acc[q][sp][c].i;
-        }
-      const float gg = 1.f / sqrtf(1.f + n * (1.f / 12.f));
-      const float cr = rho * (-0.5f * gg * gg * gg) * (1.f / 6.f);
-#pragma unroll
-      for (int sp = 0; sp < 4; ++sp)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) acc[q][sp][c] = gg * acc[q][sp][c] + cr * ps[sp][c];
+      for (int c = 0; c < 12; ++c) {
+        ps[c] = elem(pre + ((size_t)i * 12 + c) * V, (unsigned)s);
+        n += ps[c].r * ps[c].r + ps[c].i * ps[c].i;
+        rho += ps[c].r * re[c][v] + ps[c].i * im[c][v];
+      }
+      gg = 1.f / sqrtf(1.f + n * (1.f / 12.f));
+      cr = rho * (-0.5f * gg * gg * gg) * (1.f / 6.f);
     }
 #pragma unroll
-    for (int sp = 0; sp < 4; ++sp)
-#pragma unroll
-      for (int c = 0; c < 3; ++c) out[((size_t)i * 12 + 3 * sp + c) * V + s] = acc[q][sp][c];
+    for (int c = 0; c < 12; ++c) {
+      cx<float> o = mk(re[c][v], im[c][v]);
+      if (GATE_BWD) o = gg * o + cr * ps[c];
+      out[((size_t)i * 12 + c) * V + s] = o;
+    }
   }
 }
 
@@ -248,110 +257,188 @@ __global__ void net_transpose_kernel(cx<float>* Wb, const cx<float>* W, int cin,
   Wb[((size_t)j * cout + i) * NFEAT + k] = conj(W[((size_t)i * cin + j) * NFEAT + ks]);
 }
 
-__device__ inline float wave_sum_f(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-
-// <a, b> summed over spin and colour
-__device__ inline cx<float> sdot(const cx<float> a[4][3], const cx<float> b[4][3]) {
-  cx<float> s = mk(0.f, 0.f);
-#pragma unroll
-  for (int sp = 0; sp < 4; ++sp)
-#pragma unroll
-    for (int c = 0; c < 3; ++c) s = cfmac(a[sp][c], b[sp][c], s);
-  return s;
-}
-
-template <int MU, int OG, bool GATE>
-__device__ inline void wgrad_hops(cx<float> acc[OG][NFEAT], const cx<float>* f, const cx<float> gm[OG][4][3],
-                                  const SitePos& p, const Geom& g, const GaugeView<float>& gv, size_t V) {
-  cx<float> t[4][3], gt[4][3];
-  hop_feature<MU, true, GATE>(t, f, p, g, gv, V);
-  gamma_mul<MU>(gt, t);
-#pragma unroll
-  for (int q = 0; q < OG; ++q) {
-    acc[q][2 + 4 * MU] = acc[q][2 + 4 * MU] + sdot(t, gm[q]);
-    acc[q][3 + 4 * MU] = acc[q][3 + 4 * MU] + sdot(gt, gm[q]);
-  }
-  asm volatile("" ::: "memory");
-  hop_feature<MU, false, GATE>(t, f, p, g, gv, V);
-  gamma_mul<MU>(gt, t);
-#pragma unroll
-  for (int q = 0; q < OG; ++q) {
-    acc[q][4 + 4 * MU] = acc[q][4 + 4 * MU] + sdot(t, gm[q]);
-    acc[q][5 + 4 * MU] = acc[q][5 + 4 * MU] + sdot(gt, gm[q]);
-  }
-  asm volatile("" ::: "memory");
-}
-
 // Partial weight gradients Gamma_w[i][j][k] = sum_x <F_k(in_j)(x), gam_i(x)>
-// over the sites of one chunk (blockIdx.x, spt sites per thread), for the
-// input channel j and the OG output channels of job blockIdx.y:
-// part[(chunk * cout + i) * cin + j][k] (FP64).
-template <int OG, bool GATE_IN>
-__global__ __launch_bounds__(NTPB) void net_wgrad_kernel(cx<double>* __restrict__ part,
-                                                         const cx<float>* __restrict__ in,
-                                                         const cx<float>* __restrict__ gam, int cin, int cout,
-                                                         GaugeView<float> gv, Geom g, int spt) {
-  __shared__ cx<float> red[NTPB / 64][OG * NFEAT];
-  const int ngroup = (cout + OG - 1) / OG;
-  const int j = blockIdx.y / ngroup, i0 = (blockIdx.y % ngroup) * OG;
+// over the sites of one chunk (blockIdx.x) for the two features of one hop
+// (blockIdx.y = 0 .. 7) or of the site itself (8):
+// part[(chunk cout + i) cin + j][k] (FP64).
+// A wave takes 16 sites at a time: lane (li, lg) transports channel 4 jj + lg
+// at site li, spin by spin into the wave's LDS tile, from which lane (li, lg)
+// reads channel li at the sites 4 lg .. 4 lg + 3: the A operand of products
+// over sites (K) with gam_i at the same sites, read as 32-byte runs.  FP32
+// accumulators are emptied into FP64 ones after each spin, chains of 48 products.
+// Bound: the FP32 matrix cores (768 products per hop and 16 sites at 24
+// output channels).  16 x 16 channels on 16^4: 762 us (first layer without gate 510),
+// from 1997 (1074) with one site and 2 x 2 channels per lane.
+constexpr int WG_LD = 18;  // padded row (16 sites) of the LDS tile
+
+template <int JOB, bool GATE>
+__device__ inline void wgrad_job(cx<double>* __restrict__ part, const cx<float>* __restrict__ in,
+                                 const cx<float>* __restrict__ gam, int cin, int cout, const GaugeView<float>& gv,
+                                 const Geom& g, int jb, int ctot, int ib, cx<float>* smem) {
+  constexpr bool SELF = JOB == 8;
+  constexpr int MU = SELF ? 0 : JOB / 2;
+  constexpr bool FWD = JOB % 2 == 0;
+  constexpr SpinMap G = gamma_map<MU>();
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, li = lane & 15, lg = lane >> 4;
   const size_t V = g.V;
-  const cx<float>* f = in + (size_t)j * 12 * V;
-  cx<float> acc[OG][NFEAT];
+  cx<float>* tile = smem + (size_t)w * 3 * 16 * WG_LD;
+  double* red = reinterpret_cast<double*>(smem);
+  const int nunit = g.V / 16, stride = gridDim.x * (NTPB / 64);
+  mm_f4 acc[4];  // feature 0 re, im, feature 1 re, im
+  double tot[4][4];
 #pragma unroll
-  for (int q = 0; q < OG; ++q)
+  for (int q = 0; q < 4; ++q)
 #pragma unroll
-    for (int k = 0; k < NFEAT; ++k) acc[q][k] = mk(0.f, 0.f);
-  const int base = blockIdx.x * spt * NTPB;
-  for (int it = 0; it < spt; ++it) {
-    const int s = base + it * NTPB + threadIdx.x;
-    if (s >= g.V) break;
+      for (int v = 0; v < 4; ++v) {
+        acc[q][v] = 0.f;
+        tot[q][v] = 0.0;
+      }
+    const cx<float>* gp = gam + (size_t)min(ib + li, cout - 1) * 12 * V + 4 * lg;
+  for (int unit = blockIdx.x * (NTPB / 64) + w; unit < nunit; unit += stride) {
+    const int s0 = unit * 16, s = s0 + li;
     const SitePos p = site_pos(g, s);
-    cx<float> gm[OG][4][3];
-#pragma unroll
-    for (int q = 0; q < OG; ++q) {
-      const int i = min(i0 + q, cout - 1);
-#pragma unroll
-      for (int sp = 0; sp < 4; ++sp)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) gm[q][sp][c] = elem(gam + ((size_t)i * 12 + 3 * sp + c) * V, (unsigned)s);
-    }
-    {
-      cx<float> ph[4][3], g5[4][3];
-      load_in<GATE_IN>(ph, f, s, V, 1.f);
-#pragma unroll
-      for (int sp = 0; sp < 4; ++sp)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) g5[sp][c] = sp < 2 ? neg(ph[sp][c]) : ph[sp][c];
-#pragma unroll
-      for (int q = 0; q < OG; ++q) {
-        acc[q][0] = acc[q][0] + sdot(ph, gm[q]);
-        acc[q][1] = acc[q][1] + sdot(g5, gm[q]);
+    cx<float> U[3][3];
+    int sn = s;
+    float sign = 1.f;
+    if constexpr (!SELF) {
+      if (FWD) {
+        sn = nbr_fwd(g, p, MU);
+        if (MU == 3 && p.lc[3] == g.bs[3] - 1 && p.bc[3] == g.NB[3] - 1) sign = -1.f;
+        load_link<float, float>(U, gv, MU, s, V);
+      } else {
+        sn = nbr_bwd(g, p, MU);
+        if (MU == 3 && p.lc[3] == 0 && p.bc[3] == 0) sign = -1.f;
+        load_link<float, float>(U, gv, MU, sn, V);
       }
     }
-    wgrad_hops<0, OG, GATE_IN>(acc, f, gm, p, g, gv, V);
-    wgrad_hops<1, OG, GATE_IN>(acc, f, gm, p, g, gv, V);
-    wgrad_hops<2, OG, GATE_IN>(acc, f, gm, p, g, gv, V);
-    wgrad_hops<3, OG, GATE_IN>(acc, f, gm, p, g, gv, V);
-  }
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    float sc[4];  // sign and gate of channel 4 jj + lg at sn
 #pragma unroll
-  for (int q = 0; q < OG; ++q)
+    for (int jj = 0; jj < 4; ++jj) {
+      sc[jj] = sign;
+      if constexpr (GATE) {
+        const cx<float>* f = in + (size_t)min(4 * jj + lg, cin - 1) * 12 * V;
+        float n = 0.f;
 #pragma unroll
-    for (int k = 0; k < NFEAT; ++k) {
-      const float re = wave_sum_f(acc[q][k].r), im = wave_sum_f(acc[q][k].i);
-      if (lane == 0) red[wid][q * NFEAT + k] = mk(re, im);
+        for (int c = 0; c < 12; ++c) {
+          const cx<float> v = elem(f + (size_t)c * V, (unsigned)sn);
+          n += v.r * v.r + v.i * v.i;
+        }
+        sc[jj] *= 1.f / sqrtf(1.f + n * (1.f / 12.f));
+        asm volatile("" ::: "memory");  // one channel's loads at a time: registers
+      }
     }
+#pragma unroll
+    for (int sp = 0; sp < 4; ++sp) {
+#pragma unroll
+      for (int jj = 0; jj < 4; ++jj) {
+        const cx<float>* f = in + ((size_t)min(4 * jj + lg, cin - 1) * 12 + 3 * sp) * V;
+        cx<float> x[3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) x[c] = sc[jj] * elem(f + (size_t)c * V, (unsigned)sn);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          cx<float> t = x[c];
+          if constexpr (!SELF) {
+            t = mk(0.f, 0.f);
+#pragma unroll
+            for (int b = 0; b < 3; ++b) t = FWD ? cfma(U[c][b], x[b], t) : cfmac(U[b][c], x[b], t);
+          }
+          tile[(c * 16 + 4 * jj + lg) * WG_LD + li] = t;
+        }
+      }
+      // the tile is the wave's own: order its writes before the reads below
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      // spin d of g_mu t is i^ph times this spin (g5: -1, -1, +1, +1 in place)
+      int d = sp, ph = sp < 2 ? 2 : 0;
+      if constexpr (!SELF) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (G.src[q] == sp) {
+            d = q;
+            ph = G.phase[q];
+          }
+      }
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        Run<cx<float>, 4> t;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) t.v[i] = tile[(c * 16 + li) * WG_LD + 4 * lg + i];
+        const Run<cx<float>, 4> g0 = load_run<cx<float>, 4>(gp + (size_t)(3 * sp + c) * V + s0);
+        const Run<cx<float>, 4> g1 = load_run<cx<float>, 4>(gp + (size_t)(3 * d + c) * V + s0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            // conj(t) gam: (tr gr + ti gi) + i (tr gi - ti gr)
+            const cx<float> a = t.v[i], na = neg(a);
+            mm_c(acc[0], acc[1], a.r, na.i, a.i, g0.v[i]);
+            // conj(i^ph t) gam = i^-ph conj(t) gam
+            mm_cp(acc[2], acc[3], (4 - ph) & 3, mk(a.r, na.i), mk(na.r, a.i), g1.v[i]);
+          }
+        asm volatile("" ::: "memory");
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          tot[q][v] += (double)acc[q][v];
+          acc[q][v] = 0.f;
+        }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();  // the reads are done before the next spin is written
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+  }
+  // the waves' sums, one after the other in a fixed order: red [16][64],
+  // in the tiles' place
   __syncthreads();
-  for (int e = threadIdx.x; e < OG * NFEAT; e += NTPB) {
-    const int q = e / NFEAT, k = e % NFEAT;
-    if (i0 + q >= cout) continue;
-    cx<double> sum = mk(0.0, 0.0);
-    for (int w = 0; w < NTPB / 64; ++w) sum = sum + cvt<double>(red[w][e]);
-    part[(((size_t)blockIdx.x * cout + i0 + q) * cin + j) * NFEAT + k] = sum;
+  for (int k = 0; k < NTPB / 64; ++k) {
+    if (w == k) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            double& r = red[(q * 4 + v) * 64 + lane];
+            const double t = tot[q][v];
+            r = k == 0 ? t : r + t;
+          }
+    }
+    __syncthreads();
+  }
+  // lane: rows j = 4 lg + v, column i = li + 16 n
+  if (w == 0) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int j = 4 * lg + v, i = ib + li;
+        if (j >= cin || i >= cout) continue;
+        cx<double>* o = part + (((size_t)blockIdx.x * cout + i) * ctot + jb + j) * NFEAT + (SELF ? 0 : 2 + 2 * JOB);
+        auto at = [&](int q) { return red[(q * 4 + v) * 64 + lane]; };
+        o[0] = mk(at(0), at(1));
+        o[1] = mk(at(2), at(3));
+      }
+  }
+}
+
+// blockIdx: chunk, job, tile of 16 input channels and 16 output channels
+template <bool GATE>
+__global__ __launch_bounds__(NTPB, 2) void net_wgrad_kernel(cx<double>* __restrict__ part,
+                                                            const cx<float>* __restrict__ in,
+                                                            const cx<float>* __restrict__ gam, int cin, int cout,
+                                                            GaugeView<float> gv, Geom g) {
+  __shared__ __attribute__((aligned(16))) cx<float> smem[(NTPB / 64) * 3 * 16 * WG_LD];
+  static_assert(sizeof(smem) >= sizeof(double) * 16 * 64, "reduction area");
+  const int nj = (cin + 15) / 16, jb = 16 * (blockIdx.z % nj), ib = 16 * (blockIdx.z / nj), cl = min(16, cin - jb);
+  const cx<float>* ij = in + (size_t)jb * 12 * g.V;
+  switch (blockIdx.y) {
+    case 0: wgrad_job<0, GATE>(part, ij, gam, cl, cout, gv, g, jb, cin, ib, smem); break;
+    case 1: wgrad_job<1, GATE>(part, ij, gam, cl, cout, gv, g, jb, cin, ib, smem); break;
+    case 2: wgrad_job<2, GATE>(part, ij, gam, cl, cout, gv, g, jb, cin, ib, smem); break;
+    case 3: wgrad_job<3, GATE>(part, ij, gam, cl, cout, gv, g, jb, cin, ib, smem); break;
+    case 4: wgrad_job<4, GATE>(part, ij, gam, cl, cout, gv, g, jb, cin, ib, smem); break;
+    case 5: wgrad_job<5, GATE>(part, ij, gam, cl, cout, gv, g, jb, cin, ib, smem); break;
+    case 6: wgrad_job<6, GATE>(part, ij, gam, cl, cout, gv, g, jb, cin, ib, smem); break;
+    case 7: wgrad_job<7, GATE>(part, ij, gam, cl, cout, gv, g, jb, cin, ib, smem); break;
+    default: wgrad_job<8, GATE>(part, ij, gam, cl, cout, gv, g, jb, cin, ib, smem); break;
   }
 }
 
@@ -366,147 +453,277 @@ __global__ void net_wgrad_final_kernel(cx<float>* grad, const cx<double>* part, 
 }
 
 // Span loss of the proposal X against the target basis T on one aggregate
-// per workgroup (blockIdx.x = 2 ci + h), N_tv <= 32:
-//   G = X^H X, C = X^H T, Z = G^-1 C (Cholesky, FP64),
+// per workgroup (blockIdx.x = 2 ci + h), N_tv <= 32, in FP64:
+//   G = X^H X, C = X^H T, Z = G^-1 C (Cholesky),
 //   loss_agg = ||T||^2 - Re tr(C^H Z),
-//   gam = -scale (T - X Z) Z^H on the aggregate's components.
-// Rows of the aggregate: r = 6 l + q, l the site in the block, q = 3 spin'
-// + colour with spin = 2 h + spin'.  status is set to 1 if G is not
-// positive definite.
-constexpr int SL_CHUNK = 32;  // rows staged per pass
-__global__ __launch_bounds__(256) void net_span_loss_kernel(cx<float>* __restrict__ gam, double* __restrict__ loss_agg,
-                                                            const cx<float>* __restrict__ X,
-                                                            const cx<float>* __restrict__ T, Geom g, int ntv,
-                                                            double scale, int* status) {
-  __shared__ cx<double> Gs[32][33], Cs[32][33], Zs[32][33];
-  __shared__ cx<float> xs[SL_CHUNK][32], ts[SL_CHUNK][32];
-  __shared__ double tn[32];
-  __shared__ int bad;
+//   gam = -scale (T - X Z) Z^H = T M_T + X M_X on the aggregate's components,
+//   M_T = -scale Z^H, M_X = scale Z Z^H.
+// status is set to 1 if G is not positive definite.
+// The products over the aggregate's rows run on the FP64 matrix cores
+// (16x16x4), fed from memory: for G and C lane (li, lg) holds vector li and
+// the sites 4 lg .. 4 lg + 3 of a 16-site run (the K order is the same for both
+// operands), for gam vector 4 k + lg and site li, so that the results leave
+// in 128-byte runs.  Cholesky and the triangular solves go by columns, all
+// lanes on the rest.  One lane did the Cholesky and one lane per row the
+// gradient, with X read again for every entry of Z: 16^4, N_tv 24 (512
+// aggregates): 455 us, from 3130.
+constexpr int SLT = 256;  // lanes
+constexpr int SLD = 33;   // padded row of the LDS matrices
+
+template <int MT>
+__global__ __launch_bounds__(SLT, 2) void net_span_loss_kernel(cx<float>* __restrict__ gam,
+                                                               double* __restrict__ loss_agg,
+                                                               const cx<float>* __restrict__ X,
+                                                               const cx<float>* __restrict__ T, Geom g, int ntv,
+                                                               double scale, int* status) {
+  __shared__ cx<double> Gs[32 * SLD], Cs[32 * SLD], Zs[32 * SLD];
+  __shared__ double wsum[SLT / 64];
+  constexpr int NP = MT * (MT + 1) / 2 + MT * MT;  // tiles of G (m <= n) and of C
+  // the waves' tiles meet in the matrices' place
+  double* red = reinterpret_cast<double*>(Gs);
+  static_assert(sizeof(double) * NP * 8 * 64 <= sizeof(Gs) + sizeof(Cs) + sizeof(Zs), "reduction area");
   const int ci = blockIdx.x >> 1, h = blockIdx.x & 1;
   const size_t V = g.V;
-  const int vb = g.vblock, nrow = 6 * vb;
-  const int t = threadIdx.x;
-  const int np = ntv * ntv;
-  if (t == 0) bad = 0;
-  // element (row r, vector a) of a field F
-  auto at = [&](const cx<float>* F, int r, int a) -> cx<float> {
-    const int l = r / 6, q = r - 6 * (r / 6);
-    return F[((size_t)a * 12 + 6 * h + q) * V + (size_t)ci * vb + l];
-  };
-  cx<double> gacc[4], cacc[4];  // pairs t, t + 256, ... (np <= 1024)
-  double tacc = 0.0;
+  const int vb = g.vblock;
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6, li = lane & 15, lg = lane >> 4;
+  const size_t base = (size_t)(6 * h) * V + (size_t)ci * vb;
+  mm_d4 re[NP], im[NP];
 #pragma unroll
-  for (int u = 0; u < 4; ++u) gacc[u] = cacc[u] = mk(0.0, 0.0);
-  for (int r0 = 0; r0 < nrow; r0 += SL_CHUNK) {
-    __syncthreads();
-    for (int e = t; e < SL_CHUNK * ntv; e += 256) {
-      const int rr = e % SL_CHUNK, a = e / SL_CHUNK;
-      const int r = r0 + rr;
-      xs[rr][a] = r < nrow ? at(X, r, a) : mk(0.f, 0.f);
-      ts[rr][a] = r < nrow ? at(T, r, a) : mk(0.f, 0.f);
+  for (int q = 0; q < NP; ++q)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) re[q][v] = im[q][v] = 0.0;
+  double tn = 0.0;
+  {
+    const cx<float>*Xp[MT], *Tp[MT];
+    bool real[MT];  // vectors beyond the last are read as the last
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+      const int a = min(li + 16 * m, ntv - 1);
+      real[m] = li + 16 * m < ntv;
+      Xp[m] = X + (size_t)a * 12 * V + base;
+      Tp[m] = T + (size_t)a * 12 * V + base;
     }
-    __syncthreads();
+    for (int s0 = 16 * w; s0 < vb; s0 += 16 * (SLT / 64)) {
+      const int s = s0 + 4 * lg;
+      const bool full = s0 + 16 <= vb;
+      for (int k = 0; k < 6; ++k) {
+        Run<cx<float>, 4> xv[MT], tv[MT];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int pi = t + 256 * u;
-      if (pi < np) {
-        const int a = pi / ntv, b = pi % ntv;
-        for (int rr = 0; rr < SL_CHUNK; ++rr) {
-          const cx<double> xa = cvt<double>(xs[rr][a]);
-          gacc[u] = cfmac(xa, cvt<double>(xs[rr][b]), gacc[u]);
-          cacc[u] = cfmac(xa, cvt<double>(ts[rr][b]), cacc[u]);
+        for (int m = 0; m < MT; ++m) {
+          if (full) {
+            xv[m] = load_run<cx<float>, 4>(Xp[m] + (size_t)k * V + s);
+            tv[m] = load_run<cx<float>, 4>(Tp[m] + (size_t)k * V + s);
+          } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {  // sites beyond the block contribute zero
+              const bool in = s + i < vb;
+              const size_t at = (size_t)k * V + min(s + i, vb - 1);
+              const cx<float> xa = Xp[m][at], ta = Tp[m][at];
+              xv[m].v[i] = in ? xa : mk(0.f, 0.f);
+              tv[m].v[i] = in ? ta : mk(0.f, 0.f);
+            }
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          cx<double> x[MT], y[MT];
+#pragma unroll
+          for (int m = 0; m < MT; ++m) {
+            x[m] = cvt<double>(xv[m].v[i]);
+            y[m] = cvt<double>(tv[m].v[i]);
+            if (real[m]) tn += y[m].r * y[m].r + y[m].i * y[m].i;
+          }
+          int q = 0;
+          auto tile = [&](cx<double> a, cx<double> b) {  // conj(a) b
+            re[q] = mm_mfma(a.r, b.r, re[q]);
+            im[q] = mm_mfma(a.r, b.i, im[q]);
+            re[q] = mm_mfma(a.i, b.i, re[q]);
+            im[q] = mm_mfma(-a.i, b.r, im[q]);
+            ++q;
+          };
+#pragma unroll
+          for (int m = 0; m < MT; ++m)
+#pragma unroll
+            for (int n = m; n < MT; ++n) tile(x[m], x[n]);
+#pragma unroll
+          for (int m = 0; m < MT; ++m)
+#pragma unroll
+            for (int n = 0; n < MT; ++n) tile(x[m], y[n]);
         }
       }
     }
-    if (t < ntv)
-      for (int rr = 0; rr < SL_CHUNK; ++rr) {
-        const cx<float> v = ts[rr][t];
-        tacc += (double)v.r * v.r + (double)v.i * v.i;
-      }
   }
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int pi = t + 256 * u;
-    if (pi < np) {
-      Gs[pi / ntv][pi % ntv] = gacc[u];
-      Cs[pi / ntv][pi % ntv] = cacc[u];
-    }
+  for (int o = 32; o > 0; o >>= 1) tn += __shfl_xor(tn, o, 64);
+  if (lane == 0) wsum[w] = tn;
+  for (int k = 0; k < SLT / 64; ++k) {
+    if (w == k)
+#pragma unroll
+      for (int q = 0; q < NP; ++q)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          double& r = red[(q * 8 + v) * 64 + lane];
+          double& i = red[(q * 8 + 4 + v) * 64 + lane];
+          r = k == 0 ? re[q][v] : r + re[q][v];
+          i = k == 0 ? im[q][v] : i + im[q][v];
+        }
+    __syncthreads();
   }
-  if (t < ntv) tn[t] = tacc;
-  __syncthreads();
-  // Cholesky G = L L^H in place (lower triangle), one thread
-  if (t == 0) {
-    for (int k = 0; k < ntv; ++k) {
-      double d = Gs[k][k].r;
-      for (int m = 0; m < k; ++m) d -= Gs[k][m].r * Gs[k][m].r + Gs[k][m].i * Gs[k][m].i;
-      if (!(d > 0.0)) {
-        bad = 1;
-        break;
+  if (w == 0)
+#pragma unroll
+    for (int q = 0; q < NP; ++q)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        re[q][v] = red[(q * 8 + v) * 64 + lane];
+        im[q][v] = red[(q * 8 + 4 + v) * 64 + lane];
       }
-      const double lk = sqrt(d);
-      Gs[k][k] = mk(lk, 0.0);
-      for (int i = k + 1; i < ntv; ++i) {
-        cx<double> v = Gs[i][k];
-        for (int m = 0; m < k; ++m) v = v - Gs[i][m] * conj(Gs[k][m]);
-        Gs[i][k] = (1.0 / lk) * v;
-      }
-    }
+  __syncthreads();
+  if (w == 0) {
+    int q = 0;
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+      for (int n = m; n < MT; ++n, ++q)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int a = 16 * m + mm_row<double>(lg, v), b = 16 * n + li;
+          const cx<double> e = mk(re[q][v], im[q][v]);
+          Gs[a * SLD + b] = e;
+          if (n > m) Gs[b * SLD + a] = conj(e);
+        }
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+      for (int n = 0; n < MT; ++n, ++q)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int a = 16 * m + mm_row<double>(lg, v), b = 16 * n + li;
+          Cs[a * SLD + b] = Zs[a * SLD + b] = mk(re[q][v], im[q][v]);
+        }
   }
   __syncthreads();
-  if (bad) {
-    if (t == 0) {
-      atomicExch(status, 1);
-      loss_agg[blockIdx.x] = 0.0;
+  // G = L L^H in place (lower triangle), right-looking; every lane reads the
+  // same pivot, so a failure is uniform
+  for (int k = 0; k < ntv; ++k) {
+    const double d = Gs[k * SLD + k].r;
+    if (!(d > 0.0)) {
+      if (t == 0) {
+        atomicExch(status, 1);
+        loss_agg[blockIdx.x] = 0.0;
+      }
+      return;
     }
-    return;
+    const double lk = sqrt(d);
+    __syncthreads();
+    for (int i = k + t; i < ntv; i += SLT)
+      Gs[i * SLD + k] = i == k ? mk(lk, 0.0) : (1.0 / lk) * Gs[i * SLD + k];
+    __syncthreads();
+    const int m = ntv - k - 1;
+    for (int e = t; e < m * m; e += SLT) {
+      const int i = k + 1 + e / m, j = k + 1 + e % m;
+      if (j <= i) Gs[i * SLD + j] = Gs[i * SLD + j] - Gs[i * SLD + k] * conj(Gs[j * SLD + k]);
+    }
+    __syncthreads();
   }
-  // Z[:, b] = G^-1 C[:, b] by forward and back substitution, one column per thread
-  if (t < ntv) {
-    const int b = t;
-    cx<double> y[32];
-    for (int i = 0; i < ntv; ++i) {
-      cx<double> v = Cs[i][b];
-      for (int m = 0; m < i; ++m) v = v - Gs[i][m] * y[m];
-      y[i] = (1.0 / Gs[i][i].r) * v;
+  // Z = L^-H L^-1 C, column by column of L
+  for (int k = 0; k < ntv; ++k) {
+    const double inv = 1.0 / Gs[k * SLD + k].r;
+    if (t < ntv) Zs[k * SLD + t] = inv * Zs[k * SLD + t];
+    __syncthreads();
+    for (int e = t; e < (ntv - k - 1) * ntv; e += SLT) {
+      const int i = k + 1 + e / ntv, b = e % ntv;
+      Zs[i * SLD + b] = Zs[i * SLD + b] - Gs[i * SLD + k] * Zs[k * SLD + b];
     }
-    for (int i = ntv - 1; i >= 0; --i) {
-      cx<double> v = y[i];
-      for (int m = i + 1; m < ntv; ++m) v = v - conj(Gs[m][i]) * Zs[m][b];
-      Zs[i][b] = (1.0 / Gs[i][i].r) * v;
-    }
+    __syncthreads();
   }
+  for (int k = ntv - 1; k >= 0; --k) {
+    const double inv = 1.0 / Gs[k * SLD + k].r;
+    if (t < ntv) Zs[k * SLD + t] = inv * Zs[k * SLD + t];
+    __syncthreads();
+    for (int e = t; e < k * ntv; e += SLT) {
+      const int i = e / ntv, b = e % ntv;
+      Zs[i * SLD + b] = Zs[i * SLD + b] - conj(Gs[k * SLD + i]) * Zs[k * SLD + b];
+    }
+    __syncthreads();
+  }
+  // loss: ||T||^2 - Re tr(C^H Z)
+  double tr = 0.0;
+  for (int e = t; e < ntv * ntv; e += SLT) {
+    const int at = e / ntv * SLD + e % ntv;
+    tr += Cs[at].r * Zs[at].r + Cs[at].i * Zs[at].i;
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) tr += __shfl_xor(tr, o, 64);
+  double tt = 0.0;
+  for (int k = 0; k < SLT / 64; ++k) tt += wsum[k];
+  __syncthreads();
+  if (lane == 0) wsum[w] = tr;
   __syncthreads();
   if (t == 0) {
-    double tr = 0.0, tt = 0.0;
-    for (int a = 0; a < ntv; ++a) {
-      tt += tn[a];
-      for (int b = 0; b < ntv; ++b) tr += Cs[a][b].r * Zs[a][b].r + Cs[a][b].i * Zs[a][b].i;
-    }
-    loss_agg[blockIdx.x] = tt - tr;
+    for (int k = 0; k < SLT / 64; ++k) tt -= wsum[k];
+    loss_agg[blockIdx.x] = tt;
   }
-  // gradient rows: v = T_r - X_r Z, gam_r = -scale v Z^H
-  for (int r = t; r < nrow; r += 256) {
-    cx<double> v[32];
-    for (int b = 0; b < ntv; ++b) {
-      cx<double> s = cvt<double>(at(T, r, b));
-      for (int c = 0; c < ntv; ++c) s = s - cvt<double>(at(X, r, c)) * Zs[c][b];
-      v[b] = s;
+  // M_X = scale (Z Z^H) into Gs (row c, column a: what multiplies X_c in
+  // gam_a), M_T into Cs (row b, column a), zero rows up to a multiple of 4
+  const int nk = (ntv + 3) / 4;
+  for (int e = t; e < 4 * nk * 32; e += SLT) {
+    const int c = e / 32, a = e % 32;
+    cx<double> q = mk(0.0, 0.0), m = q;
+    if (c < ntv && a < ntv) {
+      for (int b = 0; b < ntv; ++b) q = q + Zs[c * SLD + b] * conj(Zs[a * SLD + b]);
+      m = conj(Zs[a * SLD + c]);
     }
-    const int l = r / 6, q = r - 6 * l;
-    for (int a = 0; a < ntv; ++a) {
-      cx<double> s = mk(0.0, 0.0);
-      for (int b = 0; b < ntv; ++b) s = s + v[b] * conj(Zs[a][b]);
-      gam[((size_t)a * 12 + 6 * h + q) * V + (size_t)ci * vb + l] = cvt<float>(-scale * s);
+    Gs[c * SLD + a] = scale * q;
+    Cs[c * SLD + a] = -scale * m;
+  }
+  __syncthreads();
+  // gam_a = sum_c M_X[c][a] X_c + sum_b M_T[b][a] T_b, units of 16 sites of one component
+  const int nrun = (vb + 15) / 16;
+  for (int u = w; u < 6 * nrun; u += SLT / 64) {
+    const int k = u / nrun, s0 = 16 * (u % nrun);
+    const bool in = s0 + li < vb;
+    const size_t at = base + (size_t)k * V + min(s0 + li, vb - 1);
+    mm_d4 gr[MT], gi[MT];
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) gr[m][v] = gi[m][v] = 0.0;
+#pragma unroll 2
+    for (int kk = 0; kk < nk; ++kk) {
+      const int c = 4 * kk + lg;  // rows beyond ntv are zero in the matrices
+      const size_t plane = (size_t)min(c, ntv - 1) * 12 * V;
+      const cx<double> x = cvt<double>(X[plane + at]), y = cvt<double>(T[plane + at]);
+#pragma unroll
+      for (int m = 0; m < MT; ++m) {
+        const cx<double> ax = Gs[c * SLD + 16 * m + li], ay = Cs[c * SLD + 16 * m + li];
+        gr[m] = mm_mfma(ax.r, x.r, gr[m]);
+        gi[m] = mm_mfma(ax.r, x.i, gi[m]);
+        gr[m] = mm_mfma(-ax.i, x.i, gr[m]);
+        gi[m] = mm_mfma(ax.i, x.r, gi[m]);
+        gr[m] = mm_mfma(ay.r, y.r, gr[m]);
+        gi[m] = mm_mfma(ay.r, y.i, gi[m]);
+        gr[m] = mm_mfma(-ay.i, y.i, gr[m]);
+        gi[m] = mm_mfma(ay.i, y.r, gi[m]);
+      }
     }
+    if (in)
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int a = 16 * m + mm_row<double>(lg, v);
+          if (a < ntv) gam[(size_t)a * 12 * V + at] = mk((float)gr[m][v], (float)gi[m][v]);
+        }
   }
 }
 
-// out = scale * sum in[i], summed in a fixed order
+// out = scale * sum in[i], one wave, summed in a fixed order
 __global__ void sum_kernel(double* out, const double* in, int n, double scale) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
   double s = 0.0;
-  for (int i = 0; i < n; ++i) s += in[i];
-  *out = scale * s;
+  for (int i = threadIdx.x; i < n; i += 64) s += in[i];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+  if (threadIdx.x == 0) *out = scale * s;
 }
 
 // Adam on the real and imaginary parts (n reals), bias corrections c1, c2
@@ -526,18 +743,15 @@ inline unsigned cdiv(size_t a, size_t b) { return (unsigned)((a + b - 1) / b); }
 
 }  // namespace
 
-constexpr int NET_OG = 4;          // output channels per thread in the layer kernel
-constexpr int NET_WOG = 2;         // in the weight-gradient kernel
-
 void launch_net_layer(cx<float>* out, const cx<float>* in, const cx<float>* W, int cin, int cout, bool gate_in,
                       const cx<float>* gate_bwd_pre, const GaugeView<float>& gv, const Geom& g, hipStream_t st) {
-  const dim3 grid(cdiv(g.V, NTPB), cdiv(cout, NET_OG));
+  const dim3 grid(cdiv(g.V, 16 * (NTPB / 64)), cdiv(cout, 16));
   if (gate_bwd_pre)
-    net_layer_kernel<NET_OG, false, true><<<grid, NTPB, 0, st>>>(out, in, W, cin, cout, gv, g, gate_bwd_pre);
+    net_layer_kernel<false, true><<<grid, NTPB, 0, st>>>(out, in, W, cin, cout, gv, g, gate_bwd_pre);
   else if (gate_in)
-    net_layer_kernel<NET_OG, true, false><<<grid, NTPB, 0, st>>>(out, in, W, cin, cout, gv, g, nullptr);
+    net_layer_kernel<true, false><<<grid, NTPB, 0, st>>>(out, in, W, cin, cout, gv, g, nullptr);
   else
-    net_layer_kernel<NET_OG, false, false><<<grid, NTPB, 0, st>>>(out, in, W, cin, cout, gv, g, nullptr);
+    net_layer_kernel<false, false><<<grid, NTPB, 0, st>>>(out, in, W, cin, cout, gv, g, nullptr);
 }
 
 void launch_net_transpose(cx<float>* Wb, const cx<float>* W, int cin, int cout, hipStream_t st) {
@@ -545,16 +759,18 @@ void launch_net_transpose(cx<float>* Wb, const cx<float>* W, int cin, int cout, 
   net_transpose_kernel<<<cdiv(n, 256), 256, 0, st>>>(Wb, W, cin, cout);
 }
 
-int net_wgrad_chunks(const Geom& g) { return (int)cdiv(g.V, (size_t)NTPB * NET_WGRAD_SPT); }
+// chunks of the weight gradients: with the nine jobs some 600 workgroups on
+// lattices from 16^4 up, and at least eight units of 16 sites per wave
+int net_wgrad_chunks(const Geom& g) { return std::max(1, std::min(64, g.V / 512)); }
 
 void launch_net_wgrad(cx<float>* grad, cx<double>* part, const cx<float>* in, bool gate_in, const cx<float>* gam,
                       int cin, int cout, const GaugeView<float>& gv, const Geom& g, hipStream_t st) {
   const int nchunk = net_wgrad_chunks(g);
-  const dim3 grid(nchunk, cin * cdiv(cout, NET_WOG));
+  const dim3 grid(nchunk, 9, cdiv(cin, 16) * cdiv(cout, 16));
   if (gate_in)
-    net_wgrad_kernel<NET_WOG, true><<<grid, NTPB, 0, st>>>(part, in, gam, cin, cout, gv, g, NET_WGRAD_SPT);
+    net_wgrad_kernel<true><<<grid, NTPB, 0, st>>>(part, in, gam, cin, cout, gv, g);
   else
-    net_wgrad_kernel<NET_WOG, false><<<grid, NTPB, 0, st>>>(part, in, gam, cin, cout, gv, g, NET_WGRAD_SPT);
+    net_wgrad_kernel<false><<<grid, NTPB, 0, st>>>(part, in, gam, cin, cout, gv, g);
   const size_t n = (size_t)cout * cin * NFEAT;
   net_wgrad_final_kernel<<<cdiv(n, 256), 256, 0, st>>>(grad, part, n, nchunk);
 }
@@ -563,7 +779,10 @@ void launch_net_span_loss(cx<float>* gam, double* loss_agg, double* loss, const 
                           const Geom& g, int ntv, int* status, hipStream_t st) {
   const int nagg = 2 * g.nblocks;
   const double scale = 1.0 / ((double)nagg * ntv);
-  net_span_loss_kernel<<<nagg, 256, 0, st>>>(gam, loss_agg, X, T, g, ntv, scale, status);
+  if (ntv <= 16)
+    net_span_loss_kernel<1><<<nagg, SLT, 0, st>>>(gam, loss_agg, X, T, g, ntv, scale, status);
+  else
+    net_span_loss_kernel<2><<<nagg, SLT, 0, st>>>(gam, loss_agg, X, T, g, ntv, scale, status);
   sum_kernel<<<1, 64, 0, st>>>(loss, loss_agg, nagg, scale);
 }
 
