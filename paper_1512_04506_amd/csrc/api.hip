@@ -652,9 +652,8 @@ struct Solver final : SolverBase {
     const int maxit = fixed > 0 ? fixed : c->p.coarse_maxit;
     if (small_coarse_applies()) {
       c->timed(DDAMG_KERNEL_COARSE, nrhs, [&] {
-        launch_coarse_gmres_small<T, S>(xcv, ycv, cs_, C, Dinv.get<cx<T>>(), g, te.get<cx<T>>(), ue.get<cx<T>>(),
-                                        bo.get<cx<T>>(), cw.get<cx<T>>(), cV.get<cx<T>>(), (size_t)maxr * osz(),
-                                        m, maxit, fixed > 0 ? -1.0 : c->p.coarse_tol, small_its.get<int>(), nrhs, st);
+        launch_coarse_gmres_small<T, S>(xcv, ycv, cs_, C, Dinv.get<cx<T>>(), g, bo.get<cx<T>>(),
+                                        cV.get<cx<T>>(), (size_t)maxr * osz(), m, maxit, fixed > 0 ? -1.0 : c->p.coarse_tol, small_its.get<int>(), nrhs, st);
       });
       check_launch("coarse solve");
       ++coarse_calls;

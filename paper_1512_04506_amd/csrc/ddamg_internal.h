@@ -497,7 +497,7 @@ constexpr int COARSE_SMALL_MAX_RESTART = 32;
 constexpr int COARSE_SMALL_MAX_VECTOR = 1536;  // sites x nc: the LDS copy of a coarse vector
 template <typename T, typename S>
 void launch_coarse_gmres_small(cx<T>* xc, const cx<T>* yc, size_t cstr, const CoarseView<S>& cv, const cx<T>* Dinv,
-                               const Geom& g, cx<T>* te, cx<T>* ue, cx<T>* bo, cx<T>* cw, cx<T>* V, size_t vsj,
-                               int m, int maxit, double tol, int* its_stat, int nrhs, hipStream_t st);
+                               const Geom& g, cx<T>* bo, cx<T>* V, size_t vsj, int m, int maxit, double tol,
+                               int* its_stat, int nrhs, hipStream_t st);
 
 }  // namespace ddamg
