@@ -942,14 +942,16 @@ struct Solver final : SolverBase {
   // v_{k+1} = (w' - V h2) / |w''|, is formed in the next step's fused pass,
   // which reads V_0..V_k anyway (gs_pending: slot k + 1 holds w', h2 and the
   // factor wait in hc and wscale); the inner products of the next w with it
-  // follow from those with w' (launch_gs_defer_coef).  The preconditioner
+  // follow from those with w' (launch_gs_coef).  The preconditioner
   // then receives w' (in FP32 its copy, scaled to about unit norm by an
   // estimate of 1 / |w'| from the first pass, so that no FP32 quantity of
   // the V-cycle underflows), which FGMRES allows: it needs D z_k in the span
   // of V with the coefficients it records, whatever z_k is.  A step after which the next could not take the correction (basis
   // longer than GS_FUSED_MAXV) writes v_{k+1} in a third pass as before.
+  // Ends with column k of the Hessenberg matrix; once the stream has run,
+  // h_flags holds the active flags.
   bool gs_pending = false;
-  void cgs2(cx<double>* V, size_t vsj, int k, int nrhs, cx<float>* w32) {
+  void outer_arnoldi(cx<double>* V, size_t vsj, int k, int nrhs, cx<float>* w32) {
     const size_t n = fsz();
     const int* act = ok.active.get<int>();
     cx<double>* w = V + (size_t)(k + 1) * vsj;
@@ -959,18 +961,21 @@ struct Solver final : SolverBase {
     if (k + 1 <= GS_FUSED_MAXV) {
       // h1 = V^H w and, as the inner product of the last vector (w itself),
       // |w|^2, which gives the scale of the preconditioner's input
-      need_part(launch_mdot<double>(h1, ok.ldh, part, ok.part_cap, V, vsj, n, k + 2, w, n, n, nrhs, act, st),
+      const int nchunk = blas_nchunks(n, nrhs);
+      need_part(launch_mdot<double>(nullptr, ok.ldh, part, ok.part_cap, V, vsj, n, k + 2, w, n, n, nrhs, act, st),
                 "outer Gram-Schmidt");
-      launch_gs_defer_coef(h1, ok.hc.get<cx<double>>(), h2, ok.ldh, ok.wscale.get<double>(), k, gs_pending,
-                           ok.vscale.get<double>(), nrhs, act, st);
+      launch_gs_coef(part, nchunk, h1, ok.hc.get<cx<double>>(), h2, ok.ldh, ok.wscale.get<double>(), k, gs_pending,
+                     ok.vscale.get<double>(), nrhs, act, st);
       const bool defer = k + 2 <= GS_FUSED_MAXV;
-      need_part(launch_gs_defer(h2, ok.ldh, part, ok.part_cap, V, vsj, n, k, gs_pending, ok.hc.get<cx<double>>(),
+      need_part(launch_gs_defer(ok.ldh, part, ok.part_cap, V, vsj, n, k, gs_pending, ok.hc.get<cx<double>>(),
                                 ok.wscale.get<double>(), w, n, h1, n, nrhs, act, defer ? w32 : nullptr,
                                 ok.vscale.get<double>(), st),
                 "outer Gram-Schmidt");
-      launch_gs_norm(ok.n2.get<cx<double>>(), ok.wscale.get<double>(), h2, ok.ldh, k + 1, nrhs, act, st);
+      launch_gs_column(ok.st, k, part, nchunk, h1, h2, ok.ldh, ok.wscale.get<double>(), c->h_flags, nrhs, st);
       gs_pending = defer;
-      if (defer) return;
+      if (!defer)
+        launch_maxpy<double, double>(w, n, V, vsj, n, k + 1, h2, ok.ldh, -1.0, n, nrhs, act, st,
+                                     ok.wscale.get<double>(), w32);
     } else {  // long cycles: the same step in two passes (the last vector is w itself: |w|^2)
       need_part(launch_mdot<double>(h1, ok.ldh, part, ok.part_cap, V, vsj, n, k + 1, w, n, n, nrhs, act, st),
                 "outer Gram-Schmidt");
@@ -978,9 +983,11 @@ struct Solver final : SolverBase {
       need_part(launch_mdot<double>(h2, ok.ldh, part, ok.part_cap, V, vsj, n, k + 2, w, n, n, nrhs, act, st),
                 "outer Gram-Schmidt");
       launch_gs_norm(ok.n2.get<cx<double>>(), ok.wscale.get<double>(), h2, ok.ldh, k + 1, nrhs, act, st);
+      launch_maxpy<double, double>(w, n, V, vsj, n, k + 1, h2, ok.ldh, -1.0, n, nrhs, act, st,
+                                   ok.wscale.get<double>(), w32);
+      launch_arnoldi_column(ok.st, k, h1, h2, ok.ldh, ok.n2.get<cx<double>>(), 1, nrhs, st);
+      HIPCK(hipMemcpyAsync(c->h_flags, act, sizeof(int) * nrhs, hipMemcpyDeviceToHost, st));
     }
-    launch_maxpy<double, double>(w, n, V, vsj, n, k + 1, h2, ok.ldh, -1.0, n, nrhs, act, st,
-                                 ok.wscale.get<double>(), w32);
   }
 
   // The outer basis V (FP64) and the preconditioned vectors Z grow with the
@@ -1038,13 +1045,14 @@ struct Solver final : SolverBase {
     need_part(launch_mdot<double>(ok.n2.get<cx<double>>(), 1, ok.part.get<cx<double>>(), ok.part_cap, f, 0, n, 1, f, n,
                                   n, nrhs, nullptr, st),
               "right-hand side norm");
+    launch_set_abstol(ok.abstol.get<double>(), ok.n2.get<cx<double>>(), tol, nrhs, st);
     std::vector<cx<double>> fn2(nrhs), rn2(nrhs);
     HIPCK(hipMemcpyAsync(c->h_cx, ok.n2.get<cx<double>>(), sizeof(cx<double>) * nrhs, hipMemcpyDeviceToHost, st));
     HIPCK(hipMemcpyAsync(c->h_flags, u_nonzero.get<int>(), sizeof(int) * nrhs, hipMemcpyDeviceToHost, st));
     c->sync();
     std::copy(c->h_cx, c->h_cx + nrhs, fn2.begin());
     // all initial guesses zero: the first residual is f itself (D 0 = 0
-    // exactly), a copy instead of the FP64 operator and a subtraction
+    // exactly), its norm the one at hand
     bool u_zero = true;
     for (int r = 0; r < nrhs; ++r) u_zero = u_zero && c->h_flags[r] == 0;
     std::vector<double> fnorm(nrhs), abstol(nrhs), zero_scale(nrhs, 1.0);
@@ -1058,29 +1066,30 @@ struct Solver final : SolverBase {
         any_zero = true;
       }
     }
-    std::copy(zero_scale.begin(), zero_scale.end(), c->h_dbl);
-    std::copy(abstol.begin(), abstol.end(), c->h_dbl + 64);
-    HIPCK(hipMemcpyAsync(ok.est.get<double>(), c->h_dbl, sizeof(double) * nrhs, hipMemcpyHostToDevice, st));
-    HIPCK(hipMemcpyAsync(ok.abstol.get<double>(), c->h_dbl + 64, sizeof(double) * nrhs, hipMemcpyHostToDevice, st));
-    if (any_zero) launch_scale<double, double>(u, n, u, n, ok.est.get<double>(), n, nrhs, nullptr, st);
+    if (any_zero) {
+      std::copy(zero_scale.begin(), zero_scale.end(), c->h_dbl);
+      HIPCK(hipMemcpyAsync(ok.est.get<double>(), c->h_dbl, sizeof(double) * nrhs, hipMemcpyHostToDevice, st));
+      launch_scale<double, double>(u, n, u, n, ok.est.get<double>(), n, nrhs, nullptr, st);
+    }
     int its = 0, restarts = 0;
     bool converged = false;
     std::vector<double> relres(nrhs, 0.0);
     for (;;) {
-      // true residual r = f - D u in FP64, into V_0
-      if (u_zero && its == 0) {
-        launch_copy<double, double>(V, n, f, n, n, nrhs, st);
-      } else {
+      // true residual r = f - D u in FP64, into V_0 (or f itself)
+      const cx<double>* res = u_zero && its == 0 ? f : V;
+      if (res == V) {
         c->timed(DDAMG_KERNEL_RESIDUAL, nrhs,
                  [&] { launch_dslash<double, double, double, double>(w, u, g64, g, nrhs, DS_FULL, 0, -1, n, n, st); });
         launch_sub<double>(V, n, f, n, w, n, n, nrhs, st);
+        need_part(launch_mdot<double>(ok.n2.get<cx<double>>(), 1, ok.part.get<cx<double>>(), ok.part_cap, V, 0, n, 1, V,
+                                      n, n, nrhs, nullptr, st),
+                  "residual norm");
+        HIPCK(hipMemcpyAsync(c->h_cx, ok.n2.get<cx<double>>(), sizeof(cx<double>) * nrhs, hipMemcpyDeviceToHost, st));
+        c->sync();
+        std::copy(c->h_cx, c->h_cx + nrhs, rn2.begin());
+      } else {
+        rn2 = fn2;
       }
-      need_part(launch_mdot<double>(ok.n2.get<cx<double>>(), 1, ok.part.get<cx<double>>(), ok.part_cap, V, 0, n, 1, V,
-                                    n, n, nrhs, nullptr, st),
-                "residual norm");
-      HIPCK(hipMemcpyAsync(c->h_cx, ok.n2.get<cx<double>>(), sizeof(cx<double>) * nrhs, hipMemcpyDeviceToHost, st));
-      c->sync();
-      std::copy(c->h_cx, c->h_cx + nrhs, rn2.begin());
       bool all = true;
       for (int r = 0; r < nrhs; ++r) {
         double rn = std::sqrt(std::max(rn2[r].r, 0.0));
@@ -1099,7 +1108,7 @@ struct Solver final : SolverBase {
       constexpr bool f32 = std::is_same<T, float>::value;
       cx<float>* v32 = nullptr;
       if constexpr (f32) v32 = fy.get<cx<float>>();
-      launch_scale<double, double>(V, n, V, n, ok.inv_h.get<double>(), n, nrhs, nullptr, st, v32);
+      launch_scale<double, double>(V, n, res, n, ok.inv_h.get<double>(), n, nrhs, nullptr, st, v32);
       gs_pending = false;
       int k = 0;
       for (; k < m && its < c->p.outer_maxit; ++k) {
@@ -1121,11 +1130,12 @@ struct Solver final : SolverBase {
           else
             launch_dslash<float, double, double, double>(wk, zk, g64, g, nrhs, DS_FULL, 0, -1, n, n, st);
         });
-        c->timed(DDAMG_KERNEL_OUTER_GS, nrhs, [&] { cgs2(V, vsj, k, nrhs, v32); });
-        launch_arnoldi_column(ok.st, k, ok.h1.get<cx<double>>(), ok.h2.get<cx<double>>(), ok.ldh,
-                              ok.n2.get<cx<double>>(), 1, nrhs, st);
+        c->timed(DDAMG_KERNEL_OUTER_GS, nrhs, [&] { outer_arnoldi(V, vsj, k, nrhs, v32); });
         ++its;
-        if (!read_any_active(ok, nrhs)) {
+        c->sync();  // the active flags are in h_flags
+        int any = 0;
+        for (int r = 0; r < nrhs; ++r) any |= c->h_flags[r];
+        if (!any) {
           ++k;
           break;
         }

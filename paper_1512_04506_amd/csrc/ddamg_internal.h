@@ -392,7 +392,8 @@ void launch_net_span_loss(cx<float>* gam, double* loss_agg, double* loss, const 
 void launch_adam(float* w, float* m, float* v, const float* grad, size_t n, float lr, int64_t step, hipStream_t st);
 
 // BLAS on block vectors x[r * rstride + i], i < n, r < nrhs.
-// partial dots: part[(r * nvec + j) * nchunk + c]; final h[r * ldh + j].
+// partial dots: part[(r * nvec + j) * nchunk + c]; final h[r * ldh + j]
+// (h null: the partial dots only).
 // The multi-dot launchers take the capacity of part in entries and return
 // false, launching nothing, if the call needs more (mdot_part_entries).
 template <typename T>
@@ -405,25 +406,25 @@ template <typename Tw, typename Tv>
 void launch_maxpy(cx<Tw>* w, size_t wstride_r, const cx<Tv>* Vb, size_t vstride_j, size_t vstride_r, int nvec,
                   const cx<double>* h, int ldh, double sign, size_t n, int nrhs, const int* active, hipStream_t st,
                   const double* post = nullptr, cx<float>* w32 = nullptr);
-// Fused second Gram-Schmidt pass over FP64 vectors: w <- w - V h1, then
-// h2[r][j] = V_j^H w (j < nvec) and h2[r][nvec] = |w|^2, nvec <= GS_FUSED_MAXV
+// The outer Gram-Schmidt of step k (k + 1 <= GS_FUSED_MAXV) in four launches:
+// launch_mdot with h null (partial sums of V_j^H w, j <= k, and |w|^2 for
+// j = k + 1), launch_gs_coef, launch_gs_defer, launch_gs_column.  chunks:
+// blas_nchunks(n, nrhs), the partial sums of an inner product.
 constexpr int GS_FUSED_MAXV = 24;
-bool launch_gs_fused(cx<double>* h2, int ldh, cx<double>* part, size_t part_cap, const cx<double>* Vb,
-                     size_t vstride_j, size_t vstride_r, int nvec, cx<double>* w, size_t wstride_r,
-                     const cx<double>* h1, size_t n, int nrhs, const int* active, hipStream_t st);
-// The same pass with the previous step's second subtraction folded in: slot
-// k of Vb holds the pending vector u, replaced by v_k = sigma (u - sum_{j<k}
-// c_j V_j) if correct; then w <- w - sum_{j<=k} h_j V_j, w32 = FP32(wsc[r] w)
-// if given, h2[r][j] = V_j^H w (j <= k) and h2[r][k + 1] = |w|^2; k + 1 <= GS_FUSED_MAXV
-bool launch_gs_defer(cx<double>* h2, int ldh, cx<double>* part, size_t part_cap, cx<double>* Vb, size_t vsj,
-                     size_t vsr, int k, bool correct, const cx<double>* c, const double* sigma, cx<double>* w,
-                     size_t wsr, const cx<double>* h, size_t n, int nrhs, const int* active, cx<float>* w32,
-                     const double* wsc, hipStream_t st);
-// With h[r][k + 1] = |w|^2: if correct, c[r][j] = h2[r][j] (j < k) and h[r][k] =
-// sigma[r] (h[r][k] - sum_{j<k} conj(c_j) h[r][j]); then wsc[r] = 1 / |w - sum_{j<=k}
-// h_j V_j| estimated from |w|^2 - sum |h_j|^2 (nrhs <= 64)
-void launch_gs_defer_coef(cx<double>* h, cx<double>* c, const cx<double>* h2, int ldh, const double* sigma, int k,
-                          bool correct, double* wsc, int nrhs, const int* active, hipStream_t st);
+// h[r][j] from the partial sums; if correct, c[r][j] = h2[r][j] (j < k) and
+// h[r][k] = sigma[r] (h[r][k] - sum_{j<k} conj(c_j) h[r][j]); then wsc[r] =
+// 1 / |w - sum_{j<=k} h_j V_j| estimated from |w|^2 - sum |h_j|^2
+void launch_gs_coef(const cx<double>* part, int nchunk, cx<double>* h, cx<double>* c, const cx<double>* h2, int ldh,
+                    const double* sigma, int k, bool correct, double* wsc, int nrhs, const int* active,
+                    hipStream_t st);
+// w <- w - sum_{j<=k} h_j V_j with the previous step's second subtraction
+// folded in: slot k of Vb holds the pending vector u, replaced by v_k = sigma
+// (u - sum_{j<k} c_j V_j) if correct; w32 = FP32(wsc[r] w) if given; partial
+// sums of V_j^H w (j <= k) and |w|^2 (entry k + 1)
+bool launch_gs_defer(int ldh, cx<double>* part, size_t part_cap, cx<double>* Vb, size_t vsj, size_t vsr, int k,
+                     bool correct, const cx<double>* c, const double* sigma, cx<double>* w, size_t wsr,
+                     const cx<double>* h, size_t n, int nrhs, const int* active, cx<float>* w32, const double* wsc,
+                     hipStream_t st);
 // n2[r] = h2[r][nvec] - sum_{j<nvec} |h2[r][j]|^2, inv[r] = 1/sqrt(n2[r]) (0 if not positive)
 void launch_gs_norm(cx<double>* n2, double* inv, const cx<double>* h2, int ldh, int nvec, int nrhs,
                     const int* active, hipStream_t st);
@@ -466,6 +467,12 @@ void launch_arnoldi_start(ArnoldiState s, const cx<double>* norm2, int ldn, int 
 // est, convergence -> active, kdone
 void launch_arnoldi_column(ArnoldiState s, int k, const cx<double>* h1, const cx<double>* h2, int ldh,
                            const cx<double>* norm2, int ldn, int nrhs, hipStream_t st);
+// the outer step's end: h2[r][0..k] and |w|^2 from the partial sums, inv[r] =
+// 1 / |w''| with |w''|^2 = |w|^2 - sum_{j<=k} |h2_j|^2 (0 for a vanishing or
+// non-finite norm), then launch_arnoldi_column; host_active (pinned host
+// memory) receives the active flags
+void launch_gs_column(ArnoldiState s, int k, const cx<double>* part, int nchunk, const cx<double>* h1, cx<double>* h2,
+                      int ldh, double* inv, int* host_active, int nrhs, hipStream_t st);
 // y = H(1:kd, 1:kd)^{-1} g(1:kd) per rhs (upper triangular)
 void launch_arnoldi_solve(ArnoldiState s, int nrhs, hipStream_t st);
 // The coarse GMRES on vectors of n elements per rhs, one workgroup per rhs

@@ -1,6 +1,7 @@
 // The coarse GMRES around its operator (Alg. 2), one workgroup per rhs: the
 // start of a cycle, an Arnoldi step (classical Gram-Schmidt twice, the norm,
-// the Givens rotations and the convergence test) and the end of a cycle.
+// the Givens rotations and the convergence test) and the end of a cycle.  At
+// the end, the scalar work of the outer Gram-Schmidt.
 //
 // A coarse vector of a lattice up to 16^3x32 is some 10^4 elements, 100 KB
 // that lie in L2: what bounds a step is the number of dependent launches and
@@ -133,6 +134,41 @@ __global__ __launch_bounds__(AT) void coarse_start_kernel(ArnoldiState s, cx<T>*
   }
 }
 
+// Column k of rhs r, H[0 .. k] in LDS, subdiagonal hn: the rotations cs, sn
+// of the earlier columns, the new one, the rotated rhs (gk: its entry k), the
+// estimate and the stop test of arnoldi_column_kernel.  One lane; H[0 .. k +
+// 1] is left for the caller to store.
+__device__ inline bool finish_column(const ArnoldiState& s, int r, int k, cx<double>* H, const double* cs,
+                                     const cx<double>* sn, cx<double> gk, double tol, double hn) {
+  const int m = s.m;
+  H[k + 1] = mk(hn, 0.0);
+  for (int j = 0; j < k; ++j) {
+    const cx<double> u = cs[j] * H[j] + sn[j] * H[j + 1];
+    H[j + 1] = cs[j] * H[j + 1] - conj(sn[j]) * H[j];
+    H[j] = u;
+  }
+  double c;
+  cx<double> sv, rr;
+  givens(H[k], H[k + 1], c, sv, rr);
+  H[k] = rr;
+  H[k + 1] = mk(0.0, 0.0);
+  const cx<double> gn = neg(conj(sv) * gk);
+  const double est = sqrt(cabs2(gn));
+  const bool stop = !(hn > 0.0) || (tol >= 0.0 && est <= tol) || k + 1 >= m;
+  s.cs[(size_t)r * m + k] = mk(c, 0.0);
+  s.sn[(size_t)r * m + k] = sv;
+  s.g[(size_t)r * (m + 1) + k] = c * gk;
+  s.g[(size_t)r * (m + 1) + k + 1] = gn;
+  s.est[r] = est;
+  s.kdone[r] = k + 1;
+  s.inv_h[r] = stop ? 0.0 : 1.0 / hn;
+  if (stop) {
+    s.active[r] = 0;
+    atomicAdd(s.any, -1);
+  }
+  return stop;
+}
+
 // Arnoldi step k: w = V_{k+1} (the operator applied to V_k) orthogonalised
 // against V_0 .. V_k by classical Gram-Schmidt twice and normalised in
 // place; the column of H, the rotations and the stop test of
@@ -171,32 +207,7 @@ __global__ __launch_bounds__(AT) void coarse_arnoldi_kernel(ArnoldiState s, int 
   if (t == 0) {
     for (int j = 0; j <= k; ++j) H[j] = h1[j] + h2[j];
     const double hn = sqrt(fmax(hn2[0].r, 0.0));
-    H[k + 1] = mk(hn, 0.0);
-    for (int j = 0; j < k; ++j) {
-      const cx<double> u = cs[j] * H[j] + sn[j] * H[j + 1];
-      H[j + 1] = cs[j] * H[j + 1] - conj(sn[j]) * H[j];
-      H[j] = u;
-    }
-    double c;
-    cx<double> sv, rr;
-    givens(H[k], H[k + 1], c, sv, rr);
-    H[k] = rr;
-    H[k + 1] = mk(0.0, 0.0);
-    const cx<double> gn = neg(conj(sv) * gk);
-    const double est = sqrt(cabs2(gn));
-    const bool stop = !(hn > 0.0) || (tol >= 0.0 && est <= tol) || k + 1 >= m;
-    inv = stop ? 1.0 : 1.0 / hn;
-    s.cs[(size_t)r * m + k] = mk(c, 0.0);
-    s.sn[(size_t)r * m + k] = sv;
-    s.g[(size_t)r * (m + 1) + k] = c * gk;
-    s.g[(size_t)r * (m + 1) + k + 1] = gn;
-    s.est[r] = est;
-    s.kdone[r] = k + 1;
-    s.inv_h[r] = stop ? 0.0 : 1.0 / hn;
-    if (stop) {
-      s.active[r] = 0;
-      atomicAdd(s.any, -1);
-    }
+    inv = finish_column(s, r, k, H, cs, sn, gk, tol, hn) ? 1.0 : 1.0 / hn;
   }
   __syncthreads();
   if (t <= k + 1) s.H[(size_t)r * (m + 1) * m + (size_t)k * (m + 1) + t] = H[t];
@@ -243,6 +254,109 @@ __global__ __launch_bounds__(FT) void coarse_finish_kernel(ArnoldiState s, const
   }
 }
 
+// ------------------------------------------------------ outer Gram-Schmidt
+// The scalar work after each of the two passes over the outer basis, one
+// workgroup per rhs: the partial sums of its inner products, a wave for each,
+// and what follows from them.  Each was a chain of single-wave launches (sums
+// 4, coefficients 5; sums 4, norm 5, column 5 us and a copy of the flags to
+// the host) that no vector work hides when a lattice is small.  8^4, one rhs,
+// seven steps: 5 and 4 us now, the solve 2225 -> 2142 us; 16^3x32 3770 -> 3670.
+// out[j] (LDS), j < nvec: sum over the chunks of part[j][chunk]
+__device__ inline void sum_parts(cx<double>* out, const cx<double>* part, int nvec, int nchunk) {
+  const int lane = threadIdx.x & 63;
+  for (int j = threadIdx.x >> 6; j < nvec; j += AW) {
+    double re = 0.0, im = 0.0;
+#pragma unroll 4
+    for (int c = lane; c < nchunk; c += 64) {
+      const cx<double> v = part[(size_t)j * nchunk + c];
+      re += v.r;
+      im += v.i;
+    }
+    re = wave_sum_d(re);
+    im = wave_sum_d(im);
+    if (lane == 0) out[j] = mk(re, im);
+  }
+  __syncthreads();
+}
+
+// Before the deferred pass, with h[j] = V_j^H w (j <= k) and |w|^2: if
+// correct, c[j] = h2[j] (j < k), the pending vector's corrections, kept apart
+// from h2 (which the pass's sums overwrite), and h[k] = sigma (h[k] -
+// sum_{j<k} conj(c_j) h[j]), the inner product of w with the corrected v_k
+// from those with the stored vectors; then wsc = 1 / |w'| from |w'|^2 =
+// |w|^2 - sum_{j<=k} |h_j|^2, floored at 1e-20 |w|^2 against cancellation
+// (only a scale: the exact |w''| follows the pass).
+__global__ __launch_bounds__(AT) void gs_coef_kernel(const cx<double>* part, int nchunk, cx<double>* h, cx<double>* c,
+                                                     const cx<double>* h2, int ldh, const double* sigma, int k,
+                                                     int correct, double* wsc, const int* active) {
+  __shared__ cx<double> hs[GS_FUSED_MAXV + 1];
+  const int r = blockIdx.x, t = threadIdx.x;
+  if (!active[r]) return;
+  sum_parts(hs, part + (size_t)r * (k + 2) * nchunk, k + 2, nchunk);
+  if (t >= 64) return;
+  cx<double> hj = t <= k ? hs[t] : mk(0.0, 0.0);
+  if (correct) {
+    cx<double> d = mk(0.0, 0.0);
+    if (t < k) {
+      const cx<double> cj = h2[(size_t)r * ldh + t];
+      c[(size_t)r * ldh + t] = cj;
+      d = conj(cj) * hj;
+    }
+    d = mk(wave_sum_d(d.r), wave_sum_d(d.i));
+    if (t == k) hj = sigma[r] * (hj - d);
+  }
+  if (t <= k) h[(size_t)r * ldh + t] = hj;
+  const double n = wave_sum_d(cabs2(hj));
+  if (t == 0) {
+    const double w2 = hs[k + 1].r, e = fmax(w2 - n, 1e-20 * w2);
+    wsc[r] = (e > 0.0 && isfinite(e)) ? 1.0 / sqrt(e) : 0.0;
+  }
+}
+
+// After it, with h2[j] = V_j^H w' (j <= k) and |w'|^2: |w''|^2 = |w'|^2 -
+// sum_j |h2_j|^2 (w'' = w' - V h2 with V orthonormal), the factor that
+// normalises w'' (zero for a vanishing or non-finite norm: the step then
+// stops that rhs) and column k, H = h1 + h2.
+__global__ __launch_bounds__(AT) void gs_column_kernel(ArnoldiState s, int k, const cx<double>* part, int nchunk,
+                                                       const cx<double>* h1, cx<double>* h2, int ldh, double* inv,
+                                                       int* host_active) {
+  __shared__ cx<double> hs[GS_FUSED_MAXV + 1], H[GS_FUSED_MAXV + 2], sn[GS_FUSED_MAXV], gk;
+  __shared__ double cs[GS_FUSED_MAXV], tol, n2;
+  const int r = blockIdx.x, t = threadIdx.x, m = s.m;
+  if (!s.active[r]) {
+    if (t == 0) {
+      s.inv_h[r] = 0.0;
+      host_active[r] = 0;
+    }
+    return;
+  }
+  if (t < k) {
+    cs[t] = s.cs[(size_t)r * m + t].r;
+    sn[t] = s.sn[(size_t)r * m + t];
+  }
+  if (t <= k) H[t] = h1[(size_t)r * ldh + t];
+  if (t == 64) gk = s.g[(size_t)r * (m + 1) + k];
+  if (t == 128) tol = s.abstol[r];
+  sum_parts(hs, part + (size_t)r * (k + 2) * nchunk, k + 2, nchunk);
+  if (t < 64) {
+    const cx<double> v = t <= k ? hs[t] : mk(0.0, 0.0);
+    if (t <= k) {
+      h2[(size_t)r * ldh + t] = v;
+      H[t] = H[t] + v;
+    }
+    const double n = wave_sum_d(cabs2(v));
+    if (t == 0) n2 = fmax(hs[k + 1].r - n, 0.0);
+  }
+  __syncthreads();
+  if (t == 0) {
+    const double hn = sqrt(n2);
+    inv[r] = (hn > 0.0 && isfinite(hn)) ? 1.0 / hn : 0.0;
+    host_active[r] = finish_column(s, r, k, H, cs, sn, gk, tol, hn) ? 0 : 1;
+  }
+  __syncthreads();
+  if (t <= k + 1) s.H[(size_t)r * (m + 1) * m + (size_t)k * (m + 1) + t] = H[t];
+}
+
 // elements per thread: the narrowest of 4, 8, 16, 24 (FP64 to 16: registers)
 template <typename T, typename F>
 void with_ept(size_t n, F&& f) {
@@ -281,6 +395,19 @@ void launch_coarse_arnoldi(ArnoldiState s, int k, cx<T>* Vb, size_t vsj, size_t 
   with_ept<T>(n, [&](auto e) {
     coarse_arnoldi_kernel<T, decltype(e)::value><<<nrhs, AT, 0, st>>>(s, k, Vb, vsj, vsr, (int)n);
   });
+}
+
+void launch_gs_coef(const cx<double>* part, int nchunk, cx<double>* h, cx<double>* c, const cx<double>* h2, int ldh,
+                    const double* sigma, int k, bool correct, double* wsc, int nrhs, const int* active,
+                    hipStream_t st) {
+  if (nrhs <= 0) return;
+  gs_coef_kernel<<<nrhs, AT, 0, st>>>(part, nchunk, h, c, h2, ldh, sigma, k, correct ? 1 : 0, wsc, active);
+}
+
+void launch_gs_column(ArnoldiState s, int k, const cx<double>* part, int nchunk, const cx<double>* h1, cx<double>* h2,
+                      int ldh, double* inv, int* host_active, int nrhs, hipStream_t st) {
+  if (nrhs <= 0) return;
+  gs_column_kernel<<<nrhs, AT, 0, st>>>(s, k, part, nchunk, h1, h2, ldh, inv, host_active);
 }
 
 template <typename T>

@@ -54,7 +54,7 @@ __global__ __launch_bounds__(BT) void mdot_partial_kernel(cx<double>* part, cons
   for (int j = threadIdx.x; j < nvec; j += BT) {
     cx<double> s = mk(0.0, 0.0);
     for (int k = 0; k < BT / 64; ++k) s = s + red[j][k];
-    if (nchunk == 1)
+    if (h && nchunk == 1)
       h[(size_t)r * ldh + j] = s;
     else
       part[((size_t)r * nvec + j) * nchunk + c] = s;
@@ -99,65 +99,6 @@ __global__ __launch_bounds__(BT) void maxpy_kernel(cx<Tw>* w, size_t wsr, const 
   }
 }
 
-// Second step of classical Gram-Schmidt done twice, in one pass over the
-// data: w <- w - sum_j h_j V_j, then the partial sums of V_j^H w (j < nvec)
-// and |w|^2 (entry nvec) of the updated w, as mdot_partial_kernel writes
-// them.  The nvec basis entries of an element stay in registers between
-// the update and the inner products, so every vector is read once.
-template <int MAXV>
-__global__ __launch_bounds__(BT) void gs_fused_kernel(cx<double>* part, const cx<double>* __restrict__ Vb, size_t vsj,
-                                                      size_t vsr, int nvec, cx<double>* w, size_t wsr,
-                                                      const cx<double>* __restrict__ h, int ldh, size_t n,
-                                                      size_t chunk, int nchunk, const int* active,
-                                                      cx<double>* h2) {
-  __shared__ cx<double> red[MAXV + 1][BT / 64];
-  const int c = blockIdx.x;
-  const int r = blockIdx.y;
-  if (active && !active[r]) return;
-  const size_t beg = (size_t)c * chunk;
-  const size_t end = min(n, beg + chunk);
-  cx<double>* wr = w + (size_t)r * wsr;
-  const cx<double>* hr = h + (size_t)r * ldh;
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  cx<double> acc[MAXV];
-  double nacc = 0.0;
-#pragma unroll
-  for (int j = 0; j < MAXV; ++j) acc[j] = mk(0.0, 0.0);
-  for (size_t i = beg + threadIdx.x; i < end; i += BT) {
-    cx<double> v[MAXV];
-    cx<double> x = wr[i];
-#pragma unroll
-    for (int j = 0; j < MAXV; ++j)
-      if (j < nvec) {
-        v[j] = Vb[(size_t)j * vsj + (size_t)r * vsr + i];
-        x = x - hr[j] * v[j];
-      }
-    wr[i] = x;
-#pragma unroll
-    for (int j = 0; j < MAXV; ++j)
-      if (j < nvec) acc[j] = acc[j] + cmulc(v[j], x);
-    nacc += x.r * x.r + x.i * x.i;
-  }
-#pragma unroll
-  for (int j = 0; j < MAXV; ++j) {
-    if (j < nvec) {
-      const double re = wave_sum_d(acc[j].r), im = wave_sum_d(acc[j].i);
-      if (lane == 0) red[j][wid] = mk(re, im);
-    }
-  }
-  nacc = wave_sum_d(nacc);
-  if (lane == 0) red[nvec][wid] = mk(nacc, 0.0);
-  __syncthreads();
-  for (int j = threadIdx.x; j <= nvec; j += BT) {
-    cx<double> sum = mk(0.0, 0.0);
-    for (int k = 0; k < BT / 64; ++k) sum = sum + red[j][k];
-    if (nchunk == 1)
-      h2[(size_t)r * ldh + j] = sum;  // a single chunk: the sums are final
-    else
-      part[((size_t)r * (nvec + 1) + j) * nchunk + c] = sum;
-  }
-}
-
 // Second step of classical Gram-Schmidt done twice with the subtraction of
 // the previous step's second projection deferred into it.  Slot k holds the
 // pending vector u (the previous new vector, projected once); with the
@@ -166,7 +107,8 @@ __global__ __launch_bounds__(BT) void gs_fused_kernel(cx<double>* part, const cx
 // would have written, and is stored back (correct = false: u is v_k
 // already).  In the same pass over the data: w <- w - sum_{j<=k} h_j V_j
 // with the corrected v_k, its FP32 copy in w32 if given, and the partial
-// sums of V_j^H w (j <= k) and |w|^2 as gs_fused_kernel writes them.
+// sums of V_j^H w (j <= k) and |w|^2 (entry k + 1) as mdot_partial_kernel
+// writes them.
 // The FP32 copy is scaled by wsc[r] (an estimate of 1 / |w''|) so that the
 // preconditioner, which receives it, sees a vector of about unit norm.
 template <int MAXV>
@@ -174,8 +116,8 @@ __global__ __launch_bounds__(BT) void gs_defer_kernel(cx<double>* part, cx<doubl
                                                       int correct, const cx<double>* __restrict__ c, int ldc,
                                                       const double* __restrict__ sigma, cx<double>* w, size_t wsr,
                                                       const cx<double>* __restrict__ h, int ldh, size_t n,
-                                                      size_t chunk, int nchunk, const int* active, cx<double>* h2,
-                                                      cx<float>* w32, const double* __restrict__ wsc) {
+                                                      size_t chunk, int nchunk, const int* active, cx<float>* w32,
+                                                      const double* __restrict__ wsc) {
   __shared__ cx<double> red[MAXV + 1][BT / 64];
   const int cb = blockIdx.x;
   const int r = blockIdx.y;
@@ -234,42 +176,8 @@ __global__ __launch_bounds__(BT) void gs_defer_kernel(cx<double>* part, cx<doubl
   for (int j = threadIdx.x; j <= nvec; j += BT) {
     cx<double> sum = mk(0.0, 0.0);
     for (int q = 0; q < BT / 64; ++q) sum = sum + red[j][q];
-    if (nchunk == 1)
-      h2[(size_t)r * ldh + j] = sum;
-    else
-      part[((size_t)r * (nvec + 1) + j) * nchunk + cb] = sum;
+    part[((size_t)r * (nvec + 1) + j) * nchunk + cb] = sum;
   }
-}
-
-// Before the deferred pass, with h[r][0..k] = V_j^H w and h[r][k + 1] =
-// |w|^2 from the first pass: if correct, c[r][j] = h2[r][j] (j < k), the
-// pending vector's corrections, kept apart from h2 (which that pass
-// overwrites), and h[r][k] = sigma_r (h[r][k] - sum_{j<k} conj(c_j) h[r][j]),
-// the inner product of w with the corrected v_k from those with the stored
-// vectors; then wsc[r] = 1 / |w'| from |w'|^2 = |w|^2 - sum_{j<=k} |h_j|^2,
-// floored at 1e-20 |w|^2 against cancellation (only a scale: the exact
-// |w''| follows the pass).
-__global__ void gs_defer_coef_kernel(cx<double>* h, cx<double>* c, const cx<double>* h2, int ldh,
-                                     const double* sigma, int k, int correct, double* wsc, int nrhs,
-                                     const int* active) {
-  const int r = threadIdx.x;
-  if (r >= nrhs) return;
-  if (active && !active[r]) return;
-  cx<double>* hr = h + (size_t)r * ldh;
-  if (correct) {
-    cx<double> d = hr[k];
-    for (int j = 0; j < k; ++j) {
-      const cx<double> cj = h2[(size_t)r * ldh + j];
-      c[(size_t)r * ldh + j] = cj;
-      d = d - conj(cj) * hr[j];
-    }
-    hr[k] = sigma[r] * d;
-  }
-  const double w2 = hr[k + 1].r;
-  double e = w2;
-  for (int j = 0; j <= k; ++j) e -= hr[j].r * hr[j].r + hr[j].i * hr[j].i;
-  e = fmax(e, 1e-20 * w2);
-  wsc[r] = (e > 0.0 && isfinite(e)) ? 1.0 / sqrt(e) : 0.0;
 }
 
 // |w''|^2 = |w'|^2 - sum_j |h2_j|^2 (w'' = w' - V h2 with V orthonormal),
@@ -326,10 +234,10 @@ inline unsigned grid_for(size_t n) {
 }
 
 // ----------------------------------------------------- Arnoldi / Givens
-// active flags of all rhs into *any (one 64-lane wave, nrhs <= 64)
+// the number of active rhs into *any (one 64-lane wave, nrhs <= 64)
 __device__ inline void publish_any(const ArnoldiState& s, bool act) {
   const unsigned long long b = __ballot(act);
-  if (threadIdx.x == 0) *s.any = b != 0ull ? 1 : 0;
+  if (threadIdx.x == 0) *s.any = __popcll(b);
 }
 
 __global__ void arnoldi_start_kernel(ArnoldiState s, const cx<double>* norm2, int ldn, int nrhs) {
@@ -453,7 +361,7 @@ bool launch_mdot(cx<double>* h, int ldh, cx<double>* part, size_t part_cap, cons
   const size_t chunk = (n + nchunk - 1) / nchunk;
   mdot_partial_kernel<T><<<dim3(nchunk, nrhs), BT, 0, st>>>(part, Vb, vsj, vsr, nvec, w, wsr, n, chunk, nchunk,
                                                             active, h, ldh);
-  if (nchunk > 1) mdot_final_kernel<<<dim3(nvec, nrhs), 64, 0, st>>>(h, ldh, part, nvec, nchunk, active);
+  if (h && nchunk > 1) mdot_final_kernel<<<dim3(nvec, nrhs), 64, 0, st>>>(h, ldh, part, nvec, nchunk, active);
   return true;
 }
 
@@ -466,30 +374,7 @@ void launch_maxpy(cx<Tw>* w, size_t wsr, const cx<Tv>* Vb, size_t vsj, size_t vs
       <<<dim3(grid_for(n), nrhs), BT, 0, st>>>(w, wsr, Vb, vsj, vsr, nvec, h, ldh, sign, n, active, post, w32);
 }
 
-bool launch_gs_fused(cx<double>* h2, int ldh, cx<double>* part, size_t part_cap, const cx<double>* Vb, size_t vsj,
-                     size_t vsr, int nvec, cx<double>* w, size_t wsr, const cx<double>* h1, size_t n, int nrhs,
-                     const int* active, hipStream_t st) {
-  if (nrhs <= 0 || nvec <= 0) return true;
-  if (nvec > GS_FUSED_MAXV || mdot_part_entries(n, nvec + 1, nrhs) > part_cap) return false;
-  const int nchunk = blas_nchunks(n, nrhs);
-  const size_t chunk = (n + nchunk - 1) / nchunk;
-  // the narrowest instance that holds nvec basis entries per element (fewer
-  // registers, more waves in flight for this streaming kernel)
-  const dim3 grid(nchunk, nrhs);
-  if (nvec <= 4)
-    gs_fused_kernel<4><<<grid, BT, 0, st>>>(part, Vb, vsj, vsr, nvec, w, wsr, h1, ldh, n, chunk, nchunk, active, h2);
-  else if (nvec <= 8)
-    gs_fused_kernel<8><<<grid, BT, 0, st>>>(part, Vb, vsj, vsr, nvec, w, wsr, h1, ldh, n, chunk, nchunk, active, h2);
-  else if (nvec <= 16)
-    gs_fused_kernel<16><<<grid, BT, 0, st>>>(part, Vb, vsj, vsr, nvec, w, wsr, h1, ldh, n, chunk, nchunk, active, h2);
-  else
-    gs_fused_kernel<GS_FUSED_MAXV><<<grid, BT, 0, st>>>(part, Vb, vsj, vsr, nvec, w, wsr, h1, ldh, n, chunk, nchunk,
-                                                        active, h2);
-  if (nchunk > 1) mdot_final_kernel<<<dim3(nvec + 1, nrhs), 64, 0, st>>>(h2, ldh, part, nvec + 1, nchunk, active);
-  return true;
-}
-
-bool launch_gs_defer(cx<double>* h2, int ldh, cx<double>* part, size_t part_cap, cx<double>* Vb, size_t vsj,
+bool launch_gs_defer(int ldh, cx<double>* part, size_t part_cap, cx<double>* Vb, size_t vsj,
                      size_t vsr, int k, bool correct, const cx<double>* c, const double* sigma, cx<double>* w,
                      size_t wsr, const cx<double>* h, size_t n, int nrhs, const int* active, cx<float>* w32,
                      const double* wsc, hipStream_t st) {
@@ -502,24 +387,17 @@ bool launch_gs_defer(cx<double>* h2, int ldh, cx<double>* part, size_t part_cap,
   const int cr = correct ? 1 : 0;
   if (nvec <= 4)
     gs_defer_kernel<4><<<grid, BT, 0, st>>>(part, Vb, vsj, vsr, k, cr, c, ldh, sigma, w, wsr, h, ldh, n, chunk, nchunk,
-                                            active, h2, w32, wsc);
+                                            active, w32, wsc);
   else if (nvec <= 8)
     gs_defer_kernel<8><<<grid, BT, 0, st>>>(part, Vb, vsj, vsr, k, cr, c, ldh, sigma, w, wsr, h, ldh, n, chunk, nchunk,
-                                            active, h2, w32, wsc);
+                                            active, w32, wsc);
   else if (nvec <= 16)
     gs_defer_kernel<16><<<grid, BT, 0, st>>>(part, Vb, vsj, vsr, k, cr, c, ldh, sigma, w, wsr, h, ldh, n, chunk,
-                                             nchunk, active, h2, w32, wsc);
+                                             nchunk, active, w32, wsc);
   else
     gs_defer_kernel<GS_FUSED_MAXV><<<grid, BT, 0, st>>>(part, Vb, vsj, vsr, k, cr, c, ldh, sigma, w, wsr, h, ldh, n,
-                                                        chunk, nchunk, active, h2, w32, wsc);
-  if (nchunk > 1)
-    mdot_final_kernel<<<dim3(nvec + 1, nrhs), 64, 0, st>>>(h2, ldh, part, nvec + 1, nchunk, active);
+                                                        chunk, nchunk, active, w32, wsc);
   return true;
-}
-
-void launch_gs_defer_coef(cx<double>* h, cx<double>* c, const cx<double>* h2, int ldh, const double* sigma, int k,
-                          bool correct, double* wsc, int nrhs, const int* active, hipStream_t st) {
-  gs_defer_coef_kernel<<<1, 64, 0, st>>>(h, c, h2, ldh, sigma, k, correct ? 1 : 0, wsc, nrhs, active);
 }
 
 void launch_gs_norm(cx<double>* n2, double* inv, const cx<double>* h2, int ldh, int nvec, int nrhs, const int* active,

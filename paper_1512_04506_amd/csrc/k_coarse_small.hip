@@ -5,9 +5,10 @@
 // solve, the back substitution, then x_e = D_ee^{-1} (y_e - D_eo x_o).
 //
 // One GMRES iteration is a few microseconds of work; as separate launches it
-// is a chain of launch latencies.  Here one compute unit reads the operator once per iteration (1.2 MB on 2^4 sites at
-// N_tv 16 in FP32), at most 64 bytes a cycle from L2, 9 us: what bounds it
-// is that rate and the loads in flight.  Every lane therefore takes 16 bytes
+// is a chain of launch latencies.  Here one compute unit reads the operator
+// once per iteration (1.2 MB on 2^4 sites at N_tv 16 in FP32), at most 64
+// bytes a cycle from L2, 9 us: what bounds it is that rate and the loads in
+// flight.  Every lane therefore takes 16 bytes
 // of a column (two rows, one in FP64) with eight columns in flight, the
 // columns of all slots are split over as many lanes as the workgroup has,
 // and the vectors stay on chip: the operator's input in LDS, where each
