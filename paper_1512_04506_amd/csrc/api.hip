@@ -427,11 +427,13 @@ struct Solver final : SolverBase {
   // read the coarse convergence flags after every iteration, stalling the
   // device (the former scheme, kept for the timing comparison)
   bool sync_each_coarse_it = false;
-  // Each coarse GMRES iteration (Schur complement, CGS2, Arnoldi column,
-  // scaling: ten launches) captured once per (iteration index, nrhs) into a
-  // HIP graph and replayed: one launch call instead of ten.  The captured
-  // kernels read only buffers allocated with the solver, so the graphs stay
-  // valid for its lifetime; nothing captured is a memset or a host copy.
+  // Each coarse GMRES iteration (Schur complement and Arnoldi step: three
+  // launches, or ten for vectors beyond one workgroup's) captured once per
+  // (iteration index, nrhs) into a HIP graph and replayed: one launch call.
+  // The captured kernels use only buffers allocated with the solver and its
+  // context's pinned flags (an iteration's slot follows from its index), so
+  // the graphs stay valid for its lifetime; nothing captured is a memset or a
+  // host copy.
   // Not while kernel timing is on (its events would be captured too).
   bool use_graphs = true;
   std::map<std::pair<int, int>, hipGraphExec_t> step_graphs;
@@ -600,14 +602,16 @@ struct Solver final : SolverBase {
     });
   }
 
-  // Pipelined convergence test: post(slot) copies the per-rhs active flags
-  // into a pinned host slot behind the work enqueued so far; any_posted(slot)
-  // waits for that copy only.  Posting the flags of iteration k and reading
+  // Pipelined convergence test: the per-rhs active flags of an iteration go to
+  // a pinned host slot (written by the fused step itself, else copied behind
+  // it), post(slot) marks that point of the stream and any_posted(slot) waits
+  // for it only.  Posting the flags of iteration k and reading
   // them after iteration k + 1 is enqueued keeps the device busy while the
   // host decides; kernels of inactive rhs return at once, so the iteration
   // enqueued past convergence changes nothing.
-  void post_active(const Krylov& k, int nrhs, int slot) {
-    HIPCK(hipMemcpyAsync(c->h_ring + 64 * slot, k.active.get<int>(), sizeof(int) * nrhs, hipMemcpyDeviceToHost, st));
+  void post_active(const Krylov& k, int nrhs, int slot, bool written) {
+    if (!written)
+      HIPCK(hipMemcpyAsync(c->h_ring + 64 * slot, k.active.get<int>(), sizeof(int) * nrhs, hipMemcpyDeviceToHost, st));
     HIPCK(hipEventRecord(c->ring_ev[slot], st));
   }
   int any_posted(int nrhs, int slot) {
@@ -617,8 +621,10 @@ struct Solver final : SolverBase {
     return any;
   }
 
-  int read_any_active(const Krylov& k, int nrhs) {
-    HIPCK(hipMemcpyAsync(c->h_flags, k.active.get<int>(), sizeof(int) * nrhs, hipMemcpyDeviceToHost, st));
+  // the flags as of now, copied unless a kernel has written them to h_flags
+  int read_any_active(const Krylov& k, int nrhs, bool written = false) {
+    if (!written)
+      HIPCK(hipMemcpyAsync(c->h_flags, k.active.get<int>(), sizeof(int) * nrhs, hipMemcpyDeviceToHost, st));
     c->sync();
     int any = 0;
     for (int r = 0; r < nrhs; ++r) any |= c->h_flags[r];
@@ -684,7 +690,7 @@ struct Solver final : SolverBase {
       if (!first) schur(cw.get<cx<T>>(), osz(), xo, cs_, nrhs);
       if (fused) {
         launch_coarse_start<T>(ck.st, Vb, vsr, bo.get<cx<T>>(), first ? nullptr : cw.get<cx<T>>(), osz(), osz(), xo,
-                               cs_, ycv, cs_, cs_, tol, nrhs, st);
+                               cs_, ycv, cs_, cs_, tol, c->h_flags, nrhs, st);
       } else {
         if (first)
           launch_copy<T, T>(Vb, vsr, bo.get<cx<T>>(), osz(), osz(), nrhs, st);
@@ -698,7 +704,7 @@ struct Solver final : SolverBase {
       }
       first = false;
       // with a fixed iteration count the schedule is known: no host reads
-      if ((fixed <= 0 || sync_each_coarse_it) && !read_any_active(ck, nrhs)) break;
+      if ((fixed <= 0 || sync_each_coarse_it) && !read_any_active(ck, nrhs, fused)) break;
       int k = 0;
       for (; k < m && its < maxit; ++k) {
         cx<T>* w = Vb + (size_t)(k + 1) * vsj;
@@ -708,7 +714,7 @@ struct Solver final : SolverBase {
           schur(w, vsr, Vb + (size_t)k * vsj, vsr, nrhs, ck.any.get<int>());
           if (fused) {
             c->timed(DDAMG_KERNEL_COARSE_GS, nrhs,
-                     [&] { launch_coarse_arnoldi<T>(ck.st, k, Vb, vsj, vsr, osz(), nrhs, st); });
+                     [&] { launch_coarse_arnoldi<T>(ck.st, k, Vb, vsj, vsr, osz(), c->h_ring + 64 * (k & 1), nrhs, st); });
             return;
           }
           c->timed(DDAMG_KERNEL_COARSE_GS, nrhs, [&] { cgs2(ck, Vb, vsj, vsr, k, w, vsr, osz(), nrhs); });
@@ -725,7 +731,7 @@ struct Solver final : SolverBase {
           continue;
         }
         if (fixed > 0) continue;
-        post_active(ck, nrhs, k & 1);
+        post_active(ck, nrhs, k & 1, fused);
         // iteration k is enqueued: decide on the flags of iteration k - 1
         if (k >= 1 && !any_posted(nrhs, (k - 1) & 1)) {
           --its;  // iteration k ran on inactive rhs only
@@ -1132,10 +1138,7 @@ struct Solver final : SolverBase {
         });
         c->timed(DDAMG_KERNEL_OUTER_GS, nrhs, [&] { outer_arnoldi(V, vsj, k, nrhs, v32); });
         ++its;
-        c->sync();  // the active flags are in h_flags
-        int any = 0;
-        for (int r = 0; r < nrhs; ++r) any |= c->h_flags[r];
-        if (!any) {
+        if (!read_any_active(ok, nrhs, true)) {
           ++k;
           break;
         }

@@ -11,7 +11,8 @@
 // the norm, the column, the scaling: 9 + 3 + 3, 9 + 3 + 3, 9 + 3, 4, 2 us on
 // 16^3x32, 1 rhs, N_tv 24; now 15 us there, 9.8 us for 8 rhs on 16^4 at N_tv
 // 20) and a start one instead of five.  The solves: 16^3x32 5.15 -> 4.47 ms,
-// 16^4 with 8 rhs 8.57 -> 7.94 ms.  A thread holds at most 24 elements in
+// 16^4 with 8 rhs 8.57 -> 7.94 ms; with the flags stored to the host's memory
+// by the steps and the start's loads all in flight 3.67 -> 3.59, 7.34 -> 7.25.  A thread holds at most 24 elements in
 // FP32, 16 in FP64 (the registers of a 1024-lane workgroup); longer vectors
 // keep the many-workgroup kernels of k_blas.hip.
 #include "krylov_device.h"
@@ -77,6 +78,12 @@ __device__ inline void sw_update(cx<T> w[EPT], const cx<double>* h, const cx<T>*
   }
 }
 
+// an rhs's active flag for the host, in its pinned memory: a copy of the
+// flags behind the kernel was another 3 us on the stream for each step
+__device__ inline void post_flag(int* host_active, int r, int act) {
+  __hip_atomic_store(host_active + r, act, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Start of a cycle: V_0 = r / |r| with r = b_o - c_w (c_w null: b_o, the
 // first cycle, whose x_o is set to zero and whose stop threshold tol |y_c|
 // is computed, tol < 0: never test), the state of arnoldi_start_kernel.
@@ -84,7 +91,8 @@ __device__ inline void sw_update(cx<T> w[EPT], const cx<double>* h, const cx<T>*
 template <typename T, int EPT>
 __global__ __launch_bounds__(AT) void coarse_start_kernel(ArnoldiState s, cx<T>* V0, size_t vsr, const cx<T>* bo,
                                                           const cx<T>* cw, size_t bstr, int n, cx<T>* xo, size_t xstr,
-                                                          const cx<T>* yc, size_t ystr, int nc_all, double tol) {
+                                                          const cx<T>* yc, size_t ystr, int nc_all, double tol,
+                                                          int* host_active) {
   __shared__ double red[8][AW];
   __shared__ cx<double> h[AJ];
   const int r = blockIdx.x, t = threadIdx.x, m = s.m;
@@ -92,28 +100,32 @@ __global__ __launch_bounds__(AT) void coarse_start_kernel(ArnoldiState s, cx<T>*
   V0 += (size_t)r * vsr;
   cx<T> w[EPT];
 #pragma unroll
-  for (int i = 0; i < EPT; ++i) {
-    const int e = t + AT * i;
-    w[i] = e < n ? bo[e] : mk((T)0, (T)0);
-    if (cw && e < n) w[i] = w[i] - cw[(size_t)r * bstr + e];
-  }
-  double abstol;
-  if (!cw) {
-    const cx<T>* y = yc + (size_t)r * ystr;
-    cx<double> d[AJ];
+  for (int i = 0; i < EPT; ++i) w[i] = t < n - AT * i ? elem(bo + AT * i, (unsigned)t) : mk((T)0, (T)0);
+  // |r|^2 and, in the first cycle, |y_c|^2 in one reduction
+  cx<double> d[AJ];
 #pragma unroll
-    for (int q = 0; q < AJ; ++q) d[q] = mk(0.0, 0.0);
-    T a = (T)0;
-    for (int e = t; e < nc_all; e += AT) a += y[e].r * y[e].r + y[e].i * y[e].i;
-    d[0].r = (double)a;
-    block_sum(h, d, 1, red);
-    abstol = tol < 0.0 ? -1.0 : tol * sqrt(fmax(h[0].r, 0.0));
-    for (int e = t; e < n; e += AT) xo[(size_t)r * xstr + e] = mk((T)0, (T)0);
-    __syncthreads();  // h is written again
+  for (int q = 0; q < AJ; ++q) d[q] = mk(0.0, 0.0);
+  if (cw) {
+    cw += (size_t)r * bstr;
+#pragma unroll
+    for (int i = 0; i < EPT; ++i) {
+      if (t < n - AT * i) w[i] = w[i] - elem(cw + AT * i, (unsigned)t);
+      if (i % hold<EPT>() == hold<EPT>() - 1) asm volatile("" ::: "memory");
+    }
   } else {
-    abstol = s.abstol[r];
+    const cx<T>* y = yc + (size_t)r * ystr;
+    T a = (T)0;
+#pragma unroll 8
+    for (int e = t; e < nc_all; e += AT) a += y[e].r * y[e].r + y[e].i * y[e].i;
+    d[1].r = (double)a;
+    for (int e = t; e < n; e += AT) xo[(size_t)r * xstr + e] = mk((T)0, (T)0);
   }
-  sw_norm2<T, EPT>(h, w, red);
+  T a = (T)0;
+#pragma unroll
+  for (int i = 0; i < EPT; ++i) a += w[i].r * w[i].r + w[i].i * w[i].i;
+  d[0].r = (double)a;
+  block_sum(h, d, 2, red);
+  const double abstol = cw ? s.abstol[r] : tol < 0.0 ? -1.0 : tol * sqrt(fmax(h[1].r, 0.0));
   const double beta = sqrt(fmax(h[0].r, 0.0));
   const bool act = abstol < 0.0 ? beta > 0.0 : beta > abstol;
   const double inv = act ? 1.0 / beta : 0.0;
@@ -125,6 +137,7 @@ __global__ __launch_bounds__(AT) void coarse_start_kernel(ArnoldiState s, cx<T>*
   if (t <= m) s.g[(size_t)r * (m + 1) + t] = mk(t == 0 ? beta : 0.0, 0.0);
   if (t == 0) {
     const int was = s.active[r], now = act ? 1 : 0;
+    post_flag(host_active, r, now);
     s.abstol[r] = abstol;
     s.active[r] = now;
     s.inv_h[r] = inv;
@@ -177,13 +190,16 @@ __device__ inline bool finish_column(const ArnoldiState& s, int r, int k, cx<dou
 // the inner products).  An rhs that stops keeps its vector unscaled.
 template <typename T, int EPT>
 __global__ __launch_bounds__(AT) void coarse_arnoldi_kernel(ArnoldiState s, int k, cx<T>* Vb, size_t vsj, size_t vsr,
-                                                            int n) {
+                                                            int n, int* host_active) {
   __shared__ double red[8][AW];
   __shared__ cx<double> h1[64 + AJ], h2[64 + AJ], hn2[AJ], sn[64], H[66], gk;
   __shared__ double cs[64], tol, inv;
   const int r = blockIdx.x, t = threadIdx.x, m = s.m;
   if (!s.active[r]) {
-    if (t == 0) s.inv_h[r] = 0.0;
+    if (t == 0) {
+      s.inv_h[r] = 0.0;
+      post_flag(host_active, r, 0);
+    }
     return;
   }
   const cx<T>* V = Vb + (size_t)r * vsr;
@@ -207,7 +223,9 @@ __global__ __launch_bounds__(AT) void coarse_arnoldi_kernel(ArnoldiState s, int 
   if (t == 0) {
     for (int j = 0; j <= k; ++j) H[j] = h1[j] + h2[j];
     const double hn = sqrt(fmax(hn2[0].r, 0.0));
-    inv = finish_column(s, r, k, H, cs, sn, gk, tol, hn) ? 1.0 : 1.0 / hn;
+    const bool stop = finish_column(s, r, k, H, cs, sn, gk, tol, hn);
+    post_flag(host_active, r, stop ? 0 : 1);
+    inv = stop ? 1.0 : 1.0 / hn;
   }
   __syncthreads();
   if (t <= k + 1) s.H[(size_t)r * (m + 1) * m + (size_t)k * (m + 1) + t] = H[t];
@@ -232,14 +250,22 @@ __global__ __launch_bounds__(FT) void coarse_finish_kernel(ArnoldiState s, const
   if (threadIdx.x < 64) {
     const cx<double>* H = s.H + (size_t)r * (m + 1) * m;
     cx<double> g = lane < kd ? s.g[(size_t)r * (m + 1) + lane] : mk(0.0, 0.0);
-    for (int i = kd - 1; i >= 0; --i) {
-      const cx<double> hc = lane <= i ? H[(size_t)i * (m + 1) + lane] : mk(0.0, 0.0);
-      const cx<double> d = mk(__shfl(hc.r, i, 64), __shfl(hc.i, i, 64));
-      const cx<double> gi = mk(__shfl(g.r, i, 64), __shfl(g.i, i, 64));
-      const double dn = cabs2(d);
-      const cx<double> yi = dn > 0.0 ? (1.0 / dn) * (conj(d) * gi) : mk(0.0, 0.0);
-      if (lane == i) g = yi;
-      if (lane < i) g = g - hc * yi;
+    for (int i0 = kd - 1; i0 >= 0; i0 -= 4) {
+      cx<double> hc[4];  // four columns in flight
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        hc[q] = lane <= i0 - q ? H[(size_t)(i0 - q) * (m + 1) + lane] : mk(0.0, 0.0);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int i = i0 - q;
+        if (i < 0) break;
+        const cx<double> d = mk(__shfl(hc[q].r, i, 64), __shfl(hc[q].i, i, 64));
+        const cx<double> gi = mk(__shfl(g.r, i, 64), __shfl(g.i, i, 64));
+        const double dn = cabs2(d);
+        const cx<double> yi = dn > 0.0 ? (1.0 / dn) * (conj(d) * gi) : mk(0.0, 0.0);
+        if (lane == i) g = yi;
+        if (lane < i) g = g - hc[q] * yi;
+      }
     }
     if (lane < kd) y[lane] = cvt<T>(g);
   }
@@ -249,6 +275,7 @@ __global__ __launch_bounds__(FT) void coarse_finish_kernel(ArnoldiState s, const
   const size_t e0 = (size_t)blockIdx.x * F_ELEMS;
   for (size_t e = e0 + threadIdx.x; e < min(n, e0 + F_ELEMS); e += FT) {
     cx<T> acc = x[e];
+#pragma unroll 4
     for (int j = 0; j < kd; ++j) acc = acc + y[j] * V[(size_t)j * vsj + e];
     x[e] = acc;
   }
@@ -326,7 +353,7 @@ __global__ __launch_bounds__(AT) void gs_column_kernel(ArnoldiState s, int k, co
   if (!s.active[r]) {
     if (t == 0) {
       s.inv_h[r] = 0.0;
-      host_active[r] = 0;
+      post_flag(host_active, r, 0);
     }
     return;
   }
@@ -351,7 +378,7 @@ __global__ __launch_bounds__(AT) void gs_column_kernel(ArnoldiState s, int k, co
   if (t == 0) {
     const double hn = sqrt(n2);
     inv[r] = (hn > 0.0 && isfinite(hn)) ? 1.0 / hn : 0.0;
-    host_active[r] = finish_column(s, r, k, H, cs, sn, gk, tol, hn) ? 0 : 1;
+    post_flag(host_active, r, finish_column(s, r, k, H, cs, sn, gk, tol, hn) ? 0 : 1);
   }
   __syncthreads();
   if (t <= k + 1) s.H[(size_t)r * (m + 1) * m + (size_t)k * (m + 1) + t] = H[t];
@@ -379,21 +406,22 @@ bool arnoldi_fits(size_t n) {
 
 template <typename T>
 void launch_coarse_start(ArnoldiState s, cx<T>* V0, size_t vsr, const cx<T>* bo, const cx<T>* cw, size_t bstr, size_t n,
-                         cx<T>* xo, size_t xstr, const cx<T>* yc, size_t ystr, size_t n_all, double tol, int nrhs,
-                         hipStream_t st) {
+                         cx<T>* xo, size_t xstr, const cx<T>* yc, size_t ystr, size_t n_all, double tol, int* host_active,
+                         int nrhs, hipStream_t st) {
   if (nrhs <= 0) return;
   with_ept<T>(n, [&](auto e) {
     coarse_start_kernel<T, decltype(e)::value>
-        <<<nrhs, AT, 0, st>>>(s, V0, vsr, bo, cw, bstr, (int)n, xo, xstr, yc, ystr, (int)n_all, tol);
+        <<<nrhs, AT, 0, st>>>(s, V0, vsr, bo, cw, bstr, (int)n, xo, xstr, yc, ystr, (int)n_all, tol,
+                               host_active);
   });
 }
 
 template <typename T>
-void launch_coarse_arnoldi(ArnoldiState s, int k, cx<T>* Vb, size_t vsj, size_t vsr, size_t n, int nrhs,
-                           hipStream_t st) {
+void launch_coarse_arnoldi(ArnoldiState s, int k, cx<T>* Vb, size_t vsj, size_t vsr, size_t n, int* host_active,
+                           int nrhs, hipStream_t st) {
   if (nrhs <= 0) return;
   with_ept<T>(n, [&](auto e) {
-    coarse_arnoldi_kernel<T, decltype(e)::value><<<nrhs, AT, 0, st>>>(s, k, Vb, vsj, vsr, (int)n);
+    coarse_arnoldi_kernel<T, decltype(e)::value><<<nrhs, AT, 0, st>>>(s, k, Vb, vsj, vsr, (int)n, host_active);
   });
 }
 
@@ -421,8 +449,8 @@ void launch_coarse_finish(ArnoldiState s, const cx<T>* Vb, size_t vsj, size_t vs
 #define INST(T)                                                                                                        \
   template bool arnoldi_fits<T>(size_t);                                                                               \
   template void launch_coarse_start<T>(ArnoldiState, cx<T>*, size_t, const cx<T>*, const cx<T>*, size_t, size_t,       \
-                                       cx<T>*, size_t, const cx<T>*, size_t, size_t, double, int, hipStream_t);        \
-  template void launch_coarse_arnoldi<T>(ArnoldiState, int, cx<T>*, size_t, size_t, size_t, int, hipStream_t);         \
+                                       cx<T>*, size_t, const cx<T>*, size_t, size_t, double, int*, int, hipStream_t);  \
+  template void launch_coarse_arnoldi<T>(ArnoldiState, int, cx<T>*, size_t, size_t, size_t, int*, int, hipStream_t);   \
   template void launch_coarse_finish<T>(ArnoldiState, const cx<T>*, size_t, size_t, cx<T>*, size_t, size_t, int,       \
                                         hipStream_t);
 INST(double)
