@@ -406,7 +406,7 @@ struct Solver final : SolverBase {
   void ensure_setup_ws() {
     if (ws_Wd.p) return;
     ws_Wd.alloc<cx<double>>((size_t)g.ntv * fsz());
-    ws_T.alloc<cx<double>>((size_t)2 * g.nblocks * QR_TWS_PER_AGG);
+    ws_T.alloc<cx<double>>(qr_tws_entries(g));
     if (is_half<S>()) ws_Wt.alloc<cx<T>>((size_t)g.ntv * fsz());  // else the stored basis is already cx<T>
     ws_D.alloc<cx<T>>((size_t)g.nblocks * 9 * g.nc * g.nc);
     ws_Z.alloc<cx<T>>((size_t)g.ntv * fsz());
@@ -777,21 +777,26 @@ struct Solver final : SolverBase {
     if (stat) throw Fail{DDAMG_ENUMERIC, "test vector with zero or non-finite norm"};
   }
 
-  // Alg. 5 from an orthonormal FP64 basis Wd: store R (storage S), build
-  // D_c = R D P from the stored basis, fill backward couplings by Eq. dagger,
-  // quantise, and invert the even self blocks.
+  // the FP32 values scale * half of an FP16 basis, written as it is stored
+  cx<float>* basis_wt() {
+    if constexpr (is_half<S>()) return ws_Wt.get<cx<float>>();
+    return nullptr;
+  }
+  // Alg. 5 from an orthonormal FP64 basis Wd: store R (storage S)
   void build_coarse_from(cx<double>* Wd) {
-    ensure_setup_ws();
+    launch_quantize_basis<S>(Wq.get<stc_t<S>>(), Wsc.get<float>(), Wd, g, st, basis_wt());
+    build_coarse_op();
+  }
+  // From the stored basis: D_c = R D P, backward couplings by Eq. dagger,
+  // quantise, and invert the even self blocks.
+  void build_coarse_op() {
     const size_t nc = g.nc, nn = nc * nc;
-    // the block pass reads the stored basis in T: for FP16 storage the FP32
-    // values scale * half, written by the quantisation itself
+    // the block pass reads the stored basis in T
     const cx<T>* Wtp;
     if constexpr (is_half<S>()) {
       static_assert(std::is_same<T, float>::value, "FP16 basis storage goes with FP32 arithmetic");
-      launch_quantize_basis<S>(Wq.get<stc_t<S>>(), Wsc.get<float>(), Wd, g, st, ws_Wt.get<cx<float>>());
       Wtp = ws_Wt.get<cx<T>>();
     } else {
-      launch_quantize_basis<S>(Wq.get<stc_t<S>>(), Wsc.get<float>(), Wd, g, st);
       Wtp = reinterpret_cast<const cx<T>*>(Wq.get<stc_t<S>>());
     }
     cx<T>* D = ws_D.get<cx<T>>();
@@ -823,18 +828,19 @@ struct Solver final : SolverBase {
   // Gram-Schmidt of the current test vectors on every aggregate, then D_c
   void build_coarse() {
     ensure_setup_ws();
-    cx<double>* W = ws_Wd.get<cx<double>>();
     HIPCK(hipMemsetAsync(c->status.get<int>(), 0, sizeof(int), st));
-    // the first CholQR pass reads the test vectors in their own precision and
-    // writes the FP64 copy W, the second works on W in place
-    c->timed(DDAMG_KERNEL_SETUP_QR, g.ntv,
-             [&] { launch_aggregate_qr<T>(W, tv.get<cx<T>>(), g, c->status.get<int>(), ws_T.get<cx<double>>(), st); });
-    check_launch("aggregate qr");
+    const cx<T>* X = tv.get<cx<T>>();
+    cx<double>* tws = ws_T.get<cx<double>>();
     int stat = 0;
-    HIPCK(hipMemcpyAsync(&stat, c->status.get<int>(), sizeof(int), hipMemcpyDeviceToHost, st));
-    c->sync();
+    c->timed(DDAMG_KERNEL_SETUP_QR, g.ntv, [&] {
+      launch_aggregate_qr<T>(X, g, c->status.get<int>(), tws, st);
+      check_launch("aggregate qr");
+      HIPCK(hipMemcpyAsync(&stat, c->status.get<int>(), sizeof(int), hipMemcpyDeviceToHost, st));
+      c->sync();
+      if (!stat) launch_qr_store<T, S>(Wq.get<stc_t<S>>(), Wsc.get<float>(), basis_wt(), X, g, tws, st);
+    });
     if (stat) throw Fail{DDAMG_ENUMERIC, "rank-deficient aggregate in the Gram-Schmidt of the test vectors"};
-    build_coarse_from(W);
+    build_coarse_op();
   }
 
   void setup(const double* tv_canon) override {

@@ -337,14 +337,24 @@ void launch_block_matvec(cx<T>* out, size_t ostr, const cx<T>* M, const cx<T>* x
                          int nrhs, hipStream_t st);
 
 // setup kernels
-// tws: workspace of 2 nblocks * QR_TWS_PER_AGG complex doubles (per aggregate the
-// Gram matrix, then T^{-1})
+// Orthonormalises the test vectors X on every aggregate (CholQR2 in FP64):
+// the two triangular factors' inverses into tws (qr_tws_entries complex
+// doubles; status set to 1 for a rank-deficient aggregate), then the basis
+// from X and tws in storage S, as launch_quantize_basis stores it
 constexpr int QR_TWS_PER_AGG = 32 * 32;
-// Orthonormalises the test vectors X (precision Tin) on every aggregate into
-// the FP64 basis W (CholQR2; status set to 1 for a rank-deficient aggregate)
-template <typename Tin>
-void launch_aggregate_qr(cx<double>* W, const cx<Tin>* X, const Geom& g, int* status, cx<double>* tws,
-                         hipStream_t st);
+// parts of an aggregate's sites whose Gram matrices are formed by workgroups
+// of their own (at least 16 sites each)
+inline int qr_parts(const Geom& g) {
+  int p = 512 / (2 * g.nblocks);
+  if (p > (g.vblock + 15) / 16) p = (g.vblock + 15) / 16;
+  return p < 1 ? 1 : p > 4 ? 4 : p;
+}
+inline size_t qr_tws_entries(const Geom& g) { return (size_t)2 * g.nblocks * QR_TWS_PER_AGG * (1 + qr_parts(g)); }
+template <typename T>
+void launch_aggregate_qr(const cx<T>* X, const Geom& g, int* status, cx<double>* tws, hipStream_t st);
+template <typename T, typename S>
+void launch_qr_store(stc_t<S>* Wq, float* Wsc, cx<float>* Wt, const cx<T>* X, const Geom& g, const cx<double>* tws,
+                     hipStream_t st);
 // Stores the FP64 basis W in precision S (FP16 with a per-(vector, site)
 // scale in Wsc); for FP16, Wt (if given) receives the dequantised FP32
 // values scale * half, the same numbers launch_dequantize_basis produces

@@ -9,6 +9,9 @@
 // doing it twice restores orthogonality to rounding.  The result is the
 // unique Q of X = Q T with positive diag(T), i.e. the basis Gram-Schmidt
 // produces.
+#include <algorithm>
+#include <type_traits>
+
 #include "ddamg_internal.h"
 
 namespace ddamg {
@@ -22,21 +25,72 @@ constexpr int QR_ROWS = QR_CS * 6;   // rows (site, spin-colour) per chunk
 constexpr int QR_LD = MAX_NTV + 1;   // padded LDS row
 // An aggregate is (internal block ci, chirality h): rows are the 6 V_block
 // (spin of chirality h x colour, site) entries, columns the ntv test
-// vectors.  Per CholQR pass, three kernels with one workgroup per aggregate:
-//   G = X^H X: on the FP64 matrix cores.  A 16x16x4 f64 MFMA takes, in lane
-//              l, entry (row l/16, column l%16) of a 4-row slice for both of
-//              its operands, so one load per lane and column tile feeds all
-//              of Re/Im X^T X; the waves split the rows and their partial
-//              tiles are summed through LDS.  Every entry of X is read once.
-//              G goes to the per-aggregate workspace.  The kernel holds no
-//              LDS beyond its staging buffer, so several aggregates share a
-//              compute unit and keep enough loads in flight.
-//   G = T^H T: Cholesky (real positive diagonal) and T^{-1} by back
-//              substitution, one 64-lane workgroup per aggregate on an
-//              ntv x (ntv+1) LDS matrix; T^{-1} replaces G in the workspace;
-//   X <- X T^{-1}: on the FP64 matrix cores, tiles of 16 sites x 16 test
-//              vectors (in place for the second pass).
+// vectors.  The products run on the FP64 matrix cores (16x16x4).  The FP64
+// basis is never stored: the test vectors are read three times in their own
+// precision and the stored basis is written once,
+//   G1 = X^H X, T1 = its Cholesky factor,
+//   G2 = Q^H Q with Q = X T1^{-1} formed in registers, T2 = its factor,
+//   the stored basis (X T1^{-1}) T2^{-1}, for FP16 with its scales,
+// the arithmetic of a stored Q in FP64 step by step.  Storing Q and W in FP64
+// and quantising in a pass of its own moved 20 GB on 24^3x48 at N_tv 24
+// (FP16, 4.81 ms), now 7 (3.74 ms: 0.62 the first Gram matrix, 1.25 the
+// second, 1.66 the store, 0.11 each factor); what bounds it is the FP64 matrix
+// cores (0.47, 1.06 and 1.18 ms of products).  8^3x16 at N_tv 16 in FP64: 180
+// -> 69 us.
+// x rounded once to FP16, in a dozen instructions (the compiler's conversion
+// takes forty): to FP32 with the last bit odd if that was inexact, which
+// leaves the rounding to FP16 to decide alone
+__device__ inline __half half_rn(double x) {
+  float f = (float)x;
+  const double d = (double)f;
+  unsigned u = __float_as_uint(f);
+  if (d != x && !(u & 1)) u = fabs(d) < fabs(x) ? u + 1 : u - 1;
+  return __float2half_rn(__uint_as_float(u));
+}
+
 typedef double qr_v4d __attribute__((ext_vector_type(4)));
+
+// The waves' Gram tiles summed (waves 2, 3 hand theirs to 0, 1, then 1 to 0)
+// and the upper triangle of G written, row-major, stride MAX_NTV
+template <int NT>
+__device__ inline void gram_out(qr_v4d (&acc)[2 * NT], qr_v4d (*part)[2 * NT][64], int n, cx<double>* G) {
+  constexpr int NACC = 2 * NT;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, col0 = lane & 15, rsub = lane >> 4;
+  if (w >= 2)
+#pragma unroll
+    for (int t = 0; t < NACC; ++t) part[w - 2][t][lane] = acc[t];
+  __syncthreads();
+  if (w < 2)
+#pragma unroll
+    for (int t = 0; t < NACC; ++t) acc[t] += part[w][t][lane];
+  __syncthreads();
+  if (w == 1)
+#pragma unroll
+    for (int t = 0; t < NACC; ++t) part[0][t][lane] = acc[t];
+  __syncthreads();
+  if (w == 0) {
+#pragma unroll
+    for (int t = 0; t < NACC; ++t) acc[t] += part[0][t][lane];
+    // f64 16x16x4 result v of lane l: row l/16 + 4v (first operand's
+    // column), column l%16 (second operand's column)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int i = rsub + 4 * v, j = col0;
+      if constexpr (NT == 1) {
+        if (i < n && j < n) G[i * MAX_NTV + j] = mk(acc[0][v], acc[1][v]);
+      } else if constexpr (NT == 2) {
+        const int ib = 8 + j;  // tile 0: rows 0..15, columns 8..23
+        if (i <= ib && ib < n) G[i * MAX_NTV + ib] = mk(acc[0][v], acc[1][v]);
+        const int ic = i < 8 ? i : i + 8, jc = j < 8 ? j : j + 8;  // tile 1
+        if (ic <= jc && jc < n && !(ic < 8 && jc >= 16)) G[ic * MAX_NTV + jc] = mk(acc[2][v], acc[3][v]);
+      } else {
+        if (i < n && j < n) G[i * MAX_NTV + j] = mk(acc[0][v], acc[1][v]);
+        if (i < n && 16 + j < n) G[i * MAX_NTV + 16 + j] = mk(acc[2][v], acc[3][v]);
+        if (16 + i < n && 16 + j < n) G[(16 + i) * MAX_NTV + 16 + j] = mk(acc[4][v], acc[5][v]);
+      }
+    }
+  }
+}
 
 // Column layouts of the Gram tiles (upper triangle of G = X^H X, 16x16
 // tiles, one lane per column in each operand):
@@ -46,7 +100,8 @@ typedef double qr_v4d __attribute__((ext_vector_type(4)));
 //          pair i <= j (the pairs 0..7 x 16..23 of the second are dropped);
 //   NT = 3, ntv <= 32: 0..15 x 0..15, 0..15 x 16..31 and 16..31 x 16..31.
 template <typename Tin, int NT>
-__global__ __launch_bounds__(QR_THREADS) void qr_gram_kernel(const cx<Tin>* W, Geom g, cx<double>* Gout) {
+__global__ __launch_bounds__(QR_THREADS) void qr_gram_kernel(const cx<Tin>* W, Geom g, int part_sites,
+                                                             cx<double>* Gout) {
   constexpr int NACC = 2 * NT;  // Re and Im of each tile
   // the staged rows of the Gram matrix pass, later the partial tiles of two
   // waves
@@ -60,9 +115,9 @@ __global__ __launch_bounds__(QR_THREADS) void qr_gram_kernel(const cx<Tin>* W, G
   const int h = blockIdx.x & 1;
   const int n = g.ntv;
   const size_t V = g.V;
-  const int vb = g.vblock;
+  const int beg = blockIdx.y * part_sites, vb = min(g.vblock, beg + part_sites);  // the sites of this part
   const int l = threadIdx.x, lane = l & 63, w = l >> 6;
-  const size_t base = (size_t)ci * vb;
+  const size_t base = (size_t)ci * g.vblock;
   const int col0 = lane & 15, rsub = lane >> 4;
   // operand columns of this lane: ca (first operand of tile 0), cb (second
   // operand of tile 0), cc (both operands of the last tile)
@@ -135,214 +190,373 @@ __global__ __launch_bounds__(QR_THREADS) void qr_gram_kernel(const cx<Tin>* W, G
       }
     }
   };
-  fetch(xq0, 0);
-  if (QR_CS < vb) fetch(xq1, QR_CS);
-  for (int s0 = 0; s0 < vb; s0 += 2 * QR_CS) {
+  fetch(xq0, beg);
+  if (beg + QR_CS < vb) fetch(xq1, beg + QR_CS);
+  for (int s0 = beg; s0 < vb; s0 += 2 * QR_CS) {
     chunk(xq0, s0);
     if (s0 + QR_CS < vb) chunk(xq1, s0 + QR_CS);
   }
   __syncthreads();  // the staging buffer is reused for the partial tiles
-  // sum the four waves' tiles: waves 2,3 hand theirs to waves 0,1, then wave 1
-  // to wave 0, which writes the upper triangle of G (row-major, stride
-  // MAX_NTV)
-  if (w >= 2)
-#pragma unroll
-    for (int t = 0; t < NACC; ++t) part[w - 2][t][lane] = acc[t];
-  __syncthreads();
-  if (w < 2)
-#pragma unroll
-    for (int t = 0; t < NACC; ++t) acc[t] += part[w][t][lane];
-  __syncthreads();
-  if (w == 1)
-#pragma unroll
-    for (int t = 0; t < NACC; ++t) part[0][t][lane] = acc[t];
-  __syncthreads();
-  if (w == 0) {
-#pragma unroll
-    for (int t = 0; t < NACC; ++t) acc[t] += part[0][t][lane];
-    cx<double>* G = Gout + (size_t)blockIdx.x * QR_TWS_PER_AGG;
-    // f64 16x16x4 result v of lane l: row l/16 + 4v (first operand's
-    // column), column l%16 (second operand's column)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int i = rsub + 4 * v, j = col0;
-      if constexpr (NT == 1) {
-        if (i < n && j < n) G[i * MAX_NTV + j] = mk(acc[0][v], acc[1][v]);
-      } else if constexpr (NT == 2) {
-        const int ib = 8 + j;  // tile 0: rows 0..15, columns 8..23
-        if (i <= ib && ib < n) G[i * MAX_NTV + ib] = mk(acc[0][v], acc[1][v]);
-        const int ic = i < 8 ? i : i + 8, jc = j < 8 ? j : j + 8;  // tile 1
-        if (ic <= jc && jc < n && !(ic < 8 && jc >= 16)) G[ic * MAX_NTV + jc] = mk(acc[2][v], acc[3][v]);
-      } else {
-        if (i < n && j < n) G[i * MAX_NTV + j] = mk(acc[0][v], acc[1][v]);
-        if (i < n && 16 + j < n) G[i * MAX_NTV + 16 + j] = mk(acc[2][v], acc[3][v]);
-        if (16 + i < n && 16 + j < n) G[(16 + i) * MAX_NTV + 16 + j] = mk(acc[4][v], acc[5][v]);
-      }
-    }
-  }
+  gram_out<NT>(acc, part, n, Gout + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * QR_TWS_PER_AGG);
 }
 
-// Cholesky G = T^H T (T upper, real positive diagonal) and T^{-1} of one
-// aggregate per 64-lane workgroup.  G (upper triangle, stride MAX_NTV) is
-// read from the workspace into an n x (n+1) LDS matrix; T overwrites its
-// upper triangle and the strictly upper part of T^{-1} is kept transposed in
-// the free lower triangle, its diagonal in dg.  T^{-1} (n x n, row-major)
-// replaces G in the workspace; a pivot that is not positive sets *status
-// and leaves zeros.
-__global__ __launch_bounds__(64) void qr_chol_kernel(cx<double>* tws, Geom g, int* status) {
-  extern __shared__ cx<double> sh[];
-  __shared__ double dg[MAX_NTV];
-  __shared__ int fail;
-  const int n = g.ntv, ld = n + 1;
-  const int l = threadIdx.x;
-  cx<double>* Tg = tws + (size_t)blockIdx.x * QR_TWS_PER_AGG;
-  for (int e = l; e < n * n; e += 64) {
-    const int i = e / n, j = e % n;
-    if (j >= i) sh[i * ld + j] = Tg[i * MAX_NTV + j];
+// Cholesky G = T^H T (T upper, real positive diagonal) and T^{-1}, one
+// workgroup of L lanes per aggregate, every entry of the W x W matrix (W >=
+// ntv) in the register of one lane: a step hands one row to the others
+// through LDS.  G is the sum of nparts upper triangles (stride MAX_NTV,
+// pstride apart).  T^{-1} (n x n, row-major) goes to Tout, which may be the
+// first part of G; a pivot that is not positive sets *status and leaves
+// zeros.  Bound: the chain of n steps and reciprocal square roots.  N_tv 24,
+// 5184 aggregates 106 us (109 with 64 lanes on a matrix in LDS), N_tv 16, 64
+// aggregates 17 (20).
+template <int W, int L>
+__global__ __launch_bounds__(L) void qr_chol_kernel(const cx<double>* G, size_t pstride, int nparts, cx<double>* Tout,
+                                                    Geom g, int* status) {
+  __shared__ cx<double> row[2][W];
+  __shared__ cx<double> Ts[W][W + 1];
+  __shared__ double dinv[W];
+  constexpr int NQ = W * W / L, RS = L / W;  // rows RS apart per lane
+  const int n = g.ntv, t = threadIdx.x, j = t % W, i0 = t / W;
+  const cx<double>* Gg = G + (size_t)blockIdx.x * QR_TWS_PER_AGG;
+  cx<double>* Tg = Tout + (size_t)blockIdx.x * QR_TWS_PER_AGG;
+  cx<double> a[NQ];
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    const int i = i0 + RS * q;
+    a[q] = mk(0.0, 0.0);
+    if (i <= j && j < n)
+      for (int p = 0; p < nparts; ++p) a[q] = a[q] + Gg[(size_t)p * pstride + i * MAX_NTV + j];
   }
-  if (l == 0) fail = 0;
-  __syncthreads();
-  // right-looking: step k scales row k by the pivot and updates the
-  // trailing upper triangle, its entries spread over the lanes
+  // right-looking: step k scales row k by the pivot and updates the rows below
+  bool ok = true;
   for (int k = 0; k < n; ++k) {
-    const double dk = sh[k * ld + k].r;  // every lane reads the same pivot
+    cx<double>* rk = row[k & 1];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+      if (i0 + RS * q == k) rk[j] = a[q];
+    __syncthreads();
+    const double dk = rk[k].r;  // every lane reads the same pivot
     if (!(dk > 0.0)) {
-      if (l == 0) fail = 1;
+      ok = false;
       break;
     }
-    const double d = sqrt(dk);
-    __syncthreads();
-    for (int j = k + l; j < n; j += 64) sh[k * ld + j] = j == k ? mk(d, 0.0) : (1.0 / d) * sh[k * ld + j];
-    __syncthreads();
-    const int m = n - k - 1;  // trailing size
-    for (int p = l; p < m * m; p += 64) {
-      const int i = k + 1 + p / m, j = k + 1 + p % m;
-      if (j >= i) sh[i * ld + j] = sh[i * ld + j] - cmulc(sh[k * ld + i], sh[k * ld + j]);
+    const double inv = rsqrt(dk);
+    if (t == 0) dinv[k] = inv;
+    const cx<double> tj = inv * rk[j];  // of the diagonal only 1 / d is used
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      if (RS * q + RS - 1 < k) continue;  // rows that are done
+      const int i = i0 + RS * q;
+      if (i == k) a[q] = tj;
+      if (i > k && i <= j) a[q] = a[q] - cmulc(inv * rk[i], tj);
     }
-    __syncthreads();
   }
-  __syncthreads();
-  if (fail) {
-    if (l == 0) atomicExch(status, 1);
-    for (int e = l; e < n * n; e += 64) Tg[e] = mk(0.0, 0.0);
+  if (!ok) {
+    if (t == 0) atomicExch(status, 1);
+    for (int e = t; e < n * n; e += L) Tg[e] = mk(0.0, 0.0);
     return;
   }
-  // T^{-1} by back substitution, one column j per lane: entry (i, j), i < j,
-  // lives at sh[j][i]; lane j reads T (i < mm) and its own column only
-  if (l < n) {
-    const int j = l;
-    dg[j] = 1.0 / sh[j * ld + j].r;
-#pragma unroll 1
-    for (int i = j - 1; i >= 0; --i) {
-      cx<double> vv = mk(0.0, 0.0);
-#pragma unroll 1
-      for (int mm = i + 1; mm < j; ++mm) vv = cfma(sh[i * ld + mm], sh[j * ld + mm], vv);
-      vv = cfma(sh[i * ld + j], mk(dg[j], 0.0), vv);
-      sh[j * ld + i] = (-1.0 / sh[i * ld + i].r) * vv;
-    }
+  // T^{-1}: T's rows in LDS, the unit matrix reduced from the last row up
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    const int i = i0 + RS * q;
+    Ts[i][j] = a[q];
+    a[q] = mk(i == j ? 1.0 : 0.0, 0.0);
   }
   __syncthreads();
-  for (int e = l; e < n * n; e += 64) {
-    const int i = e / n, j = e % n;
-    Tg[e] = i < j ? sh[j * ld + i] : i == j ? mk(dg[i], 0.0) : mk(0.0, 0.0);
+  for (int k = n - 1; k >= 0; --k) {
+    cx<double>* rk = row[k & 1];
+    const double inv = dinv[k];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q)
+      if (i0 + RS * q == k) rk[j] = a[q] = inv * a[q];
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      if (RS * q >= k) continue;
+      const int i = i0 + RS * q;
+      if (i < k && j >= k) a[q] = a[q] - Ts[i][k] * rk[j];
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    const int i = i0 + RS * q;
+    if (i < n && j < n) Tg[i * n + j] = a[q];
   }
 }
 
-// Wout <- Xin T^{-1} on the FP64 matrix cores (16x16x4 MFMA): per aggregate
-// W (rows = 16 consecutive sites of one component, columns = test vectors)
-// = X T^{-1}, T^{-1} (upper triangular, from the Cholesky kernel) in LDS, the
-// rows of X loaded straight from memory (16 consecutive sites per lane
-// group, coalesced).  The K loop runs over NQ = ceil(ntv / 4) steps of 4 test
-// vectors, unrolled, with clamped loads and zero factors for the padding, so
-// all loads of a tile are in flight together.  Since T^{-1} is upper
-// triangular, the column tile 0..15 takes only the K steps below 16 and the
-// column tile 16..31 exists only for ntv > 16: the skipped products are
-// exact zeros.  The result tile is transposed through the wave's own LDS
-// tile so that each store writes 16 consecutive sites (256 bytes) of 4 test
-// vectors.  A wave finishes reading its row tile before it writes it and no
-// other wave touches those rows, so the update may run in place.  Waves may
-// run different numbers of tiles, so the LDS exchange is ordered by
-// wave-scope fences, not workgroup barriers.
-template <typename Tin, int NQ>
-__global__ __launch_bounds__(QR_THREADS) void qr_update_mfma_kernel(cx<double>* Wout, const cx<Tin>* Xin, Geom g,
-                                                                    const cx<double>* Tinv) {
-  __shared__ cx<double> Ti[MAX_NTV][MAX_NTV + 1];
-  __shared__ cx<double> Sw[QR_THREADS / 64][MAX_NTV * 17];
-  const int ci = blockIdx.x >> 1;
-  const int h = blockIdx.x & 1;
-  const int n = g.ntv;
-  const size_t V = g.V;
-  const int vb = g.vblock;
-  const int l = threadIdx.x, lane = l & 63, w = l >> 6;
-  const int i16 = lane & 15, k4 = lane >> 4;
-  const size_t base = (size_t)ci * vb;
-  const int tiles_per_comp = (vb + 15) / 16;
-  const int ntile = 6 * tiles_per_comp;
-  // the X rows of this wave's next tile, loaded (in the input precision)
-  // while the current tile is multiplied and stored; the rows of different
-  // tiles are disjoint, so this holds in place too
-  cx<Tin> xr[NQ];
-  auto fetch = [&](int tile) {
-    const int c = tile / tiles_per_comp, s0 = (tile % tiles_per_comp) * 16;
-    const int sa = min(s0 + i16, vb - 1);  // A operand: site of this lane's row (clamped)
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      const int k = min(4 * q + k4, n - 1);
-      xr[q] = Xin[((size_t)k * 12 + 6 * h + c) * V + base + sa];
-    }
-  };
-  if (w < ntile) fetch(w);
-  const cx<double>* Tg = Tinv + (size_t)blockIdx.x * MAX_NTV * MAX_NTV;
-  for (int e = l; e < MAX_NTV * MAX_NTV; e += blockDim.x) {
-    const int i = e / MAX_NTV, j = e % MAX_NTV;
-    Ti[i][j] = (i < n && j < n) ? Tg[i * n + j] : mk(0.0, 0.0);
+// T^{-1} as the matrix cores take it, one 64-entry block per step of four
+// rows and tile of 16 columns (lane l: row l / 16, column l % 16).  T^{-1} is
+// upper triangular: the columns 0 .. 15 have only the steps below 16.
+template <int NQ>
+struct TBlocks {
+  static constexpr int NT = NQ > 4 ? 2 : 1;           // column tiles
+  static constexpr int N = NQ > 4 ? 4 + NQ : NQ;      // blocks
+  __device__ static constexpr int at(int q, int tj) { return tj ? 4 + q : q; }
+  // does step q of tile tj exist
+  __device__ static constexpr bool has(int q, int tj) { return tj || q < 4; }
+};
+template <int NQ>
+__device__ inline void load_tinv(cx<double> (*B)[64], const cx<double>* T, int n) {
+  for (int e = threadIdx.x; e < TBlocks<NQ>::N * 64; e += blockDim.x) {
+    const int b = e >> 6, l = e & 63, tj = b >= 4 ? 1 : 0;
+    const int i = 4 * (b - 4 * tj) + (l >> 4), j = 16 * tj + (l & 15);
+    B[b][l] = i < n && j < n ? T[i * n + j] : mk(0.0, 0.0);
   }
+}
+
+// A barrier for data exchanged through LDS: global loads and stores stay in
+// flight across it (__syncthreads waits for them)
+__device__ inline void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// The rows of X for one tile: site s0 + lane % 16, component comp, vectors 4 q + lane / 16
+template <typename Tin, int NQ>
+__device__ inline void load_x(cx<Tin> x[NQ], const cx<Tin>* X, int comp, size_t base, int s0, int vb, int n,
+                              size_t V) {
+  const int lane = threadIdx.x & 63, k4 = lane >> 4, sa = min(s0 + (lane & 15), vb - 1);
+  // n > 4 (NQ - 1): only the last step can run past the vectors, it reads the first step's again
+  const cx<Tin>* p = X + ((size_t)min(k4, n - 1) * 12 + comp) * V + base + sa;
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) x[q] = p[q < NQ - 1 || 4 * q + k4 < n ? (size_t)(48 * q) * V : 0];
+}
+
+// G = Q^H Q with Q = X T^{-1} of one aggregate (and part of its sites).  A
+// wave takes tiles of 16 sites of one component: the products with T^{-1}
+// leave site lane / 16 + 4 v, vector lane % 16 in register v, which is the
+// operand of the Gram products for the sites 4 v .. 4 v + 3 as it stands.
+// The column tiles of the Gram matrix are those of qr_gram_kernel (NT == 2:
+// the shifted ones by moves within rows of 16 lanes).
+__device__ inline double ror8(double v) {  // lane ^ 8 within rows of 16
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, 0x128, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), 0x128, 0xF, 0xF, true);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+template <typename Tin, int NQ>
+__global__ __launch_bounds__(QR_THREADS, 2) void qr_gram2_kernel(const cx<Tin>* X, Geom g, int part_sites,
+                                                                 const cx<double>* Tinv, cx<double>* Gout) {
+  using TB = TBlocks<NQ>;
+  constexpr int NT = NQ <= 4 ? 1 : NQ <= 6 ? 2 : 3, NACC = 2 * NT;
+  constexpr size_t T_BYTES = sizeof(cx<double>) * TB::N * 64, P_BYTES = sizeof(qr_v4d) * 2 * NACC * 64;
+  __shared__ __attribute__((aligned(32))) char raw[T_BYTES > P_BYTES ? T_BYTES : P_BYTES];
+  auto Tb = reinterpret_cast<cx<double>(*)[64]>(raw);
+  auto part = reinterpret_cast<qr_v4d(*)[NACC][64]>(raw);
+  const int ci = blockIdx.x >> 1, h = blockIdx.x & 1, n = g.ntv;
+  const size_t V = g.V, base = (size_t)ci * g.vblock;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, k4 = lane >> 4;
+  const bool lo8 = (lane & 8) == 0;
+  const int beg = blockIdx.y * part_sites, end = min(g.vblock, beg + part_sites);
+  const int ntile = 6 * ((end - beg + 15) / 16);  // tile: component tile % 6, sites beg + 16 (tile / 6)
+  cx<Tin> xr[NQ];
+  if (w < ntile) load_x<Tin, NQ>(xr, X, 6 * h + w % 6, base, beg + 16 * (w / 6), end, n, V);
+  load_tinv<NQ>(Tb, Tinv + (size_t)blockIdx.x * QR_TWS_PER_AGG, n);
+  qr_v4d acc[NACC];
+#pragma unroll
+  for (int t = 0; t < NACC; ++t) acc[t] = (qr_v4d){0.0, 0.0, 0.0, 0.0};
   __syncthreads();
   for (int tile = w; tile < ntile; tile += QR_THREADS / 64) {
-    const int c = tile / tiles_per_comp, s0 = (tile % tiles_per_comp) * 16;
-    cx<double> xa[NQ];
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) xa[q] = cvt<double>(xr[q]);
-    if (tile + QR_THREADS / 64 < ntile) fetch(tile + QR_THREADS / 64);
-    qr_v4d RR[2], II[2], RI[2], IR[2];
-#pragma unroll
-    for (int tj = 0; tj < 2; ++tj)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) RR[tj][v] = II[tj][v] = RI[tj][v] = IR[tj][v] = 0.0;
+    const int s0 = beg + 16 * (tile / 6), nt = tile + QR_THREADS / 64;
+    double xa[NQ], xi[NQ];
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
-      const double f = 4 * q + k4 < n ? 1.0 : 0.0;  // padded test vectors add nothing
-      const double ar = f * xa[q].r, ai = f * xa[q].i;
+      const bool in = 4 * q + k4 < n;  // padded test vectors add nothing
+      xa[q] = in ? (double)xr[q].r : 0.0;
+      xi[q] = in ? (double)xr[q].i : 0.0;
+    }
+    if (nt < ntile) load_x<Tin, NQ>(xr, X, 6 * h + nt % 6, base, beg + 16 * (nt / 6), end, n, V);
+    qr_v4d yr[TB::NT], yi[TB::NT];
 #pragma unroll
-      for (int tj = 0; tj < 2; ++tj) {
-        if (tj == 0 && q >= 4) continue;  // rows 16.. of T^{-1} vanish in columns 0..15
-        if (tj == 1 && NQ <= 4) continue;  // no columns 16..31
-        const cx<double> b = Ti[4 * q + k4][16 * tj + i16];
-        RR[tj] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, b.r, RR[tj], 0, 0, 0);
-        II[tj] = __builtin_amdgcn_mfma_f64_16x16x4f64(ai, b.i, II[tj], 0, 0, 0);
-        RI[tj] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, b.i, RI[tj], 0, 0, 0);
-        IR[tj] = __builtin_amdgcn_mfma_f64_16x16x4f64(ai, b.r, IR[tj], 0, 0, 0);
+    for (int tj = 0; tj < TB::NT; ++tj) {
+      qr_v4d RR, II, RI, IR;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) RR[v] = II[v] = RI[v] = IR[v] = 0.0;
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        if (!TB::has(q, tj)) continue;
+        const cx<double> b = Tb[TB::at(q, tj)][lane];
+        RR = __builtin_amdgcn_mfma_f64_16x16x4f64(xa[q], b.r, RR, 0, 0, 0);
+        II = __builtin_amdgcn_mfma_f64_16x16x4f64(xi[q], b.i, II, 0, 0, 0);
+        RI = __builtin_amdgcn_mfma_f64_16x16x4f64(xa[q], b.i, RI, 0, 0, 0);
+        IR = __builtin_amdgcn_mfma_f64_16x16x4f64(xi[q], b.r, IR, 0, 0, 0);
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const bool in = s0 + k4 + 4 * v < end;
+        yr[tj][v] = in ? RR[v] - II[v] : 0.0;
+        yi[tj][v] = in ? RI[v] + IR[v] : 0.0;
       }
     }
-    // result row lane / 16 + 4 v (site), column lane % 16 (test vector):
-    // transposed through this wave's LDS tile [column][site] (stride 17)
-    cx<double>* St = Sw[w];
 #pragma unroll
-    for (int tj = 0; tj < (NQ > 4 ? 2 : 1); ++tj)
-#pragma unroll
-      for (int v = 0; v < 4; ++v)
-        St[(16 * tj + i16) * 17 + k4 + 4 * v] = mk(RR[tj][v] - II[tj][v], RI[tj][v] + IR[tj][v]);
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-    for (int r = 0; r < (NQ > 4 ? 8 : 4); ++r) {
-      const int j = 4 * r + k4, srow = s0 + i16;
-      if (srow < vb && j < n) Wout[((size_t)j * 12 + 6 * h + c) * V + base + srow] = St[j * 17 + i16];
+    for (int v = 0; v < 4; ++v) {
+      const double ar = yr[0][v], ai = yi[0][v];
+      if constexpr (NT == 1) {
+        acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, ar, acc[0], 0, 0, 0);
+        acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, ai, acc[1], 0, 0, 0);
+        acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(ai, ai, acc[0], 0, 0, 0);
+        acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(-ai, ar, acc[1], 0, 0, 0);
+      } else {
+        const double cr = yr[TB::NT - 1][v], cim = yi[TB::NT - 1][v];
+        // second operand of tile 0 / both of the last tile
+        double br = ar, bi = ai, dr = cr, di = cim;
+        if constexpr (NT == 2) {
+          const double a8 = ror8(ar), i8 = ror8(ai), c8 = ror8(cr), ci8 = ror8(cim);
+          br = lo8 ? a8 : c8;  // columns 8 .. 23
+          bi = lo8 ? i8 : ci8;
+          dr = lo8 ? ar : c8;  // columns 0 .. 7, 16 .. 23
+          di = lo8 ? ai : ci8;
+        }
+        constexpr int L = NACC - 2;
+        acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, br, acc[0], 0, 0, 0);
+        acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, bi, acc[1], 0, 0, 0);
+        acc[L] = __builtin_amdgcn_mfma_f64_16x16x4f64(dr, dr, acc[L], 0, 0, 0);
+        acc[L + 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(dr, di, acc[L + 1], 0, 0, 0);
+        if constexpr (NT == 3) {
+          acc[2] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, cr, acc[2], 0, 0, 0);
+          acc[3] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar, cim, acc[3], 0, 0, 0);
+        }
+        acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(ai, bi, acc[0], 0, 0, 0);
+        acc[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(-ai, br, acc[1], 0, 0, 0);
+        acc[L] = __builtin_amdgcn_mfma_f64_16x16x4f64(di, di, acc[L], 0, 0, 0);
+        acc[L + 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(-di, dr, acc[L + 1], 0, 0, 0);
+        if constexpr (NT == 3) {
+          acc[2] = __builtin_amdgcn_mfma_f64_16x16x4f64(ai, cim, acc[2], 0, 0, 0);
+          acc[3] = __builtin_amdgcn_mfma_f64_16x16x4f64(-ai, cr, acc[3], 0, 0, 0);
+        }
+      }
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
+  __syncthreads();  // T^{-1} gives way to the partial tiles
+  gram_out<NT>(acc, part, n, Gout + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * QR_TWS_PER_AGG);
+}
+
+// The stored basis (X T1^{-1}) T2^{-1} of one block (blockIdx.x), both
+// chiralities, 16 sites at a time: wave w takes the components 3 w .. 3 w + 2.
+// The products are formed transposed (T^T X^T), so that register v of the
+// first one, vector lane / 16 + 4 v at site lane % 16, is the operand of step
+// v of the second, and the stores are runs of 16 sites.  FP16: the scale of a
+// (vector, site), its largest component, is exchanged between the waves, and
+// Wt receives scale * half, as quantize_basis_kernel writes them.  Bound: the
+// FP64 matrix cores (80 products of 64 cycles per wave, component and 16
+// sites at N_tv 24).  Barriers that leave loads and stores in flight, one base
+// address per lane and the short FP16 rounding took it from 1.99 to 1.66 ms.
+template <typename Tin, typename S, int NQ>
+__global__ __launch_bounds__(QR_THREADS, 2) void qr_store_kernel(stc_t<S>* Wq, float* Wsc, cx<float>* Wt,
+                                                                 const cx<Tin>* X, Geom g, const cx<double>* T1,
+                                                                 const cx<double>* T2) {
+  using TB = TBlocks<NQ>;
+  __shared__ cx<double> Tb[2][2][TB::N][64];  // [chirality][factor]
+  __shared__ float mx[is_half<S>() ? 4 : 1][TB::NT * 4][64];
+  const int ci = blockIdx.x, n = g.ntv, vb = g.vblock;
+  const size_t V = g.V, base = (size_t)ci * vb;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, k4 = lane >> 4, h = w >> 1;
+  for (int e = 0; e < 2; ++e) {
+    const size_t agg = (size_t)(2 * ci + e) * QR_TWS_PER_AGG;
+    load_tinv<NQ>(Tb[e][0], T1 + agg, n);
+    load_tinv<NQ>(Tb[e][1], T2 + agg, n);
+  }
+  const int ngroup = (vb + 15) / 16, step = 16 * gridDim.y;
+  int s0 = 16 * blockIdx.y;
+  cx<Tin> xr[NQ];  // the next component's rows
+  if (blockIdx.y < ngroup) load_x<Tin, NQ>(xr, X, 3 * w, base, s0, vb, n, V);
+  __syncthreads();
+  // z = T^T x for factor f of this wave's chirality, steps and tiles in registers
+  auto product = [&](double zr[TB::NT][4], double zi[TB::NT][4], int f, const double xr_[NQ], const double xi_[NQ]) {
+#pragma unroll
+    for (int tj = 0; tj < TB::NT; ++tj) {
+      qr_v4d RR, II, RI, IR;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) RR[v] = II[v] = RI[v] = IR[v] = 0.0;
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        if (!TB::has(q, tj)) continue;
+        const cx<double> a = Tb[h][f][TB::at(q, tj)][lane];
+        RR = __builtin_amdgcn_mfma_f64_16x16x4f64(a.r, xr_[q], RR, 0, 0, 0);
+        II = __builtin_amdgcn_mfma_f64_16x16x4f64(a.i, xi_[q], II, 0, 0, 0);
+        RI = __builtin_amdgcn_mfma_f64_16x16x4f64(a.r, xi_[q], RI, 0, 0, 0);
+        IR = __builtin_amdgcn_mfma_f64_16x16x4f64(a.i, xr_[q], IR, 0, 0, 0);
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        zr[tj][v] = RR[v] - II[v];
+        zi[tj][v] = RI[v] + IR[v];
+      }
+      asm volatile("" ::: "memory");  // one tile's operands at a time: registers
+    }
+  };
+  for (; s0 < vb; s0 += step) {
+    const int s = s0 + (lane & 15);
+    const size_t o0 = (size_t)(12 * k4 + 3 * w) * V + base + s;  // vector k4, component 3 w
+    constexpr int HC = is_half<S>() ? 3 : 1;  // components held until their scale is known
+    double wr[HC][TB::NT][4], wi[HC][TB::NT][4];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      const int hc = c % HC;
+      double xd[NQ], xe[NQ], zr[TB::NT][4], zi[TB::NT][4];
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        const bool in = 4 * q + k4 < n;  // padded test vectors add nothing
+        xd[q] = in ? (double)xr[q].r : 0.0;
+        xe[q] = in ? (double)xr[q].i : 0.0;
+      }
+      if (c < 2)
+        load_x<Tin, NQ>(xr, X, 3 * w + c + 1, base, s0, vb, n, V);
+      else if (s0 + step < vb)
+        load_x<Tin, NQ>(xr, X, 3 * w, base, s0 + step, vb, n, V);
+      product(zr, zi, 0, xd, xe);
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) {
+        xd[q] = zr[q >> 2][q & 3];
+        xe[q] = zi[q >> 2][q & 3];
+      }
+      product(wr[hc], wi[hc], 1, xd, xe);
+      asm volatile("" ::: "memory");
+      if constexpr (!is_half<S>()) {
+#pragma unroll
+        for (int tj = 0; tj < TB::NT; ++tj)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const int a = 16 * tj + k4 + 4 * v;
+            if (s < vb && a < n)
+              stc_store(Wq, o0 + (size_t)(12 * (16 * tj + 4 * v) + c) * V, mk(wr[0][tj][v], wi[0][tj][v]));
+          }
+      }
+    }
+    if constexpr (is_half<S>()) {
+      // the largest component of each (vector, site): this wave's three, then all
+#pragma unroll
+      for (int tj = 0; tj < TB::NT; ++tj)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          double m = 0.0;
+#pragma unroll
+          for (int c = 0; c < 3; ++c) m = fmax(m, fmax(fabs(wr[c][tj][v]), fabs(wi[c][tj][v])));
+          mx[w][4 * tj + v][lane] = (float)m;
+        }
+      lds_barrier();
+#pragma unroll
+      for (int tj = 0; tj < TB::NT; ++tj)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int a = 16 * tj + k4 + 4 * v, e = 4 * tj + v;
+          if (s >= vb || a >= n) continue;
+          const float fm = fmaxf(fmaxf(mx[0][e][lane], mx[1][e][lane]), fmaxf(mx[2][e][lane], mx[3][e][lane]));
+          if (w == 0) Wsc[(size_t)k4 * V + base + s + (size_t)(16 * tj + 4 * v) * V] = fm;
+          const double inv = fm > 0.f ? 1.0 / (double)fm : 0.0;
+#pragma unroll
+          for (int c = 0; c < 3; ++c) {
+            const size_t at = o0 + (size_t)(12 * (16 * tj + 4 * v) + c) * V;
+            const __half2 hq = __halves2half2(half_rn(wr[c][tj][v] * inv), half_rn(wi[c][tj][v] * inv));
+            Wq[at] = hq;
+            const float2 f = __half22float2(hq);
+            Wt[at] = mk(fm * f.x, fm * f.y);
+          }
+        }
+      lds_barrier();  // mx is written again
+    }
   }
 }
 
@@ -365,7 +579,7 @@ __global__ void quantize_basis_kernel(stc_t<S>* Wq, float* Wsc, const cx<double>
     const double inv = fm > 0.f ? 1.0 / (double)fm : 0.0;
 #pragma unroll
     for (int k = 0; k < 12; ++k) {
-      const __half2 hq = __floats2half2_rn((float)(v[k].r * inv), (float)(v[k].i * inv));
+      const __half2 hq = __halves2half2(half_rn(v[k].r * inv), half_rn(v[k].i * inv));
       Wq[((size_t)a * 12 + k) * V + s] = hq;
       if (Wt) {
         const float2 f = __half22float2(hq);
@@ -390,44 +604,67 @@ __global__ void dequantize_basis_kernel(cx<T>* out, BasisView<S> bv, int V, int 
 
 // the Gram kernel with the fewest column tiles for ntv (ntv <= 32 is validated)
 template <typename Tin>
-void launch_qr_gram(const cx<Tin>* X, const Geom& g, cx<double>* tws, hipStream_t st) {
-  const unsigned nagg = 2 * g.nblocks;
+void launch_qr_gram(const cx<Tin>* X, const Geom& g, int nparts, int part_sites, cx<double>* G, hipStream_t st) {
+  const dim3 grid(2 * g.nblocks, nparts);
   if (g.ntv <= 16)
-    qr_gram_kernel<Tin, 1><<<nagg, QR_THREADS, 0, st>>>(X, g, tws);
+    qr_gram_kernel<Tin, 1><<<grid, QR_THREADS, 0, st>>>(X, g, part_sites, G);
   else if (g.ntv <= 24)
-    qr_gram_kernel<Tin, 2><<<nagg, QR_THREADS, 0, st>>>(X, g, tws);
+    qr_gram_kernel<Tin, 2><<<grid, QR_THREADS, 0, st>>>(X, g, part_sites, G);
   else
-    qr_gram_kernel<Tin, 3><<<nagg, QR_THREADS, 0, st>>>(X, g, tws);
+    qr_gram_kernel<Tin, 3><<<grid, QR_THREADS, 0, st>>>(X, g, part_sites, G);
 }
-// the update kernel for K = ceil(ntv / 4) steps (ntv <= 32 is validated)
-template <typename Tin, int NQ = 8>
-void launch_qr_update(cx<double>* W, const cx<Tin>* X, const Geom& g, const cx<double>* tws, hipStream_t st) {
+// f with NQ = ceil(ntv / 4), the steps of four test vectors
+template <int NQ = 8, typename F>
+void with_nq(int ntv, F&& f) {
   if constexpr (NQ > 1) {
-    if ((g.ntv + 3) / 4 < NQ) {
-      launch_qr_update<Tin, NQ - 1>(W, X, g, tws, st);
+    if ((ntv + 3) / 4 < NQ) {
+      with_nq<NQ - 1>(ntv, f);
       return;
     }
   }
-  qr_update_mfma_kernel<Tin, NQ><<<2 * g.nblocks, QR_THREADS, 0, st>>>(W, X, g, tws);
+  f(std::integral_constant<int, NQ>());
 }
 }  // namespace
 
-template <typename Tin>
-void launch_aggregate_qr(cx<double>* W, const cx<Tin>* X, const Geom& g, int* status, cx<double>* tws,
-                         hipStream_t st) {
-  // CholQR2: pass 1 from X into W, pass 2 on W in place
+template <typename T>
+void launch_aggregate_qr(const cx<T>* X, const Geom& g, int* status, cx<double>* tws, hipStream_t st) {
+  // the Gram matrices of a small lattice's few aggregates in parts, about a
+  // workgroup per compute unit
   const unsigned nagg = 2 * g.nblocks;
-  const size_t chol_lds = sizeof(cx<double>) * g.ntv * (g.ntv + 1);
-  launch_qr_gram<Tin>(X, g, tws, st);
-  qr_chol_kernel<<<nagg, 64, chol_lds, st>>>(tws, g, status);
-  launch_qr_update<Tin>(W, X, g, tws, st);
-  launch_qr_gram<double>(W, g, tws, st);
-  qr_chol_kernel<<<nagg, 64, chol_lds, st>>>(tws, g, status);
-  launch_qr_update<double>(W, W, g, tws, st);
+  const int nparts = qr_parts(g), part_sites = ((g.vblock + nparts - 1) / nparts + 15) / 16 * 16;
+  cx<double>*T1 = tws, *G = tws + (size_t)nagg * QR_TWS_PER_AGG;  // T2 replaces G's first part
+  const size_t pstride = (size_t)nagg * QR_TWS_PER_AGG;
+  launch_qr_gram<T>(X, g, nparts, part_sites, G, st);
+  const auto chol = [&](cx<double>* out) {
+    if (g.ntv <= 16)
+      qr_chol_kernel<16, 64><<<nagg, 64, 0, st>>>(G, pstride, nparts, out, g, status);
+    else
+      qr_chol_kernel<MAX_NTV, 256><<<nagg, 256, 0, st>>>(G, pstride, nparts, out, g, status);
+  };
+  chol(T1);
+  with_nq(g.ntv, [&](auto q) {
+    qr_gram2_kernel<T, decltype(q)::value><<<dim3(nagg, nparts), QR_THREADS, 0, st>>>(X, g, part_sites, T1, G);
+  });
+  chol(G);
 }
-template void launch_aggregate_qr<double>(cx<double>*, const cx<double>*, const Geom&, int*, cx<double>*,
-                                          hipStream_t);
-template void launch_aggregate_qr<float>(cx<double>*, const cx<float>*, const Geom&, int*, cx<double>*, hipStream_t);
+template <typename T, typename S>
+void launch_qr_store(stc_t<S>* Wq, float* Wsc, cx<float>* Wt, const cx<T>* X, const Geom& g, const cx<double>* tws,
+                     hipStream_t st) {
+  const int ngroup = (g.vblock + 15) / 16;
+  const int gy = std::max(1, std::min(ngroup, 1024 / g.nblocks));
+  const cx<double>*T1 = tws, *T2 = tws + (size_t)2 * g.nblocks * QR_TWS_PER_AGG;
+  with_nq(g.ntv, [&](auto q) {
+    qr_store_kernel<T, S, decltype(q)::value><<<dim3(g.nblocks, gy), QR_THREADS, 0, st>>>(Wq, Wsc, Wt, X, g, T1, T2);
+  });
+}
+template void launch_aggregate_qr<double>(const cx<double>*, const Geom&, int*, cx<double>*, hipStream_t);
+template void launch_aggregate_qr<float>(const cx<float>*, const Geom&, int*, cx<double>*, hipStream_t);
+template void launch_qr_store<double, double>(stc_t<double>*, float*, cx<float>*, const cx<double>*, const Geom&,
+                                              const cx<double>*, hipStream_t);
+template void launch_qr_store<float, float>(stc_t<float>*, float*, cx<float>*, const cx<float>*, const Geom&,
+                                            const cx<double>*, hipStream_t);
+template void launch_qr_store<float, __half>(stc_t<__half>*, float*, cx<float>*, const cx<float>*, const Geom&,
+                                             const cx<double>*, hipStream_t);
 
 template <typename S>
 void launch_quantize_basis(stc_t<S>* Wq, float* Wsc, const cx<double>* W, const Geom& g, hipStream_t st,
