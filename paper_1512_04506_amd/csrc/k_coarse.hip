@@ -397,98 +397,6 @@ __global__ __launch_bounds__(256) void quantize_coarse_kernel(stc_t<S>* Dq, floa
   }
 }
 
-// ------------------------------------ inversion of the even self blocks
-// In-place Gauss-Jordan with partial (row) pivoting in FP64 LDS, one
-// workgroup per even coarse site; the inverse is stored column-major in T.
-template <typename T, typename S>
-__global__ __launch_bounds__(256) void invert_even_kernel(cx<T>* Dinv, CoarseView<S> cv, int nc, int* status) {
-  extern __shared__ __attribute__((aligned(16))) char smem_raw[];
-  cx<double>* M = reinterpret_cast<cx<double>*>(smem_raw);  // row-major nc x nc
-  cx<double>* colk = M + (size_t)nc * nc;                    // column k before elimination
-  int* perm = reinterpret_cast<int*>(colk + nc);
-  __shared__ int piv_row;
-  __shared__ int singular;
-  const int ci = blockIdx.x;  // even sites are internal indices [0, neven)
-  const size_t nn = (size_t)nc * nc;
-  double sc = 1.0;
-  if constexpr (is_half<S>()) sc = (double)cv.Dsc[ci * 9];
-  for (int e = threadIdx.x; e < nc * nc; e += blockDim.x) {
-    const int col = e / nc, row = e % nc;
-    M[row * nc + col] = sc * ldc<double>(cv.D, (size_t)ci * 9 * nn + e);
-  }
-  if (threadIdx.x == 0) singular = 0;
-  __syncthreads();
-  for (int k = 0; k < nc; ++k) {
-    if (threadIdx.x < 64) {
-      double best = -1.0;
-      int bi = k;
-      for (int i = k + threadIdx.x; i < nc; i += 64) {
-        cx<double> v = M[i * nc + k];
-        double a = v.r * v.r + v.i * v.i;
-        if (a > best) { best = a; bi = i; }
-      }
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) {
-        double ob = __shfl_xor(best, o, 64);
-        int oi = __shfl_xor(bi, o, 64);
-        if (ob > best || (ob == best && oi < bi)) { best = ob; bi = oi; }
-      }
-      if (threadIdx.x == 0) {
-        piv_row = bi;
-        perm[k] = bi;
-        if (!(best > 0.0)) singular = 1;
-      }
-    }
-    __syncthreads();
-    if (singular) break;
-    const int p = piv_row;
-    if (p != k)
-      for (int j = threadIdx.x; j < nc; j += blockDim.x) {
-        cx<double> t = M[k * nc + j];
-        M[k * nc + j] = M[p * nc + j];
-        M[p * nc + j] = t;
-      }
-    __syncthreads();
-    const cx<double> pv = M[k * nc + k];
-    const double pn = pv.r * pv.r + pv.i * pv.i;
-    const cx<double> ipv = mk(pv.r / pn, -pv.i / pn);
-    __syncthreads();
-    // scale the pivot row (the pivot entry becomes 1/pv)
-    for (int j = threadIdx.x; j < nc; j += blockDim.x) M[k * nc + j] = (j == k ? mk(1.0, 0.0) : M[k * nc + j]) * ipv;
-    __syncthreads();
-    for (int i = threadIdx.x; i < nc; i += blockDim.x) colk[i] = M[i * nc + k];
-    __syncthreads();
-    // eliminate column k from the other rows
-    for (int e = threadIdx.x; e < nc * nc; e += blockDim.x) {
-      const int i = e / nc, j = e % nc;
-      if (i == k) continue;
-      const cx<double> f = colk[i];
-      const cx<double> rk = M[k * nc + j];
-      M[i * nc + j] = (j == k ? mk(0.0, 0.0) : M[i * nc + j]) - f * rk;
-    }
-    __syncthreads();
-  }
-  if (singular) {
-    if (threadIdx.x == 0) atomicExch(status, 1);
-    return;
-  }
-  // undo the row interchanges as column interchanges, last first
-  for (int k = nc - 1; k >= 0; --k) {
-    const int p = perm[k];
-    if (p != k)
-      for (int i = threadIdx.x; i < nc; i += blockDim.x) {
-        cx<double> t = M[i * nc + k];
-        M[i * nc + k] = M[i * nc + p];
-        M[i * nc + p] = t;
-      }
-    __syncthreads();
-  }
-  for (int e = threadIdx.x; e < nc * nc; e += blockDim.x) {
-    const int col = e / nc, row = e % nc;
-    Dinv[(size_t)ci * nn + e] = cvt<T>(M[row * nc + col]);
-  }
-}
-
 // ------------------------------------------------------ layout conversion
 template <typename S>
 __global__ void export_coarse_kernel(cx<double>* out, CoarseView<S> cv, Geom g) {
@@ -623,12 +531,6 @@ void launch_quantize_coarse(stc_t<S>* Dq, float* Dsc, const cx<T>* Dc, const Geo
 }
 
 template <typename T, typename S>
-void launch_invert_even_blocks(cx<T>* Dinv, const CoarseView<S>& cv, const Geom& g, int* status, hipStream_t st) {
-  size_t lds = (size_t)(g.nc * g.nc + g.nc) * sizeof(cx<double>) + (size_t)g.nc * sizeof(int);
-  invert_even_kernel<T, S><<<g.neven, 256, lds, st>>>(Dinv, cv, g.nc, status);
-}
-
-template <typename T, typename S>
 void launch_export_coarse(cx<double>* out, const CoarseView<S>& cv, const Geom& g, hipStream_t st) {
   export_coarse_kernel<S><<<dim3(g.nblocks, 9), 256, 0, st>>>(out, cv, g);
 }
@@ -655,7 +557,6 @@ void launch_coarse_to_canonical(cx<double>* canon, const cx<T>* in, const Geom& 
   template void launch_prolong<T, S>(cx<T>*, size_t, const cx<T>*, size_t, const BasisView<S>&, const Geom&, int,    \
                                      hipStream_t);                                                                   \
   template void launch_quantize_coarse<T, S>(stc_t<S>*, float*, const cx<T>*, const Geom&, hipStream_t);             \
-  template void launch_invert_even_blocks<T, S>(cx<T>*, const CoarseView<S>&, const Geom&, int*, hipStream_t);       \
   template void launch_export_coarse<T, S>(cx<double>*, const CoarseView<S>&, const Geom&, hipStream_t);
 INST_TS(double, double)
 INST_TS(float, float)
