@@ -456,7 +456,9 @@ def sap_flops_per_site(block, n_mr):
     """Algorithmic flops of one SAP colour phase per site of that colour and
     rhs: residual y - D x (1320 hop + 504 clover + 24), n_mr MR steps each
     with B rho (clover 504 + the in-block share of the 1320 hop flops) and
-    two inner products and two axpys (336), and the update x += e (24)."""
+    two inner products and two axpys (336), and the update x += e (24).  That
+    is Alg. 3 as it stands; the kernels for 4^4 blocks carry the residual from
+    phase to phase and execute about 1500 fewer per site of most phases."""
     inblock = sum((b - 1) / b for b in block) / 4.0
     return 1320 + 504 + 24 + n_mr * (504 + 1320 * inblock + 336) + 24
 

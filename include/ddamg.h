@@ -273,8 +273,8 @@ int dirac_apply_noalloc(ddamg_ctx* ctx, double* out, const double* in, int nrhs,
 
 /* Convergence test of the coarse GMRES (Alg. 2), for timing comparisons.
  * Default (each_iteration = 0): pipelined -- the per-rhs convergence flags
- * of coarse iteration k are copied to pinned host memory behind its
- * kernels, and the host reads them only after it has enqueued iteration
+ * of coarse iteration k reach pinned host memory with its last
+ * kernel, and the host reads them only after it has enqueued iteration
  * k + 1, so the device never waits for the host's decision; every kernel of
  * an iteration is predicated on the flags, so the one iteration enqueued
  * past convergence does no work and changes no result.  With a fixed
@@ -311,10 +311,10 @@ int ddamg_batch_solve(ddamg_ctx* const* ctx, int n, double* const* u, const doub
                       double tol, int workers, int32_t* rc, double* begin_ms, double* end_ms);
 
 /* HIP graphs for the coarse GMRES (Alg. 2): on (the default), each coarse
- * iteration's launches (the Schur-complement stencil, the Gram-Schmidt
- * passes, the Arnoldi column, the scaling) are captured once per iteration
- * index and rhs count into a HIP graph on the context's stream and
- * replayed, one launch call per iteration instead of ten.  (Measured on
+ * iteration's launches (two of the Schur-complement stencil and the Arnoldi
+ * step; ten for vectors beyond one workgroup's) are captured once per
+ * iteration index and rhs count into a HIP graph on the context's stream and
+ * replayed, one launch call per iteration.  (Measured on
  * small lattices this changes little: the chain of small dependent kernels
  * on the device, not the host's launch calls, bounds such a solve.)
  * Results are identical either way.  Contexts on the null stream, and any context while
@@ -328,7 +328,7 @@ int ddamg_set_graphs(ddamg_ctx* ctx, int on);
  * rhs -- the even/odd Schur complement, restarted GMRES with classical
  * Gram-Schmidt twice, the same Givens rotations and convergence test, the
  * back substitution and the even sites -- runs in one workgroup in one
- * launch, instead of about ten launches per GMRES iteration whose latencies
+ * launch, instead of three launches per GMRES iteration whose latencies
  * bound the solve of such a lattice.  One workgroup reads the operator at
  * the L2 bandwidth of one compute unit, hence the byte bound.  Results agree
  * with the multi-launch solve to rounding (sums in a different order).  Not
