@@ -8,6 +8,7 @@
 // (column-major 2ntv x 2ntv blocks) so that the lanes of a wave, one per row,
 // read consecutive addresses for every column.
 #include <algorithm>
+#include <type_traits>
 
 #include "mfma_device.h"
 
@@ -297,24 +298,31 @@ __global__ __launch_bounds__(512) void restrict_mm_kernel(cx<T>* __restrict__ ou
 // once per pass of PT rhs and feeds them all; the block's coarse vectors of
 // chirality h sit in LDS and each broadcast read feeds the KP components
 // (three in FP32; one in FP64, for the register file).
-constexpr int PT = 12;  // rhs per pass of the prolongation
+// PT rhs per pass (12 hold the registers; 1, 4 and 8 compute no padded rhs),
+// the coarse vectors padded with zeros to whole passes so that the loop over
+// the test vectors has no branch and four of them (eight for one rhs) are in
+// flight.  Bound: HBM for few rhs, VALU beside it for 12.  FP16, N_tv 24: 1 rhs
+// on 16^3x32 43.6 -> 27.7 us, 12 rhs on 24^3x48 564 -> 447 us; FP32, 8 rhs on
+// 16^4 36 -> 30 us; 1 rhs on 8^4 8.3 -> 5.2 us.
 template <typename T>
 constexpr int prolong_kp() { return sizeof(T) == 8 ? 1 : 3; }
 
-template <typename T, typename S>
+template <typename T, typename S, int PT>
 __global__ __launch_bounds__(256) void prolong_kernel(cx<T>* __restrict__ x, size_t xstr, const cx<T>* __restrict__ xc,
                                                       size_t cstr, BasisView<S> bv, Geom g, int nrhs) {
   constexpr int KP = prolong_kp<T>(), NG = 12 / KP;
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
-  cx<T>* xl = reinterpret_cast<cx<T>*>(smem_raw);  // [nrhs][ntv] of chirality h
+  cx<T>* xl = reinterpret_cast<cx<T>*>(smem_raw);  // [ntv][rhs of the pass] of chirality h, pass after pass
   const int wl = xcd_swizzle(blockIdx.x, gridDim.x);
   const int ci = wl / NG, k0 = (wl % NG) * KP, h = k0 / 6;
   const int l = threadIdx.x;
   const int ntv = g.ntv;
   const size_t V = g.V;
-  for (int e = l; e < nrhs * ntv; e += blockDim.x) {
+  const int npad = (nrhs + PT - 1) / PT * PT;  // zeros beyond nrhs: no test per rhs in the loop
+  for (int e = l; e < npad * ntv; e += blockDim.x) {
     const int r = e / ntv, a = e % ntv;
-    xl[e] = xc[(size_t)r * cstr + (size_t)ci * g.nc + h * ntv + a];
+    xl[((r / PT) * ntv + a) * PT + r % PT] =
+        r < nrhs ? xc[(size_t)r * cstr + (size_t)ci * g.nc + h * ntv + a] : mk((T)0, (T)0);
   }
   __syncthreads();
   if (l >= g.vblock) return;
@@ -326,20 +334,19 @@ __global__ __launch_bounds__(256) void prolong_kernel(cx<T>* __restrict__ x, siz
     for (int j = 0; j < PT; ++j)
 #pragma unroll
       for (int q = 0; q < KP; ++q) acc[j][q] = mk((T)0, (T)0);
-#pragma unroll 2
+#pragma unroll (PT == 1 ? 8 : 4)
     for (int a = 0; a < ntv; ++a) {
       T sc = (T)1;
       if constexpr (is_half<S>()) sc = (T)elem(bv.Wsc + (size_t)a * V, site);
       cx<T> wv[KP];
 #pragma unroll
       for (int q = 0; q < KP; ++q) wv[q] = sc * ldc<T>(bv.W + ((size_t)a * 12 + k0 + q) * V, site);
+      const cx<T>* xa = xl + (size_t)r0 * ntv + a * PT;
 #pragma unroll
       for (int j = 0; j < PT; ++j) {
-        if (j < nr) {
-          const cx<T> c = xl[(r0 + j) * ntv + a];
+        const cx<T> c = xa[j];
 #pragma unroll
-          for (int q = 0; q < KP; ++q) acc[j][q] = acc[j][q] + wv[q] * c;
-        }
+        for (int q = 0; q < KP; ++q) acc[j][q] = cfma(wv[q], c, acc[j][q]);
       }
     }
 #pragma unroll
@@ -516,8 +523,20 @@ void launch_prolong(cx<T>* x, size_t xstr, const cx<T>* xc, size_t cstr, const B
                     int nrhs, hipStream_t st) {
   if (nrhs <= 0) return;
   const int threads = ((g.vblock + 63) / 64) * 64;
-  const size_t lds = (size_t)nrhs * g.ntv * sizeof(cx<T>);
-  prolong_kernel<T, S><<<g.nblocks * (12 / prolong_kp<T>()), threads, lds, st>>>(x, xstr, xc, cstr, bv, g, nrhs);
+  const auto run = [&](auto pt) {
+    constexpr int PT = decltype(pt)::value;
+    const size_t lds = (size_t)((nrhs + PT - 1) / PT * PT) * g.ntv * sizeof(cx<T>);
+    prolong_kernel<T, S, PT>
+        <<<g.nblocks * (12 / prolong_kp<T>()), threads, lds, st>>>(x, xstr, xc, cstr, bv, g, nrhs);
+  };
+  if (nrhs == 1)
+    run(std::integral_constant<int, 1>());
+  else if (nrhs <= 4)
+    run(std::integral_constant<int, 4>());
+  else if (nrhs <= 8)
+    run(std::integral_constant<int, 8>());
+  else
+    run(std::integral_constant<int, 12>());
 }
 
 template <typename T>
