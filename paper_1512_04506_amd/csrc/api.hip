@@ -659,7 +659,8 @@ struct Solver final : SolverBase {
     if (small_coarse_applies()) {
       c->timed(DDAMG_KERNEL_COARSE, nrhs, [&] {
         launch_coarse_gmres_small<T, S>(xcv, ycv, cs_, C, Dinv.get<cx<T>>(), g, bo.get<cx<T>>(),
-                                        cV.get<cx<T>>(), (size_t)maxr * osz(), m, maxit, fixed > 0 ? -1.0 : c->p.coarse_tol, small_its.get<int>(), nrhs, st);
+                                        cV.get<cx<T>>(), (size_t)maxr * osz(), m, maxit,
+                                        fixed > 0 ? -1.0 : c->p.coarse_tol, small_its.get<int>(), nrhs, st);
       });
       check_launch("coarse solve");
       ++coarse_calls;
@@ -713,8 +714,9 @@ struct Solver final : SolverBase {
         replay_step(k, nrhs, [&] {
           schur(w, vsr, Vb + (size_t)k * vsj, vsr, nrhs, ck.any.get<int>());
           if (fused) {
-            c->timed(DDAMG_KERNEL_COARSE_GS, nrhs,
-                     [&] { launch_coarse_arnoldi<T>(ck.st, k, Vb, vsj, vsr, osz(), c->h_ring + 64 * (k & 1), nrhs, st); });
+            c->timed(DDAMG_KERNEL_COARSE_GS, nrhs, [&] {
+              launch_coarse_arnoldi<T>(ck.st, k, Vb, vsj, vsr, osz(), c->h_ring + 64 * (k & 1), nrhs, st);
+            });
             return;
           }
           c->timed(DDAMG_KERNEL_COARSE_GS, nrhs, [&] { cgs2(ck, Vb, vsj, vsr, k, w, vsr, osz(), nrhs); });
@@ -958,8 +960,9 @@ struct Solver final : SolverBase {
   // then receives w' (in FP32 its copy, scaled to about unit norm by an
   // estimate of 1 / |w'| from the first pass, so that no FP32 quantity of
   // the V-cycle underflows), which FGMRES allows: it needs D z_k in the span
-  // of V with the coefficients it records, whatever z_k is.  A step after which the next could not take the correction (basis
-  // longer than GS_FUSED_MAXV) writes v_{k+1} in a third pass as before.
+  // of V with the coefficients it records, whatever z_k is.  A step after
+  // which the next could not take the correction (basis longer than
+  // GS_FUSED_MAXV) writes v_{k+1} in a third pass as before.
   // Ends with column k of the Hessenberg matrix; once the stream has run,
   // h_flags holds the active flags.
   bool gs_pending = false;

@@ -406,8 +406,8 @@ bool arnoldi_fits(size_t n) {
 
 template <typename T>
 void launch_coarse_start(ArnoldiState s, cx<T>* V0, size_t vsr, const cx<T>* bo, const cx<T>* cw, size_t bstr, size_t n,
-                         cx<T>* xo, size_t xstr, const cx<T>* yc, size_t ystr, size_t n_all, double tol, int* host_active,
-                         int nrhs, hipStream_t st) {
+                         cx<T>* xo, size_t xstr, const cx<T>* yc, size_t ystr, size_t n_all, double tol,
+                         int* host_active, int nrhs, hipStream_t st) {
   if (nrhs <= 0) return;
   with_ept<T>(n, [&](auto e) {
     coarse_start_kernel<T, decltype(e)::value>
