@@ -476,12 +476,14 @@ __global__ __launch_bounds__(SLT, 2) void net_span_loss_kernel(cx<float>* __rest
                                                                const cx<float>* __restrict__ X,
                                                                const cx<float>* __restrict__ T, Geom g, int ntv,
                                                                double scale, int* status) {
-  __shared__ cx<double> Gs[32 * SLD], Cs[32 * SLD], Zs[32 * SLD];
-  __shared__ double wsum[SLT / 64];
   constexpr int NP = MT * (MT + 1) / 2 + MT * MT;  // tiles of G (m <= n) and of C
-  // the waves' tiles meet in the matrices' place
-  double* red = reinterpret_cast<double*>(Gs);
-  static_assert(sizeof(double) * NP * 8 * 64 <= sizeof(Gs) + sizeof(Cs) + sizeof(Zs), "reduction area");
+  // G, C and Z, and in their place before them the tiles of the waves, which
+  // need more than one matrix's room: one array, whose parts may overlap
+  __shared__ cx<double> mats[3 * 32 * SLD];
+  __shared__ double wsum[SLT / 64];
+  cx<double>*Gs = mats, *Cs = mats + 32 * SLD, *Zs = mats + 2 * 32 * SLD;
+  double* red = reinterpret_cast<double*>(mats);
+  static_assert(sizeof(double) * NP * 8 * 64 <= sizeof(mats), "reduction area");
   const int ci = blockIdx.x >> 1, h = blockIdx.x & 1;
   const size_t V = g.V;
   const int vb = g.vblock;
