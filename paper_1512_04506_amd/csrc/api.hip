@@ -404,7 +404,7 @@ struct Solver final : SolverBase {
   // accumulation buffer and the block operator applied to the basis columns
   DevBuf ws_Wd, ws_Wt, ws_D, ws_Z, ws_T;
   void ensure_setup_ws() {
-    if (ws_Wd.p) return;
+    if (ws_Z.p) return;  // the last of them: a failed allocation leaves the rest to the next call
     ws_Wd.alloc<cx<double>>((size_t)g.ntv * fsz());
     ws_T.alloc<cx<double>>(qr_tws_entries(g));
     if (is_half<S>()) ws_Wt.alloc<cx<T>>((size_t)g.ntv * fsz());  // else the stored basis is already cx<T>
