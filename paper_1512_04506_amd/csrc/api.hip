@@ -281,6 +281,7 @@ struct ddamg_ctx {
   void ensure_stage(int nrhs) {
     if ((size_t)nrhs <= stage_rhs) return;
     size_t n = (size_t)nrhs * 12 * g.V;
+    stage_rhs = 0;  // until both are there
     stage_in.alloc<cx<double>>(n);
     stage_out.alloc<cx<double>>(n);
     stage_rhs = nrhs;
@@ -1012,7 +1013,7 @@ struct Solver final : SolverBase {
   int outer_cap = 0;  // vectors held by oV; oZ holds outer_cap - 1
   void ensure_outer(int m, int nrhs) {
     if (m == outer_m && nrhs <= outer_r) return;
-    outer_m = m;
+    outer_m = 0;  // until all are there
     outer_r = nrhs;
     const size_t n = fsz();
     outer_cap = std::min(m + 1, 2);  // doubled on demand by grow_outer
@@ -1022,6 +1023,7 @@ struct Solver final : SolverBase {
     of.alloc<cx<double>>((size_t)nrhs * n);
     ou.alloc<cx<double>>((size_t)nrhs * n);
     ok.alloc(m, nrhs, n, st);
+    outer_m = m;
   }
 
   // room for basis vectors 0..kv-1 (and Z vectors 0..kv-2), contents kept
@@ -1321,12 +1323,16 @@ struct ddamg_net {
   void ensure(NetWork& w, const Geom& gl, bool training) {
     if (w.have && same_lattice(w.g, gl)) return;
     w.g = gl;
-    w.have = true;
+    w.have = false;
     const size_t V = gl.V;
     size_t tot = 0;
     for (int c : ch) tot += (size_t)c;
     w.act.alloc<cx<float>>(tot * 12 * V);
-    if (!training) return;
+    if (training) ensure_training(w, gl);
+    w.have = true;
+  }
+  void ensure_training(NetWork& w, const Geom& gl) {
+    const size_t V = gl.V;
     w.gam0.alloc<cx<float>>((size_t)cmax() * 12 * V);
     w.gam1.alloc<cx<float>>((size_t)cmax() * 12 * V);
     w.lagg.alloc<double>((size_t)2 * gl.nblocks);
