@@ -692,7 +692,7 @@ struct Solver final : SolverBase {
       if (!first) schur(cw.get<cx<T>>(), osz(), xo, cs_, nrhs);
       if (fused) {
         launch_coarse_start<T>(ck.st, Vb, vsr, bo.get<cx<T>>(), first ? nullptr : cw.get<cx<T>>(), osz(), osz(), xo,
-                               cs_, ycv, cs_, cs_, tol, c->h_flags, nrhs, st);
+                               cs_, ycv, cs_, cs_, tol, c->h_flags, nrhs, maxr, st);
       } else {
         if (first)
           launch_copy<T, T>(Vb, vsr, bo.get<cx<T>>(), osz(), osz(), nrhs, st);

@@ -489,13 +489,14 @@ void launch_arnoldi_solve(ArnoldiState s, int nrhs, hipStream_t st);
 // (arnoldi_fits): the start of a cycle (r = bo - cw, or bo with xo zeroed and
 // the stop threshold tol |yc| set if cw is null), Arnoldi step k on V_{k+1},
 // and the end of a cycle (xo += V y; any n).  The first two leave the active
-// flags in host_active (pinned host memory)
+// flags in host_active (pinned host memory); nflags: the flags that the state
+// holds, of which a first cycle clears those beyond nrhs
 template <typename T>
 bool arnoldi_fits(size_t n);
 template <typename T>
 void launch_coarse_start(ArnoldiState s, cx<T>* V0, size_t vsr, const cx<T>* bo, const cx<T>* cw, size_t bstr, size_t n,
                          cx<T>* xo, size_t xstr, const cx<T>* yc, size_t ystr, size_t n_all, double tol, int* host_active,
-                         int nrhs, hipStream_t st);
+                         int nrhs, int nflags, hipStream_t st);
 template <typename T>
 void launch_coarse_arnoldi(ArnoldiState s, int k, cx<T>* Vb, size_t vsj, size_t vsr, size_t n, int* host_active,
                            int nrhs, hipStream_t st);

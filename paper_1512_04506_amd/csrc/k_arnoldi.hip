@@ -87,12 +87,14 @@ __device__ inline void post_flag(int* host_active, int r, int act) {
 // Start of a cycle: V_0 = r / |r| with r = b_o - c_w (c_w null: b_o, the
 // first cycle, whose x_o is set to zero and whose stop threshold tol |y_c|
 // is computed, tol < 0: never test), the state of arnoldi_start_kernel.
-// s.any counts the active rhs: every rhs adds the change of its own flag.
+// s.any counts the active rhs: every rhs adds the change of its own flag, and
+// the first cycle takes down what an earlier call of more rhs, stopped by its
+// iteration limit, left in the flags beyond this one's (of nflags).
 template <typename T, int EPT>
 __global__ __launch_bounds__(AT) void coarse_start_kernel(ArnoldiState s, cx<T>* V0, size_t vsr, const cx<T>* bo,
                                                           const cx<T>* cw, size_t bstr, int n, cx<T>* xo, size_t xstr,
                                                           const cx<T>* yc, size_t ystr, int nc_all, double tol,
-                                                          int* host_active) {
+                                                          int* host_active, int nflags) {
   __shared__ double red[8][AW];
   __shared__ cx<double> h[AJ];
   const int r = blockIdx.x, t = threadIdx.x, m = s.m;
@@ -119,6 +121,12 @@ __global__ __launch_bounds__(AT) void coarse_start_kernel(ArnoldiState s, cx<T>*
     for (int e = t; e < nc_all; e += AT) a += y[e].r * y[e].r + y[e].i * y[e].i;
     d[1].r = (double)a;
     for (int e = t; e < n; e += AT) xo[(size_t)r * xstr + e] = mk((T)0, (T)0);
+    if (r == 0)
+      for (int q = gridDim.x + t; q < nflags; q += AT)
+        if (s.active[q]) {
+          s.active[q] = 0;
+          atomicAdd(s.any, -1);
+        }
   }
   T a = (T)0;
 #pragma unroll
@@ -407,12 +415,12 @@ bool arnoldi_fits(size_t n) {
 template <typename T>
 void launch_coarse_start(ArnoldiState s, cx<T>* V0, size_t vsr, const cx<T>* bo, const cx<T>* cw, size_t bstr, size_t n,
                          cx<T>* xo, size_t xstr, const cx<T>* yc, size_t ystr, size_t n_all, double tol,
-                         int* host_active, int nrhs, hipStream_t st) {
+                         int* host_active, int nrhs, int nflags, hipStream_t st) {
   if (nrhs <= 0) return;
   with_ept<T>(n, [&](auto e) {
     coarse_start_kernel<T, decltype(e)::value>
         <<<nrhs, AT, 0, st>>>(s, V0, vsr, bo, cw, bstr, (int)n, xo, xstr, yc, ystr, (int)n_all, tol,
-                               host_active);
+                               host_active, nflags);
   });
 }
 
@@ -449,7 +457,8 @@ void launch_coarse_finish(ArnoldiState s, const cx<T>* Vb, size_t vsj, size_t vs
 #define INST(T)                                                                                                        \
   template bool arnoldi_fits<T>(size_t);                                                                               \
   template void launch_coarse_start<T>(ArnoldiState, cx<T>*, size_t, const cx<T>*, const cx<T>*, size_t, size_t,       \
-                                       cx<T>*, size_t, const cx<T>*, size_t, size_t, double, int*, int, hipStream_t);  \
+                                       cx<T>*, size_t, const cx<T>*, size_t, size_t, double, int*, int, int,           \
+                                       hipStream_t);                                                                   \
   template void launch_coarse_arnoldi<T>(ArnoldiState, int, cx<T>*, size_t, size_t, size_t, int*, int, hipStream_t);   \
   template void launch_coarse_finish<T>(ArnoldiState, const cx<T>*, size_t, size_t, cx<T>*, size_t, size_t, int,       \
                                         hipStream_t);
