@@ -116,10 +116,13 @@ __global__ __launch_bounds__(AT) void coarse_start_kernel(ArnoldiState s, cx<T>*
     }
   } else {
     const cx<T>* y = yc + (size_t)r * ystr;
-    T a = (T)0;
-#pragma unroll 8
-    for (int e = t; e < nc_all; e += AT) a += y[e].r * y[e].r + y[e].i * y[e].i;
-    d[1].r = (double)a;
+    for (int e0 = t; e0 < nc_all; e0 += 8 * AT) {  // at most eight in a chain of T
+      T a = (T)0;
+#pragma unroll
+      for (int q = 0; q < 8; ++q)
+        if (e0 + q * AT < nc_all) a += y[e0 + q * AT].r * y[e0 + q * AT].r + y[e0 + q * AT].i * y[e0 + q * AT].i;
+      d[1].r += (double)a;
+    }
     for (int e = t; e < n; e += AT) xo[(size_t)r * xstr + e] = mk((T)0, (T)0);
     if (r == 0)
       for (int q = gridDim.x + t; q < nflags; q += AT)

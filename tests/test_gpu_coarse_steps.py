@@ -78,3 +78,16 @@ def test_flags_left_by_a_call_of_more_rhs():
     assert K.active.tolist() == [1] * 2 + [0] * 6 and K.any.item() == 2
     start(K, V, bo, bo, x, yc, -1.0, 2)  # a later cycle whose residual is zero: both stop
     assert K.active.tolist() == [0] * 8 and K.any.item() == 0 and K.host[:2].tolist() == [0] * 2
+
+
+def test_stop_threshold():
+    """|y_c| of the longest vectors with one element per lane that swallows the
+    squares added to it in FP32 (each below half its last bit): off by at most
+    what a chain of 32 FP32 additions may lose, in the square 31 2^-24."""
+    n, n_all, K = 24576, 49152, Krylov(3, 1)
+    y = torch.full((1, n_all), (0.99 * 2.0 ** -24) ** 0.5, dtype=torch.complex64, device="cuda")
+    y[0, :1024] = 1.0
+    bo, x, V = (fields(1, n, seed=4) for _ in range(3))
+    start(K, V, bo, None, x, y, 0.5, 1)
+    want = 0.25 * float((y.to(torch.complex128).abs() ** 2).sum())
+    assert abs(K.abstol.item() ** 2 / want - 1.0) <= 31 * 2.0 ** -24
