@@ -312,7 +312,7 @@ int ddamg_batch_solve(ddamg_ctx* const* ctx, int n, double* const* u, const doub
 
 /* HIP graphs for the coarse GMRES (Alg. 2): on (the default), each coarse
  * iteration's launches (two of the Schur-complement stencil and the Arnoldi
- * step; ten for vectors beyond one workgroup's) are captured once per
+ * step; twelve where the step takes many workgroups) are captured once per
  * iteration index and rhs count into a HIP graph on the context's stream and
  * replayed, one launch call per iteration.  (Measured on
  * small lattices this changes little: the chain of small dependent kernels

@@ -429,7 +429,7 @@ struct Solver final : SolverBase {
   // device (the former scheme, kept for the timing comparison)
   bool sync_each_coarse_it = false;
   // Each coarse GMRES iteration (Schur complement and Arnoldi step: three
-  // launches, or ten for vectors beyond one workgroup's) captured once per
+  // launches, or twelve where the step takes many workgroups) captured once per
   // (iteration index, nrhs) into a HIP graph and replayed: one launch call.
   // The captured kernels use only buffers allocated with the solver and its
   // context's pinned flags (an iteration's slot follows from its index), so
@@ -667,7 +667,8 @@ struct Solver final : SolverBase {
       ++coarse_calls;
       return 0;  // the iterations are counted on the device
     }
-    // vectors that one workgroup per rhs holds: the fused steps
+    // vectors that one workgroup per rhs holds: fused starts, and fused steps
+    // while the basis is short enough for one workgroup to read it
     const bool fused = arnoldi_fits<T>(osz());
     const double tol = fixed > 0 ? -1.0 : c->p.coarse_tol;
     // b_o = y_o - D_oe D_ee^{-1} y_e
@@ -710,11 +711,12 @@ struct Solver final : SolverBase {
       int k = 0;
       for (; k < m && its < maxit; ++k) {
         cx<T>* w = Vb + (size_t)(k + 1) * vsj;
+        const bool one_group = fused && arnoldi_one_group(osz(), k);
         // every kernel of the iteration is predicated: on the rhs-wise
         // active flags, and the operator on "some rhs active"
         replay_step(k, nrhs, [&] {
           schur(w, vsr, Vb + (size_t)k * vsj, vsr, nrhs, ck.any.get<int>());
-          if (fused) {
+          if (one_group) {
             c->timed(DDAMG_KERNEL_COARSE_GS, nrhs, [&] {
               launch_coarse_arnoldi<T>(ck.st, k, Vb, vsj, vsr, osz(), c->h_ring + 64 * (k & 1), nrhs, st);
             });
@@ -734,7 +736,7 @@ struct Solver final : SolverBase {
           continue;
         }
         if (fixed > 0) continue;
-        post_active(ck, nrhs, k & 1, fused);
+        post_active(ck, nrhs, k & 1, one_group);
         // iteration k is enqueued: decide on the flags of iteration k - 1
         if (k >= 1 && !any_posted(nrhs, (k - 1) & 1)) {
           --its;  // iteration k ran on inactive rhs only

@@ -40,6 +40,18 @@ inline size_t mdot_part_capacity(size_t n, int nvec, int nrhs) {
   return c;
 }
 
+// Whether coarse GMRES step k on vectors of n elements runs in one workgroup
+// per rhs (k_arnoldi.hip) or in the ten many-workgroup launches.  A step reads
+// k + 1 basis vectors four times: one compute unit takes 0.59 us per 1000
+// elements and vector, the many workgroups 2.6 us per vector whatever its
+// length (up to 24576 elements) and some 18 us more to begin with.  So the one
+// workgroup wins for any k up to about 4096 elements and for ever fewer
+// vectors beyond.  FP32, one rhs, us per step (with the operator, one workgroup
+// against many): 6144 elements k = 8..11 73/80, k = 24..29 145/130; 12288
+// elements k = 3 61/59, k = 24..29 253/140; 24576 elements k = 1 81/76, k =
+// 24..29 777/145.  FP64 and 4 or 12 rhs cross within two vectors of it.
+inline bool arnoldi_one_group(size_t n, int k) { return n <= 4096 || (size_t)(k + 1) * (n - 4096) <= 32768; }
+
 // Krylov workspace of GMRES(m) on vectors of n elements per rhs: the
 // widest multi-dot is the Gram-Schmidt of a new vector against all m + 1
 // basis vectors of a cycle; the norm of a coarse right-hand side runs over

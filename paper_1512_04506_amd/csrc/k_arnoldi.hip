@@ -4,17 +4,19 @@
 // the end, the scalar work of the outer Gram-Schmidt.
 //
 // A coarse vector of a lattice up to 16^3x32 is some 10^4 elements, 100 KB
-// that lie in L2: what bounds a step is the number of dependent launches and
-// of reductions over workgroups, not the data.  One workgroup holds the new
-// vector in registers through the whole step and reduces within itself, so a
-// step is one launch instead of ten (mdot and its final sum, maxpy, twice,
-// the norm, the column, the scaling: 9 + 3 + 3, 9 + 3 + 3, 9 + 3, 4, 2 us on
-// 16^3x32, 1 rhs, N_tv 24; now 15 us there, 9.8 us for 8 rhs on 16^4 at N_tv
-// 20) and a start one instead of five.  The solves: 16^3x32 5.15 -> 4.47 ms,
-// 16^4 with 8 rhs 8.57 -> 7.94 ms; with the flags stored to the host's memory
-// by the steps and the start's loads all in flight 3.67 -> 3.59, 7.34 -> 7.25.  A thread holds at most 24 elements in
-// FP32, 16 in FP64 (the registers of a 1024-lane workgroup); longer vectors
-// keep the many-workgroup kernels of k_blas.hip.
+// that lie in L2: what bounds the first steps of a cycle is the number of
+// dependent launches and of reductions over workgroups, not the data.  One
+// workgroup holds the new vector in registers through the whole step and
+// reduces within itself, so a step is one launch instead of ten (mdot and its
+// final sum, maxpy, twice, the norm, the column, the scaling) and a start one
+// instead of five.  It reads the k + 1 basis vectors four times through one
+// compute unit, so its time grows with k where theirs hardly does: 12288
+// elements, FP32, one rhs, 22 us a step over the first two, 46 over eight, 72
+// over fifteen, against 49, 76 and 108 of the separate launches with 8192
+// elements to a workgroup.  arnoldi_one_group (blas_sizes.h) says up to which k
+// a step is taken here.  A thread holds at most 24 elements in FP32, 16 in
+// FP64 (the registers of a 1024-lane workgroup); longer vectors keep the
+// many-workgroup kernels of k_blas.hip throughout.
 #include "krylov_device.h"
 
 namespace ddamg {
