@@ -52,6 +52,56 @@ inline size_t mdot_part_capacity(size_t n, int nvec, int nrhs) {
 // 24..29 777/145.  FP64 and 4 or 12 rhs cross within two vectors of it.
 inline bool arnoldi_one_group(size_t n, int k) { return n <= 4096 || (size_t)(k + 1) * (n - 4096) <= 32768; }
 
+// Shape of the coarse stencil's vector kernel (k_stencil.hip): rows of a
+// column per lane and waves per workgroup; waves = 0: the matrix cores.
+struct GemvShape {
+  int rows, waves;
+};
+// esize: bytes of a complex entry of the vectors; half: D_c stored in FP16;
+// nslot slots of nc columns; nrhs rhs, nout output sites.
+// Sixteen waves hide the chain of a workgroup while there are few of them.
+// Once they fill the chip, the sum over the waves and their column groups is
+// all that more waves add, so four do (eight for the longest columns), each
+// group with four columns at least: 2 rhs on 4096 sites, FP32, N_tv 8 126 us
+// with sixteen waves, 18 with four; N_tv 24 192 and 127; 256 sites, N_tv 24, one
+// rhs 9.8 and 13.5.  Two rows per lane where four would leave lanes idle or,
+// with the sums of four rhs, fill the registers: FP32, 4 rhs, 4096 sites, N_tv
+// 16 58 us against 64.  The matrix cores compute 16 rhs at one price: FP16, 4
+// rhs, 4096 sites, N_tv 24 92 us against 114, 2 rhs 89 against 73.
+inline GemvShape stencil_gemv_shape(size_t esize, bool half, int nc, int nslot, int nrhs, int nout) {
+  if (nrhs > 4 || (nrhs == 4 && half && nc >= 32)) return {0, 0};
+  const bool f32 = esize == 8;
+  const bool four = f32 && nc % 4 == 0 && (nrhs == 1 || nc > (half ? 16 : 32)) && !(nrhs == 4 && nout > 512 && nc <= 48);
+  const int rows = four ? 4 : 2;
+  int waves = 16, lanes = 1;  // lanes for the rows of a column
+  while (lanes * rows < nc) lanes *= 2;
+  const size_t col = (size_t)nc * nrhs * esize;
+  if ((nslot + waves) * col > 49152) waves /= 2;
+  if (nout > 512 && nc * esize <= 384) {
+    waves = waves < 4 ? waves : 4;
+  } else if (nout > 256 && nrhs > 1) {
+    waves = waves < 8 ? waves : 8;
+  }
+  const int groups = 64 / lanes, least = nslot > 1 || nout > 256 ? 4 : 1;
+  while (waves > 1 && waves * groups * least > nslot * nc) waves /= 2;
+  return {rows, waves};
+}
+
+// Whether the stencil of 5 and more rhs in FP32 arithmetic takes a wave per 16
+// rows (at most two) instead of the kernel that deals columns in chunks of 16
+// to four or eight waves; groups: output sites times groups of 16 rhs.  The
+// chunks and row tiles of the latter are partly empty for few rows, and its
+// sum over the waves costs a grid that fills the chip without it (us, row
+// tiles against chunks): FP32, 5 rhs, 4096 sites, N_tv 4 12/24, 8 22/25, 10
+// 43/59, 12 50/59, and 12 rhs, 8192 sites, N_tv 12 157/135; FP16, 5 rhs, 8192
+// sites, N_tv 6 29/36, 12 88/72; FP32, 5 rhs, 256 sites, N_tv 12 13/8.
+inline bool stencil_by_tiles(bool half, int nc, int nrhs, int groups) {
+  if (half) return nc <= 12 && groups > 2048;
+  if (nc <= 12) return groups > 512;
+  if (nc <= 16) return groups > 2048;
+  return nc <= 20 ? groups > 1000 : nc <= 24 && (nrhs - 1) % 16 < 8 && groups > 1500;
+}
+
 // Krylov workspace of GMRES(m) on vectors of n elements per rhs: the
 // widest multi-dot is the Gram-Schmidt of a new vector against all m + 1
 // basis vectors of a cycle; the norm of a coarse right-hand side runs over

@@ -12,6 +12,7 @@
 // over the waves of the workgroup, with no barrier between the slots, and
 // add the waves' partial results through LDS once at the end.
 #include <algorithm>
+#include <type_traits>
 
 #include "mfma_device.h"
 
@@ -68,8 +69,9 @@ __device__ inline T st_coef(const StArgs<T, S>& a, int ci, int q) {
 // for the rows, 64 / GL columns per wave and SW waves: column c of all slots
 // belongs to column group c mod (SW 64 / GL), so every load of a lane is
 // independent of the others.  The inputs, times the slot's factor, sit in
-// LDS.  Against one workgroup walking the slots with two barriers each:
-// 19.9 -> 7.6 us for one rhs on 256 sites (16^3x32, FP16, N_tv 24).
+// LDS.  RP and SW: stencil_gemv_shape (blas_sizes.h).  Against one workgroup
+// walking the slots with two barriers each: 19.9 -> 7.6 us for one rhs on 256
+// sites (16^3x32, FP16, N_tv 24).
 constexpr int ST_T = 1024;
 
 template <typename T, int RP, int RB>
@@ -389,17 +391,52 @@ __global__ __launch_bounds__(512) void stencil_mm_kernel(StArgs<T, S> a) {
   }
 }
 
+// Few rows on many sites (FP32 arithmetic, no second product): a wave per 16
+// rows and 16 rhs walks the slots four columns at a time, which wastes none of
+// a short column, and leaves its tile straight from the registers
+// (stencil_by_tiles, blas_sizes.h, with times).
+template <typename S>
+__global__ __launch_bounds__(128) void stencil_tile_kernel(StArgs<float, S> a) {
+  if (a.gate && *a.gate == 0) return;
+  const int nc = a.nc, ls = blockIdx.x, ci = a.out_first + ls;
+  const int r0 = blockIdx.y * MM_RHS, nr = min(MM_RHS, a.nrhs - r0);
+  const int lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
+  const int r16 = 16 * (threadIdx.x >> 6);       // the wave's first row
+  const int bj = r0 + min(li, nr - 1);           // this lane's rhs (clamped)
+  const stc_t<S>* D = a.D + (size_t)ci * a.dsite + min(r16 + li, nc - 1);
+  mm_f4 re = {0.f, 0.f, 0.f, 0.f}, im = {0.f, 0.f, 0.f, 0.f};
+  for (int q = 0; q < a.nslot; ++q, D += (size_t)nc * nc) {
+    size_t str;
+    const cx<float>* x = st_input(a, ci, q, str);
+    x += (size_t)bj * str;
+    const float coef = st_coef(a, ci, q);
+#pragma unroll 4
+    for (int k0 = 0; k0 < nc; k0 += 4) {
+      const int k = k0 + lg, kc = min(k, nc - 1);
+      const cx<float> d = ldc<float>(D, (size_t)kc * nc), xk = x[kc];
+      const float br = k < nc ? coef * xk.r : 0.f, bi = k < nc ? coef * xk.i : 0.f;
+      re = mm_mfma(d.r, br, re);
+      im = mm_mfma(d.r, bi, im);
+      re = mm_mfma(d.i, -bi, re);
+      im = mm_mfma(d.i, br, im);
+    }
+  }
+  if (li >= nr) return;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int rw = r16 + mm_row<float>(lg, v);
+    if (rw >= nc) continue;
+    cx<float> s = mk(re[v], im[v]);
+    if (a.add) s = s + a.add[(size_t)bj * a.astr + (size_t)ls * nc + rw];
+    a.out[(size_t)bj * a.ostr + (size_t)ls * nc + rw] = s;
+  }
+}
+
 template <typename T, typename S, int RP, int RB>
-void gemv_launch(const StArgs<T, S>& a, int nout, hipStream_t st) {
+void gemv_launch(const StArgs<T, S>& a, int nout, int nw, hipStream_t st) {
   int GL = 1;
-  while (GL * RP < a.nc) GL *= 2;  // <= 64: nc <= 64
-  // 16 waves; 8 where the partial results of 16 would need over 48 KB
-  int nw = ST_T / 64;
-  const size_t in = (size_t)a.nslot * a.nc * RB * sizeof(cx<T>);
-  if (in + (size_t)nw * a.nc * RB * sizeof(cx<T>) > 49152) nw /= 2;
-  // fewer where the columns do not give every column group one
-  while (nw > 1 && (nw / 2) * (64 / GL) >= a.nslot * a.nc) nw /= 2;
-  const size_t lds = in + (size_t)nw * a.nc * RB * sizeof(cx<T>);
+  while (GL * RP < a.nc) GL *= 2;  // <= 32: nc <= 64, RP >= 2
+  const size_t lds = ((size_t)a.nslot + nw) * a.nc * RB * sizeof(cx<T>);
   stencil_gemv_kernel<T, S, RP, RB><<<nout, 64 * nw, lds, st>>>(a, GL);
 }
 
@@ -416,20 +453,32 @@ void mm_launch(const StArgs<T, S>& a, int nout, hipStream_t st) {
 template <typename T, typename S>
 void stencil_launch(const StArgs<T, S>& a, int nout, hipStream_t st) {
   if (a.nrhs <= 0 || nout <= 0) return;
-  if (a.nrhs <= 4) {
-    // four rows per lane where the columns are whole multiples of it
-    if (sizeof(T) == 4 && a.nc % 4 == 0) {
-      if (a.nrhs == 1)
-        gemv_launch<T, S, sizeof(T) == 4 ? 4 : 2, 1>(a, nout, st);
-      else
-        gemv_launch<T, S, sizeof(T) == 4 ? 4 : 2, 4>(a, nout, st);
-    } else {
-      if (a.nrhs == 1)
-        gemv_launch<T, S, 2, 1>(a, nout, st);
-      else
-        gemv_launch<T, S, 2, 4>(a, nout, st);
+  const GemvShape g = stencil_gemv_shape(sizeof(cx<T>), is_half<S>(), a.nc, a.nslot, a.nrhs, nout);
+  if (g.waves) {
+    const auto run = [&](auto rb) {
+      constexpr int RB = decltype(rb)::value;
+      if constexpr (sizeof(T) == 4) {
+        if (g.rows == 4) {
+          gemv_launch<T, S, 4, RB>(a, nout, g.waves, st);
+          return;
+        }
+      }
+      gemv_launch<T, S, 2, RB>(a, nout, g.waves, st);
+    };
+    switch (a.nrhs) {
+      case 1: run(std::integral_constant<int, 1>()); break;
+      case 2: run(std::integral_constant<int, 2>()); break;
+      case 3: run(std::integral_constant<int, 3>()); break;
+      default: run(std::integral_constant<int, 4>()); break;
     }
     return;
+  }
+  if constexpr (sizeof(T) == 4) {
+    const int ngr = (a.nrhs + MM_RHS - 1) / MM_RHS;
+    if (!a.M && stencil_by_tiles(is_half<S>(), a.nc, a.nrhs, nout * ngr)) {
+      stencil_tile_kernel<S><<<dim3(nout, ngr), 64 * ((a.nc + 15) / 16), 0, st>>>(a);
+      return;
+    }
   }
   switch ((a.nc + 15) / 16) {  // nc = 2 ntv <= 64
     case 1: mm_launch<T, S, 1>(a, nout, st); break;

@@ -2,6 +2,7 @@
 // measured for both (us).  Prints one line per point; exit status 1 where a
 // rule takes the slower side by more than a twentieth.
 #include <cstdio>
+#include <initializer_list>
 
 #include "blas_sizes.h"
 
@@ -32,5 +33,51 @@ int main() {
   for (size_t n = 16; n <= 24576; n += 16)
     for (int k = 0; k < 64; ++k)
       if (!arnoldi_one_group(n, k) && (arnoldi_one_group(n, k + 1) || arnoldi_one_group(n + 16, k))) ++fails;
+  // coarse stencil of few rhs, sites and rows: four waves per workgroup, sixteen
+  const struct {
+    int nout, nc, nrhs;
+    bool half;
+    double four, sixteen;
+  } gemv[] = {{4096, 8, 2, false, 11.0, 34.3},   {4096, 16, 2, false, 20.0, 125.8}, {4096, 16, 4, true, 19.6, 126.6},
+              {4096, 24, 3, false, 32.1, 121.0}, {8192, 32, 2, true, 66.0, 122.6},  {8192, 48, 2, true, 141.0, 172.0},
+              {256, 48, 1, false, 13.5, 9.8},    {256, 48, 2, false, 19.2, 13.3},   {256, 64, 1, true, 16.0, 8.5}};
+  for (const auto& g : gemv) {
+    const int w = stencil_gemv_shape(8, g.half, g.nc, 9, g.nrhs, g.nout).waves;
+    point("coarse stencil", g.nc, g.nrhs, w <= 4, g.four, g.sixteen);
+  }
+  // every shape: lanes for the rows of a column within a wave, the rows of a
+  // lane within a column, the partial results in LDS
+  for (int ntv = 1; ntv <= 32; ++ntv)
+    for (int nslot : {1, 8, 9})
+      for (int nrhs = 1; nrhs <= 5; ++nrhs)
+        for (int nout = 1; nout <= 16384; nout *= 2)
+          for (int type = 0; type < 3; ++type) {
+            const int nc = 2 * ntv;
+            const size_t es = type == 0 ? 16 : 8;
+            const GemvShape g = stencil_gemv_shape(es, type == 2, nc, nslot, nrhs, nout);
+            if (g.waves == 0 ? nrhs < 4 : nrhs > 4) ++fails;
+            if (g.waves == 0) continue;
+            int lanes = 1;
+            while (lanes * g.rows < nc) lanes *= 2;
+            const size_t lds = (size_t)(nslot + g.waves) * nc * nrhs * es;
+            if (lanes > 64 || nc % g.rows || g.rows < 2 || (es == 16 && g.rows != 2) || g.waves > 16 ||
+                (g.waves & (g.waves - 1)) || lds > 80 * 1024) {
+              std::printf("shape ntv %d nslot %d nrhs %d nout %d type %d: rows %d waves %d lds %zu FAIL\n", ntv, nslot,
+                          nrhs, nout, type, g.rows, g.waves, lds);
+              ++fails;
+            }
+          }
+  // a wave per row tile (at most two), chunks of columns; FP32, 5 and 12 rhs, FP16
+  for (int nc = 2; nc <= 64; nc += 2)
+    for (bool half : {false, true})
+      if (stencil_by_tiles(half, nc, 5, 1 << 20) && nc > 32) ++fails;
+  point("row tiles", 8, 5, stencil_by_tiles(false, 8, 5, 4096), 12.5, 24.0);
+  point("row tiles", 16, 5, stencil_by_tiles(false, 16, 5, 4096), 22.1, 25.4);
+  point("row tiles", 20, 5, stencil_by_tiles(false, 20, 5, 4096), 42.5, 58.8);
+  point("row tiles", 24, 5, stencil_by_tiles(false, 24, 5, 4096), 50.2, 59.4);
+  point("row tiles", 24, 12, stencil_by_tiles(false, 24, 12, 8192), 157.7, 134.9);
+  point("row tiles", 24, 5, stencil_by_tiles(false, 24, 5, 256), 12.7, 7.6);
+  point("row tiles", 12, 5, stencil_by_tiles(true, 12, 5, 8192), 28.9, 35.7);
+  point("row tiles", 24, 5, stencil_by_tiles(true, 24, 5, 8192), 88.4, 72.3);
   return fails ? 1 : 0;
 }
