@@ -102,6 +102,19 @@ inline bool stencil_by_tiles(bool half, int nc, int nrhs, int groups) {
   return nc <= 20 ? groups > 1000 : nc <= 24 && (nrhs - 1) % 16 < 8 && groups > 1500;
 }
 
+// Whether the restriction runs on the vector units, a lane per site, instead
+// of the matrix cores (k_coarse.hip).  4 rhs in FP32 and 2 in FP64 fit the
+// registers, so the basis is read once; the matrix cores do 16 rhs and 16 test
+// vectors at one price.  Up to four test vectors, that price is more than a
+// second pass over their few planes on all but the smallest blocks (us, matrix
+// cores against lanes): N_tv 4, 16^3x32 on 4^4, FP16, 5 rhs 69/58, 12 rhs
+// 135/138; FP64, 3 rhs 92/68, 8 rhs 153/169; 16^4 on 2^4, FP32, 5 rhs 41/54; N_tv
+// 8, 16^3x32 on 4^4, FP32, 5 rhs 82/85.
+inline bool restrict_by_lanes(bool f32, int ntv, int vblock, int nrhs) {
+  const bool thin = ntv <= 4 && vblock > 16;
+  return nrhs <= (f32 ? 4 : 2) * (thin ? 2 : 1);
+}
+
 // Krylov workspace of GMRES(m) on vectors of n elements per rhs: the
 // widest multi-dot is the Gram-Schmidt of a new vector against all m + 1
 // basis vectors of a cycle; the norm of a coarse right-hand side runs over

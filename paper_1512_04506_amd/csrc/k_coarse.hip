@@ -26,10 +26,10 @@ using namespace dev;
 //
 // Few rhs, on the vector units: workgroup = (block, share of the test-vector
 // tiles), one lane per site of the block (its sites are contiguous in the
-// block-major layout, so every load is coalesced), RT right-hand sides kept
-// in registers and AT test vectors at a time; the 64 lanes of a wave are
-// summed by a butterfly reduce-scatter (63 shuffle-adds for 32 values) and
-// the waves through LDS.  One rhs: 8^4 (N_tv 16, FP32) 22.3 -> 5.1 us, 16^3x32
+// block-major layout, so every load is coalesced), RT right-hand sides
+// (blockIdx.y) kept in registers and AT test vectors at a time; the 64 lanes
+// of a wave are summed by a butterfly reduce-scatter (63 shuffle-adds for 32
+// values) and the waves through LDS.  One rhs: 8^4 (N_tv 16, FP32) 22.3 -> 5.1 us, 16^3x32
 // (N_tv 24, FP16) 49 -> 34.6 us = 5.0 TB/s; a lone rhs used to run as four.
 
 // One halving step of the butterfly, unrolled at compile time so that every
@@ -69,6 +69,10 @@ __global__ __launch_bounds__(256) void restrict_kernel(cx<T>* __restrict__ out, 
   __shared__ T red[4][MAXAT][NV];
   const int wl = xcd_swizzle(blockIdx.x, gridDim.x);
   const int ci = wl / na, share = wl - ci * na;  // the shares of a block read the same y side by side
+  const int r0 = blockIdx.y * RT;                // rhs of this workgroup
+  y += (size_t)r0 * ystr;
+  out += (size_t)r0 * ostr_r;
+  nrhs -= r0;
   const int l = threadIdx.x;
   const int lane = l & 63, w = l >> 6;
   const int nw = blockDim.x >> 6;
@@ -480,7 +484,8 @@ void restrict_few(cx<T>* out, size_t ostr_r, size_t ostr_b, const cx<T>* y, size
   const int nat = (g.ntv + AT - 1) / AT;
   const int na = std::max(1, std::min(nat, 1024 / g.nblocks));
   const int threads = ((g.vblock + 63) / 64) * 64;
-  restrict_kernel<T, S, RT, AT><<<g.nblocks * na, threads, 0, st>>>(out, ostr_r, ostr_b, y, ystr, bv, g, nrhs, na);
+  restrict_kernel<T, S, RT, AT>
+      <<<dim3(g.nblocks * na, (nrhs + RT - 1) / RT), threads, 0, st>>>(out, ostr_r, ostr_b, y, ystr, bv, g, nrhs, na);
 }
 template <typename T, typename S, int MT, int NT>
 void restrict_many(cx<T>* out, size_t ostr_r, size_t ostr_b, const cx<T>* y, size_t ystr, const BasisView<S>& bv,
@@ -499,14 +504,12 @@ template <typename T, typename S>
 void launch_restrict(cx<T>* out, size_t ostr_r, size_t ostr_b, const cx<T>* y, size_t ystr, const BasisView<S>& bv,
                      const Geom& g, int nrhs, hipStream_t st) {
   if (nrhs <= 0) return;
-  // up to 4 rhs in FP32 and 2 in FP64 fit the registers of the vector kernel,
-  // which then reads the basis once; the matrix cores do 16 at one price
   constexpr bool f32 = sizeof(T) == 4;
   if (nrhs == 1)
     restrict_few<T, S, 1, f32 ? 4 : 2>(out, ostr_r, ostr_b, y, ystr, bv, g, nrhs, st);
   else if (nrhs == 2)
     restrict_few<T, S, 2, f32 ? 2 : 1>(out, ostr_r, ostr_b, y, ystr, bv, g, nrhs, st);
-  else if (f32 && nrhs <= 4)
+  else if (restrict_by_lanes(f32, g.ntv, g.vblock, nrhs))
     restrict_few<T, S, f32 ? 4 : 2, f32 ? 2 : 1>(out, ostr_r, ostr_b, y, ystr, bv, g, nrhs, st);
   else if (g.ntv <= 16 && nrhs <= 16)
     restrict_many<T, S, 1, 1>(out, ostr_r, ostr_b, y, ystr, bv, g, nrhs, st);

@@ -79,5 +79,15 @@ int main() {
   point("row tiles", 24, 5, stencil_by_tiles(false, 24, 5, 256), 12.7, 7.6);
   point("row tiles", 12, 5, stencil_by_tiles(true, 12, 5, 8192), 28.9, 35.7);
   point("row tiles", 24, 5, stencil_by_tiles(true, 24, 5, 8192), 88.4, 72.3);
+  // restriction by lanes, on the matrix cores
+  point("restriction", 4, 5, restrict_by_lanes(true, 4, 256, 5), 58.0, 69.0);
+  point("restriction", 4, 8, restrict_by_lanes(true, 4, 90, 8), 107.0, 126.0);
+  point("restriction", 4, 12, restrict_by_lanes(true, 4, 256, 12), 148.0, 140.0);
+  point("restriction", 4, 5, restrict_by_lanes(true, 4, 16, 5), 54.0, 41.0);
+  point("restriction", 8, 5, restrict_by_lanes(true, 8, 256, 5), 85.0, 82.0);
+  point("restriction", 24, 4, restrict_by_lanes(true, 24, 256, 4), 106.0, 134.0);
+  point("restriction", 4, 3, restrict_by_lanes(false, 4, 256, 3), 68.0, 92.0);
+  point("restriction", 4, 8, restrict_by_lanes(false, 4, 256, 8), 169.0, 153.0);
+  point("restriction", 24, 3, restrict_by_lanes(false, 24, 256, 3), 261.0, 202.0);
   return fails ? 1 : 0;
 }
