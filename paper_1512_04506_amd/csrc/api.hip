@@ -549,10 +549,6 @@ struct Solver final : SolverBase {
     small_its.alloc<int>(2);
     HIPCK(hipMemsetAsync(small_its.get<int>(), 0, 2 * sizeof(int), st));
     u_nonzero.alloc<int>(maxr);
-    if (sap4_applies<S>(g) && c->p.max_rhs > g.ntv) {
-      sap_r.alloc<cx<T>>((size_t)c->p.max_rhs * fsz());
-      sap_f.alloc<cx<T>>((size_t)c->p.max_rhs * fsz());
-    }
   }
 
   // ------------------------------------------------------------ smoother
@@ -560,24 +556,9 @@ struct Solver final : SolverBase {
   // whatever it holds
   void sap(cx<T>* x, const cx<T>* y, int nrhs, int nu, bool x_zero = false) {
     if (sap4_applies<S>(g) && nu > 0) {
-      // the residual of every field and the faces of the last corrections: in
-      // setup workspace that is idle whenever the smoother runs and holds
-      // N_tv fields, or in buffers of their own for more rhs
-      const bool own = nrhs > g.ntv;
-      cx<T>* r = own ? sap_r.get<cx<T>>() : ws_Z.get<cx<T>>();
-      cx<T>* faces = own ? sap_f.get<cx<T>>() : ws_Wd.get<cx<T>>();
-      Sap4Args<T, S> a{x, nullptr, r, faces, gv, g, 0, 0, c->p.n_mr, nrhs, false, false, false};
-      const int phases = 2 * nu;
-      for (int ph = 0; ph < phases; ++ph) {
-        const bool first = ph < 2;  // of its colour
-        a.colour = ph & 1;
-        a.src = first ? y : r;
-        a.mode = first && !x_zero ? SAP4_FULL : (ph == 0 ? SAP4_SRC : SAP4_FACES);
-        a.x_zero = first && x_zero;
-        a.store_r = ph + 2 < phases;
-        a.store_faces = ph + 1 < phases && (x_zero || ph >= 1);
-        c->timed(DDAMG_KERNEL_SAP, nrhs, [&] { launch_sap4<T, S>(a, st); });
-      }
+      const int step = sap_rhs(nrhs);
+      for (int r0 = 0; r0 < nrhs; r0 += step)
+        sap4(x + (size_t)r0 * fsz(), y + (size_t)r0 * fsz(), std::min(step, nrhs - r0), nu, x_zero);
       return;
     }
     if (x_zero) HIPCK(hipMemsetAsync(x, 0, sizeof(cx<T>) * fsz() * nrhs, st));
@@ -585,7 +566,67 @@ struct Solver final : SolverBase {
       for (int col = 0; col < 2; ++col)
         c->timed(DDAMG_KERNEL_SAP, nrhs, [&] { launch_sap_phase<T, S>(x, y, gv, g, col, c->p.n_mr, nrhs, st); });
   }
+  // The carried residual of every field and the faces of the last corrections
+  // lie in setup workspace that is idle whenever the smoother runs and holds
+  // N_tv fields.  More rhs get buffers of their own (max_rhs fields each) at the
+  // first call that has them; where there is no memory for those, and in a
+  // graph capture that comes first, the rhs go in groups of N_tv.
   DevBuf sap_r, sap_f;
+  bool sap_in_groups = false;  // no memory for the buffers
+  bool sap_captured = false;   // a caller's graph may hold their addresses
+  // rhs of one pass of the smoother
+  int sap_rhs(int nrhs) {
+    if (nrhs <= g.ntv || sap_in_groups) return std::min(nrhs, g.ntv);
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (st && hipStreamIsCapturing(st, &cap) != hipSuccess) (void)hipGetLastError();
+    if (cap != hipStreamCaptureStatusNone) {
+      if (!sap_r.p) return g.ntv;
+      sap_captured = true;
+    }
+    if (sap_r.p) return nrhs;
+    try {
+      sap_f.alloc<cx<T>>((size_t)c->p.max_rhs * fsz());
+      sap_r.alloc<cx<T>>((size_t)c->p.max_rhs * fsz());
+    } catch (const Fail& e) {
+      if (e.code != DDAMG_ENOMEM) throw;
+      sap_f.release();
+      sap_in_groups = true;
+      return g.ntv;
+    }
+    return nrhs;
+  }
+  // f allocates what a solve cannot do without: if that fails, once more
+  // without the smoother's own buffers
+  template <typename F>
+  void need_memory(F&& f) {
+    try {
+      f();
+    } catch (const Fail& e) {
+      if (e.code != DDAMG_ENOMEM || !sap_r.p || sap_captured) throw;
+      c->sync();
+      sap_r.release();
+      sap_f.release();
+      sap_in_groups = true;
+      f();
+    }
+  }
+  void sap4(cx<T>* x, const cx<T>* y, int nrhs, int nu, bool x_zero) {
+    const bool own = nrhs > g.ntv;
+    cx<T>* r = own ? sap_r.get<cx<T>>() : ws_Z.get<cx<T>>();
+    cx<T>* faces = own ? sap_f.get<cx<T>>() : ws_Wd.get<cx<T>>();
+    Sap4Args<T, S> a{x, nullptr, r, faces, gv, g, 0, 0, c->p.n_mr, nrhs, false, false, false};
+    const int phases = 2 * nu;
+    for (int ph = 0; ph < phases; ++ph) {
+      const bool first = ph < 2;  // of its colour
+      a.colour = ph & 1;
+      a.src = first ? y : r;
+      a.mode = first && !x_zero ? SAP4_FULL : (ph == 0 ? SAP4_SRC : SAP4_FACES);
+      a.x_zero = first && x_zero;
+      a.store_r = ph + 2 < phases;
+      a.store_faces = ph + 1 < phases && (x_zero || ph >= 1);
+      c->timed(DDAMG_KERNEL_SAP, nrhs, [&] { launch_sap4<T, S>(a, st); });
+    }
+  }
 
   // -------------------------------------------------------- coarse solve
   // S v = D_oo v - D_oe D_ee^{-1} D_eo v on odd compact vectors
@@ -1046,7 +1087,7 @@ struct Solver final : SolverBase {
 
   int solve(double* u_canon, const double* f_canon, int nrhs, double tol) override {
     const int m = c->p.outer_restart;
-    ensure_outer(m, nrhs);
+    need_memory([&] { ensure_outer(m, nrhs); });
     const size_t n = fsz();
     const size_t vsj = (size_t)outer_r * n;  // stride between basis vectors
     cx<double>* V = oV.get<cx<double>>();
@@ -1131,7 +1172,7 @@ struct Solver final : SolverBase {
       gs_pending = false;
       int k = 0;
       for (; k < m && its < c->p.outer_maxit; ++k) {
-        grow_outer(k + 2);
+        need_memory([&] { grow_outer(k + 2); });
         V = oV.get<cx<double>>();
         Z = oZ.get<cx<T>>();
         cx<double>* vk = V + (size_t)k * vsj;
