@@ -1380,8 +1380,9 @@ struct ddamg_net {
     w.gam1.alloc<cx<float>>((size_t)cmax() * 12 * V);
     w.lagg.alloc<double>((size_t)2 * gl.nblocks);
     size_t pmax = 0;
-    for (int l = 0; l < nl(); ++l) pmax = std::max(pmax, (size_t)ch[l] * ch[l + 1] * NET_NFEAT);
-    w.part.alloc<cx<double>>((size_t)net_wgrad_chunks(gl) * pmax);
+    for (int l = 0; l < nl(); ++l)
+      pmax = std::max(pmax, (size_t)net_wgrad_chunks(ch[l], ch[l + 1], gl) * ch[l] * ch[l + 1] * NET_NFEAT);
+    w.part.alloc<cx<double>>(pmax);
   }
   void sync() { HIPCK(hipStreamSynchronize(st)); }
 

@@ -115,6 +115,28 @@ inline bool restrict_by_lanes(bool f32, int ntv, int vblock, int nrhs) {
   return nrhs <= (f32 ? 4 : 2) * (thin ? 2 : 1);
 }
 
+// Whether a layer of the network runs on the vector units, a lane per site and
+// four output channels, instead of the matrix cores (k_learn.hip).  The matrix
+// cores compute 4 input and 16 output channels at one price, so few
+// channels in either place leave them mostly idle; the lanes need some 8000 sites
+// to fill the chip with two or more input channels and repeat gate and
+// transport for every four outputs (us, matrix cores against lanes): 16^3x32, 1
+// to 1 channels 192/63, 4 to 4 270/195, 3 to 12 348/394, 16 to 2 770/553, 8 to
+// 8 493/546; 16^3x8, 4 to 4 86/81, 8 to 4 127/128; 8^3x16, 1 to 8 51/41, 4 to 4
+// 50/68.
+inline bool net_layer_thin(int cin, int cout, int V) {
+  const int lanes = cin * ((cout + 3) / 4), tiles = ((cin + 3) / 4) * ((cout + 15) / 16);
+  if (cin <= 4) return (cin == 1 || V >= (cin == 2 ? 8192 : 32768)) && lanes <= 8 * tiles;
+  return V >= 65536 && lanes <= 6 * tiles;
+}
+
+// The same for its weight gradients, tiles of 16 by 16 channels against a lane
+// per site, one input and two output channels: 16^3x32, 1 to 1 channels 970/266,
+// 8 to 8 1094/900, 12 to 8 1163/1261, 4 to 24 2328/1777, 8 to 24 2374/2903.
+inline bool net_wgrad_thin(int cin, int cout, int V) {
+  return V >= 65536 && cin * ((cout + 1) / 2) <= 32 * ((cin + 15) / 16) * ((cout + 15) / 16);
+}
+
 // Krylov workspace of GMRES(m) on vectors of n elements per rhs: the
 // widest multi-dot is the Gram-Schmidt of a new vector against all m + 1
 // basis vectors of a cycle; the norm of a coarse right-hand side runs over

@@ -391,7 +391,7 @@ void launch_net_layer(cx<float>* out, const cx<float>* in, const cx<float>* W, i
 // weights of the transposed layer (C_in x C_out) from W (C_out x C_in)
 void launch_net_transpose(cx<float>* Wb, const cx<float>* W, int cin, int cout, hipStream_t st);
 // chunks of the weight-gradient reduction; part needs chunks * cin * cout * 18 entries
-int net_wgrad_chunks(const Geom& g);
+int net_wgrad_chunks(int cin, int cout, const Geom& g);
 void launch_net_wgrad(cx<float>* grad, cx<double>* part, const cx<float>* in, bool gate_in, const cx<float>* gam,
                       int cin, int cout, const GaugeView<float>& gv, const Geom& g, hipStream_t st);
 // span loss (device *loss), per-aggregate terms loss_agg[2 nblocks] and its

@@ -15,6 +15,7 @@
 #include <algorithm>
 #include <cmath>
 
+#include "blas_sizes.h"
 #include "dirac_device.h"
 #include "mfma_device.h"
 
@@ -96,23 +97,25 @@ __device__ inline void mm_cp(mm_f4& re, mm_f4& im, int ph, cx<float> w, cx<float
     mm_c(re, im, w.i, nw.r, w.r, x);
 }
 
+// neighbour, boundary sign and link of hop (MU, FWD) at site p
+template <int MU, bool FWD>
+__device__ inline int hop_link(cx<float> U[3][3], float& sign, const SitePos& p, const Geom& g,
+                               const GaugeView<float>& gv, size_t V) {
+  const int sn = FWD ? nbr_fwd(g, p, MU) : nbr_bwd(g, p, MU);
+  const bool wrap = MU == 3 && (FWD ? p.lc[3] == g.bs[3] - 1 && p.bc[3] == g.NB[3] - 1 : p.lc[3] == 0 && p.bc[3] == 0);
+  sign = wrap ? -1.f : 1.f;
+  load_link<float, float>(U, gv, MU, FWD ? p.S : sn, V);
+  return sn;
+}
+
 // hop (MU, FWD) of every input channel for 16 sites and 16 output channels
 template <int MU, bool FWD, bool GATE>
 __device__ inline void layer_hop(mm_f4 re[12], mm_f4 im[12], const cx<float>* in, int cin, const cx<float>* Wi,
                                  const SitePos& p, const Geom& g, const GaugeView<float>& gv, size_t V, int lg) {
   constexpr SpinMap G = gamma_map<MU>();
   cx<float> U[3][3];
-  int sn;
   float sign;
-  if (FWD) {
-    sn = nbr_fwd(g, p, MU);
-    sign = MU == 3 && p.lc[3] == g.bs[3] - 1 && p.bc[3] == g.NB[3] - 1 ? -1.f : 1.f;
-    load_link<float, float>(U, gv, MU, p.S, V);
-  } else {
-    sn = nbr_bwd(g, p, MU);
-    sign = MU == 3 && p.lc[3] == 0 && p.bc[3] == 0 ? -1.f : 1.f;
-    load_link<float, float>(U, gv, MU, sn, V);
-  }
+  const int sn = hop_link<MU, FWD>(U, sign, p, g, gv, V);
   constexpr int k = 2 + 2 * (2 * MU + (FWD ? 0 : 1));
   for (int j0 = 0; j0 < cin; j0 += 4) {
     const int j = min(j0 + lg, cin - 1);
@@ -131,6 +134,25 @@ __device__ inline void layer_hop(mm_f4 re[12], mm_f4 im[12], const cx<float>* in
       }
   }
   asm volatile("" ::: "memory");
+}
+
+// o, the gradient with respect to the gate's output, becomes the one with
+// respect to the pre-gate value psi of channel plane f at site s:
+// psi -> psi g(n), n = |psi|^2 / 12, g = (1 + n)^(-1/2):
+// g o + (rho g'(n) / 6) psi with rho = Re <psi, o>, g' = -g^3 / 2
+__device__ inline void gate_backward(cx<float> o[12], const cx<float>* f, int s, size_t V) {
+  cx<float> ps[12];
+  float n = 0.f, rho = 0.f;
+#pragma unroll
+  for (int c = 0; c < 12; ++c) {
+    ps[c] = elem(f + (size_t)c * V, (unsigned)s);
+    n += ps[c].r * ps[c].r + ps[c].i * ps[c].i;
+    rho += ps[c].r * o[c].r + ps[c].i * o[c].i;
+  }
+  const float gg = 1.f / sqrtf(1.f + n * (1.f / 12.f));
+  const float cr = rho * (-0.5f * gg * gg * gg) * (1.f / 6.f);
+#pragma unroll
+  for (int c = 0; c < 12; ++c) o[c] = gg * o[c] + cr * ps[c];
 }
 
 // out[i] = sum_jk W[i][j][k] F_k(in_j) for 16 output channels (blockIdx.y).
@@ -218,27 +240,107 @@ __global__ __launch_bounds__(NTPB, 2) void net_layer_kernel(cx<float>* __restric
       re[c][v] += o.r;
       im[c][v] += o.i;
     }
-    float gg = 1.f, cr = 0.f;
-    cx<float> ps[12];
-    if (GATE_BWD) {
-      // gradient through psi -> psi g(n), n = |psi|^2 / 12, g = (1 + n)^(-1/2):
-      // g gam + (rho g'(n) / 6) psi with rho = Re <psi, gam>, g' = -g^3 / 2
-      float n = 0.f, rho = 0.f;
+    cx<float> o[12];
 #pragma unroll
-      for (int c = 0; c < 12; ++c) {
-        ps[c] = elem(pre + ((size_t)i * 12 + c) * V, (unsigned)s);
-        n += ps[c].r * ps[c].r + ps[c].i * ps[c].i;
-        rho += ps[c].r * re[c][v] + ps[c].i * im[c][v];
-      }
-      gg = 1.f / sqrtf(1.f + n * (1.f / 12.f));
-      cr = rho * (-0.5f * gg * gg * gg) * (1.f / 6.f);
+    for (int c = 0; c < 12; ++c) o[c] = mk(re[c][v], im[c][v]);
+    if (GATE_BWD) gate_backward(o, pre + (size_t)i * 12 * V, s, V);
+#pragma unroll
+    for (int c = 0; c < 12; ++c) out[((size_t)i * 12 + c) * V + s] = o[c];
+  }
+}
+
+// i^ph a
+__device__ inline cx<float> times_ip(int ph, cx<float> a) {
+  return ph == 0 ? a : ph == 1 ? times_i(a) : ph == 2 ? neg(a) : times_mi(a);
+}
+
+// hop (MU, FWD) of every input channel for a lane's site and OG output channels
+constexpr int OG = 4;
+template <int MU, bool FWD, bool GATE>
+__device__ inline void thin_hop(cx<float> acc[OG][12], const cx<float>* in, int cin, const cx<float>* const w[OG],
+                                const SitePos& p, const Geom& g, const GaugeView<float>& gv, size_t V) {
+  constexpr SpinMap G = gamma_map<MU>();
+  constexpr int k = 2 + 2 * (2 * MU + (FWD ? 0 : 1));
+  cx<float> U[3][3];
+  float sign;
+  const int sn = hop_link<MU, FWD>(U, sign, p, g, gv, V);
+  for (int j = 0; j < cin; ++j) {
+    cx<float> ph[4][3], t[4][3];
+    load_in<GATE>(ph, in + (size_t)j * 12 * V, sn, V, sign);
+    transport<FWD>(t, ph, U);
+#pragma unroll
+    for (int q = 0; q < OG; ++q) {
+      const cx<float> c = w[q][(size_t)j * NFEAT + k], d = w[q][(size_t)j * NFEAT + k + 1];
+#pragma unroll
+      for (int sp = 0; sp < 4; ++sp)
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+          acc[q][3 * sp + a] = cfma(d, times_ip(G.phase[sp], t[G.src[sp]][a]), cfma(c, t[sp][a], acc[q][3 * sp + a]));
     }
+  }
+  asm volatile("" ::: "memory");
+}
+
+// The same layer for few channels: a lane per site and four output channels
+// (blockIdx.y), which repeats loads, gate and transport for every four outputs
+// but computes no channels that are not there.  Bound: loads and transports.  1
+// to 1 channels on 16^3x32 63 us (192 on the matrix cores), 4 to 4 195 (270).
+template <bool GATE_IN, bool GATE_BWD>
+__global__ __launch_bounds__(NTPB, 2) void net_thin_layer_kernel(cx<float>* __restrict__ out,
+                                                                 const cx<float>* __restrict__ in,
+                                                                 const cx<float>* __restrict__ W, int cin, int cout,
+                                                                 GaugeView<float> gv, Geom g,
+                                                                 const cx<float>* __restrict__ pre) {
+  const int s = blockIdx.x * NTPB + threadIdx.x;
+  if (s >= g.V) return;
+  const int i0 = blockIdx.y * OG;
+  const size_t V = g.V;
+  const SitePos p = site_pos(g, s);
+  cx<float> acc[OG][12], half[OG][12];
+  const cx<float>* w[OG];  // weights of input channel 0
+#pragma unroll
+  for (int q = 0; q < OG; ++q) {
+    w[q] = W + (size_t)min(i0 + q, cout - 1) * cin * NFEAT;
+#pragma unroll
+    for (int c = 0; c < 12; ++c) acc[q][c] = mk(0.f, 0.f);
+  }
+  for (int j = 0; j < cin; ++j) {
+    cx<float> ph[4][3];
+    load_in<GATE_IN>(ph, in + (size_t)j * 12 * V, s, V, 1.f);
+    // a phi + b g5 phi, g5 = diag(-1, -1, +1, +1)
+#pragma unroll
+    for (int q = 0; q < OG; ++q) {
+      const cx<float> a = w[q][(size_t)j * NFEAT], b = w[q][(size_t)j * NFEAT + 1];
+      const cx<float> lo = a - b, hi = a + b;
+#pragma unroll
+      for (int c = 0; c < 12; ++c) acc[q][c] = cfma(c < 6 ? lo : hi, ph[c / 3][c % 3], acc[q][c]);
+    }
+  }
+  thin_hop<0, true, GATE_IN>(acc, in, cin, w, p, g, gv, V);
+  thin_hop<0, false, GATE_IN>(acc, in, cin, w, p, g, gv, V);
+  thin_hop<1, true, GATE_IN>(acc, in, cin, w, p, g, gv, V);
+  thin_hop<1, false, GATE_IN>(acc, in, cin, w, p, g, gv, V);
+  // two chains of half the length, as above
+#pragma unroll
+  for (int q = 0; q < OG; ++q)
 #pragma unroll
     for (int c = 0; c < 12; ++c) {
-      cx<float> o = mk(re[c][v], im[c][v]);
-      if (GATE_BWD) o = gg * o + cr * ps[c];
-      out[((size_t)i * 12 + c) * V + s] = o;
+      half[q][c] = acc[q][c];
+      acc[q][c] = mk(0.f, 0.f);
     }
+  thin_hop<2, true, GATE_IN>(acc, in, cin, w, p, g, gv, V);
+  thin_hop<2, false, GATE_IN>(acc, in, cin, w, p, g, gv, V);
+  thin_hop<3, true, GATE_IN>(acc, in, cin, w, p, g, gv, V);
+  thin_hop<3, false, GATE_IN>(acc, in, cin, w, p, g, gv, V);
+#pragma unroll
+  for (int q = 0; q < OG; ++q) {
+    const int i = i0 + q;
+    if (i >= cout) break;
+#pragma unroll
+    for (int c = 0; c < 12; ++c) acc[q][c] = acc[q][c] + half[q][c];
+    if (GATE_BWD) gate_backward(acc[q], pre + (size_t)i * 12 * V, s, V);
+#pragma unroll
+    for (int c = 0; c < 12; ++c) out[((size_t)i * 12 + c) * V + s] = acc[q][c];
   }
 }
 
@@ -300,17 +402,7 @@ __device__ inline void wgrad_job(cx<double>* __restrict__ part, const cx<float>*
     cx<float> U[3][3];
     int sn = s;
     float sign = 1.f;
-    if constexpr (!SELF) {
-      if (FWD) {
-        sn = nbr_fwd(g, p, MU);
-        if (MU == 3 && p.lc[3] == g.bs[3] - 1 && p.bc[3] == g.NB[3] - 1) sign = -1.f;
-        load_link<float, float>(U, gv, MU, s, V);
-      } else {
-        sn = nbr_bwd(g, p, MU);
-        if (MU == 3 && p.lc[3] == 0 && p.bc[3] == 0) sign = -1.f;
-        load_link<float, float>(U, gv, MU, sn, V);
-      }
-    }
+    if constexpr (!SELF) sn = hop_link<MU, FWD>(U, sign, p, g, gv, V);
     float sc[4];  // sign and gate of channel 4 jj + lg at sn
 #pragma unroll
     for (int jj = 0; jj < 4; ++jj) {
@@ -439,6 +531,101 @@ __global__ __launch_bounds__(NTPB, 2) void net_wgrad_kernel(cx<double>* __restri
     case 6: wgrad_job<6, GATE>(part, ij, gam, cl, cout, gv, g, jb, cin, ib, smem); break;
     case 7: wgrad_job<7, GATE>(part, ij, gam, cl, cout, gv, g, jb, cin, ib, smem); break;
     default: wgrad_job<8, GATE>(part, ij, gam, cl, cout, gv, g, jb, cin, ib, smem); break;
+  }
+}
+
+// <t, gam> and <g_mu t, gam> of both hops of direction MU, added to acc
+template <int MU, bool FWD, bool GATE>
+__device__ inline void thin_wgrad_hop(cx<float> acc[2][NFEAT], const cx<float>* f, const cx<float> gm[2][12],
+                                      const SitePos& p, const Geom& g, const GaugeView<float>& gv, size_t V) {
+  constexpr SpinMap G = gamma_map<MU>();
+  constexpr int k = 2 + 2 * (2 * MU + (FWD ? 0 : 1));
+  cx<float> U[3][3], ph[4][3], t[4][3];
+  float sign;
+  const int sn = hop_link<MU, FWD>(U, sign, p, g, gv, V);
+  load_in<GATE>(ph, f, sn, V, sign);
+  transport<FWD>(t, ph, U);
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    cx<float> a = mk(0.f, 0.f), b = mk(0.f, 0.f);
+#pragma unroll
+    for (int c = 0; c < 12; ++c) {
+      a = cfmac(t[c / 3][c % 3], gm[q][c], a);
+      b = cfmac(times_ip(G.phase[c / 3], t[G.src[c / 3]][c % 3]), gm[q][c], b);
+    }
+    acc[q][k] = acc[q][k] + a;
+    acc[q][k + 1] = acc[q][k + 1] + b;
+  }
+  asm volatile("" ::: "memory");
+}
+
+// The same for few channels: a lane per site, one input and two output
+// channels (blockIdx.y), all features; at most 16 sites per lane in FP32,
+// then FP64.  Bound: loads and transports, repeated for every two outputs.  The
+// backward pass of a layer of 1 to 1 channels on 16^3x32 266 us (970 on the matrix
+// cores), 4 to 4 354 (1013).
+template <bool GATE>
+__global__ __launch_bounds__(NTPB) void net_thin_wgrad_kernel(cx<double>* __restrict__ part,
+                                                              const cx<float>* __restrict__ in,
+                                                              const cx<float>* __restrict__ gam, int cin, int cout,
+                                                              GaugeView<float> gv, Geom g) {
+  __shared__ cx<double> red[NTPB / 64][2 * NFEAT];
+  const int ngroup = (cout + 1) / 2, j = blockIdx.y / ngroup, i0 = 2 * (blockIdx.y % ngroup);
+  const size_t V = g.V;
+  const cx<float>* f = in + (size_t)j * 12 * V;
+  cx<float> acc[2][NFEAT];
+#pragma unroll
+  for (int q = 0; q < 2; ++q)
+#pragma unroll
+    for (int k = 0; k < NFEAT; ++k) acc[q][k] = mk(0.f, 0.f);
+  for (int s = blockIdx.x * NTPB + threadIdx.x; s < g.V; s += gridDim.x * NTPB) {
+    const SitePos p = site_pos(g, s);
+    cx<float> gm[2][12], ph[4][3];
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int c = 0; c < 12; ++c) gm[q][c] = elem(gam + ((size_t)min(i0 + q, cout - 1) * 12 + c) * V, (unsigned)s);
+    load_in<GATE>(ph, f, s, V, 1.f);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      cx<float> lo = mk(0.f, 0.f), hi = mk(0.f, 0.f);  // spins 0, 1 and 2, 3
+#pragma unroll
+      for (int c = 0; c < 6; ++c) {
+        lo = cfmac(ph[c / 3][c % 3], gm[q][c], lo);
+        hi = cfmac(ph[2 + c / 3][c % 3], gm[q][6 + c], hi);
+      }
+      acc[q][0] = acc[q][0] + (hi + lo);
+      acc[q][1] = acc[q][1] + (hi - lo);
+    }
+    thin_wgrad_hop<0, true, GATE>(acc, f, gm, p, g, gv, V);
+    thin_wgrad_hop<0, false, GATE>(acc, f, gm, p, g, gv, V);
+    thin_wgrad_hop<1, true, GATE>(acc, f, gm, p, g, gv, V);
+    thin_wgrad_hop<1, false, GATE>(acc, f, gm, p, g, gv, V);
+    thin_wgrad_hop<2, true, GATE>(acc, f, gm, p, g, gv, V);
+    thin_wgrad_hop<2, false, GATE>(acc, f, gm, p, g, gv, V);
+    thin_wgrad_hop<3, true, GATE>(acc, f, gm, p, g, gv, V);
+    thin_wgrad_hop<3, false, GATE>(acc, f, gm, p, g, gv, V);
+  }
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+#pragma unroll
+  for (int q = 0; q < 2; ++q)
+#pragma unroll
+    for (int k = 0; k < NFEAT; ++k) {
+      double re = acc[q][k].r, im = acc[q][k].i;
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) {
+        re += __shfl_xor(re, o, 64);
+        im += __shfl_xor(im, o, 64);
+      }
+      if (lane == 0) red[w][q * NFEAT + k] = mk(re, im);
+    }
+  __syncthreads();
+  for (int e = threadIdx.x; e < 2 * NFEAT; e += NTPB) {
+    const int q = e / NFEAT, k = e % NFEAT;
+    if (i0 + q >= cout) continue;
+    cx<double> sum = red[0][e];
+    for (int x = 1; x < NTPB / 64; ++x) sum = sum + red[x][e];
+    part[(((size_t)blockIdx.x * cout + i0 + q) * cin + j) * NFEAT + k] = sum;
   }
 }
 
@@ -747,13 +934,15 @@ inline unsigned cdiv(size_t a, size_t b) { return (unsigned)((a + b - 1) / b); }
 
 void launch_net_layer(cx<float>* out, const cx<float>* in, const cx<float>* W, int cin, int cout, bool gate_in,
                       const cx<float>* gate_bwd_pre, const GaugeView<float>& gv, const Geom& g, hipStream_t st) {
-  const dim3 grid(cdiv(g.V, 16 * (NTPB / 64)), cdiv(cout, 16));
+  const bool thin = net_layer_thin(cin, cout, g.V);
+  const dim3 grid(thin ? cdiv(g.V, NTPB) : cdiv(g.V, 16 * (NTPB / 64)), cdiv(cout, thin ? OG : 16));
+  auto go = [&](auto kernel) { kernel<<<grid, NTPB, 0, st>>>(out, in, W, cin, cout, gv, g, gate_bwd_pre); };
   if (gate_bwd_pre)
-    net_layer_kernel<false, true><<<grid, NTPB, 0, st>>>(out, in, W, cin, cout, gv, g, gate_bwd_pre);
+    go(thin ? net_thin_layer_kernel<false, true> : net_layer_kernel<false, true>);
   else if (gate_in)
-    net_layer_kernel<true, false><<<grid, NTPB, 0, st>>>(out, in, W, cin, cout, gv, g, nullptr);
+    go(thin ? net_thin_layer_kernel<true, false> : net_layer_kernel<true, false>);
   else
-    net_layer_kernel<false, false><<<grid, NTPB, 0, st>>>(out, in, W, cin, cout, gv, g, nullptr);
+    go(thin ? net_thin_layer_kernel<false, false> : net_layer_kernel<false, false>);
 }
 
 void launch_net_transpose(cx<float>* Wb, const cx<float>* W, int cin, int cout, hipStream_t st) {
@@ -762,17 +951,26 @@ void launch_net_transpose(cx<float>* Wb, const cx<float>* W, int cin, int cout, 
 }
 
 // chunks of the weight gradients: with the nine jobs some 600 workgroups on
-// lattices from 16^4 up, and at least eight units of 16 sites per wave
-int net_wgrad_chunks(const Geom& g) { return std::max(1, std::min(64, g.V / 512)); }
+// lattices from 16^4 up, and at least eight units of 16 sites per wave; for few
+// channels 256 workgroups or 16 sites per lane, whichever is more
+int net_wgrad_chunks(int cin, int cout, const Geom& g) {
+  if (net_wgrad_thin(cin, cout, g.V)) {
+    const int jobs = cin * (int)cdiv(cout, 2);
+    return std::max((int)cdiv(g.V, 16 * NTPB), std::min((int)cdiv(g.V, NTPB), 256 / jobs));
+  }
+  return std::max(1, std::min(64, g.V / 512));
+}
 
 void launch_net_wgrad(cx<float>* grad, cx<double>* part, const cx<float>* in, bool gate_in, const cx<float>* gam,
                       int cin, int cout, const GaugeView<float>& gv, const Geom& g, hipStream_t st) {
-  const int nchunk = net_wgrad_chunks(g);
-  const dim3 grid(nchunk, 9, cdiv(cin, 16) * cdiv(cout, 16));
+  const int nchunk = net_wgrad_chunks(cin, cout, g);
+  const bool thin = net_wgrad_thin(cin, cout, g.V);
+  const dim3 grid(nchunk, thin ? cin * cdiv(cout, 2) : 9, thin ? 1 : cdiv(cin, 16) * cdiv(cout, 16));
+  auto go = [&](auto kernel) { kernel<<<grid, NTPB, 0, st>>>(part, in, gam, cin, cout, gv, g); };
   if (gate_in)
-    net_wgrad_kernel<true><<<grid, NTPB, 0, st>>>(part, in, gam, cin, cout, gv, g);
+    go(thin ? net_thin_wgrad_kernel<true> : net_wgrad_kernel<true>);
   else
-    net_wgrad_kernel<false><<<grid, NTPB, 0, st>>>(part, in, gam, cin, cout, gv, g);
+    go(thin ? net_thin_wgrad_kernel<false> : net_wgrad_kernel<false>);
   const size_t n = (size_t)cout * cin * NFEAT;
   net_wgrad_final_kernel<<<cdiv(n, 256), 256, 0, st>>>(grad, part, n, nchunk);
 }

@@ -89,5 +89,17 @@ int main() {
   point("restriction", 4, 3, restrict_by_lanes(false, 4, 256, 3), 68.0, 92.0);
   point("restriction", 4, 8, restrict_by_lanes(false, 4, 256, 8), 169.0, 153.0);
   point("restriction", 24, 3, restrict_by_lanes(false, 24, 256, 3), 261.0, 202.0);
+  // network layers on the vector units, on the matrix cores
+  const struct {
+    int cin, cout, V;
+    double lanes, cores;
+  } layer[] = {{1, 1, 8192, 35, 43},     {4, 4, 8192, 68, 50},      {2, 12, 8192, 54, 58},     {4, 4, 32768, 81, 86},
+               {8, 4, 32768, 128, 127},  {12, 1, 32768, 172, 158},  {1, 1, 131072, 63, 192},   {4, 4, 131072, 195, 270},
+               {3, 12, 131072, 394, 348}, {16, 2, 131072, 553, 770}, {8, 8, 131072, 546, 493},  {16, 16, 131072, 1760, 958},
+               {2, 24, 131072, 559, 609}, {4, 24, 131072, 865, 641}},
+    wgrad[] = {{1, 1, 131072, 266, 970},     {8, 8, 131072, 900, 1094},  {12, 8, 131072, 1261, 1163},
+               {4, 24, 131072, 1777, 2328}, {8, 24, 131072, 2903, 2374}, {16, 16, 131072, 3147, 1393}};
+  for (const auto& x : layer) point("network layer", x.cin, x.cout, net_layer_thin(x.cin, x.cout, x.V), x.lanes, x.cores);
+  for (const auto& x : wgrad) point("weight gradient", x.cin, x.cout, net_wgrad_thin(x.cin, x.cout, x.V), x.lanes, x.cores);
   return fails ? 1 : 0;
 }
