@@ -855,7 +855,7 @@ struct Solver final : SolverBase {
     for (int hp = 0; hp < 2; ++hp) {
       cx<T>* out = D + (size_t)(hp * g.ntv) * nc;  // slot 0, columns of chirality hp
       c->timed(DDAMG_KERNEL_SETUP_GALERKIN, g.ntv, [&] {
-        launch_dslash<T, T, T, T>(Zp, Wtp, gva, g, g.ntv, DS_BLOCK, 0, hp, fsz(), fsz(), st);
+        launch_dslash<T, T, T, T>(Zp, Wtp, gva, g, g.ntv, DS_BLOCK, hp, fsz(), fsz(), st);
         launch_restrict<T, S>(out, nc, 9 * nn, Zp, fsz(), bv(), g, g.ntv, st);
       });
     }
@@ -1139,7 +1139,7 @@ struct Solver final : SolverBase {
       const cx<double>* res = u_zero && its == 0 ? f : V;
       if (res == V) {
         c->timed(DDAMG_KERNEL_RESIDUAL, nrhs,
-                 [&] { launch_dslash<double, double, double, double>(w, u, g64, g, nrhs, DS_FULL, 0, -1, n, n, st); });
+                 [&] { launch_dslash<double, double, double, double>(w, u, g64, g, nrhs, DS_FULL, -1, n, n, st); });
         launch_sub<double>(V, n, f, n, w, n, n, nrhs, st);
         need_part(launch_mdot<double>(ok.n2.get<cx<double>>(), 1, ok.part.get<cx<double>>(), ok.part_cap, V, 0, n, 1, V,
                                       n, n, nrhs, nullptr, st),
@@ -1164,7 +1164,7 @@ struct Solver final : SolverBase {
       if (its >= c->p.outer_maxit) break;
       launch_arnoldi_start(ok.st, ok.n2.get<cx<double>>(), 1, nrhs, st);
       // V-cycle input: in FP32 a copy written with each new basis vector (or
-      // with the w' that stands for it, see cgs2), in FP64 slot k itself
+      // with the w' that stands for it, see outer_arnoldi), in FP64 slot k itself
       constexpr bool f32 = std::is_same<T, float>::value;
       cx<float>* v32 = nullptr;
       if constexpr (f32) v32 = fy.get<cx<float>>();
@@ -1186,9 +1186,9 @@ struct Solver final : SolverBase {
         cx<double>* wk = V + (size_t)(k + 1) * vsj;
         c->timed(DDAMG_KERNEL_DSLASH, nrhs, [&] {
           if constexpr (std::is_same<T, double>::value)
-            launch_dslash<double, double, double, double>(wk, zk, g64, g, nrhs, DS_FULL, 0, -1, n, n, st);
+            launch_dslash<double, double, double, double>(wk, zk, g64, g, nrhs, DS_FULL, -1, n, n, st);
           else
-            launch_dslash<float, double, double, double>(wk, zk, g64, g, nrhs, DS_FULL, 0, -1, n, n, st);
+            launch_dslash<float, double, double, double>(wk, zk, g64, g, nrhs, DS_FULL, -1, n, n, st);
         });
         c->timed(DDAMG_KERNEL_OUTER_GS, nrhs, [&] { outer_arnoldi(V, vsj, k, nrhs, v32); });
         ++its;
@@ -1815,15 +1815,15 @@ int dirac_apply_internal(ddamg_ctx* c, void* out, const void* in, int nrhs, int 
   switch (prec) {
     case DDAMG_FP64:
       launch_dslash<double, double, double, double>(static_cast<cx<double>*>(out), static_cast<const cx<double>*>(in),
-                                                    c->gv64(), g, nrhs, DS_FULL, 0, -1, n, n, c->st);
+                                                    c->gv64(), g, nrhs, DS_FULL, -1, n, n, c->st);
       break;
     case DDAMG_FP32:
       launch_dslash<float, float, float, float>(static_cast<cx<float>*>(out), static_cast<const cx<float>*>(in),
-                                                c->gv32(), g, nrhs, DS_FULL, 0, -1, n, n, c->st);
+                                                c->gv32(), g, nrhs, DS_FULL, -1, n, n, c->st);
       break;
     case DDAMG_MIXED16:
       launch_dslash<float, float, __half, float>(static_cast<cx<float>*>(out), static_cast<const cx<float>*>(in),
-                                                 c->gvh(), g, nrhs, DS_FULL, 0, -1, n, n, c->st);
+                                                 c->gvh(), g, nrhs, DS_FULL, -1, n, n, c->st);
       break;
     default:
       c->err = "unknown precision";

@@ -239,7 +239,7 @@ struct CoarseView {
 };
 
 // dslash variants
-enum { DS_FULL = 0, DS_BLOCK = 1, DS_CROSS_FWD = 2, DS_CROSS_BWD = 3 };
+enum { DS_FULL = 0, DS_BLOCK = 1 };
 
 // ---------------------------------------------------------------- launchers
 // fields
@@ -261,13 +261,11 @@ void launch_clover_export(cx<double>* out, const cx<double>* A, const Geom& g, h
 template <typename T>
 void launch_gaussian_fields(cx<T>* out, const Geom& g, int n, uint64_t seed, hipStream_t st);
 
-// dslash: out[r] = piece of D applied to in[r] (chi_in >= 0 keeps only that
-// chirality of the input; mu selects the direction of the cross variants).
-// The cross variants write only the block layer they reach (lc[mu] = bs - 1
-// forward, 0 backward); out keeps its values on every other site.
+// dslash: out[r] = D or its block operator B applied to in[r] (B: chi_in >= 0
+// keeps only that chirality of the input)
 template <typename Tin, typename Tout, typename S, typename Tc>
 void launch_dslash(cx<Tout>* out, const cx<Tin>* in, const GaugeView<S>& gv, const Geom& g, int nrhs, int mode,
-                   int mu, int chi_in, size_t in_rstride, size_t out_rstride, hipStream_t st);
+                   int chi_in, size_t in_rstride, size_t out_rstride, hipStream_t st);
 
 // out = D in on canonical fields (complex128 [rhs][site][4][3], not
 // overlapping), links and clover in storage S, arithmetic in Tc

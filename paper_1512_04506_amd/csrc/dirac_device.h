@@ -70,17 +70,12 @@ __device__ inline void reconstruct(cx<T> acc[4][3], const Half2<T>& u, T coef) {
   }
 }
 
-template <typename Tin, typename Tc, bool CHI = true>
-__device__ inline void load_spinor(cx<Tc> p[4][3], const cx<Tin>* in, int s, size_t V, int chi_in, Tc sign) {
+template <typename T>
+__device__ inline void load_spinor(cx<T> p[4][3], const cx<T>* in, int s, size_t V, T sign) {
 #pragma unroll
-  for (int sp = 0; sp < 4; ++sp) {
-    const bool keep = !CHI || chi_in < 0 || (sp >> 1) == chi_in;
+  for (int sp = 0; sp < 4; ++sp)
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      cx<Tc> v = cvt<Tc>(elem(in + (size_t)(3 * sp + c) * V, (unsigned)s));
-      p[sp][c] = keep ? sign * v : mk((Tc)0, (Tc)0);
-    }
-  }
+    for (int c = 0; c < 3; ++c) p[sp][c] = sign * elem(in + (size_t)(3 * sp + c) * V, (unsigned)s);
 }
 
 // link entries as stored (FP16: without the per-site scale, which the hop
@@ -91,28 +86,6 @@ __device__ inline void load_link(cx<Tc> u[3][3], const GaugeView<S>& gv, int mu,
   for (int a = 0; a < 3; ++a)
 #pragma unroll
     for (int b = 0; b < 3; ++b) u[a][b] = ldc<Tc>(gv.U + (size_t)(mu * 9 + 3 * a + b) * V, (unsigned)s);
-}
-
-// acc += -1/2 (1 -+ g_mu) [U_mu(slink) or U_mu(slink)^dag] p
-template <int MU, bool FWD, typename Tc, typename S>
-__device__ inline void hop_spinor(cx<Tc> acc[4][3], const cx<Tc> p[4][3], const GaugeView<S>& gv, int slink,
-                                  size_t V) {
-  Half2<Tc> h, u;
-  project<MU, FWD, Tc>(h, p);
-  cx<Tc> U[3][3];
-  load_link<Tc, S>(U, gv, MU, slink, V);
-  Tc coef = (Tc)-0.5;
-  if constexpr (is_half<S>()) coef *= (Tc)gv.Usc[slink];
-#pragma unroll
-  for (int sp = 0; sp < 2; ++sp)
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      cx<Tc> t = mk((Tc)0, (Tc)0);
-#pragma unroll
-      for (int b = 0; b < 3; ++b) t = FWD ? cfma(U[a][b], h.h[sp][b], t) : cfmac(U[b][a], h.h[sp][b], t);
-      u.h[sp][a] = t;
-    }
-  reconstruct<MU, FWD, Tc>(acc, u, coef);
 }
 
 // acc[r] += coef (1 -+ g_mu) [U or U^dag] p[r] for NR spinors and a link
@@ -146,47 +119,6 @@ __device__ inline void hop_spinor_multi(cx<Tc> acc[NR][4][3], const cx<Tc> p[NR]
   Tc coef = (Tc)-0.5;
   if constexpr (is_half<S>()) coef *= (Tc)gv.Usc[slink];
   hop_spinor_multi_u<MU, FWD, NR, Tc>(acc, p, U, coef);
-}
-
-template <int MU, bool FWD, typename Tin, typename Tc, typename S, bool CHI>
-__device__ inline void hop(cx<Tc> acc[4][3], const cx<Tin>* in, const GaugeView<S>& gv, int sn, int slink, size_t V,
-                           int chi_in, Tc sign) {
-  cx<Tc> p[4][3];
-  load_spinor<Tin, Tc, CHI>(p, in, sn, V, chi_in, sign);
-  hop_spinor<MU, FWD, Tc, S>(acc, p, gv, slink, V);
-}
-
-// acc += A(x) psi(x) for the two chirality blocks
-template <typename Tc, typename S>
-__device__ inline void clover_apply(cx<Tc> acc[4][3], const cx<Tc> p[4][3], const GaugeView<S>& gv, int s, size_t V) {
-  Tc sc = (Tc)1;
-  if constexpr (is_half<S>()) sc = (Tc)gv.Asc[s];
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const stc_t<S>* Ah = gv.A + (size_t)h * CLOVER_PAIRS * V;
-    cx<Tc> v[6];
-#pragma unroll
-    for (int k = 0; k < 6; ++k) v[k] = p[2 * h + k / 3][k % 3];
-    cx<Tc> o[6];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      const cx<Tc> d = ldc<Tc>(Ah + (size_t)k * V, (unsigned)s);
-      o[2 * k] = d.r * v[2 * k];
-      o[2 * k + 1] = d.i * v[2 * k + 1];
-    }
-    int q = 0;
-#pragma unroll
-    for (int i = 0; i < 6; ++i)
-#pragma unroll
-      for (int j = i + 1; j < 6; ++j) {
-        const cx<Tc> a = ldc<Tc>(Ah + (size_t)(3 + q) * V, (unsigned)s);
-        o[i] = cfma(a, v[j], o[i]);
-        o[j] = cfmac(a, v[i], o[j]);
-        ++q;
-      }
-#pragma unroll
-    for (int k = 0; k < 6; ++k) acc[2 * h + k / 3][k % 3] = acc[2 * h + k / 3][k % 3] + sc * o[k];
-  }
 }
 
 // acc[r] += sc A_h p[r] on chirality h for NR spinors, the 18 stored pairs
@@ -263,57 +195,6 @@ __device__ inline int nbr_bwd(const Geom& g, const SitePos& p, int mu) {
   int bc[4] = {p.bc[0], p.bc[1], p.bc[2], p.bc[3]};
   bc[mu] = bc[mu] == 0 ? g.NB[mu] - 1 : bc[mu] - 1;
   return block_to_int(g, bc) * g.vblock + p.l + (g.bs[mu] - 1) * g.lstr[mu];
-}
-
-// hops of direction MU selected by MODE: all (full D), inside the block
-// (block operator B), or the block-crossing forward / backward hops of
-// direction mu_sel.  A hop across the time boundary carries the factor -1.
-template <int MU, typename Tin, typename Tc, typename S, int MODE>
-__device__ inline void hops_mu(cx<Tc> acc[4][3], const cx<Tin>* in, const GaugeView<S>& gv, const Geom& g,
-                               const SitePos& p, int mu_sel, int chi_in) {
-  const size_t V = g.V;
-  const int l = p.lc[MU];
-  bool do_f, do_b;
-  if (MODE == DS_FULL) {
-    // true at run time; being opaque to the compiler it keeps each hop in
-    // its own branch, so its loads are issued with its arithmetic instead of
-    // all being hoisted to the top of the kernel
-    do_f = do_b = g.V > 0;
-  } else if (MODE == DS_BLOCK) {
-    do_f = l != g.bs[MU] - 1;
-    do_b = l != 0;
-  } else if (MODE == DS_CROSS_FWD) {
-    do_f = MU == mu_sel && l == g.bs[MU] - 1;
-    do_b = false;
-  } else {
-    do_f = false;
-    do_b = MU == mu_sel && l == 0;
-  }
-  if (do_f) {
-    const bool wrap = MU == 3 && l == g.bs[3] - 1 && p.bc[3] == g.NB[3] - 1;
-    hop<MU, true, Tin, Tc, S, MODE != DS_FULL>(acc, in, gv, nbr_fwd(g, p, MU), p.S, V, chi_in, wrap ? (Tc)-1 : (Tc)1);
-  }
-  if (do_b) {
-    const bool wrap = MU == 3 && l == 0 && p.bc[3] == 0;
-    const int sb = nbr_bwd(g, p, MU);
-    hop<MU, false, Tin, Tc, S, MODE != DS_FULL>(acc, in, gv, sb, sb, V, chi_in, wrap ? (Tc)-1 : (Tc)1);
-  }
-}
-
-// All four directions, one after the other.  The empty asm statements with a
-// memory clobber keep the compiler from hoisting the loads of later
-// directions above the arithmetic of earlier ones, which would keep all
-// eight neighbours live at once and overflow the register file.
-template <typename Tin, typename Tc, typename S, int MODE>
-__device__ inline void hops_all(cx<Tc> acc[4][3], const cx<Tin>* in, const GaugeView<S>& gv, const Geom& g,
-                                const SitePos& p, int mu_sel, int chi_in) {
-  hops_mu<0, Tin, Tc, S, MODE>(acc, in, gv, g, p, mu_sel, chi_in);
-  asm volatile("" ::: "memory");
-  hops_mu<1, Tin, Tc, S, MODE>(acc, in, gv, g, p, mu_sel, chi_in);
-  asm volatile("" ::: "memory");
-  hops_mu<2, Tin, Tc, S, MODE>(acc, in, gv, g, p, mu_sel, chi_in);
-  asm volatile("" ::: "memory");
-  hops_mu<3, Tin, Tc, S, MODE>(acc, in, gv, g, p, mu_sel, chi_in);
 }
 
 }  // namespace dev

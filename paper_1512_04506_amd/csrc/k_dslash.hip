@@ -118,25 +118,19 @@ __device__ inline void clover_group(cx<Tc> acc[NR][4][3], const cx<Tin>* in, siz
   }
 }
 
-// the hops of direction MU that MODE selects (see hops_mu in dirac_device.h);
-// a hop across the time boundary carries the factor -1
+// the hops of direction MU that MODE selects: all, or inside the block.  A hop
+// across the time boundary carries the factor -1
 template <int MU, int MODE, int NR, typename Tin, typename Tc, typename S>
 __device__ inline void hops_group_mu(cx<Tc> acc[NR][4][3], const cx<Tin>* in, size_t rs, int nr,
-                                     const GaugeView<S>& gv, const Geom& g, const SitePos& p, int mu_sel, int chi) {
+                                     const GaugeView<S>& gv, const Geom& g, const SitePos& p, int chi) {
   const size_t V = g.V;
   const int l = p.lc[MU];
   bool do_f, do_b;
   if (MODE == DS_FULL) {
     do_f = do_b = g.V > 0;  // opaque: keeps every hop in its own branch
-  } else if (MODE == DS_BLOCK) {
+  } else {
     do_f = l != g.bs[MU] - 1;
     do_b = l != 0;
-  } else if (MODE == DS_CROSS_FWD) {
-    do_f = MU == mu_sel && l == g.bs[MU] - 1;
-    do_b = false;
-  } else {
-    do_f = false;
-    do_b = MU == mu_sel && l == 0;
   }
   if (do_f) {
     const bool wrap = MU == 3 && l == g.bs[3] - 1 && p.bc[3] == g.NB[3] - 1;
@@ -151,7 +145,7 @@ __device__ inline void hops_group_mu(cx<Tc> acc[NR][4][3], const cx<Tin>* in, si
 
 template <typename Tin, typename Tout, typename S, typename Tc, int MODE, int NR>
 __global__ __launch_bounds__(TPB) void dslash_kernel(cx<Tout>* __restrict__ out, const cx<Tin>* __restrict__ in,
-                                                     GaugeView<S> gv, Geom g, int mu_sel, int chi_in, size_t in_rs,
+                                                     GaugeView<S> gv, Geom g, int chi_in, size_t in_rs,
                                                      size_t out_rs, int nrhs) {
   // workgroup = (run of 256 sites, group of NR rhs) with the group fastest,
   // so the workgroups that read the same links and clover run side by side
@@ -161,20 +155,14 @@ __global__ __launch_bounds__(TPB) void dslash_kernel(cx<Tout>* __restrict__ out,
   const int r0 = (wl % ngroup) * NR;
   const int nr = min(NR, nrhs - r0);
   const int ls = (wl / ngroup) * blockDim.x + threadIdx.x;  // lexicographic-block order
-  // the block-crossing pieces only touch one layer of every block: one
-  // thread per site of that layer (the output elsewhere is left alone)
-  constexpr bool CROSS = MODE == DS_CROSS_FWD || MODE == DS_CROSS_BWD;
-  const int per_block = CROSS ? g.vblock / g.bs[mu_sel] : g.vblock;
-  if (ls >= g.nblocks * per_block) return;
-  const int bl = ls / per_block;
-  const int lo = ls - bl * per_block;
+  if (ls >= g.V) return;
+  const int bl = ls / g.vblock;
   int bc[4];
   bc[0] = bl % g.NB[0];
   bc[1] = (bl / g.NB[0]) % g.NB[1];
   bc[2] = (bl / (g.NB[0] * g.NB[1])) % g.NB[2];
   bc[3] = bl / (g.NB[0] * g.NB[1] * g.NB[2]);
-  const int s = block_to_int(g, bc) * g.vblock +
-                (CROSS ? face_site(g, mu_sel, MODE == DS_CROSS_FWD ? g.bs[mu_sel] - 1 : 0, lo) : lo);
+  const int s = block_to_int(g, bc) * g.vblock + ls - bl * g.vblock;
   const cx<Tin>* ip = in + (size_t)r0 * in_rs;
   cx<Tout>* op = out + (size_t)r0 * out_rs;
   const size_t V = g.V;
@@ -188,14 +176,14 @@ __global__ __launch_bounds__(TPB) void dslash_kernel(cx<Tout>* __restrict__ out,
     for (int sp = 0; sp < 4; ++sp)
 #pragma unroll
       for (int k = 0; k < 3; ++k) acc[r][sp][k] = mk((Tc)0, (Tc)0);
-  if (MODE == DS_FULL || MODE == DS_BLOCK) clover_group<NR, Tin, Tc, S>(acc, ip, in_rs, nr, gv, s, V, chi);
-  hops_group_mu<0, MODE, NR, Tin, Tc, S>(acc, ip, in_rs, nr, gv, g, pos, mu_sel, chi);
+  clover_group<NR, Tin, Tc, S>(acc, ip, in_rs, nr, gv, s, V, chi);
+  hops_group_mu<0, MODE, NR, Tin, Tc, S>(acc, ip, in_rs, nr, gv, g, pos, chi);
   asm volatile("" ::: "memory");
-  hops_group_mu<1, MODE, NR, Tin, Tc, S>(acc, ip, in_rs, nr, gv, g, pos, mu_sel, chi);
+  hops_group_mu<1, MODE, NR, Tin, Tc, S>(acc, ip, in_rs, nr, gv, g, pos, chi);
   asm volatile("" ::: "memory");
-  hops_group_mu<2, MODE, NR, Tin, Tc, S>(acc, ip, in_rs, nr, gv, g, pos, mu_sel, chi);
+  hops_group_mu<2, MODE, NR, Tin, Tc, S>(acc, ip, in_rs, nr, gv, g, pos, chi);
   asm volatile("" ::: "memory");
-  hops_group_mu<3, MODE, NR, Tin, Tc, S>(acc, ip, in_rs, nr, gv, g, pos, mu_sel, chi);
+  hops_group_mu<3, MODE, NR, Tin, Tc, S>(acc, ip, in_rs, nr, gv, g, pos, chi);
 #pragma unroll
   for (int r = 0; r < NR; ++r) {
     if (r >= nr) break;
@@ -384,7 +372,7 @@ __device__ inline void fetch_link(RawLink<S>& r, const GaugeView<S>& gv, int mu,
 }
 
 // acc += -1/2 (1 -+ g_mu) [U or U^dag] psi for a neighbour given by its
-// projected 2-spinor h and its link (as hop_spinor applies them)
+// projected 2-spinor h and its link (as hop_spinor_multi applies them)
 template <int MU, bool FWD, typename Tc, typename S>
 __device__ inline void hop_projected(cx<Tc> acc[4][3], const Half2<Tc>& h, const RawLink<S>& r) {
   cx<Tc> U[3][3];
@@ -790,26 +778,26 @@ void launch_staged(cx<Tout>* out, const cx<Tin>* in, const GaugeView<S>& gv, con
 }
 
 template <typename Tin, typename Tout, typename S, typename Tc, int MODE, int NR>
-void launch_mode(cx<Tout>* out, const cx<Tin>* in, const GaugeView<S>& gv, const Geom& g, int nrhs, int mu, int chi_in,
-                 size_t in_rs, size_t out_rs, size_t nsite, hipStream_t st) {
-  const unsigned grid = (unsigned)((nsite + TPB - 1) / TPB) * (unsigned)((nrhs + NR - 1) / NR);
-  dslash_kernel<Tin, Tout, S, Tc, MODE, NR><<<grid, TPB, 0, st>>>(out, in, gv, g, mu, chi_in, in_rs, out_rs, nrhs);
+void launch_mode(cx<Tout>* out, const cx<Tin>* in, const GaugeView<S>& gv, const Geom& g, int nrhs, int chi_in,
+                 size_t in_rs, size_t out_rs, hipStream_t st) {
+  const unsigned grid = (unsigned)((g.V + TPB - 1) / TPB) * (unsigned)((nrhs + NR - 1) / NR);
+  dslash_kernel<Tin, Tout, S, Tc, MODE, NR><<<grid, TPB, 0, st>>>(out, in, gv, g, chi_in, in_rs, out_rs, nrhs);
 }
 
 // rhs per thread: 1 for a lone rhs; otherwise as many as the registers hold
 // without spilling (the accumulators of FP64 spinors are twice the size)
 template <typename Tin, typename Tout, typename S, typename Tc, int MODE>
-void launch_nr(cx<Tout>* out, const cx<Tin>* in, const GaugeView<S>& gv, const Geom& g, int nrhs, int mu, int chi_in,
-               size_t in_rs, size_t out_rs, size_t nsite, hipStream_t st) {
+void launch_nr(cx<Tout>* out, const cx<Tin>* in, const GaugeView<S>& gv, const Geom& g, int nrhs, int chi_in,
+               size_t in_rs, size_t out_rs, hipStream_t st) {
   if (nrhs == 1) {
-    launch_mode<Tin, Tout, S, Tc, MODE, 1>(out, in, gv, g, nrhs, mu, chi_in, in_rs, out_rs, nsite, st);
+    launch_mode<Tin, Tout, S, Tc, MODE, 1>(out, in, gv, g, nrhs, chi_in, in_rs, out_rs, st);
   } else if constexpr (sizeof(Tc) == 8) {
-    launch_mode<Tin, Tout, S, Tc, MODE, 2>(out, in, gv, g, nrhs, mu, chi_in, in_rs, out_rs, nsite, st);
+    launch_mode<Tin, Tout, S, Tc, MODE, 2>(out, in, gv, g, nrhs, chi_in, in_rs, out_rs, st);
   } else {
     if (nrhs < 4)
-      launch_mode<Tin, Tout, S, Tc, MODE, 2>(out, in, gv, g, nrhs, mu, chi_in, in_rs, out_rs, nsite, st);
+      launch_mode<Tin, Tout, S, Tc, MODE, 2>(out, in, gv, g, nrhs, chi_in, in_rs, out_rs, st);
     else
-      launch_mode<Tin, Tout, S, Tc, MODE, 4>(out, in, gv, g, nrhs, mu, chi_in, in_rs, out_rs, nsite, st);
+      launch_mode<Tin, Tout, S, Tc, MODE, 4>(out, in, gv, g, nrhs, chi_in, in_rs, out_rs, st);
   }
 }
 
@@ -817,39 +805,26 @@ void launch_nr(cx<Tout>* out, const cx<Tin>* in, const GaugeView<S>& gv, const G
 
 template <typename Tin, typename Tout, typename S, typename Tc>
 void launch_dslash(cx<Tout>* out, const cx<Tin>* in, const GaugeView<S>& gv, const Geom& g, int nrhs, int mode,
-                   int mu, int chi_in, size_t in_rstride, size_t out_rstride, hipStream_t st) {
+                   int chi_in, size_t in_rstride, size_t out_rstride, hipStream_t st) {
   if (nrhs <= 0) return;
-  const size_t nsite = (mode == DS_CROSS_FWD || mode == DS_CROSS_BWD) ? (size_t)g.nblocks * (g.vblock / g.bs[mu])
-                                                                      : (size_t)g.V;
-  switch (mode) {
-    case DS_FULL:
-      // blocks of up to 256 sites: the block-staged kernel, one or two rhs per lane
-      if (g.vblock <= 256) {
-        if (nrhs == 1) {
-          // 4^4 blocks, FP32 input and arithmetic: the x and y faces staged as well
-          if constexpr (sizeof(Tin) == 4 && sizeof(Tc) == 4) {
-            if (g.bs[0] == HB && g.bs[1] == HB && g.bs[2] == HB && g.bs[3] == HB) {
-              dslash_halo_kernel<Tin, Tout, S, Tc><<<g.nblocks, HVB, 0, st>>>(out, in, gv, g);
-              break;
-            }
-          }
-          launch_staged<Tin, Tout, S, Tc, 1>(out, in, gv, g, nrhs, in_rstride, out_rstride, st);
-        }
-        else
-          launch_staged<Tin, Tout, S, Tc, 2>(out, in, gv, g, nrhs, in_rstride, out_rstride, st);
-        break;
+  if (mode == DS_BLOCK) {
+    launch_nr<Tin, Tout, S, Tc, DS_BLOCK>(out, in, gv, g, nrhs, chi_in, in_rstride, out_rstride, st);
+    return;
+  }
+  // blocks of up to 256 sites: the block-staged kernel, one or two rhs per lane
+  if (g.vblock > 256) {
+    launch_nr<Tin, Tout, S, Tc, DS_FULL>(out, in, gv, g, nrhs, chi_in, in_rstride, out_rstride, st);
+  } else if (nrhs > 1) {
+    launch_staged<Tin, Tout, S, Tc, 2>(out, in, gv, g, nrhs, in_rstride, out_rstride, st);
+  } else {
+    // 4^4 blocks, FP32 input and arithmetic: the x and y faces staged as well
+    if constexpr (sizeof(Tin) == 4 && sizeof(Tc) == 4) {
+      if (g.bs[0] == HB && g.bs[1] == HB && g.bs[2] == HB && g.bs[3] == HB) {
+        dslash_halo_kernel<Tin, Tout, S, Tc><<<g.nblocks, HVB, 0, st>>>(out, in, gv, g);
+        return;
       }
-      launch_nr<Tin, Tout, S, Tc, DS_FULL>(out, in, gv, g, nrhs, mu, chi_in, in_rstride, out_rstride, nsite, st);
-      break;
-    case DS_BLOCK:
-      launch_nr<Tin, Tout, S, Tc, DS_BLOCK>(out, in, gv, g, nrhs, mu, chi_in, in_rstride, out_rstride, nsite, st);
-      break;
-    case DS_CROSS_FWD:
-      launch_nr<Tin, Tout, S, Tc, DS_CROSS_FWD>(out, in, gv, g, nrhs, mu, chi_in, in_rstride, out_rstride, nsite, st);
-      break;
-    default:
-      launch_nr<Tin, Tout, S, Tc, DS_CROSS_BWD>(out, in, gv, g, nrhs, mu, chi_in, in_rstride, out_rstride, nsite, st);
-      break;
+    }
+    launch_staged<Tin, Tout, S, Tc, 1>(out, in, gv, g, nrhs, in_rstride, out_rstride, st);
   }
 }
 
@@ -893,7 +868,7 @@ void preload_dslash_code() {
 
 #define INST(Tin, Tout, S, Tc)                                                                                   \
   template void launch_dslash<Tin, Tout, S, Tc>(cx<Tout>*, const cx<Tin>*, const GaugeView<S>&, const Geom&, int, \
-                                                int, int, int, size_t, size_t, hipStream_t);
+                                                int, int, size_t, size_t, hipStream_t);
 INST(double, double, double, double)
 INST(float, float, float, float)
 INST(float, float, __half, float)

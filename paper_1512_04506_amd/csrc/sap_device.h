@@ -229,7 +229,7 @@ __device__ inline void staged_hops(cx<T> acc[NR][4][3], const cx<T>* lds, const 
       const bool wrap = MU == 3 && p.bc[3] == g.NB[3] - 1;
 #pragma unroll
       for (int r = 0; r < NR; ++r)
-        load_spinor<T, T, false>(q[r], x + (size_t)min(r, nr - 1) * rs, sn, V, -1, wrap ? (T)-1 : (T)1);
+        load_spinor(q[r], x + (size_t)min(r, nr - 1) * rs, sn, V, wrap ? (T)-1 : (T)1);
     }
     sap_hop<MU, true, NR, T, S>(acc, q, gl, p.S);
   }
@@ -249,7 +249,7 @@ __device__ inline void staged_hops(cx<T> acc[NR][4][3], const cx<T>* lds, const 
       const bool wrap = MU == 3 && p.bc[3] == 0;
 #pragma unroll
       for (int r = 0; r < NR; ++r)
-        load_spinor<T, T, false>(q[r], x + (size_t)min(r, nr - 1) * rs, sb, V, -1, wrap ? (T)-1 : (T)1);
+        load_spinor(q[r], x + (size_t)min(r, nr - 1) * rs, sb, V, wrap ? (T)-1 : (T)1);
     }
     sap_hop<MU, false, NR, T, S>(acc, q, gl, sb);
   }
