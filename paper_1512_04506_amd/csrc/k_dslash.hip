@@ -325,9 +325,11 @@ __global__ __launch_bounds__(256) void dslash_staged_kernel(cx<Tout>* __restrict
 // same lines, and keeps only its projection (1 -+ g_mu) psi, the 2-spinor
 // the hop multiplies (half the LDS of the full spinor).  The z and t faces
 // are contiguous runs and stay global, fetched a direction ahead; the links
-// are fetched two hops ahead (each hop loading its own waited for it: 82 ->
-// 76 us on 24^3x48 in FP16 storage, 17.9 -> 16.2 on 16^3x32, 269 -> 260 on
-// 32^3x64).  Bound: memory at 3.9 to 4.3 TB/s of algorithmic bytes.
+// are fetched two hops ahead (each hop loading its own waited for it: 80.9 ->
+// 75.1 us on 24^3x48 in FP16 storage, 267.5 -> 261.0 on 32^3x64; in FP32 121.8 ->
+// 119.2 and 387.8 -> 384.1).  Bound: bytes in flight.  3.9 to 4.3 TB/s of
+// algorithmic bytes where a stream kernel reaches 6.05, and no more without
+// any halo read: a workgroup stages, waits, computes and stores in turn.
 constexpr int HB = 4;                 // block extent
 constexpr int HVB = HB * HB * HB * HB;  // sites per block
 constexpr int HF = HVB / HB;          // sites per face
