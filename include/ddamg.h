@@ -33,7 +33,8 @@
  *
  * Ownership: the caller owns every pointer it passes and keeps it valid for
  * the duration of the call; the library never frees caller memory.  The
- * library owns the context and its device workspace (hipMalloc at create).
+ * library owns the context and its device workspace (hipMalloc at create, and
+ * at the first call that needs more).
  *
  * Streams: every call enqueues work on the context's stream.  dirac_apply,
  * coarse_apply, mg_apply, mg_restrict, mg_prolong and the *_internal calls
