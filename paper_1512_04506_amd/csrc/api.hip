@@ -400,14 +400,18 @@ struct Solver final : SolverBase {
   DevBuf Wq, Wsc, Dq, Dsc, Dinv, tv;
   // fine work vectors (T): y, x, r [maxr][12][V]
   DevBuf fy, fx;
-  // setup workspace, allocated at the first setup and kept: FP64 copy of
-  // the test vectors for the Gram-Schmidt, dequantised basis, D_c
-  // accumulation buffer and the block operator applied to the basis columns
+  // setup workspace, allocated at the first setup and kept: an FP64 field of
+  // N_tv vectors (an imported basis), dequantised basis, D_c accumulation
+  // buffer, the block operator applied to the basis columns, and the first
+  // triangular factor of the Gram-Schmidt
   DevBuf ws_Wd, ws_Wt, ws_D, ws_Z, ws_T;
+  // its Gram matrices and second factor lie in the FP64 field, where they fit
+  // (aggregates of fewer than N_tv rows, too small for them, are rank deficient)
+  bool gram_in_Wd() const { return qr_gram_entries(g) <= (size_t)g.ntv * fsz(); }
   void ensure_setup_ws() {
     if (ws_Z.p) return;  // the last of them: a failed allocation leaves the rest to the next call
     ws_Wd.alloc<cx<double>>((size_t)g.ntv * fsz());
-    ws_T.alloc<cx<double>>(qr_tws_entries(g));
+    ws_T.alloc<cx<double>>(qr_factor_entries(g) + (gram_in_Wd() ? 0 : qr_gram_entries(g)));
     if (is_half<S>()) ws_Wt.alloc<cx<T>>((size_t)g.ntv * fsz());  // else the stored basis is already cx<T>
     ws_D.alloc<cx<T>>((size_t)g.nblocks * 9 * g.nc * g.nc);
     ws_Z.alloc<cx<T>>((size_t)g.ntv * fsz());
@@ -876,14 +880,15 @@ struct Solver final : SolverBase {
     ensure_setup_ws();
     HIPCK(hipMemsetAsync(c->status.get<int>(), 0, sizeof(int), st));
     const cx<T>* X = tv.get<cx<T>>();
-    cx<double>* tws = ws_T.get<cx<double>>();
+    cx<double>* T1 = ws_T.get<cx<double>>();
+    cx<double>* T2 = gram_in_Wd() ? ws_Wd.get<cx<double>>() : T1 + qr_factor_entries(g);
     int stat = 0;
     c->timed(DDAMG_KERNEL_SETUP_QR, g.ntv, [&] {
-      launch_aggregate_qr<T>(X, g, c->status.get<int>(), tws, st);
+      launch_aggregate_qr<T>(X, g, c->status.get<int>(), T1, T2, st);
       check_launch("aggregate qr");
       HIPCK(hipMemcpyAsync(&stat, c->status.get<int>(), sizeof(int), hipMemcpyDeviceToHost, st));
       c->sync();
-      if (!stat) launch_qr_store<T, S>(Wq.get<stc_t<S>>(), Wsc.get<float>(), basis_wt(), X, g, tws, st);
+      if (!stat) launch_qr_store<T, S>(Wq.get<stc_t<S>>(), Wsc.get<float>(), basis_wt(), X, g, T1, T2, st);
     });
     if (stat) throw Fail{DDAMG_ENUMERIC, "rank-deficient aggregate in the Gram-Schmidt of the test vectors"};
     build_coarse_op();

@@ -336,10 +336,10 @@ void launch_block_matvec(cx<T>* out, size_t ostr, const cx<T>* M, const cx<T>* x
 
 // setup kernels
 // Orthonormalises the test vectors X on every aggregate (CholQR2 in FP64):
-// the two triangular factors' inverses into tws (qr_tws_entries complex
-// doubles; status set to 1 for a rank-deficient aggregate), then the basis
-// from X and tws in storage S, as launch_quantize_basis stores it
-constexpr int QR_TWS_PER_AGG = 32 * 32;
+// the two triangular factors' inverses into T1 (qr_factor_entries complex
+// doubles) and the beginning of T2 (qr_gram_entries, the parts of the Gram
+// matrices; status set to 1 for a rank-deficient aggregate), then the basis
+// from X and both in storage S, as launch_quantize_basis stores it
 // parts of an aggregate's sites whose Gram matrices are formed by workgroups
 // of their own (at least 16 sites each)
 inline int qr_parts(const Geom& g) {
@@ -347,12 +347,13 @@ inline int qr_parts(const Geom& g) {
   if (p > (g.vblock + 15) / 16) p = (g.vblock + 15) / 16;
   return p < 1 ? 1 : p > 4 ? 4 : p;
 }
-inline size_t qr_tws_entries(const Geom& g) { return (size_t)2 * g.nblocks * QR_TWS_PER_AGG * (1 + qr_parts(g)); }
+inline size_t qr_factor_entries(const Geom& g) { return (size_t)2 * g.nblocks * g.ntv * g.ntv; }
+inline size_t qr_gram_entries(const Geom& g) { return qr_factor_entries(g) * qr_parts(g); }
 template <typename T>
-void launch_aggregate_qr(const cx<T>* X, const Geom& g, int* status, cx<double>* tws, hipStream_t st);
+void launch_aggregate_qr(const cx<T>* X, const Geom& g, int* status, cx<double>* T1, cx<double>* T2, hipStream_t st);
 template <typename T, typename S>
-void launch_qr_store(stc_t<S>* Wq, float* Wsc, cx<float>* Wt, const cx<T>* X, const Geom& g, const cx<double>* tws,
-                     hipStream_t st);
+void launch_qr_store(stc_t<S>* Wq, float* Wsc, cx<float>* Wt, const cx<T>* X, const Geom& g, const cx<double>* T1,
+                     const cx<double>* T2, hipStream_t st);
 // Stores the FP64 basis W in precision S (FP16 with a per-(vector, site)
 // scale in Wsc); for FP16, Wt (if given) receives the dequantised FP32
 // values scale * half, the same numbers launch_dequantize_basis produces

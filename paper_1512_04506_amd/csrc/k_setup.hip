@@ -51,7 +51,7 @@ __device__ inline __half half_rn(double x) {
 typedef double qr_v4d __attribute__((ext_vector_type(4)));
 
 // The waves' Gram tiles summed (waves 2, 3 hand theirs to 0, 1, then 1 to 0)
-// and the upper triangle of G written, row-major, stride MAX_NTV
+// and the upper triangle of G (n x n) written, row-major
 template <int NT>
 __device__ inline void gram_out(qr_v4d (&acc)[2 * NT], qr_v4d (*part)[2 * NT][64], int n, cx<double>* G) {
   constexpr int NACC = 2 * NT;
@@ -77,16 +77,16 @@ __device__ inline void gram_out(qr_v4d (&acc)[2 * NT], qr_v4d (*part)[2 * NT][64
     for (int v = 0; v < 4; ++v) {
       const int i = rsub + 4 * v, j = col0;
       if constexpr (NT == 1) {
-        if (i < n && j < n) G[i * MAX_NTV + j] = mk(acc[0][v], acc[1][v]);
+        if (i < n && j < n) G[i * n + j] = mk(acc[0][v], acc[1][v]);
       } else if constexpr (NT == 2) {
         const int ib = 8 + j;  // tile 0: rows 0..15, columns 8..23
-        if (i <= ib && ib < n) G[i * MAX_NTV + ib] = mk(acc[0][v], acc[1][v]);
+        if (i <= ib && ib < n) G[i * n + ib] = mk(acc[0][v], acc[1][v]);
         const int ic = i < 8 ? i : i + 8, jc = j < 8 ? j : j + 8;  // tile 1
-        if (ic <= jc && jc < n && !(ic < 8 && jc >= 16)) G[ic * MAX_NTV + jc] = mk(acc[2][v], acc[3][v]);
+        if (ic <= jc && jc < n && !(ic < 8 && jc >= 16)) G[ic * n + jc] = mk(acc[2][v], acc[3][v]);
       } else {
-        if (i < n && j < n) G[i * MAX_NTV + j] = mk(acc[0][v], acc[1][v]);
-        if (i < n && 16 + j < n) G[i * MAX_NTV + 16 + j] = mk(acc[2][v], acc[3][v]);
-        if (16 + i < n && 16 + j < n) G[(16 + i) * MAX_NTV + 16 + j] = mk(acc[4][v], acc[5][v]);
+        if (i < n && j < n) G[i * n + j] = mk(acc[0][v], acc[1][v]);
+        if (i < n && 16 + j < n) G[i * n + 16 + j] = mk(acc[2][v], acc[3][v]);
+        if (16 + i < n && 16 + j < n) G[(16 + i) * n + 16 + j] = mk(acc[4][v], acc[5][v]);
       }
     }
   }
@@ -197,14 +197,14 @@ __global__ __launch_bounds__(QR_THREADS) void qr_gram_kernel(const cx<Tin>* W, G
     if (s0 + QR_CS < vb) chunk(xq1, s0 + QR_CS);
   }
   __syncthreads();  // the staging buffer is reused for the partial tiles
-  gram_out<NT>(acc, part, n, Gout + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * QR_TWS_PER_AGG);
+  gram_out<NT>(acc, part, n, Gout + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * n * n);
 }
 
 // Cholesky G = T^H T (T upper, real positive diagonal) and T^{-1}, one
 // workgroup of L lanes per aggregate, every entry of the W x W matrix (W >=
 // ntv) in the register of one lane: a step hands one row to the others
-// through LDS.  G is the sum of nparts upper triangles (stride MAX_NTV,
-// pstride apart).  T^{-1} (n x n, row-major) goes to Tout, which may be the
+// through LDS.  G is the sum of nparts upper triangles (pstride
+// apart).  T^{-1} goes to Tout (both n x n, row-major), which may be the
 // first part of G; a pivot that is not positive sets *status and leaves
 // zeros.  Bound: the chain of n steps and reciprocal square roots.  N_tv 24,
 // 5184 aggregates 106 us (109 with 64 lanes on a matrix in LDS), N_tv 16, 64
@@ -217,15 +217,15 @@ __global__ __launch_bounds__(L) void qr_chol_kernel(const cx<double>* G, size_t 
   __shared__ double dinv[W];
   constexpr int NQ = W * W / L, RS = L / W;  // rows RS apart per lane
   const int n = g.ntv, t = threadIdx.x, j = t % W, i0 = t / W;
-  const cx<double>* Gg = G + (size_t)blockIdx.x * QR_TWS_PER_AGG;
-  cx<double>* Tg = Tout + (size_t)blockIdx.x * QR_TWS_PER_AGG;
+  const cx<double>* Gg = G + (size_t)blockIdx.x * n * n;
+  cx<double>* Tg = Tout + (size_t)blockIdx.x * n * n;
   cx<double> a[NQ];
 #pragma unroll
   for (int q = 0; q < NQ; ++q) {
     const int i = i0 + RS * q;
     a[q] = mk(0.0, 0.0);
     if (i <= j && j < n)
-      for (int p = 0; p < nparts; ++p) a[q] = a[q] + Gg[(size_t)p * pstride + i * MAX_NTV + j];
+      for (int p = 0; p < nparts; ++p) a[q] = a[q] + Gg[(size_t)p * pstride + i * n + j];
   }
   // right-looking: step k scales row k by the pivot and updates the rows below
   bool ok = true;
@@ -353,7 +353,7 @@ __global__ __launch_bounds__(QR_THREADS, 2) void qr_gram2_kernel(const cx<Tin>* 
   const int ntile = 6 * ((end - beg + 15) / 16);  // tile: component tile % 6, sites beg + 16 (tile / 6)
   cx<Tin> xr[NQ];
   if (w < ntile) load_x<Tin, NQ>(xr, X, 6 * h + w % 6, base, beg + 16 * (w / 6), end, n, V);
-  load_tinv<NQ>(Tb, Tinv + (size_t)blockIdx.x * QR_TWS_PER_AGG, n);
+  load_tinv<NQ>(Tb, Tinv + (size_t)blockIdx.x * n * n, n);
   qr_v4d acc[NACC];
 #pragma unroll
   for (int t = 0; t < NACC; ++t) acc[t] = (qr_v4d){0.0, 0.0, 0.0, 0.0};
@@ -430,7 +430,7 @@ __global__ __launch_bounds__(QR_THREADS, 2) void qr_gram2_kernel(const cx<Tin>* 
     }
   }
   __syncthreads();  // T^{-1} gives way to the partial tiles
-  gram_out<NT>(acc, part, n, Gout + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * QR_TWS_PER_AGG);
+  gram_out<NT>(acc, part, n, Gout + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * n * n);
 }
 
 // The stored basis (X T1^{-1}) T2^{-1} of one block (blockIdx.x), both
@@ -454,7 +454,7 @@ __global__ __launch_bounds__(QR_THREADS, 2) void qr_store_kernel(stc_t<S>* Wq, f
   const size_t V = g.V, base = (size_t)ci * vb;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, k4 = lane >> 4, h = w >> 1;
   for (int e = 0; e < 2; ++e) {
-    const size_t agg = (size_t)(2 * ci + e) * QR_TWS_PER_AGG;
+    const size_t agg = (size_t)(2 * ci + e) * n * n;
     load_tinv<NQ>(Tb[e][0], T1 + agg, n);
     load_tinv<NQ>(Tb[e][1], T2 + agg, n);
   }
@@ -627,13 +627,13 @@ void with_nq(int ntv, F&& f) {
 }  // namespace
 
 template <typename T>
-void launch_aggregate_qr(const cx<T>* X, const Geom& g, int* status, cx<double>* tws, hipStream_t st) {
+void launch_aggregate_qr(const cx<T>* X, const Geom& g, int* status, cx<double>* T1, cx<double>* T2, hipStream_t st) {
   // the Gram matrices of a small lattice's few aggregates in parts, about a
   // workgroup per compute unit
   const unsigned nagg = 2 * g.nblocks;
   const int nparts = qr_parts(g), part_sites = ((g.vblock + nparts - 1) / nparts + 15) / 16 * 16;
-  cx<double>*T1 = tws, *G = tws + (size_t)nagg * QR_TWS_PER_AGG;  // T2 replaces G's first part
-  const size_t pstride = (size_t)nagg * QR_TWS_PER_AGG;
+  cx<double>* G = T2;  // T2 replaces G's first part
+  const size_t pstride = qr_factor_entries(g);
   launch_qr_gram<T>(X, g, nparts, part_sites, G, st);
   const auto chol = [&](cx<double>* out) {
     if (g.ntv <= 16)
@@ -648,23 +648,22 @@ void launch_aggregate_qr(const cx<T>* X, const Geom& g, int* status, cx<double>*
   chol(G);
 }
 template <typename T, typename S>
-void launch_qr_store(stc_t<S>* Wq, float* Wsc, cx<float>* Wt, const cx<T>* X, const Geom& g, const cx<double>* tws,
-                     hipStream_t st) {
+void launch_qr_store(stc_t<S>* Wq, float* Wsc, cx<float>* Wt, const cx<T>* X, const Geom& g, const cx<double>* T1,
+                     const cx<double>* T2, hipStream_t st) {
   const int ngroup = (g.vblock + 15) / 16;
   const int gy = std::max(1, std::min(ngroup, 1024 / g.nblocks));
-  const cx<double>*T1 = tws, *T2 = tws + (size_t)2 * g.nblocks * QR_TWS_PER_AGG;
   with_nq(g.ntv, [&](auto q) {
     qr_store_kernel<T, S, decltype(q)::value><<<dim3(g.nblocks, gy), QR_THREADS, 0, st>>>(Wq, Wsc, Wt, X, g, T1, T2);
   });
 }
-template void launch_aggregate_qr<double>(const cx<double>*, const Geom&, int*, cx<double>*, hipStream_t);
-template void launch_aggregate_qr<float>(const cx<float>*, const Geom&, int*, cx<double>*, hipStream_t);
+template void launch_aggregate_qr<double>(const cx<double>*, const Geom&, int*, cx<double>*, cx<double>*, hipStream_t);
+template void launch_aggregate_qr<float>(const cx<float>*, const Geom&, int*, cx<double>*, cx<double>*, hipStream_t);
 template void launch_qr_store<double, double>(stc_t<double>*, float*, cx<float>*, const cx<double>*, const Geom&,
-                                              const cx<double>*, hipStream_t);
+                                              const cx<double>*, const cx<double>*, hipStream_t);
 template void launch_qr_store<float, float>(stc_t<float>*, float*, cx<float>*, const cx<float>*, const Geom&,
-                                            const cx<double>*, hipStream_t);
+                                            const cx<double>*, const cx<double>*, hipStream_t);
 template void launch_qr_store<float, __half>(stc_t<__half>*, float*, cx<float>*, const cx<float>*, const Geom&,
-                                             const cx<double>*, hipStream_t);
+                                             const cx<double>*, const cx<double>*, hipStream_t);
 
 template <typename S>
 void launch_quantize_basis(stc_t<S>* Wq, float* Wsc, const cx<double>* W, const Geom& g, hipStream_t st,
