@@ -405,13 +405,13 @@ struct Solver final : SolverBase {
   // buffer, the block operator applied to the basis columns, and the first
   // triangular factor of the Gram-Schmidt
   DevBuf ws_Wd, ws_Wt, ws_D, ws_Z, ws_T;
-  // its Gram matrices and second factor lie in the FP64 field, where they fit
-  // (aggregates of fewer than N_tv rows, too small for them, are rank deficient)
-  bool gram_in_Wd() const { return qr_gram_entries(g) <= (size_t)g.ntv * fsz(); }
+  // its Gram matrices and second factor lie in the FP64 field: 2 N_tv^2 entries per
+  // block and part (each of more than one has 16 sites but the last) against
+  // 12 N_tv per site, with N_tv <= 32 and N_tv <= 6 sites
   void ensure_setup_ws() {
     if (ws_Z.p) return;  // the last of them: a failed allocation leaves the rest to the next call
     ws_Wd.alloc<cx<double>>((size_t)g.ntv * fsz());
-    ws_T.alloc<cx<double>>(qr_factor_entries(g) + (gram_in_Wd() ? 0 : qr_gram_entries(g)));
+    ws_T.alloc<cx<double>>(qr_factor_entries(g));
     if (is_half<S>()) ws_Wt.alloc<cx<T>>((size_t)g.ntv * fsz());  // else the stored basis is already cx<T>
     ws_D.alloc<cx<T>>((size_t)g.nblocks * 9 * g.nc * g.nc);
     ws_Z.alloc<cx<T>>((size_t)g.ntv * fsz());
@@ -881,7 +881,7 @@ struct Solver final : SolverBase {
     HIPCK(hipMemsetAsync(c->status.get<int>(), 0, sizeof(int), st));
     const cx<T>* X = tv.get<cx<T>>();
     cx<double>* T1 = ws_T.get<cx<double>>();
-    cx<double>* T2 = gram_in_Wd() ? ws_Wd.get<cx<double>>() : T1 + qr_factor_entries(g);
+    cx<double>* T2 = ws_Wd.get<cx<double>>();
     int stat = 0;
     c->timed(DDAMG_KERNEL_SETUP_QR, g.ntv, [&] {
       launch_aggregate_qr<T>(X, g, c->status.get<int>(), T1, T2, st);
